@@ -129,6 +129,14 @@ def _buckets(sizes, dtype, most=4):
 
 
 def prepare(case, seed):
+    shapes, r, bf16 = _shapes(case), case["r"], case["dtype"] == "bf16"
+    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_BF16 if bf16 else psgd.PSGD_F32, ld) for rows, cols, ld in shapes],
+                           case["n_workers"], lazy_residual=case["lazy"],
+                           q_resident=case["op"] == "step" and case["factors"] == "kept")
+    return dict(_inputs(case, seed), comp=comp)
+
+
+def _inputs(case, seed):
     shapes, r, n, sk = _shapes(case), case["r"], case["n_workers"], case["signal"]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
@@ -137,9 +145,7 @@ def prepare(case, seed):
         return torch.randn(size, generator=gen, device="cuda")
 
     bf16 = case["dtype"] == "bf16"
-    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_BF16 if bf16 else psgd.PSGD_F32, ld) for rows, cols, ld in shapes],
-                           n, lazy_residual=case["lazy"], q_resident=case["op"] == "step" and case["factors"] == "kept")
-    state = {"case": dict(case), "comp": comp, "t": 100}
+    state = {"case": dict(case), "t": 100}
     full = [(rows, ld) for rows, cols, ld in shapes]
     state["E_flat"], E = _buckets(full, torch.float32)
     state["P_flat"], P = _buckets([(max(rows, cols), r) for rows, cols, ld in shapes], torch.float32)
@@ -213,6 +219,68 @@ def run(state):
         comp.decompress(fp, fq, state["out"], psgd.PSGD_BF16 if case["update"] == "bf16" else psgd.PSGD_F32)
         out["update"] = state["O_flat"]
     return out
+
+
+def exact(case, seed):
+    """The first pass on a new state in 64 bits (the flat buffers' padding stays zero); None for the largest sets."""
+    shapes, r = _shapes(case), case["r"]
+    if sum(rows * cols for rows, cols, ld in shapes) > 450e6:
+        return None
+    state = _inputs(case, seed)
+    full = [(rows, ld) for rows, cols, ld in shapes]
+    flat, view = {}, {}
+    for key, sizes in (("E", full), ("P", [(max(rows, cols), r) for rows, cols, ld in shapes]),
+                       ("Q", [(min(rows, cols), r) for rows, cols, ld in shapes]), ("update", full),
+                       ("X", full), ("M1", full), ("M2", full)):
+        if key in ("E", "P", "Q") or key in state or (key == "update" and "out" in state):
+            flat[key], view[key] = _buckets(sizes, torch.float64)
+    for l, (rows, cols, ld) in enumerate(shapes):
+        m = sum(g[:, :cols].double() for g in state["G"][l]) / case["n_workers"] + state["E"][l][:, :cols].double()
+        tall = m if rows >= cols else m.T
+        p = _leading(tall, r, case["signal"]) if case["op"] == "refresh" else _orth(tall @ state["Q"][l].double())
+        q = tall.T @ p
+        d = p @ q.T if rows >= cols else q @ p.T
+        view["P"][l].copy_(p)
+        view["Q"][l].copy_(q)
+        view["E"][l][:, :cols] = m if case["lazy"] else m - d
+        if case["update"] == "msgd":
+            m1 = 0.9 * state["M1"][l][:, :cols].double() + d
+            view["M1"][l][:, :cols] = m1
+            view["X"][l][:, :cols] = state["X"][l][:, :cols].double() - 1e-3 * m1
+        elif case["update"] == "adam":
+            t, x = state["t"] + 1, state["X"][l][:, :cols].double()
+            m1 = 0.9 * state["M1"][l][:, :cols].double() + 0.1 * d
+            m2 = 0.999 * state["M2"][l][:, :cols].double() + 0.001 * d * d
+            view["M1"][l][:, :cols] = m1
+            view["M2"][l][:, :cols] = m2
+            step = (m1 / (1 - 0.9 ** t)) / ((m2 / (1 - 0.999 ** t)).sqrt() + 1e-8)
+            view["X"][l][:, :cols] = x - 1e-3 * (step + 0.01 * x)
+        else:
+            view["update"][l][:, :cols] = d
+    if case["op"] == "refresh":
+        del flat["P"], flat["Q"]
+    return flat
+
+
+def _orth(a):
+    """The Q factor with R's diagonal positive."""
+    q, upper = torch.linalg.qr(a)
+    return q * torch.sign(torch.diagonal(upper))
+
+
+def _leading(a, r, signal):
+    """The r leading left singular vectors; by block iteration where a whole decomposition would take long (the block
+    holds all of the signal, and the singular values after it are the noise's)."""
+    n = a.shape[1]
+    if n <= 512:
+        return torch.linalg.svd(a, full_matrices=False)[0][:, :r]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    y = torch.randn((n, min(n, signal + 64)), generator=gen, device="cuda", dtype=torch.float64)
+    for _ in range(50):
+        z = _orth(a @ y)
+        y = a.T @ z
+    return z @ torch.linalg.eigh(y.T @ y)[1].flip(1)[:, :r]
 
 
 def work(case):
