@@ -732,7 +732,8 @@ __global__ __launch_bounds__(kThreads, ((PL == 2 && NB == 1) ? 3 : 2)) void col_
     }
     const LayerDev& L = layers[ids[layer_pos]];
     if (!gate_open(L, gate)) return;
-    const int epi = epi_flags & EPI_KIND_MASK;
+    int copies;
+    const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const int n_cb = (L.colsP + CW - 1) / CW;
     const int n_split = L.split_col_v2;
     if (tile >= n_cb * n_split) return;
@@ -895,7 +896,9 @@ __global__ __launch_bounds__(kThreads, ((PL == 2 && NB == 1) ? 3 : 2)) void col_
             }
             continue;
         }
-        if (T.ld == w && (w & 3) == 0) {
+        if (copies == 2) {
+            // (only the transposed operand copies are read)
+        } else if (T.ld == w && (w & 3) == 0) {
             // (rows of the result are one run of memory: 16-byte stores over the flat range)
             const int n_valid = (min(L.cols, r0 + 128) - r0) * w;
             const float inv_w = 1.0f / (float)w;
@@ -915,7 +918,7 @@ __global__ __launch_bounds__(kThreads, ((PL == 2 && NB == 1) ? 3 : 2)) void col_
         }
         // the partial Gram matrix or the operand copies of the result, per 128 rows as the other kernels expect them
         if (epi == EPI_GRAM) gram_tile_f64(otile, tw, 128, w, L.gram + (int64_t)(r0 / 128) * ((w * (w + 1)) / 2));
-        else if (epi == EPI_PACK) write_packs<PL>(L.pack[SIDE_W], L.planes, otile, tw, cp, r0, 128, L.colsP, 3, (epi_flags & EPI_KEPT) ? L.lzf[SIDE_W] : nullptr);
+        else if (epi == EPI_PACK) write_packs<PL>(L.pack[SIDE_W], L.planes, otile, tw, cp, r0, 128, L.colsP, copies, (epi_flags & EPI_KEPT) ? L.lzf[SIDE_W] : nullptr);
     }
 }
 

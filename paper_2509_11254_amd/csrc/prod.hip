@@ -213,17 +213,18 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
 // thin result, then either the partial Gram matrix of these rows (fp64, upper triangle, slot = block
 // index) or the split-bf16 operand copies of the rows.  Called by all threads of the workgroup.
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
-                                     int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false) {
+                                     int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
+                                     int copies = 3) {
     const int t = threadIdx.x;
     const int w = T.width;
-    for (int e = t; e < BT * w; e += kThreads) {
+    for (int e = t; copies != 2 && e < BT * w; e += kThreads) {
         const int row = e / w, col = e % w;
         if (ob * BT + row < out_len) as_global(T.ptr)[(int64_t)(ob * BT + row) * T.ld + col] = otile[row * tw + col];
     }
     if (epi == EPI_GRAM) {
         gram_tile_f64(otile, tw, BT, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2));
     } else if (epi == EPI_PACK) {
-        write_packs(L.pack[out_side], L.planes, otile, tw, cp, ob * BT, BT, out_lenP, 3, kept ? L.lzf[out_side] : nullptr);
+        write_packs(L.pack[out_side], L.planes, otile, tw, cp, ob * BT, BT, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
     }
 }
 
@@ -258,7 +259,8 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
                                                         int epi_flags, int gate) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
-    const int epi = epi_flags & EPI_KIND_MASK;
+    int copies;
+    const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const bool store_m = FORM && !(epi_flags & EPI_KEEP_E);
     const int out_side = COLMODE ? SIDE_W : SIDE_L;
     const int src_side = COLMODE ? SIDE_L : SIDE_W;
@@ -631,7 +633,7 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
             otile[row * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0);
+    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per 128-row
@@ -648,7 +650,8 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
     __shared__ int s_last;
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
-    const int epi = epi_flags & EPI_KIND_MASK;
+    int copies;
+    const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const int out_side = colmode ? SIDE_W : SIDE_L;
     const int out_len = colmode ? L.cols : L.rows;
     // form (whose partial sums): 0 = a product of prod_kernel that reads M, 1 = a forming pass of prod_kernel,
@@ -717,7 +720,7 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
         else reduce_items(std::integral_constant<int, 1>{}, 0, n_items);
     }
     __syncthreads();
-    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0);
+    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
     if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && gate_open(L, chol_gate)) {
         const int n_wg = (out_len + BT - 1) / BT;      // = number of Gram slots (BT == kGramRows1)
         if (grouped_slot_sum(T.width, n_wg)) {
@@ -727,7 +730,7 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
             const int in_grp = min(kSlotGroup, n_wg - grp * kSlotGroup);
             if (last_to_arrive(&L.status[8 + grp], in_grp, &s_last)) sum_slot_group(L.gram, T.width, n_wg, grp);
         } else if (last_to_arrive(&L.status[6], n_wg, &s_last)) {
-            chol_body(L, out_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem, L.tmat);
+            chol_body(L, out_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, 1, scales_next(L, out_role, chol_gate));
         }
     }
 }

@@ -56,6 +56,8 @@ enum Side { SIDE_L = 0, SIDE_W = 1 };
 // blocks of the subspace iteration (leading dimension wz).
 // what a product's epilogue does besides storing the thin result
 enum Epilogue { EPI_NONE = 0, EPI_GRAM = 1, EPI_PACK = 2, EPI_KIND_MASK = 3,
+                EPI_ITERATE = 3,     // Y = M^T Z of the subspace iteration: EPI_GRAM in a layer's last iteration, else only
+                                     // the transposed operand copies (see resolve_epilogue)
                 EPI_KEEP_E = 16,     // flag: a FORM pass uses M but leaves E in place (M is formed again later)
                 EPI_KEPT = 32 };     // flag: EPI_PACK writes the kept copies (fragment order) in place of the row-major ones
 enum Role { ROLE_P = 0, ROLE_Q = 1, ROLE_ZP = 2, ROLE_ZQ = 3, ROLE_COUNT = 4 };
@@ -265,6 +267,23 @@ __device__ inline bool gate_open(const LayerDev& L, int gate) {
     k = k < launched ? k : launched;
     if (kind == 2) return it == k - 1;
     return it < k - kind;
+}
+
+// What a product of the launch does with its result for this layer.  `copies`: the operand copies EPI_PACK leaves (1 =
+// row-major, 2 = transposed, 3 = both; 2: nothing else of the result is read, its rows are not stored either).
+__device__ inline int resolve_epilogue(const LayerDev& L, int epi_flags, int gate, int& copies) {
+    const int epi = epi_flags & EPI_KIND_MASK;
+    copies = 3;
+    if (epi != EPI_ITERATE) return epi;
+    if (!gate_open(L, gate_with_kind(gate, 1))) return EPI_GRAM;
+    copies = 2;
+    return EPI_PACK;
+}
+// Whether the Z that a factorisation inside the subspace iteration orthonormalises is followed by a Y that is not
+// orthonormalised itself: from the second iteration on, except in the layer's last one.
+constexpr int kOrthYIterations = 1;
+__device__ inline bool scales_next(const LayerDev& L, int role, int gate) {
+    return gate >= 0 && role == ROLE_ZP && (gate & 0xff) >= kOrthYIterations && gate_open(L, gate_with_kind(gate, 1));
 }
 
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double doublex4;

@@ -108,7 +108,8 @@ __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ l
         stride = kSlotGroup;
     }
     extern __shared__ __align__(16) unsigned char smem[];
-    chol_body(L, role, tol2, pass, slot_rows, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, stride);
+    chol_body(L, role, tol2, pass, slot_rows, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, stride,
+              pass == 1 && scales_next(L, role, gate));
 }
 
 // --------------------------------------------------------------------------------------------
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
         }
         double* tml = reinterpret_cast<double*>(smem + main_lds);
         chol_body<true>(L, src_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
-                  tml, blockIdx.x == 0, &s_need2);
+                  tml, blockIdx.x == 0, &s_need2, 1, scales_next(L, src_role, gate));
         __syncthreads();
         need2 = s_need2;
         tm = tml;

@@ -73,6 +73,16 @@ __device__ inline double rcp_nr(double x) {
     return y;
 }
 
+// Power of two next to a column's scaling 1 / ||x||, kept within what fp32 can hold.  Z = X T columns multiplied by it
+// give Y = M^T Z columns of norm about 1 where X = M Y' did with a Y' of such columns: the subspace iteration then needs
+// no orthonormalised Y (its columns are as independent as Z's are once these have lined up with the singular vectors,
+// which one iteration from the warm start does), and nothing drifts out of range however small the gradients are.
+__device__ inline double next_scale(double dsc) {
+    if (!(dsc > 0.0)) return 1.0;
+    const int e = __builtin_amdgcn_frexp_exp(dsc);
+    return __builtin_ldexp(1.0, e > 110 ? 110 : (e < -110 ? -110 : e));
+}
+
 // Ordering point for LDS traffic inside one wavefront (its LDS accesses execute in program order; this
 // keeps the compiler from moving them across).
 __device__ inline void wave_sync() {
@@ -106,7 +116,7 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
 // those of an identity matrix.
 template <int W>
 __device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                           bool allow2, double* tm, bool write_status, int* need2_out) {
+                                           bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
     const int j = threadIdx.x & 63;
     const bool aug = j >= 16;                          // identity column c = j - 16
     const int c = (j - 16) & 15;
@@ -145,11 +155,14 @@ __device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, i
             a[i] = __builtin_fma(-bcast_lane(ak, i), mult, a[i]);   // row i <- row i - R[k][i] row k  (on a matrix lane
                                                                     // j < i an entry below the diagonal: never read)
     }
+    double csc[W];                                                // (scale: see next_scale)
+#pragma unroll
+    for (int i = 0; i < W; ++i) csc[i] = scale ? next_scale(bcast_lane(dsc_own, i < w ? i : 0)) : 1.0;
     // lane 16 + c: row c of tmat = D T with the dependent columns zeroed
     if (aug && j < 16 + w) {
 #pragma unroll
         for (int i = 0; i < W; ++i)
-            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : a[i] * dsc_row;
+            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : a[i] * dsc_row * csc[i];
     }
     if (j == 0) {
         const int nbad = __popc(badmask & ((1 << w) - 1));
@@ -167,11 +180,11 @@ __device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, i
 }
 
 __device__ inline void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                         bool allow2, double* tm, bool write_status, int* need2_out) {
-    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out);
-    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out);
-    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out);
-    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out);
+                                         bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
+    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
+    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
+    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
+    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
 }
 
 // Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers (same scheme as above):
@@ -238,7 +251,7 @@ __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
 template <bool NARROW = false>
 __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
                                  unsigned char* smem, double* tm, bool write_status = true,
-                                 int* need2_out = nullptr, int slot_stride = 1) {
+                                 int* need2_out = nullptr, int slot_stride = 1, bool scale = false) {
     const int side = side_of_role(L.transposed, role);
     // slot_stride > 1: the slots were already added up in groups of that many, each sum left in its group's
     // first slot (sum_slot_groups); what remains is one matrix per group
@@ -340,7 +353,7 @@ __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int p
     }
     __syncthreads();
     if (w <= kCholRegWidth) {
-        if (t < 64) chol_in_registers(L, a, w, tol2, pass, allow2, tm, write_status, need2_out);
+        if (t < 64) chol_in_registers(L, a, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
         return;
     }
     if constexpr (NARROW) return;
@@ -501,7 +514,7 @@ __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int p
         for (int j = tx; j < w; j += 16) {
             double v = 0.0;
             if (!bad[j]) v = (i < j) ? a[base + j] : (i == j ? rdiag[i] : 0.0);
-            tm[(int64_t)i * w + j] = v * dsc[i];
+            tm[(int64_t)i * w + j] = v * dsc[i] * (scale ? next_scale(dsc[j]) : 1.0);
         }
     }
     if (t == 0) {
