@@ -81,6 +81,10 @@ struct Plan {            // host copy of what a layer needs
     int transposed;
     int rowsP, colsP;
     int m, n;
+    // reduction splits of this layer's products (see plan_splits)
+    int split_row = 1, split_col = 1;       // prod_kernel, M read
+    int split_row_f = 1, split_col_f = 1;   // prod_kernel, forming pass
+    int split_row_v2 = 1, split_col_v2 = 1; // the kernels on 32 x 256 tiles
 };
 
 struct Lists {
@@ -107,13 +111,9 @@ struct psgd_ctx {
     bool lazy_tr = false;    // ... also for the layers stored with rows < cols (column-mode forming pass: width 32 only)
     bool pending = false;    // the E buffers of the row-major layers hold M_t, their residual is still owed
     double kernel_bytes[3] = {0.0, 0.0, 0.0};   // algorithmic bytes of the three streaming kernels of one SSP step
-    // batched splits
-    int split_row_b = 1, split_col_b = 1;       // products that read M
-    int split_row_bf = 1, split_col_bf = 1;     // forming passes
-    int split_row_v2 = 1;                       // forming pass on 32 x 256 tiles (form_row_kernel)
-    int split_col_v2 = 1;                       // column-mode product on 32 x 256 tiles (col_prod_kernel)
     int grad_kind = 0;                          // 1: every layer has fp32 gradients, 2: every layer bf16, 0: mixed
     bool nt_m = false;                          // the row-major layers' M is too large to be found in a cache again
+    bool nt_mt = false;                         // ... the M of the layers stored with rows < cols
     // XCD table of the forming pass on 32 x 256 tiles (see form_row_kernel): 16 rows of xstride ints; built when the
     // row-major layers are many enough to be dealt evenly to the 8 XCDs
     std::vector<int> hXtab, hXtabC;             // (forming pass; column-mode product: other tile counts)
@@ -194,10 +194,8 @@ LayerRegion layer_region(const psgd_ctx* c, const Plan& p) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = (size_t)round_up((int64_t)(o + bytes), 256); return at; };
     const int lenP[2] = {p.rowsP, p.colsP};
-    int split[2] = {c->split_row_b > c->split_row_bf ? c->split_row_b : c->split_row_bf,
-                    c->split_col_b > c->split_col_bf ? c->split_col_b : c->split_col_bf};
-    if (c->split_row_v2 > split[0]) split[0] = c->split_row_v2;
-    if (c->split_col_v2 > split[1]) split[1] = c->split_col_v2;
+    const int split[2] = {std::max(std::max(p.split_row, p.split_row_f), p.split_row_v2),
+                          std::max(std::max(p.split_col, p.split_col_f), p.split_col_v2)};
     for (int s = 0; s < 2; ++s) R.part[s] = take((size_t)split[s] * lenP[s] * c->wz * sizeof(float));
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 2 * c->planes; ++k) R.pack[s][k] = take((size_t)lenP[s] * c->cpmax * sizeof(bf16_t));
@@ -242,16 +240,63 @@ bool form_row_env() {
 // up grow with the width, and the wide product kernels do not gain from more workgroups (4096 x 4096: the step at
 // r = 64 takes 0.325 ms with 1024 workgroups, 0.302 with 256; at r = 128 0.514 and 0.473; at r = 16 and 32 it is
 // the other way round).
-int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp) {
+int split_target(bool form, int cp) {
     int target = target_tiles_env();
     if (target == 0) target = cp >= 64 ? kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);
     else if (!form && target > kTargetTilesPlain) target = target / 2;
-    if (base_tiles >= target) return 1;
+    return target;
+}
+// (A launch that reaches three quarters of the target by itself is left whole: the forming pass of the 22 matrices of a
+// 1B-shaped model stored as the transpose, 968 workgroups, is 0.1 ms faster than in halves with their finish_kernel.)
+int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp) {
+    const int target = split_target(form, cp);
+    if (4 * base_tiles >= 3 * target) return 1;
     int64_t s = (target + base_tiles - 1) / base_tiles;
     if (s > kMaxSplit) s = kMaxSplit;
     if (s > min_chunks) s = min_chunks;
     if (s < 1) s = 1;
     return (int)s;
+}
+
+// Splits of one kind of product over the layers of one launch (a launch serves the layers of one orientation, and the
+// launches follow each other, so each has to fill the GPU by itself).  A layer has tiles(p) output blocks, each a walk over
+// chunks(p) steps; with fewer blocks than the target the walks are cut into pieces of about the same number of steps.
+// Either no layer of a launch is split or all are (their sums then all come from finish_kernel).
+// Measured against one split per batch, bounded by its shortest walk: eight small matrices of 64 x 24 to 1000 x 264, fp32,
+// r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 96 us; two 1B-shaped fp32 blocks at r = 16: row product of
+// the two matrices stored as the transpose (64 workgroups before) 101 -> 33 us, step 939 -> 865 us.
+template <class Tiles, class Chunks>
+void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, Tiles tiles, Chunks chunks,
+                 int Plan::*split) {
+    int64_t base = 0, steps = 0;
+    int most = 1;
+    for (int l : ids) {
+        base += tiles(plan[l]);
+        steps += (int64_t)tiles(plan[l]) * chunks(plan[l]);
+        most = std::max(most, (int)chunks(plan[l]));
+    }
+    if (base == 0) return;
+    const int s = choose_split(base, most, form, cp);
+    if (s <= 1) return;
+    // Steps per workgroup: with walks of one length as many pieces as choose_split says, with several lengths the fewest
+    // steps that keep the launch within its target (pieces of one size run in whole rounds of the GPU: 608 of them where
+    // 512 fit at a time took longer than 576 of different lengths, the column product of the two blocks above 107 us
+    // against 92).
+    int64_t per = 1;
+    if (steps != base * most) {
+        auto total = [&](int64_t q) {
+            int64_t n = 0;
+            for (int l : ids) n += (int64_t)tiles(plan[l]) * std::max<int64_t>(2, std::min<int64_t>((chunks(plan[l]) + q - 1) / q, kMaxSplit));
+            return n;
+        };
+        const int64_t target = split_target(form, cp);
+        per = std::max<int64_t>(1, steps / target);
+        while (per < most && total(per) > target) ++per;
+    }
+    for (int l : ids) {
+        const int64_t mine = steps == base * most ? s : (chunks(plan[l]) + per - 1) / per;
+        plan[l].*split = (int)std::max<int64_t>(2, std::min<int64_t>(mine, kMaxSplit));
+    }
 }
 
 void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
@@ -262,10 +307,10 @@ void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
     L.rows = (int)p.d.rows; L.cols = (int)p.d.cols; L.ld = p.d.ld; L.r = p.d.r; L.wz = c->wz;
     L.gdt = p.d.grad_dtype; L.n_workers = c->n_workers; L.transposed = p.transposed; L.planes = c->planes;
     L.rowsP = p.rowsP; L.colsP = p.colsP;
-    L.split_row = c->split_row_b; L.split_col = c->split_col_b;
-    L.split_row_f = c->split_row_bf; L.split_col_f = c->split_col_bf;
-    L.split_row_v2 = c->split_row_v2;
-    L.split_col_v2 = c->split_col_v2;
+    L.split_row = p.split_row; L.split_col = p.split_col;
+    L.split_row_f = p.split_row_f; L.split_col_f = p.split_col_f;
+    L.split_row_v2 = p.split_row_v2;
+    L.split_col_v2 = p.split_col_v2;
     L.G = reinterpret_cast<const void* const*>(ws + c->off_gtab_s[slot]) + (size_t)l * c->n_workers;
     L.S = c->hE.empty() ? nullptr : c->hE[l];
     const int side_p = side_of_role(p.transposed, ROLE_P), side_q = side_of_role(p.transposed, ROLE_Q);
@@ -394,11 +439,14 @@ struct Launcher {
     int n_all, n_norm, n_tr;
     // geometry maxima over the layers addressed by this launcher
     int max_rows = 0, max_cols = 0, max_rowsP = 0, max_colsP = 0;
-    int tiles_row = 0, tiles_col = 0, tiles_outer = 0, blocks_row = 0, blocks_col = 0;
-    int tiles_row_f = 0, tiles_col_f = 0;       // forming passes
-    int tiles_row_v2 = 0, split_row_v2 = 1;     // the forming pass on 32 x 256 tiles
-    int tiles_col_v2 = 0, split_col_v2 = 1;     // the column-mode product on 32 x 256 tiles
-    int split_row = 1, split_col = 1, split_row_f = 1, split_col_f = 1;
+    int tiles_outer = 0;
+    struct Geometry {       // of the layers of one orientation
+        int tiles_row = 0, tiles_col = 0, blocks_row = 0, blocks_col = 0;
+        int tiles_row_f = 0, tiles_col_f = 0;       // forming passes
+        int tiles_row_v2 = 0, tiles_col_v2 = 0;     // the kernels on 32 x 256 tiles
+        bool split_row = false, split_col = false, split_row_f = false, split_col_f = false, split_row_v2 = false,
+             split_col_v2 = false;                  // (all layers of a launch are split or none is)
+    } norm, tr;
     hipError_t err = hipSuccess;
     bool prof_mute = false;   // the refresh's products are not part of the per-kernel timing
     bool capturing = false;   // the stream records into a graph: no event records
@@ -439,8 +487,6 @@ struct Launcher {
         // normal storage: P-like result is L-side -> row mode; transposed storage: column mode
         const int k = prof_begin(p_like ? PSGD_PROF_SWEEP1 : PSGD_PROF_SWEEP2);
         const int ef = epi | (keep_e ? EPI_KEEP_E : 0) | (kept_packs && epi == EPI_PACK ? EPI_KEPT : 0);
-        const int tiles_row = form ? tiles_row_f : this->tiles_row, tiles_col = form ? tiles_col_f : this->tiles_col;
-        const int split_row = form ? split_row_f : this->split_row, split_col = form ? split_col_f : this->split_col;
         const bool onew = ctx->n_workers == 1;
         // forming pass on row-major layers at compress-step widths: the kernel built on 32 x 256 tiles
         // (never inside the gated part of the subspace iteration: its first product carries gate iteration 0,
@@ -452,27 +498,33 @@ struct Launcher {
                               ? reinterpret_cast<const int*>(ws + ctx->off_xtab) : nullptr;
         // the same product on a matrix that is already formed (the refresh's iteration, further power steps)
         const bool r2 = !form && p_like && n_norm > 0 && use_form_row && row_prod_supported(nb, ctx->planes);
-        const bool gram32 = (v2 || r2) && split_row_v2 == 1 && epi == EPI_GRAM && w > 16 && chol_gate >= -1;
+        const bool gram32 = (v2 || r2) && !norm.split_row_v2 && epi == EPI_GRAM && w > 16 && chol_gate >= -1;
         // the second product on row-major layers at those widths likewise
         const bool c2 = !form && !p_like && n_norm > 0 && use_form_row && col_prod_supported(nb, ctx->planes);
         const int* xtab_c = (ctx->xstride > 0 && use_xtab && use_xtab_c && nb >= 2 && ids_norm == ids_all + ctx->n_layers)
                                 ? reinterpret_cast<const int*>(ws + ctx->off_xtab_c) : nullptr;
-        if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, tiles_col_v2, out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
-        else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, p_like ? tiles_row : tiles_col, out_role, ef, gate, st));
-        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, p_like ? tiles_col : tiles_row, out_role, ef, gate, st));
+        if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles_col_v2, out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
+        else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
+        else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
+        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, p_like ? (form ? norm.tiles_row_f : norm.tiles_row) : (form ? norm.tiles_col_f : norm.tiles_col), out_role, ef, gate, st));
+        // the row product of the layers stored with rows < cols (their Q): on 32 x 256 tiles as well, where finish_kernel
+        // or a plain set of operand copies completes it (22 matrices 2048 x 5632 of a 1B-shaped bf16 model at r = 32, not
+        // split: 275 us on prod_kernel's 128 x 64 tiles, 262 on these; two of them in fp32 at r = 16, split: 101 -> 33)
+        const bool t2 = !form && !p_like && n_tr > 0 && use_form_row && row_prod_supported(nb, ctx->planes) && (tr.split_row_v2 || epi == EPI_PACK);
+        if (t2) note(launch_row_prod(nb, ctx->planes, layers, ids_tr, n_tr, tr.tiles_row_v2, out_role, ef, gate, ctx->nt_mt ? 1 : 0, nullptr, 0, 0, st));
+        else note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, p_like ? (form ? tr.tiles_col_f : tr.tiles_col) : (form ? tr.tiles_row_f : tr.tiles_row), out_role, ef, gate, st));
         prof_end(k);
         // split reductions are completed (and the epilogue run) by a second, small launch, whose last
         // workgroup per layer also factorises the Gram matrix; unsplit products need a launch for that
         const bool rv2 = v2 || r2;
-        const bool split_n = rv2 ? split_row_v2 > 1 : c2 ? split_col_v2 > 1 : (p_like ? split_row > 1 : split_col > 1), split_t = p_like ? split_col > 1 : split_row > 1;
-        if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? blocks_row : blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
-        if (split_t) note(launch_finish(p_like, form ? 1 : 0, layers, ids_tr, n_tr, p_like ? blocks_col : blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
+        const bool split_n = n_norm > 0 && (rv2 ? norm.split_row_v2 : c2 ? norm.split_col_v2 : p_like ? (form ? norm.split_row_f : norm.split_row) : (form ? norm.split_col_f : norm.split_col));
+        const bool split_t = n_tr > 0 && (t2 ? tr.split_row_v2 : p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
+        if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
+        if (split_t) note(launch_finish(p_like, t2 ? 2 : form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself where the
         // factorisation is a launch of its own -- widths above 16 --, and leaves them to a small pass over the result,
         // one per 128 rows, where the apply kernel factorises for itself)
-        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, blocks_row, out_role, 32 * nb, gate, st));
+        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks_row, out_role, 32 * nb, gate, st));
         // (after a split product only the layers finish_kernel leaves to it -- wide, many Gram slots -- and none at
         // widths where there are no such layers)
         if (chol_gate >= -1) {
@@ -537,24 +589,21 @@ struct Launcher {
     }
 };
 
-void geometry(const psgd_ctx* c, int l, int split_row, int split_col, int split_row_f, int split_col_f, Launcher& L) {
-    const Plan& p = c->plan[l];
+void geometry(const Plan& p, Launcher& L) {
     auto mx = [](int& a, int b) { if (b > a) a = b; };
     mx(L.max_rows, (int)p.d.rows); mx(L.max_cols, (int)p.d.cols);
     mx(L.max_rowsP, p.rowsP); mx(L.max_colsP, p.colsP);
-    mx(L.tiles_row, (int)((p.d.rows + 127) / 128) * split_row);
-    mx(L.tiles_col, (int)((p.d.cols + 127) / 128) * split_col);
-    mx(L.tiles_row_f, (int)((p.d.rows + 127) / 128) * split_row_f);
-    mx(L.tiles_col_f, (int)((p.d.cols + 127) / 128) * split_col_f);
-    mx(L.blocks_row, (int)((p.d.rows + 127) / 128));
-    mx(L.blocks_col, (int)((p.d.cols + 127) / 128));
-    L.split_row = split_row; L.split_col = split_col;
-    L.split_row_f = split_row_f; L.split_col_f = split_col_f;
-    L.split_row_v2 = c->split_row_v2;
-    mx(L.tiles_row_v2, (p.rowsP / 32) * c->split_row_v2);
-    L.split_col_v2 = c->split_col_v2;
-    mx(L.tiles_col_v2, ((p.colsP + 255) / 256) * c->split_col_v2);
-    mx(L.tiles_outer, (int)((p.d.rows + 127) / 128) * (int)((p.d.cols + 127) / 128));
+    const int rb = (int)((p.d.rows + 127) / 128), cb = (int)((p.d.cols + 127) / 128);
+    mx(L.tiles_outer, rb * cb);
+    Launcher::Geometry& g = p.transposed ? L.tr : L.norm;
+    mx(g.blocks_row, rb); mx(g.blocks_col, cb);
+    mx(g.tiles_row, rb * p.split_row); mx(g.tiles_col, cb * p.split_col);
+    mx(g.tiles_row_f, rb * p.split_row_f); mx(g.tiles_col_f, cb * p.split_col_f);
+    mx(g.tiles_row_v2, (p.rowsP / 32) * p.split_row_v2);
+    mx(g.tiles_col_v2, ((p.colsP + 255) / 256) * p.split_col_v2);
+    g.split_row |= p.split_row > 1; g.split_col |= p.split_col > 1;
+    g.split_row_f |= p.split_row_f > 1; g.split_col_f |= p.split_col_f > 1;
+    g.split_row_v2 |= p.split_row_v2 > 1; g.split_col_v2 |= p.split_col_v2 > 1;
 }
 
 Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
@@ -566,7 +615,7 @@ Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
     const int* ids = reinterpret_cast<const int*>(L.ws + ctx->off_ids);
     L.ids_all = ids; L.ids_norm = ids + nl; L.ids_tr = ids + 2 * (size_t)nl;
     L.n_all = nl; L.n_norm = (int)ctx->lists.norm.size(); L.n_tr = (int)ctx->lists.tr.size();
-    for (int l = 0; l < nl; ++l) geometry(ctx, l, ctx->split_row_b, ctx->split_col_b, ctx->split_row_bf, ctx->split_col_bf, L);
+    for (const Plan& p : ctx->plan) geometry(p, L);
     L.use_form_row = form_row_env();
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab = v == 1; }
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB_C"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab_c = v == 1; }
@@ -706,39 +755,35 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
     }
     if (rc != PSGD_OK) { delete c; return rc; }
     // reduction splits of the batched launches
-    int64_t base_row = 0, base_col = 0;
-    int min_chunks_row = 1 << 30, min_chunks_col = 1 << 30;
-    for (auto& p : c->plan) {
-        base_row += (p.d.rows + 127) / 128;
-        base_col += (p.d.cols + 127) / 128;
-        const int cr = (int)((p.d.cols + 63) / 64), cc = (int)((p.d.rows + 63) / 64);
-        if (cr < min_chunks_row) min_chunks_row = cr;
-        if (cc < min_chunks_col) min_chunks_col = cc;
+    for (const std::vector<int>* ids : {&c->lists.norm, &c->lists.tr}) {
+        auto row_tiles = [](const Plan& p) { return (int)((p.d.rows + 127) / 128); };
+        auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
+        auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
+        auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
+        plan_splits(c->plan, *ids, false, c->cpc, row_tiles, row_chunks, &Plan::split_row);
+        plan_splits(c->plan, *ids, false, c->cpc, col_tiles, col_chunks, &Plan::split_col);
+        plan_splits(c->plan, *ids, true, c->cpc, row_tiles, row_chunks, &Plan::split_row_f);
+        plan_splits(c->plan, *ids, true, c->cpc, col_tiles, col_chunks, &Plan::split_col_f);
+        // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split), their
+        // column products, and the row products of the layers stored with rows < cols
+        auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
+        auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
+        auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
+        auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
+        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, row_tiles_v2, row_chunks_v2, &Plan::split_row_v2);
+        plan_splits(c->plan, *ids, false, 32, col_tiles_v2, col_chunks_v2, &Plan::split_col_v2);
     }
-    c->split_row_b = choose_split(base_row, min_chunks_row, false, c->cpc);
-    c->split_col_b = choose_split(base_col, min_chunks_col, false, c->cpc);
-    c->split_row_bf = choose_split(base_row, min_chunks_row, true, c->cpc);
-    c->split_col_bf = choose_split(base_col, min_chunks_col, true, c->cpc);
     {
-        // the forming pass on 32 x 256 tiles: row-major layers only
-        int64_t base = 0, base_c = 0, m_bytes = 0;
-        int min_chunks = 1 << 30, min_chunks_c = 1 << 30;
+        int64_t m_bytes = 0, mt_bytes = 0;
         bool f32 = false, b16 = false;
         for (auto& p : c->plan) {
             (p.d.grad_dtype == PSGD_F32 ? f32 : b16) = true;
-            if (p.transposed) continue;
-            base += p.rowsP / 32;
-            base_c += (p.colsP + 255) / 256;
-            m_bytes += p.d.rows * p.d.cols * 4;
-            const int ch = (int)((p.d.cols + 255) / 256), chc = (int)((p.d.rows + 31) / 32);
-            if (ch < min_chunks) min_chunks = ch;
-            if (chc < min_chunks_c) min_chunks_c = chc;
+            (p.transposed ? mt_bytes : m_bytes) += p.d.rows * p.d.cols * 4;
         }
-        c->split_row_v2 = base > 0 ? choose_split(base, min_chunks, true, 32) : 1;
-        c->split_col_v2 = base_c > 0 ? choose_split(base_c, min_chunks_c, false, 32) : 1;
         c->grad_kind = f32 && b16 ? 0 : (f32 ? 1 : 2);
         // M that the second pass can find in the 256 MB memory-side cache is stored with plain stores
         c->nt_m = m_bytes > ((int64_t)96 << 20);
+        c->nt_mt = mt_bytes > ((int64_t)96 << 20);
         if (const char* e = std::getenv("PSGD_NT_M")) c->nt_m = e[0] != '0';     // (measurement knob)
         // XCD table: the row-major layers (positions in the id list `norm`), largest first, each to the XCD with the
         // least work so far
@@ -768,8 +813,8 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
                     if (total[x] > xtiles) xtiles = total[x];
                 }
             };
-            build(c->hXtab, c->xtiles, [&](int pos) { return (c->plan[c->lists.norm[pos]].rowsP / 32) * c->split_row_v2; });
-            build(c->hXtabC, c->xtiles_c, [&](int pos) { return ((c->plan[c->lists.norm[pos]].colsP + 255) / 256) * c->split_col_v2; });
+            build(c->hXtab, c->xtiles, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return (p.rowsP / 32) * p.split_row_v2; });
+            build(c->hXtabC, c->xtiles_c, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return ((p.colsP + 255) / 256) * p.split_col_v2; });
         }
     }
     // workspace layout
@@ -1101,9 +1146,12 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     D.S = const_cast<float*>(M);
     D.thin[ROLE_P].ptr = P;
     D.thin[ROLE_Q].ptr = Q;
-    D.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz);
-    D.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz);
-    D.split_row_f = D.split_row; D.split_col_f = D.split_col;      // (no forming pass in this call)
+    Plan one = p;
+    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz);
+    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz);
+    one.split_row_f = one.split_row; one.split_col_f = one.split_col;      // (no forming pass in this call)
+    D.split_row = one.split_row; D.split_col = one.split_col;
+    D.split_row_f = one.split_row_f; D.split_col_f = one.split_col_f;
     D.part[0] = reinterpret_cast<float*>(ws + ctx->off_single_part[0]);
     D.part[1] = reinterpret_cast<float*>(ws + ctx->off_single_part[1]);
     ctx->hLayers[ctx->n_layers] = D;
@@ -1117,7 +1165,7 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     L.ids_all = ids; L.n_all = 1;
     L.ids_norm = ids; L.n_norm = p.transposed ? 0 : 1;
     L.ids_tr = ids; L.n_tr = p.transposed ? 1 : 0;
-    geometry(ctx, layer, D.split_row, D.split_col, D.split_row_f, D.split_col_f, L);
+    geometry(one, L);
     refresh_sequence(ctx, L, false, false, sigma, 0);
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;

@@ -155,14 +155,16 @@ __device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, i
             a[i] = __builtin_fma(-bcast_lane(ak, i), mult, a[i]);   // row i <- row i - R[k][i] row k  (on a matrix lane
                                                                     // j < i an entry below the diagonal: never read)
     }
-    double csc[W];                                                // (scale: see next_scale)
+    if (scale) {                                          // (uniform: every lane takes part in the lane reads)
+        const double csc_own = next_scale(dsc_own);
 #pragma unroll
-    for (int i = 0; i < W; ++i) csc[i] = scale ? next_scale(bcast_lane(dsc_own, i < w ? i : 0)) : 1.0;
+        for (int i = 0; i < W; ++i) a[i] *= bcast_lane(csc_own, i < w ? i : 0);
+    }
     // lane 16 + c: row c of tmat = D T with the dependent columns zeroed
     if (aug && j < 16 + w) {
 #pragma unroll
         for (int i = 0; i < W; ++i)
-            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : a[i] * dsc_row * csc[i];
+            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : a[i] * dsc_row;
     }
     if (j == 0) {
         const int nbad = __popc(badmask & ((1 << w) - 1));

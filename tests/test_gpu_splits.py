@@ -1,0 +1,58 @@
+"""Batches of layers of very different sizes and both orientations: every launch cuts its layers' reductions into pieces of
+about the same length, so one batch holds layers cut many times, twice, and (where a launch fills the GPU) not at all."""
+import numpy as np
+import pytest
+
+from oracle import psgd_oracle as orc
+from paper_2509_11254_amd import synth
+from gpu_harness import Case, back, logical, to_dev_grad
+
+pytestmark = pytest.mark.gpu
+
+MIXED = [(72, 200), (200, 72), (264, 1000), (1000, 264), (64, 64), (70, 2056), (2056, 70), (130, 136), (65, 80)]
+TOL = {synth.F32: 1e-4, synth.BF16: 2e-2}
+
+
+# r = 8: operands 32 wide; r = 33: 64 wide; 24 layers of 1000 rows: row products on 768 workgroups, not split; deferred
+# residual: kept operand copies from the row product (width 32) and none for these layers (width 64)
+@pytest.mark.parametrize("shapes", [MIXED, [(72, 264)], [(1000, 1032)] * 24], ids=["mixed", "single", "unsplit"])
+@pytest.mark.parametrize("r,dtype,lazy", [(8, synth.F32, False), (33, synth.BF16, False), (8, synth.BF16, True), (33, synth.F32, True)])
+def test_ssp_steps(shapes, r, dtype, lazy):
+    rng = np.random.default_rng(len(shapes) * 100 + r)
+    n_workers, steps = 2, 2
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    sig = [rng.standard_normal((rw, 12)) * 0.7 ** np.arange(12) @ rng.standard_normal((12, cl)) for rw, cl in shapes]
+
+    def grad(s):
+        g = (s + 0.05 * rng.standard_normal(s.shape)).astype(np.float32)
+        return synth.round_to_bf16(g) if dtype == synth.BF16 else g
+
+    case = Case(shapes, r, n_workers, dtype, lds=lds, lazy_residual=lazy)
+    errs = [(0.05 * rng.standard_normal(s)).astype(np.float32) for s in shapes]
+    qs = []
+    for s in sig:                                            # (a Q of a run under way: near the leading subspace)
+        v = np.linalg.svd(logical(s, *s.shape), full_matrices=False)[2][:r].T
+        qs.append((v + 0.02 * rng.standard_normal(v.shape)).astype(np.float32))
+    q_or = [q.astype(np.float64) for q in qs]
+    e_or = [logical(e.astype(np.float64), *e.shape) for e in errs]
+    for t in range(steps):
+        grads = [[grad(s) for _ in range(n_workers)] for s in sig]
+        if t == 0:
+            case.upload(grads, errs, qs)
+        else:
+            case.G = [[to_dev_grad(g, lds[l]) for g in grads[l]] for l in range(len(shapes))]
+        case.compress()
+        for l, (rw, cl) in enumerate(shapes):
+            g = [logical(synth.gradient_as_f64(x), rw, cl) for x in grads[l]]
+            m = np.mean(g, axis=0) + e_or[l]
+            out = orc.ssp_comp(q_or[l], [m])
+            p, q = back(case.P[l]), back(case.Q[l])
+            # (bound: that of the parity tests, relative Frobenius)
+            assert orc.rel_fro(p @ q.T, out.delta_hat) <= TOL[dtype], (t, l, rw, cl)
+            assert np.abs(p.T @ p - np.eye(r)).max() < 2e-5, (t, l, rw, cl)
+            # the next step continues from the library's own factors, as its error buffer does
+            q_or[l], e_or[l] = q, m - p @ q.T
+    if lazy:
+        case.comp.flush_residual(case.E)
+    for l, (rw, cl) in enumerate(shapes):
+        assert orc.rel_fro(logical(back(case.E[l], cl), rw, cl), e_or[l]) <= TOL[dtype], (l, rw, cl)
