@@ -46,15 +46,16 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
 hipError_t launch_pack(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int role_a, int role_b,
                        int cp, int which, hipStream_t st);
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows, int gate, int a2gate, int local_ok, int after_finish, hipStream_t st);
-hipError_t launch_slot_sum(const LayerDev* layers, const int* ids, int n_ids, int max_len, int role, int slot_rows,
-                           int group, int gate, hipStream_t st);
+                       int slot_rows, int gate, int a2gate, int local_ok, hipStream_t st);
+hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
+                           hipStream_t st);
+int finish_rows(int w);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, hipStream_t st);
 hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, int max_len, int w, int dst_role,
                              int src_role, int warm, uint32_t seed, hipStream_t st);
-hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, float* sigma_out,
+hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t n_bytes, hipStream_t st);
 hipError_t launch_put(void* dst, const void* src_host, size_t bytes, hipStream_t st);
@@ -447,6 +448,7 @@ struct Launcher {
         bool split_row = false, split_col = false, split_row_f = false, split_col_f = false, split_row_v2 = false,
              split_col_v2 = false;                  // (all layers of a launch are split or none is)
     } norm, tr;
+    int gram_rows_n = kGramRows1, gram_rows_t = kGramRows1;   // rows per Gram slot of the last product, per orientation
     hipError_t err = hipSuccess;
     bool prof_mute = false;   // the refresh's products are not part of the per-kernel timing
     bool capturing = false;   // the stream records into a graph: no event records
@@ -519,20 +521,29 @@ struct Launcher {
         const bool rv2 = v2 || r2;
         const bool split_n = n_norm > 0 && (rv2 ? norm.split_row_v2 : c2 ? norm.split_col_v2 : p_like ? (form ? norm.split_row_f : norm.split_row) : (form ? norm.split_col_f : norm.split_col));
         const bool split_t = n_tr > 0 && (t2 ? tr.split_row_v2 : p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
-        if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
-        if (split_t) note(launch_finish(p_like, t2 ? 2 : form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, chol_gate, a2gate, tol2, w, small ? 1 : 0, st));
+        // Widths above kWideWidth: the partial Gram matrices are added up by a launch that spreads over the chip, and one
+        // launch of the factorisation serves both orientations.
+        const int ww = w > 0 ? w : 32 * nb;
+        const bool wide = ww > kWideWidth;
+        const int fin_gate = wide ? -2 : chol_gate;
+        if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        if (split_t) note(launch_finish(p_like, t2 ? 2 : form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself where the
         // factorisation is a launch of its own -- widths above 16 --, and leaves them to a small pass over the result,
         // one per 128 rows, where the apply kernel factorises for itself)
         if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks_row, out_role, 32 * nb, gate, st));
-        // (after a split product only the layers finish_kernel leaves to it -- wide, many Gram slots -- and none at
-        // widths where there are no such layers)
+        gram_rows_n = gram32 ? 32 : split_n ? finish_rows(ww) : kGramRows1;
+        gram_rows_t = split_t ? finish_rows(ww) : kGramRows1;
         if (chol_gate >= -1) {
-            // (32-row slots: added up in groups of 16 side by side first, the factorisation's one workgroup per layer
-            // would otherwise spend most of its time on that sum)
-            if (gram32) note(launch_slot_sum(layers, ids_norm, n_norm, max_rows, out_role, 32, 16, gate, st));
-            if (!split_n || w > 16) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? 32 : kGramRows1, chol_gate, a2gate, small ? 1 : 0, gram32 ? 16 : (split_n ? 1 : 0), st));
-            if (!split_t || w > 16) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, kGramRows1, chol_gate, a2gate, small ? 1 : 0, split_t ? 1 : 0, st));
+            // (the many 32-row slots are added up before at any width)
+            if (wide || gram32) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, chol_gate, st));
+            if (wide) {
+                note(launch_gram_sum(layers, ids_tr, n_tr, ww, out_role, gram_rows_t, chol_gate, st));
+                note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, kOneSlot, chol_gate, a2gate, 0, st));
+            } else {
+                if (!split_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
+                if (!split_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
+            }
         }
     }
     // thin[out_role] = product as in prod(), then CholeskyQR2 on it: the first pass always, the second
@@ -552,7 +563,7 @@ struct Launcher {
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, g, a2, tol2, small, wh, st));
         if (a2 != -2) {
             const int g2 = a2 == -1 ? g : a2;
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g2, -2, 0, 0, st));
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g2, -2, 0, st));
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g2, a2, tol2, small, wh, st));
         }
     }
@@ -561,9 +572,10 @@ struct Launcher {
         const bool small = w <= 16;
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, st));
-        note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, kGramRows1, -1, -1, small ? 1 : 0, 0, st));
+        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, st));
+        note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, w > kWideWidth ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, st));
-        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, -1, -2, 0, 0, st));
+        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, st));
     }
     void residual(int nb, bool form = false) {
@@ -659,7 +671,12 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     }
     L.gate = -1;
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)
-    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, sigma_out, L.st));
+    const bool wide = wz > kWideWidth;
+    if (wide) {
+        L.note(launch_gram_sum(L.layers, L.ids_norm, L.n_norm, wz, ROLE_ZQ, L.gram_rows_n, -1, L.st));
+        L.note(launch_gram_sum(L.layers, L.ids_tr, L.n_tr, wz, ROLE_ZQ, L.gram_rows_t, -1, L.st));
+    }
+    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
                         final_cp, -1, -2, 0.0, false, 3, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZQ, ROLE_Q, APPLY_RITZ,

@@ -209,22 +209,23 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
     }
 }
 
-// Epilogue on a complete 128 x cp output tile held in LDS as fp32 [BT][tw]: store the rows of the
+// Epilogue on a complete ROWS x cp output tile held in LDS as fp32 [ROWS][tw]: store the rows of the
 // thin result, then either the partial Gram matrix of these rows (fp64, upper triangle, slot = block
 // index) or the split-bf16 operand copies of the rows.  Called by all threads of the workgroup.
+template <int ROWS>
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
                                      int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
                                      int copies = 3) {
     const int t = threadIdx.x;
     const int w = T.width;
-    for (int e = t; copies != 2 && e < BT * w; e += kThreads) {
+    for (int e = t; copies != 2 && e < ROWS * w; e += kThreads) {
         const int row = e / w, col = e % w;
-        if (ob * BT + row < out_len) as_global(T.ptr)[(int64_t)(ob * BT + row) * T.ld + col] = otile[row * tw + col];
+        if (ob * ROWS + row < out_len) as_global(T.ptr)[(int64_t)(ob * ROWS + row) * T.ld + col] = otile[row * tw + col];
     }
     if (epi == EPI_GRAM) {
-        gram_tile_f64(otile, tw, BT, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2));
+        gram_tile_f64(otile, tw, ROWS, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2));
     } else if (epi == EPI_PACK) {
-        write_packs(L.pack[out_side], L.planes, otile, tw, cp, ob * BT, BT, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
+        write_packs(L.pack[out_side], L.planes, otile, tw, cp, ob * ROWS, ROWS, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
     }
 }
 
@@ -633,16 +634,19 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
             otile[row * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+    tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
-// Sum of the partial products of a split launch + the same epilogue.  One workgroup per 128-row
-// output block; the partials are added in split order, so the result is deterministic.
+// Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
+// Gram matrix); the partials are added in split order, so the result is deterministic.
+// FB = 128 for narrow blocks.  Above width 32 the kernel is a pass over [split][width][rows] floats and the fp64 MFMAs of the
+// Gram matrix, with no more workgroups than row blocks: 64 rows each give it twice as many (8192 x 160, four partial sums:
+// 57 -> 20 us, of which the smaller register need without the factorisation's code is a part).
 // chol_gate >= -1: the last workgroup to finish a layer goes on to factorise the sum of the partial Gram
 // matrices (first CholeskyQR pass) if that gate is open, unless the layer is one where the apply kernel
-// does that for itself or one that is left to the chol_kernel launch that follows (see there); -2: no
-// factorisation follows.
+// does that for itself; -2: no factorisation follows, or one in a launch of its own.
 static_assert(BT == kGramRows1, "one partial Gram matrix per output block of a product");
+template <int FB>
 __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __restrict__ layers,
                                                           const int* __restrict__ ids, int colmode, int cp,
                                                           int out_role, int epi_flags, int gate, int chol_gate,
@@ -659,17 +663,17 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
     const int n_split = form == 2 ? L.split_row_v2 : form == 3 ? L.split_col_v2
                         : form ? (colmode ? L.split_col_f : L.split_row_f) : (colmode ? L.split_col : L.split_row);
     const int ob = blockIdx.x;
-    if (n_split <= 1 || ob * BT >= out_len) return;
     const int out_lenP = side_lenP(L, out_side);
+    if (n_split <= 1 || ob * FB >= out_lenP) return;      // (the operand copies' padding is written as well)
     const ThinRef T = L.thin[out_role];
     extern __shared__ __align__(16) unsigned char smem[];
-    float* otile = reinterpret_cast<float*>(smem);    // [BT][cp + 1]
+    float* otile = reinterpret_cast<float*>(smem);    // [FB][cp + 1]
     const int tw = cp + 1;
     const int t = threadIdx.x;
-    for (int e = t; e < BT * cp; e += kThreads) otile[(e / cp) * tw + e % cp] = 0.f;
+    for (int e = t; e < FB * cp; e += kThreads) otile[(e / cp) * tw + e % cp] = 0.f;
     __syncthreads();
     const int64_t plane = (int64_t)out_lenP * T.width;
-    const PSGD_GLOBAL float* __restrict__ src = as_global(L.part[out_side]) + (int64_t)ob * BT;
+    const PSGD_GLOBAL float* __restrict__ src = as_global(L.part[out_side]) + (int64_t)ob * FB;
     // U items per thread at a time (two where a thread has several: 16 loads of 16 bytes in flight at a split of 8;
     // four spill), eight splits per batch.  Every sum runs in split order.
     auto reduce_items = [&](auto u_tag, int first, int last) {
@@ -680,7 +684,7 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int item = item0 + u * kThreads < last ? item0 + u * kThreads : item0;     // (clamped: a valid address)
-                sc[u] = src + (int64_t)(item / (BT / 4)) * out_lenP + 4 * (item % (BT / 4));
+                sc[u] = src + (int64_t)(item / (FB / 4)) * out_lenP + 4 * (item % (FB / 4));
                 sum[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
             int s2 = 0;
@@ -706,7 +710,7 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
             for (int u = 0; u < U; ++u) {
                 const int item = item0 + u * kThreads;
                 if (item >= last) continue;
-                const int col = item / (BT / 4), r4 = 4 * (item % (BT / 4));
+                const int col = item / (FB / 4), r4 = 4 * (item % (FB / 4));
                 otile[(r4 + 0) * tw + col] = sum[u].x;
                 otile[(r4 + 1) * tw + col] = sum[u].y;
                 otile[(r4 + 2) * tw + col] = sum[u].z;
@@ -715,22 +719,18 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
         }
     };
     {
-        const int n_items = T.width * (BT / 4);
+        const int n_items = T.width * (FB / 4);
         if (n_items >= 2 * kThreads) reduce_items(std::integral_constant<int, 2>{}, 0, n_items);
         else reduce_items(std::integral_constant<int, 1>{}, 0, n_items);
     }
     __syncthreads();
-    tile_epilogue(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
-    if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && gate_open(L, chol_gate)) {
-        const int n_wg = (out_len + BT - 1) / BT;      // = number of Gram slots (BT == kGramRows1)
-        if (grouped_slot_sum(T.width, n_wg)) {
-            // wide block, many slots: add the slots up in groups here, side by side; a launch of chol_kernel with
-            // twice the threads does the rest
-            const int grp = ob / kSlotGroup;
-            const int in_grp = min(kSlotGroup, n_wg - grp * kSlotGroup);
-            if (last_to_arrive(&L.status[8 + grp], in_grp, &s_last)) sum_slot_group(L.gram, T.width, n_wg, grp);
-        } else if (last_to_arrive(&L.status[6], n_wg, &s_last)) {
-            chol_body(L, out_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, 1, scales_next(L, out_role, chol_gate));
+    tile_epilogue<FB>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+    // (FB = 64 is for widths whose factorisation is a launch of its own)
+    if constexpr (FB == BT) {
+        if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && gate_open(L, chol_gate)) {
+            const int n_wg = (out_len + FB - 1) / FB;      // = number of Gram slots
+            if (last_to_arrive(&L.status[6], n_wg, &s_last))
+                chol_body(L, out_role, tol2, 1, FB, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, scales_next(L, out_role, chol_gate));
         }
     }
 }
@@ -777,19 +777,25 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
     return hipGetLastError();
 }
 
+// Rows per workgroup and Gram slot.  w: widest block of the launch
+int finish_rows(int w) { return w > kWideWidth ? BT / 2 : BT; }
+
+// max_blocks: 128-row blocks of the longest result
 hipError_t launch_finish(bool colmode, int form, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st) {
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
-    dim3 grid(max_blocks, n_ids), block(kThreads);
-    size_t lds = (size_t)BT * (cp + 1) * sizeof(float);
+    const int fb = finish_rows(w > 0 ? w : cp);
+    dim3 grid(max_blocks * (BT / fb), n_ids), block(kThreads);
+    auto kfn = fb == BT ? finish_kernel<BT> : finish_kernel<BT / 2>;
+    size_t lds = (size_t)fb * (cp + 1) * sizeof(float);
     if (chol_gate >= -1 && chol_lds_bytes_upto(w) > lds) lds = chol_lds_bytes_upto(w);
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(finish_kernel),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(finish_kernel, grid, block, lds, st, layers, ids, colmode ? 1 : 0, cp, out_role, epi, gate,
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, colmode ? 1 : 0, cp, out_role, epi, gate,
                        chol_gate, a2gate, tol2, local_ok, form);
     return hipGetLastError();
 }

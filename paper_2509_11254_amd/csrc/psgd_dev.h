@@ -50,6 +50,10 @@ constexpr int kThreads = 256;      // 4 wavefronts of 64 lanes
 constexpr int kLenPad = 128;       // packed operand rows are padded (with zeros) to this multiple
 constexpr int kGramRows1 = 128;    // rows per partial Gram matrix written by a product's epilogue
 constexpr int kGramRows2 = 64;     // rows per partial Gram matrix written by the apply kernel
+// slot_rows of a Gram matrix that gram_sum_kernel has added up
+constexpr int kOneSlot = 1 << 30;
+// widths above this: the partial Gram matrices are added up by gram_sum_kernel, the factorisation is a launch of its own
+constexpr int kWideWidth = 32;
 
 enum Side { SIDE_L = 0, SIDE_W = 1 };
 // Roles: the paper's P~ and Q (user buffers, leading dimension r) and the two wide internal

@@ -89,81 +89,66 @@ hipError_t launch_max_iterations(const LayerDev* layers, const int* ids, int n_i
 // chol: one workgroup per layer runs the factorisation on the partial Gram matrices that the producing
 // kernel has left (used when that kernel cannot hand over to it itself).
 // --------------------------------------------------------------------------------------------
-// after_finish: the launch follows a split product's finish_kernel, which has factorised every layer itself except
-// the wide ones with many Gram slots: those it has only added up in groups (grouped_slot_sum) and left to this
-// kernel, which brings 512 threads to the serial part instead of the 256 of a finish workgroup.
 template <int NT>
 __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ layers,
                                                   const int* __restrict__ ids, int role, double tol2,
                                                   int pass, int slot_rows, int gate, int a2gate,
-                                                  int local_ok, int after_finish) {
+                                                  int local_ok) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
     if (pass == 2 && L.status[1] == 0) return;
     if (pass == 1 && local_chol(L, role, local_ok)) return;       // the apply kernel factorises for itself
-    int stride = after_finish > 1 ? after_finish : 1;     // (> 1: slot_sum_kernel has added the slots up in such groups)
-    if (after_finish == 1) {
-        const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
-        if (!grouped_slot_sum(L.thin[role].width, n_slots)) return;
-        stride = kSlotGroup;
-    }
     extern __shared__ __align__(16) unsigned char smem[];
-    chol_body(L, role, tol2, pass, slot_rows, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, stride,
+    chol_body(L, role, tol2, pass, slot_rows, allow2_of(L, a2gate), smem, L.tmat, true, nullptr,
               pass == 1 && scales_next(L, role, gate));
 }
 
 // --------------------------------------------------------------------------------------------
-// slot sum: the partial Gram matrices of thin[role] added up in groups of `group` consecutive slots, each sum left in
-// its group's first slot (fixed order).  For producers that leave many small slots (one per 32 rows): the
-// factorisation's one workgroup per layer then adds up one matrix per group.
+// gram sum: the partial Gram matrices of thin[role] (one per slot_rows rows) added up, fixed order, the sum left in the first
+// slot.  A workgroup owns 64 entries and its four waves every fourth slot each, 16 loads in flight per thread: the sum of
+// 64 slots of width 160 (6.6 MB) is a microsecond-scale pass over the chip instead of the factorisation's one workgroup
+// reading all of it.
 // --------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void slot_sum_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
-                                                            int role, int slot_rows, int group, int gate) {
-    typedef double doublex2 __attribute__((ext_vector_type(2)));
+__global__ __launch_bounds__(kThreads) void gram_sum_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
+                                                            int role, int slot_rows, int gate) {
+    __shared__ double part[4][64];
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;       // (the slots of a layer whose iteration is over hold what its Ritz step needs)
-    const int len = side_len(L, side_of_role(L.transposed, role));
-    const int n_slots = (len + slot_rows - 1) / slot_rows;
-    const int first = blockIdx.x * group;
-    if (first >= n_slots) return;
-    const int cnt = min(group, n_slots - first);
+    const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
     const int w = L.thin[role].width;
     const int ntri = (w * (w + 1)) / 2;
-    PSGD_GLOBAL double* g0 = as_global(L.gram) + (int64_t)first * ntri;
-    const int t = threadIdx.x;
-    if ((ntri & 1) == 0 && (((int64_t)first * ntri) & 1) == 0) {
-        for (int e = 2 * t; e < ntri; e += 2 * kThreads) {
-            doublex2 x[16];
+    if ((int)blockIdx.x * 64 >= ntri || n_slots <= 1) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane;
+    PSGD_GLOBAL double* g = as_global(L.gram) + (e < ntri ? e : 0);
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    for (int sl = wv; sl < n_slots; sl += 64) {
+        double x[16];
 #pragma unroll
-            for (int d = 0; d < 16; ++d)
-                x[d] = *reinterpret_cast<const PSGD_GLOBAL doublex2*>(g0 + (int64_t)(d < cnt ? d : 0) * ntri + e);
-            doublex2 sacc = x[0];
+        for (int d = 0; d < 16; ++d) x[d] = g[(int64_t)(sl + 4 * d < n_slots ? sl + 4 * d : wv) * ntri];
 #pragma unroll
-            for (int d = 1; d < 16; ++d) if (d < cnt) sacc += x[d];
-            *reinterpret_cast<PSGD_GLOBAL doublex2*>(g0 + e) = sacc;
-        }
-    } else {
-        for (int e = t; e < ntri; e += kThreads) {
-            double sacc = g0[e];
-            for (int d = 1; d < cnt; ++d) sacc += g0[(int64_t)d * ntri + e];
-            g0[e] = sacc;
-        }
+        for (int d = 0; d < 16; ++d) if (sl + 4 * d >= n_slots) x[d] = 0.0;
+#pragma unroll
+        for (int d = 0; d < 16; d += 4) { s0 += x[d]; s1 += x[d + 1]; s2 += x[d + 2]; s3 += x[d + 3]; }
     }
+    part[wv][lane] = (s0 + s1) + (s2 + s3);
+    __syncthreads();
+    if (wv == 0 && e < ntri) g[0] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
 }
 
-// group <= 16; gate: iteration gate of the refresh (-1: none)
-hipError_t launch_slot_sum(const LayerDev* layers, const int* ids, int n_ids, int max_len, int role, int slot_rows,
-                           int group, int gate, hipStream_t st) {
-    if (n_ids <= 0 || group < 2 || group > 16) return n_ids <= 0 ? hipSuccess : hipErrorInvalidValue;
-    const int groups = ((max_len + slot_rows - 1) / slot_rows + group - 1) / group;
-    hipLaunchKernelGGL(slot_sum_kernel, dim3(groups, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows, group, gate);
+// w: the widest of the layers' blocks; gate: iteration gate of the refresh (-1: none)
+hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
+                           hipStream_t st) {
+    if (n_ids <= 0) return hipSuccess;
+    const int ntri = (w * (w + 1)) / 2;
+    hipLaunchKernelGGL(gram_sum_kernel, dim3((ntri + 63) / 64, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows, gate);
     return hipGetLastError();
 }
 
-// Widths that take the blocked factorisation get 512 threads: its panels, trailing updates, the blocked inverse and
-// the slot sum are dealt to the waves (1024 threads halve the registers a thread may hold, and measured slower).
+// Widths above 32 get 512 threads: the panels and trailing updates of the blocked factorisation are dealt to the waves
+// (1024 threads halve the registers a thread may hold, and measured slower).
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows, int gate, int a2gate, int local_ok, int after_finish, hipStream_t st) {
+                       int slot_rows, int gate, int a2gate, int local_ok, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const bool wide = w > 32;
     dim3 grid(1, n_ids), block(wide ? 512 : kThreads);
@@ -175,7 +160,7 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, tol2, pass, slot_rows, gate, a2gate,
-                       local_ok, after_finish);
+                       local_ok);
     return hipGetLastError();
 }
 
@@ -240,7 +225,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
         }
         double* tml = reinterpret_cast<double*>(smem + main_lds);
         chol_body<true>(L, src_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
-                  tml, blockIdx.x == 0, &s_need2, 1, scales_next(L, src_role, gate));
+                  tml, blockIdx.x == 0, &s_need2, scales_next(L, src_role, gate));
         __syncthreads();
         need2 = s_need2;
         tm = tml;
@@ -763,12 +748,12 @@ __device__ inline void jacobi_rotation(const double* a, int n, int rd, int k, do
 template <int NBLK>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
-                                                      float* __restrict__ sigma_out) {
+                                                      int slot_rows, float* __restrict__ sigma_out) {
     __shared__ int s_ke;
     __shared__ double s_sum;
     const LayerDev& L = layers[ids[blockIdx.y]];
     const int w = L.thin[role].width;
-    const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + kGramRows1 - 1) / kGramRows1;
+    const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
     const int n = (w + 1) & ~1;      // even size for the round-robin schedule (a zero row/column is added)
     const int half = n / 2;
     const int row0 = blockIdx.x * v_rows;
@@ -1003,7 +988,8 @@ size_t jacobi_lds_bytes(int w, int v_rows) {
     return (size_t)(2 * n + 32 + n * sym_stride(n) + v_rows * n) * sizeof(double) + (size_t)2 * n * sizeof(int);
 }
 
-hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, float* sigma_out,
+// slot_rows: rows per partial Gram matrix of thin[role] (kOneSlot: gram_sum_kernel has added them up)
+hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const int n = (w + 1) & ~1;
@@ -1023,7 +1009,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     const int threads = w <= 48 ? 256 : 1024;
     dim3 grid((n + v_rows - 1) / v_rows, n_ids), block(threads);
     const int per_thread = (n_blocks + threads - 1) / threads;
-    void (*kfn)(const LayerDev*, const int*, int, int, float*) = nullptr;
+    void (*kfn)(const LayerDev*, const int*, int, int, int, float*) = nullptr;
     switch (per_thread) {
         case 1: kfn = jacobi_kernel<1>; break;
         case 2: kfn = jacobi_kernel<2>; break;
@@ -1038,7 +1024,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, sigma_out);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, sigma_out);
     return hipGetLastError();
 }
 

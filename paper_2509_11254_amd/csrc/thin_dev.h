@@ -26,22 +26,20 @@ __host__ __device__ inline int chol_groups(int w) {
     int g = kThreads / ntri;
     return g < 1 ? 1 : (g > kCholMaxGroups ? kCholMaxGroups : g);
 }
-// LDS doubles of chol_body besides the blocked inverse's panel, and whether the panel fits as well
-__host__ __device__ inline size_t chol_lds_doubles(int w) {
-    const int ntri = (w * (w + 1)) / 2;
-    const int g = chol_groups(w);
-    const int wp = (w + 15) & ~15;
-    return (size_t)(g > 1 ? g + 1 : 1) * ntri + 2 * w + wp;
-}
-__host__ __device__ inline bool chol_blocked_inverse(int w) {
-    const int wp = (w + 15) & ~15;
-    return w > kCholRegWidth && (chol_lds_doubles(w) + (size_t)wp * 16) * sizeof(double) + (w + 2) * sizeof(int) <= 150 * 1024;
-}
+// Widths above the register path: 16 x 16 blocks of the upper triangle in LDS (chol_blocked) as long as these, one block row
+// beside them and the vectors fit a workgroup's 160 KB, i.e. up to 11 blocks = 176; beyond that a packed triangle without
+// blocking.
+constexpr int kCholMaxBlocks = 11;
+constexpr int kTjjStride = 17;         // row stride of the diagonal block's inverse (doubles)
+__host__ __device__ inline bool chol_is_blocked(int w) { return w > kCholRegWidth && (w + 15) / 16 <= kCholMaxBlocks; }
 // LDS bytes chol_body needs
 __host__ __device__ inline size_t chol_lds_bytes(int w) {
-    const int wp = (w + 15) & ~15;
-    return (chol_lds_doubles(w) + (chol_blocked_inverse(w) ? (size_t)wp * 16 : 0)) * sizeof(double) +
-           (size_t)(w + 2) * sizeof(int);
+    const int nbk = (w + 15) / 16;
+    if (chol_is_blocked(w))
+        return ((size_t)(nbk * (nbk + 1) / 2 + nbk) * 256 + 16 * kTjjStride + 16 * nbk) * sizeof(double) + (size_t)16 * nbk * sizeof(int);
+    const int ntri = (w * (w + 1)) / 2;
+    const int g = chol_groups(w);
+    return ((size_t)(g > 1 ? g + 1 : 1) * ntri + 2 * w + 16 * nbk) * sizeof(double) + (size_t)(w + 2) * sizeof(int);
 }
 // the same for a launch that serves layers of any width up to w (the need is not monotone in w)
 inline size_t chol_lds_bytes_upto(int w) {
@@ -115,7 +113,7 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
 // outputs as the general path of chol_body.  W: compiled width (w <= W); rows and columns w .. W-1 are
 // those of an identity matrix.
 template <int W>
-__device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
+__device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                            bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
     const int j = threadIdx.x & 63;
     const bool aug = j >= 16;                          // identity column c = j - 16
@@ -181,7 +179,7 @@ __device__ inline void chol_in_registers_w(const LayerDev& L, const double* g, i
     }
 }
 
-__device__ inline void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
+__device__ __forceinline__ void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                          bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
     if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
     else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
@@ -189,12 +187,10 @@ __device__ inline void chol_in_registers(const LayerDev& L, const double* g, int
     else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
 }
 
-// Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers (same scheme as above):
-// factorises the block at rows/columns r0 .. r0 + bw - 1 of the packed triangle `a` (order w), leaves the
-// strict upper part of T_JJ = R_JJ^{-1} in its place, 1 / R_kk in rdiag, and updates the dependent-column
-// flags and the smallest accepted pivot.  All 64 lanes of the wave call it.
-__device__ inline void chol_block16(double* a, int w, int r0, int bw, double tol2, double* rdiag, int* bad,
-                                    double& min_piv) {
+// Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers (same scheme as above): factorises
+// the block `blk` (row-major, upper part), leaves T_JJ = R_JJ^{-1} (all 16 x 16 of it) in `tjj` and updates the
+// dependent-column flags and the smallest accepted pivot.  All 64 lanes of the wave call it.
+__device__ __forceinline__ void chol_block16(const double* blk, double* tjj, double tol2, int* bad, double& min_piv) {
     constexpr int W = 16;
     const int j = threadIdx.x & 63;
     const bool aug = j >= 16;
@@ -203,12 +199,12 @@ __device__ inline void chol_block16(double* a, int w, int r0, int bw, double tol
     int badmask = 0;
 #pragma unroll
     for (int i = 0; i < W; ++i) {
-        if (i < bw && bad[r0 + i]) badmask |= 1 << i;
+        if (bad[i]) badmask |= 1 << i;
         double v = (i == (aug ? c : j)) ? 1.0 : 0.0;
-        if (!aug && i <= j && j < bw) v = a[tri_idx(r0 + i, r0 + j, w)];
+        if (!aug && i <= j) v = blk[16 * i + j];
         x[i] = v;
     }
-    // (branch-free for the same reason as above; rows k >= bw are rows of the identity)
+    // (branch-free for the same reason as above)
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         const double piv = bcast_lane(x[k], k);
@@ -223,13 +219,163 @@ __device__ inline void chol_block16(double* a, int w, int r0, int bw, double tol
         for (int i = k + 1; i < W; ++i) x[i] = __builtin_fma(-bcast_lane(xk, i), mult, x[i]);
     }
     // lane 16 + c holds row c of T_JJ
-    if (aug && j < 16 + bw) {
-        rdiag[r0 + c] = x[c];
+    if (aug && j < 32) {
 #pragma unroll
-        for (int i = 1; i < W; ++i)
-            if (i > c && i < bw) a[tri_idx(r0 + c, r0 + i, w)] = x[i];
+        for (int i = 0; i < W; ++i) tjj[kTjjStride * c + i] = x[i];
     }
-    if (j < bw) bad[r0 + j] = (badmask >> j) & 1;
+    if (j < 16) bad[j] = (badmask >> j) & 1;
+}
+
+// Cholesky factorisation and inverse of its factor in one sweep over 16 x 16 blocks: the row operations that turn A into R
+// (A = R^T R) turn an identity into W = R^{-T}, and T = R^{-1} is its transpose.  In step J
+//   panel      R_JK = T_JJ^T A_JK (K > J),  W_JK <- T_JJ^T W_JK (K <= J; this row of W is final and goes to tm)
+//   trailing   A_IK -= R_JI^T R_JK (J < I <= K),  W_IK -= R_JI^T W_JK (K <= J < I)
+// on the fp64 matrix cores, blocks dealt to the waves.  W_IK lives where A_KI was (row K of A is finished by then), row J
+// of R in a buffer of its own, so one triangle of blocks holds everything; every operand is read row by row, 64 consecutive
+// doubles per instruction.
+// What bounds it is the chain of 16 steps inside each diagonal block (about 2 us): one wave updates and factorises block
+// J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.  One workgroup on a
+// 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion (packed triangle, five
+// barriers per block, spilling as a function call); 55 us now, 80 x 80 58 -> 27 us.
+// g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
+__device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
+                                    unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv) {
+    const int nbk = (w + 15) / 16, wp = 16 * nbk, nblk = (nbk * (nbk + 1)) / 2;
+    double* a = reinterpret_cast<double*>(smem);          // blocks (I, K), K >= I, row by row, each [16][16]
+    double* rj = a + nblk * 256;                          // [nbk] blocks: row J of R
+    double* tjj = rj + nbk * 256;                         // [16][17]
+    double* dsc = tjj + 16 * kTjjStride;                  // [wp] scaling
+    int* bad = reinterpret_cast<int*>(dsc + wp);          // [wp] dependent-column flags
+    const PSGD_GLOBAL double* g = as_global(gram_generic);
+    const int t = threadIdx.x, nt = blockDim.x;
+    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), nw = nt >> 6, li = lane & 15, lk = lane >> 4;
+    auto at = [&](int I, int K) { return a + (I * nbk - (I * (I - 1)) / 2 + (K - I)) * 256; };
+    // ---- blocks of the Gram matrix (256 threads per block, eight loads per thread in flight); identity in the padding
+    {
+        const int r = (t >> 4) & 15, c = t & 15, ng = nt >> 8;
+        for (int b0 = t >> 8; b0 < nblk; b0 += 8 * ng) {
+            double v[8];
+            int off[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int b = min(b0 + u * ng, nblk - 1);
+                int K = b, I = 0;
+                while (K >= nbk - I) { K -= nbk - I; ++I; }
+                K += I;
+                const int i = 16 * I + r, j = 16 * K + c;
+                off[u] = (i <= j && j < w) ? tri_idx(i, j, w) : -1;
+                v[u] = off[u] >= 0 ? g[off[u]] : (i == j ? 1.0 : 0.0);
+            }
+            if (n_slots > 1) {
+                for (int s0 = 1; s0 < n_slots; s0 += 4) {
+                    double x[4][8];
+#pragma unroll
+                    for (int d = 0; d < 4; ++d)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) x[d][u] = (s0 + d < n_slots && off[u] >= 0) ? g[(s0 + d) * sstr + off[u]] : 0.0;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) v[u] += x[d][u];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * r + c] = v[u];
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < wp; i += nt) {
+        const double d = at(i >> 4, i >> 4)[17 * (i & 15)];
+        dsc[i] = d > kTinyNorm2 ? rsqrt_nr(d) : 0.0;      // (1 in the padding)
+        bad[i] = d > kTinyNorm2 ? 0 : 1;
+    }
+    __syncthreads();
+    {
+        // (four blocks of a thread at a time)
+        const int r = (t >> 4) & 15, c = t & 15, ng = nt >> 8;
+        for (int b0 = t >> 8; b0 < nblk; b0 += 4 * ng) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b = min(b0 + u * ng, nblk - 1);
+                int K = b, I = 0;
+                while (K >= nbk - I) { K -= nbk - I; ++I; }
+                v[u] = a[b * 256 + 16 * r + c] * (dsc[16 * I + r] * dsc[16 * (K + I) + c]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * r + c] = v[u];
+        }
+    }
+    __syncthreads();
+    min_piv = 1.0;
+    if (wv == 0) chol_block16(a, tjj, tol2, bad, min_piv);
+    __syncthreads();
+    for (int J = 0; J < nbk; ++J) {
+        // ---- panel
+        for (int K = wv; K < nbk; K += nw) {
+            double* blk = K < J ? at(K, J) : at(J, K);
+            doublex4 d = {0.0, 0.0, 0.0, 0.0};
+            if (K != J) {
+                double av[4], bv[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { av[c] = tjj[kTjjStride * (4 * c + lk) + li]; bv[c] = blk[16 * (4 * c + lk) + li]; }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) d[v] = tjj[kTjjStride * li + 4 * v + lk];          // W_JJ = T_JJ^T
+            }
+            double* dst = K > J ? rj + K * 256 : blk;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 4 * v + lk, j = 16 * J + row, i = 16 * K + li;
+                const bool dep = bad[j] != 0;
+                dst[16 * row + li] = (K > J && dep) ? 0.0 : d[v];
+                // T[i][j] = W[j][i], zero below the diagonal and in the columns of dependent vectors
+                if (i < w && j < w)
+                    tm[(int64_t)i * w + j] = (K > J || dep) ? 0.0 : d[v] * dsc[i] * (scale ? next_scale(dsc[j]) : 1.0);
+            }
+        }
+        __syncthreads();
+        if (J + 1 == nbk) break;
+        // ---- trailing update; block (J + 1, J + 1) and its factorisation by wave 0
+        auto update = [&](int I, int K) {
+            double* blk = K >= I ? at(I, K) : at(K, I);
+            const double* __restrict__ ra = rj + I * 256;
+            const double* __restrict__ rb = K > J ? rj + K * 256 : at(K, J);
+            double av[4], bv[4];
+            doublex4 d;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { av[c] = -ra[16 * (4 * c + lk) + li]; bv[c] = rb[16 * (4 * c + lk) + li]; }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) d[v] = K == J ? 0.0 : blk[16 * (4 * v + lk) + li];      // (K = J: W_IJ starts at zero)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) blk[16 * (4 * v + lk) + li] = d[v];
+        };
+        if (wv == 0) {
+            update(J + 1, J + 1);
+            wave_sync();
+            chol_block16(at(J + 1, J + 1), tjj, tol2, bad + 16 * (J + 1), min_piv);
+        } else {
+            // the blocks of rows I > J one after the other, in each those of W (K <= J), then those of A (K >= I)
+            int I = J + 1, k = wv - 1, row = J + 1 + (nbk - I);
+            for (;;) {
+                while (I < nbk && k >= row) { k -= row; ++I; --row; }
+                if (I >= nbk) break;
+                const int K = k <= J ? k : I + (k - (J + 1));
+                if (I != J + 1 || K != I) update(I, K);
+                k += nw - 1;
+            }
+        }
+        __syncthreads();
+    }
+    nbad = 0;
+    if (wv == 0)
+        for (int i0 = 0; i0 < w; i0 += 64) nbad += __popcll(__ballot(i0 + lane < w && bad[i0 + lane] != 0));
 }
 
 // Layers whose factorisation is cheap enough for every workgroup of the apply kernel to repeat it for
@@ -251,16 +397,14 @@ __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
 // that receives the second-pass decision; write_status: whether this caller owns the layer's status words.
 // NARROW: compiled for widths <= 16 only (the register path; nothing else is generated).
 template <bool NARROW = false>
-__device__ inline void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
+__device__ __forceinline__ void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
                                  unsigned char* smem, double* tm, bool write_status = true,
-                                 int* need2_out = nullptr, int slot_stride = 1, bool scale = false) {
+                                 int* need2_out = nullptr, bool scale = false) {
     const int side = side_of_role(L.transposed, role);
-    // slot_stride > 1: the slots were already added up in groups of that many, each sum left in its group's
-    // first slot (sum_slot_groups); what remains is one matrix per group
-    const int n_slots = (side_len(L, side) + slot_rows * slot_stride - 1) / (slot_rows * slot_stride);
+    const int n_slots = (side_len(L, side) + slot_rows - 1) / slot_rows;      // (kOneSlot: one, the sum of all)
     const int w = L.thin[role].width;
     const int ntri = (w * (w + 1)) / 2;
-    const int64_t sstr = (int64_t)slot_stride * ntri;      // distance between the matrices to add
+    const int64_t sstr = ntri;                            // distance between the matrices to add
     const int G = chol_groups(w);
     double* a = reinterpret_cast<double*>(smem);          // packed upper triangle
     double* ps = a + ntri;                                // [G][ntri] partial slot sums (G > 1)
@@ -268,12 +412,31 @@ __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int p
     double* rdiag = dsc + w;                              // [w] diagonal of the inverse factor
     double* tcol = rdiag + w;                             // [w up to 16] copy of the column of R being replaced
     const int wp = (w + 15) & ~15;
-    const bool blocked = chol_blocked_inverse(w);
-    double* panel = tcol + wp;                            // [wp][16] original block column (blocked inverse)
-    int* bad = reinterpret_cast<int*>(panel + (blocked ? wp * 16 : 0));    // [w] dependent-column flags
+    int* bad = reinterpret_cast<int*>(tcol + wp);         // [w] dependent-column flags
     const int t = threadIdx.x;
-    const int nt = blockDim.x, nw = nt >> 6, nty = nt >> 4;      // threads, wavefronts, rows of the 16-wide thread grid
+    const int nt = blockDim.x, nty = nt >> 4;             // threads, rows of the 16-wide thread grid
     const double* __restrict__ gram = L.gram;
+    auto outcome = [&](int nbad, double min_piv) {
+        const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
+        if (need2_out) *need2_out = need2;
+        if (write_status) {
+            if (pass == 1) {
+                L.status[0] = nbad;
+                L.status[1] = need2;
+            } else {
+                L.status[0] = max(L.status[0], nbad);
+            }
+        }
+    };
+    if constexpr (!NARROW) {
+        if (chol_is_blocked(w)) {
+            int nbad = 0;
+            double min_piv = 1.0;
+            chol_blocked(gram, n_slots, sstr, w, tol2, scale, smem, tm, nbad, min_piv);
+            if (t == 0) outcome(nbad, min_piv);           // (wave 0 has factorised the diagonal blocks)
+            return;
+        }
+    }
     if (G > 1 || NARROW) {
         // thread (e, g): entries e of slots g, g + G, ...; sixteen loads in flight, those past the end
         // re-read slot g and do not count
@@ -374,142 +537,45 @@ __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int p
     __syncthreads();
     // right-looking Cholesky, A = R^T R, R overwrites the strict upper triangle; 1 / R_kk goes to rdiag
     double min_piv = 1.0;
-    const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
-    if (!blocked) {
-        for (int k = 0; k < w; ++k) {
-            // every thread reads the pivot itself; the pivot entry is never overwritten, so two barriers
-            // per step are enough
-            const double piv = a[tri_idx(k, k, w)];
-            const bool dep = bad[k] || !(piv > tol2);
-            if (!dep && piv < min_piv) min_piv = piv;
-            const int kbase = tri_idx(k, k, w) - k;             // a[tri_idx(k, j)] = a[kbase + j]
-            if (dep) {
-                if (t == 0) { bad[k] = 1; rdiag[k] = 1.0; }
-                for (int j = k + 1 + t; j < w; j += nt) a[kbase + j] = 0.0;
-            } else {
-                const double rinv = rsqrt_nr(piv);
-                if (t == 0) rdiag[k] = rinv;
-                for (int j = k + 1 + t; j < w; j += nt) a[kbase + j] *= rinv;
-            }
-            __syncthreads();
-            if (!dep) {
-                for (int i = k + 1 + ty; i < w; i += nty) {
-                    const double rki = a[kbase + i];
-                    const int base = tri_idx(i, i, w) - i;
-                    for (int j = i + tx; j < w; j += 16) a[base + j] -= rki * a[kbase + j];
-                }
-            }
-            __syncthreads();
+    for (int k = 0; k < w; ++k) {
+        // every thread reads the pivot itself; the pivot entry is never overwritten, so two barriers
+        // per step are enough
+        const double piv = a[tri_idx(k, k, w)];
+        const bool dep = bad[k] || !(piv > tol2);
+        if (!dep && piv < min_piv) min_piv = piv;
+        const int kbase = tri_idx(k, k, w) - k;             // a[tri_idx(k, j)] = a[kbase + j]
+        if (dep) {
+            if (t == 0) { bad[k] = 1; rdiag[k] = 1.0; }
+            for (int j = k + 1 + t; j < w; j += nt) a[kbase + j] = 0.0;
+        } else {
+            const double rinv = rsqrt_nr(piv);
+            if (t == 0) rdiag[k] = rinv;
+            for (int j = k + 1 + t; j < w; j += nt) a[kbase + j] *= rinv;
         }
-    } else {
-        // The same in 16 x 16 blocks: per block row J, (1) one wave factorises the diagonal block and
-        // inverts its factor (needed below and by the inverse of R), (2) R_JK = T_JJ^T A_JK for K > J and
-        // (3) A_IK -= R_JI^T R_JK for J < I <= K run on the fp64 matrix cores, blocks dealt to the waves.
-        const int nbk = wp / 16;
-        for (int J = 0; J < nbk; ++J) {
-            const int r0 = 16 * J;
-            const int bw = min(16, w - r0);
-            if (t < 64) chol_block16(a, w, r0, bw, tol2, rdiag, bad, min_piv);
-            __syncthreads();
-            // (2) row panel; rows of dependent columns are zero.  (Block J is complete: K > J exists.)
-            for (int K = J + 1 + wv; K < nbk; K += nw) {
-                doublex4 d = {0.0, 0.0, 0.0, 0.0};
-                const int col = 16 * K + li;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int kk = r0 + 4 * c + lk, ii = r0 + li;
-                    const double av = kk < ii ? a[tri_idx(kk, ii, w)] : (kk == ii ? rdiag[ii] : 0.0);   // T_JJ[kk][ii]
-                    const double bv = col < w ? a[tri_idx(kk, col, w)] : 0.0;                           // A_JK[kk][col]
-                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, d, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = r0 + 4 * v + lk;
-                    if (col < w) a[tri_idx(row, col, w)] = bad[row] ? 0.0 : d[v];
-                }
+        __syncthreads();
+        if (!dep) {
+            for (int i = k + 1 + ty; i < w; i += nty) {
+                const double rki = a[kbase + i];
+                const int base = tri_idx(i, i, w) - i;
+                for (int j = i + tx; j < w; j += 16) a[base + j] -= rki * a[kbase + j];
             }
-            __syncthreads();
-            // (3) trailing update
-            int pair = 0;
-            for (int I = J + 1; I < nbk; ++I)
-                for (int K = I; K < nbk; ++K, ++pair) {
-                    if ((pair & (nw - 1)) != wv) continue;
-                    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-                    const int ci = 16 * I + li, ck = 16 * K + li;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int kk = r0 + 4 * c + lk;
-                        const double av = ci < w ? a[tri_idx(kk, ci, w)] : 0.0;     // R_JI[kk][ci]
-                        const double bv = ck < w ? a[tri_idx(kk, ck, w)] : 0.0;     // R_JK[kk][ck]
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int row = 16 * I + 4 * v + lk;
-                        if (row <= ck && ck < w) a[tri_idx(row, ck, w)] -= acc[v];
-                    }
-                }
-            __syncthreads();
         }
+        __syncthreads();
     }
     // inverse T of the upper-triangular factor, in place in the packed triangle (T_jj = 1 / R_jj is in rdiag):
     //   T_ij = -T_jj * sum_{l=i}^{j-1} T_il R_lj   (i < j; T_il already in place)
-    if (!blocked) {
-        // column by column, one thread per row i of the new column
-        for (int j = 1; j < w; ++j) {
-            for (int i = t; i < j; i += nt) tcol[i] = a[tri_idx(i, j, w)];
-            __syncthreads();
-            const double tjj = rdiag[j];
-            for (int i = t; i < j; i += nt) {
-                const int base = tri_idx(i, i, w) - i;
-                double sacc = rdiag[i] * tcol[i];
-                for (int l = i + 1; l < j; ++l) sacc += a[base + l] * tcol[l];
-                a[base + j] = -tjj * sacc;
-            }
-            __syncthreads();
+    // column by column, one thread per row i of the new column
+    for (int j = 1; j < w; ++j) {
+        for (int i = t; i < j; i += nt) tcol[i] = a[tri_idx(i, j, w)];
+        __syncthreads();
+        const double tjj = rdiag[j];
+        for (int i = t; i < j; i += nt) {
+            const int base = tri_idx(i, i, w) - i;
+            double sacc = rdiag[i] * tcol[i];
+            for (int l = i + 1; l < j; ++l) sacc += a[base + l] * tcol[l];
+            a[base + j] = -tjj * sacc;
         }
-    } else {
-        // 16 x 16 blocks; the diagonal blocks of T were left by the factorisation,
-        const int nbk = wp / 16;
-        // then block column after block column, T_IJ = -(sum_{K=I}^{J-1} T_IK R_KJ) T_JJ on the fp64 matrix
-        // cores, the block rows I dealt to the waves.  The products are formed transposed,
-        // U^T = sum_K R_KJ^T T_IK^T and T_IJ^T = -T_JJ^T U^T, so that the accumulator of the first is the
-        // B operand of the second without a move.  R_KJ is read from a copy of the block column, T in place.
-        for (int J = 1; J < nbk; ++J) {
-            for (int e = t; e < 16 * J * 16; e += nt) {
-                const int row = e >> 4, col = 16 * J + (e & 15);
-                panel[e] = col < w ? a[tri_idx(row, col, w)] : 0.0;
-            }
-            __syncthreads();
-            for (int I = wv; I < J; I += nw) {
-                doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-                const int trow = 16 * I + li;
-                const int tbase = tri_idx(trow, trow, w) - trow;               // a[tbase + c] = T[trow][c], c > trow
-                for (int K = I; K < J; ++K)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int kk = 16 * K + 4 * c + lk;                     // < 16 J <= w
-                        const double av = panel[kk * 16 + li];                  // R[kk][16 J + li]
-                        const double bv = trow < kk ? a[tbase + kk] : (trow == kk ? rdiag[trow] : 0.0);   // T[trow][kk]
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-                    }
-                doublex4 d2 = {0.0, 0.0, 0.0, 0.0};
-                const int jcol = 16 * J + li;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int jrow = 16 * J + 4 * c + lk;
-                    double av = 0.0;                                            // T_JJ[jrow][jcol]
-                    if (jcol < w) av = jrow < jcol ? a[tri_idx(jrow, jcol, w)] : (jrow == jcol ? rdiag[jrow] : 0.0);
-                    d2 = __builtin_amdgcn_mfma_f64_16x16x4f64(av, acc[c], d2, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int col = 16 * J + 4 * v + lk;
-                    if (col < w) a[tbase + col] = -d2[v];                       // T[trow][col]
-                }
-            }
-            __syncthreads();
-        }
+        __syncthreads();
     }
     for (int i = ty; i < w; i += nty) {
         const int base = tri_idx(i, i, w) - i;
@@ -522,16 +588,7 @@ __device__ inline void chol_body(const LayerDev& L, int role, double tol2, int p
     if (t == 0) {
         int nbad = 0;
         for (int i = 0; i < w; ++i) nbad += bad[i];
-        const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
-        if (need2_out) *need2_out = need2;
-        if (write_status) {
-            if (pass == 1) {
-                L.status[0] = nbad;
-                L.status[1] = need2;
-            } else {
-                L.status[0] = max(L.status[0], nbad);
-            }
-        }
+        outcome(nbad, min_piv);
     }
 }
 
@@ -552,49 +609,6 @@ __device__ inline bool last_to_arrive(int* counter, int n_wg, int* flag) {
         if (threadIdx.x == 0) *counter = 0;
     }
     return last;
-}
-
-// Partial Gram matrices added up in two levels, so that no workgroup has to read all of them: the slots form
-// groups of kSlotGroup; the workgroup that completes a group adds the group's slots into the first one (fixed
-// order), and the one that completes the last group goes on with one matrix per group.  Used where one
-// workgroup per slot runs anyway and the matrices are large (width above the register path, many slots).
-constexpr int kSlotGroup = 8;
-constexpr int kMaxSlotGroups = 16;      // arrival counters per layer
-__device__ inline bool grouped_slot_sum(int w, int n_slots) {
-    return w > kCholRegWidth && n_slots >= 2 * kSlotGroup && n_slots <= kSlotGroup * kMaxSlotGroups;
-}
-// Called by all threads of the workgroup that completed group `grp`: slot first <- sum of the group's slots.
-__device__ inline void sum_slot_group(double* gram, int w, int n_slots, int grp) {
-    typedef double doublex2 __attribute__((ext_vector_type(2)));
-    const int ntri = (w * (w + 1)) / 2;
-    const int first = grp * kSlotGroup;
-    const int cnt = min(kSlotGroup, n_slots - first);
-    PSGD_GLOBAL double* g0 = as_global(gram) + (int64_t)first * ntri;
-    const int t = threadIdx.x, nt = blockDim.x;
-    if ((ntri & 1) == 0 && cnt == kSlotGroup) {
-        // two 16-byte entries x 8 slots in flight per thread
-        for (int e = 2 * t; e < ntri; e += 4 * nt) {
-            const bool two = e + 2 * nt < ntri;
-            const int e2 = two ? e + 2 * nt : e;
-            doublex2 x[kSlotGroup], y[kSlotGroup];
-#pragma unroll
-            for (int d = 0; d < kSlotGroup; ++d) {
-                x[d] = *reinterpret_cast<const PSGD_GLOBAL doublex2*>(g0 + (int64_t)d * ntri + e);
-                y[d] = *reinterpret_cast<const PSGD_GLOBAL doublex2*>(g0 + (int64_t)d * ntri + e2);
-            }
-            doublex2 sx = x[0], sy = y[0];
-#pragma unroll
-            for (int d = 1; d < kSlotGroup; ++d) { sx += x[d]; sy += y[d]; }
-            *reinterpret_cast<PSGD_GLOBAL doublex2*>(g0 + e) = sx;
-            if (two) *reinterpret_cast<PSGD_GLOBAL doublex2*>(g0 + e2) = sy;
-        }
-    } else {
-        for (int e = t; e < ntri; e += nt) {
-            double sacc = g0[e];
-            for (int d = 1; d < cnt; ++d) sacc += g0[(int64_t)d * ntri + e];
-            g0[e] = sacc;
-        }
-    }
 }
 
 }  // namespace psgd
