@@ -42,17 +42,17 @@ hipError_t launch_finish(bool colmode, int form, const LayerDev* layers, const i
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st);
 hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, int max_blocks, int role, int cp,
-                            int gate, hipStream_t st);
+                            int gate, int flagged, hipStream_t st);
 hipError_t launch_pack(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int role_a, int role_b,
                        int cp, int which, hipStream_t st);
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
                        int slot_rows, int gate, int a2gate, int local_ok, hipStream_t st);
 hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
-                           hipStream_t st);
+                           int flagged, hipStream_t st);
 int finish_rows(int w);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
-                        bool small, int which, hipStream_t st);
+                        bool small, int which, int slot_rows, hipStream_t st);
 hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, int max_len, int w, int dst_role,
                              int src_role, int warm, uint32_t seed, hipStream_t st);
 hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
@@ -60,7 +60,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
 hipError_t launch_copy(void* dst, const void* src, size_t n_bytes, hipStream_t st);
 hipError_t launch_put(void* dst, const void* src_host, size_t bytes, hipStream_t st);
 hipError_t launch_clear_status(const LayerDev* layers, const int* ids, int n_ids, hipStream_t st);
-enum ApplyModeHost { APPLY_PASS1 = 1, APPLY_PASS2 = 2, APPLY_RITZ = 3 };
+enum ApplyModeHost { APPLY_PASS1 = 1, APPLY_PASS2 = 2, APPLY_RITZ = 3, APPLY_PASS1_ONLY = 4 };
 }  // namespace psgd
 
 using namespace psgd;
@@ -447,6 +447,7 @@ struct Launcher {
         int tiles_row_v2 = 0, tiles_col_v2 = 0;     // the kernels on 32 x 256 tiles
         bool split_row = false, split_col = false, split_row_f = false, split_col_f = false, split_row_v2 = false,
              split_col_v2 = false;                  // (all layers of a launch are split or none is)
+        int longest = 0, shortest_max = 0;          // largest long side (P) and largest short side (Q)
     } norm, tr;
     int gram_rows_n = kGramRows1, gram_rows_t = kGramRows1;   // rows per Gram slot of the last product, per orientation
     hipError_t err = hipSuccess;
@@ -500,7 +501,7 @@ struct Launcher {
                               ? reinterpret_cast<const int*>(ws + ctx->off_xtab) : nullptr;
         // the same product on a matrix that is already formed (the refresh's iteration, further power steps)
         const bool r2 = !form && p_like && n_norm > 0 && use_form_row && row_prod_supported(nb, ctx->planes);
-        const bool gram32 = (v2 || r2) && !norm.split_row_v2 && epi == EPI_GRAM && w > 16 && chol_gate >= -1;
+        const bool gram32 = (v2 || r2) && !norm.split_row_v2 && epi == EPI_GRAM && chol_gate >= -1 && (!small || norm.longest <= kLocalGram32);
         // the second product on row-major layers at those widths likewise
         const bool c2 = !form && !p_like && n_norm > 0 && use_form_row && col_prod_supported(nb, ctx->planes);
         const int* xtab_c = (ctx->xstride > 0 && use_xtab && use_xtab_c && nb >= 2 && ids_norm == ids_all + ctx->n_layers)
@@ -528,29 +529,33 @@ struct Launcher {
         const int fin_gate = wide ? -2 : chol_gate;
         if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         if (split_t) note(launch_finish(p_like, t2 ? 2 : form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
-        // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself where the
-        // factorisation is a launch of its own -- widths above 16 --, and leaves them to a small pass over the result,
-        // one per 128 rows, where the apply kernel factorises for itself)
-        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks_row, out_role, 32 * nb, gate, st));
+        // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
+        // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
+        // per 128 rows)
+        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks_row, out_role, 32 * nb, gate, 0, st));
         gram_rows_n = gram32 ? 32 : split_n ? finish_rows(ww) : kGramRows1;
         gram_rows_t = split_t ? finish_rows(ww) : kGramRows1;
         if (chol_gate >= -1) {
             // (the many 32-row slots are added up before at any width)
-            if (wide || gram32) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, chol_gate, st));
+            if (wide || (gram32 && !small)) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, chol_gate, 0, st));
             if (wide) {
-                note(launch_gram_sum(layers, ids_tr, n_tr, ww, out_role, gram_rows_t, chol_gate, st));
+                note(launch_gram_sum(layers, ids_tr, n_tr, ww, out_role, gram_rows_t, chol_gate, 0, st));
                 note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, kOneSlot, chol_gate, a2gate, 0, st));
             } else {
-                if (!split_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
-                if (!split_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
+                // (not where the apply kernel factorises every layer for itself)
+                const bool local_n = small && (p_like ? norm.longest : norm.shortest_max) <= kLocalCholMaxRows;
+                const bool local_t = small && (p_like ? tr.longest : tr.shortest_max) <= kLocalCholMaxRows;
+                if (!split_n && !local_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
+                if (!split_t && !local_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
             }
         }
     }
     // thin[out_role] = product as in prod(), then CholeskyQR2 on it: the first pass always, the second
     // when the first one's pivots ask for it (decided on the device) and `pass2` allows it.  Inside the
     // subspace iteration the second pass is only wanted where exact orthonormality matters: on Z in a
-    // layer's last iteration.  cp > 0: also leave the split-bf16 operand copies of the result.
-    enum Pass2 { PASS2_NEVER = 0, PASS2_ALWAYS = 1, PASS2_LAST_ITERATION = 2 };
+    // layer's last iteration; that iteration only notes the need, see second_pass_deferred.  cp > 0: also leave the
+    // split-bf16 operand copies of the result.
+    enum Pass2 { PASS2_NEVER = 0, PASS2_ALWAYS = 1, PASS2_DEFERRED = 2 };
     void prod_orth(bool p_like, bool form, int nb, int out_role, int w, double tol2, int cp, int kind, Pass2 pass2) {
         const int g = gate < 0 ? -1 : gate_with_kind(gate, kind);
         const int a2 = pass2 == PASS2_ALWAYS ? -1 : (pass2 == PASS2_NEVER || gate < 0) ? -2 : gate_with_kind(gate, 2);
@@ -560,23 +565,37 @@ struct Launcher {
         // (inside the iteration only products read the result: no row-major operand copies)
         const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_ROWMAJOR | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
         prod(p_like, form, nb, out_role, EPI_GRAM, g, a2, tol2, w, small);
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, g, a2, tol2, small, wh, st));
-        if (a2 != -2) {
-            const int g2 = a2 == -1 ? g : a2;
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g2, -2, 0, st));
-            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g2, a2, tol2, small, wh, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
+        if (pass2 == PASS2_ALWAYS) {
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g, -2, 0, st));
+            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
         }
+    }
+    // The second CholeskyQR pass on Z after the subspace iteration, for the layers whose last factorisation of Z asked for
+    // it (nearly none): Z <- Z T2, and as Y = M^T Z is linear in Z, Y <- Y T2; then the Gram matrix of Y anew.  One set of
+    // launches that find nothing to do, where the second pass inside the iteration was one per iteration (the host does
+    // not know which is a layer's last): 0.1 ms of a refresh with 16 iterations at widths above 16.
+    void second_pass_deferred(int w, int cp, double tol2) {
+        const bool wide = w > kWideWidth;
+        const int blocks = (max_lenP() + 127) / 128;
+        note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZP, cp, -1, 1, st));
+        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, -1, 1, st));
+        note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, -1, -2, 0, st));
+        for (int role : {ROLE_ZP, ROLE_ZQ})
+            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, st));
+        note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZQ, cp, -1, 1, st));
+        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, -1, 1, st));
     }
     // the same CholeskyQR2 on a thin[out_role] that the caller supplied: its Gram slots come from a pass of their own
     void orth_given(int out_role, int w, double tol2, int cp) {
         const bool small = w <= 16;
         const int blocks = (max_lenP() + 127) / 128;
-        note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, st));
-        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, st));
-        note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, w > kWideWidth ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, st));
+        note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, 0, st));
+        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, 0, st));
+        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, w > kWideWidth ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
         if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, -1, -2, 0, st));
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
     void residual(int nb, bool form = false) {
         const int k = prof_begin(PSGD_PROF_RESIDUAL);
@@ -609,6 +628,7 @@ void geometry(const Plan& p, Launcher& L) {
     mx(L.tiles_outer, rb * cb);
     Launcher::Geometry& g = p.transposed ? L.tr : L.norm;
     mx(g.blocks_row, rb); mx(g.blocks_col, cb);
+    mx(g.longest, p.m); mx(g.shortest_max, p.n);
     mx(g.tiles_row, rb * p.split_row); mx(g.tiles_col, cb * p.split_col);
     mx(g.tiles_row_f, rb * p.split_row_f); mx(g.tiles_col_f, cb * p.split_col_f);
     mx(g.tiles_row_v2, (p.rowsP / 32) * p.split_row_v2);
@@ -642,7 +662,7 @@ double tol2_of(const psgd_ctx* c) {
 // Block subspace iteration + Rayleigh-Ritz for the layers of `L`: leaves P~ (Ritz vectors of the r
 // largest singular values) in thin[ROLE_P] and Q = M^T P~ in thin[ROLE_Q].
 void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, float* sigma_out, int final_cp,
-                      int launch_iters = 0, int least_iters = 0) {
+                      int launch_iters = 0) {
     const int wz = ctx->wz, cpz = ctx->cpz, nbz = cpz / 32;
     const int iters = ctx->opt.refresh_iters > 0 ? ctx->opt.refresh_iters : 16;
     const int n_launch = launch_iters > 0 && launch_iters < iters ? launch_iters : iters;
@@ -661,11 +681,7 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
         // next_scale).  Saves the factorisation and the pass over the thin matrix, half of the serial chain between the
         // products: 4096 x 4096 fp32 r = 8, 16 iterations, 1.29 -> 1.17 ms; 8192 x 8192 r = 128 15.9 -> 12.4 ms;
         // the seven matrices of a 7B-shaped block in bf16 7.9 -> 7.0 ms; errors against 64 bits unchanged.
-        // (the second CholeskyQR pass on Z belongs to a layer's last iteration: where the smallest count among the
-        // layers is known, the iterations before it need no launch for it)
-        const bool may_be_last = least_iters <= 0 || it + 1 >= least_iters;
-        L.prod_orth(true, form_first && it == 0, nbz, ROLE_ZP, wz, tol2, cpz, 0,
-                    may_be_last ? Launcher::PASS2_LAST_ITERATION : Launcher::PASS2_NEVER);
+        L.prod_orth(true, form_first && it == 0, nbz, ROLE_ZP, wz, tol2, cpz, 0, Launcher::PASS2_DEFERRED);
         if (it < kOrthYIterations) L.prod_orth(false, false, nbz, ROLE_ZQ, wz, tol2, cpz, 1, Launcher::PASS2_NEVER);
         else L.prod(false, false, nbz, ROLE_ZQ, EPI_ITERATE);
     }
@@ -673,14 +689,15 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)
     const bool wide = wz > kWideWidth;
     if (wide) {
-        L.note(launch_gram_sum(L.layers, L.ids_norm, L.n_norm, wz, ROLE_ZQ, L.gram_rows_n, -1, L.st));
-        L.note(launch_gram_sum(L.layers, L.ids_tr, L.n_tr, wz, ROLE_ZQ, L.gram_rows_t, -1, L.st));
+        L.note(launch_gram_sum(L.layers, L.ids_norm, L.n_norm, wz, ROLE_ZQ, L.gram_rows_n, -1, 0, L.st));
+        L.note(launch_gram_sum(L.layers, L.ids_tr, L.n_tr, wz, ROLE_ZQ, L.gram_rows_t, -1, 0, L.st));
     }
+    L.second_pass_deferred(wz, cpz, tol2);
     L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
-                        final_cp, -1, -2, 0.0, false, 3, L.st));
+                        final_cp, -1, -2, 0.0, false, 3, 0, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZQ, ROLE_Q, APPLY_RITZ,
-                        final_cp, -1, -2, 0.0, false, 3, L.st));
+                        final_cp, -1, -2, 0.0, false, 3, 0, L.st));
     L.prof_mute = false;
 }
 
@@ -1083,20 +1100,17 @@ int psgd_compress_refresh(psgd_ctx* ctx, void* workspace, void* stream, const vo
     // else has changed the counts since.  (None of this bookkeeping under stream capture: a captured refresh
     // launches the whole budget and fetches nothing.)
     const bool capturing = is_capturing(st);
-    int bound = 0, least = 0;
+    int bound = 0;
     if (!capturing && ctx->fetch_last >= 0) {
         psgd_ctx::IterFetch& F = ctx->fetch[ctx->fetch_last];
         if (F.pending && hipEventQuery(F.ev) == hipSuccess) {
             F.pending = false;
-            if (F.gen == ctx->iters_gen && F.seq == ctx->refresh_seq) {
-                bound = F.h[0] & 0xffff;
-                least = bound > 0 ? (F.h[0] >> 16) : 0;
-            }
+            if (F.gen == ctx->iters_gen && F.seq == ctx->refresh_seq) bound = F.h[0];
         }
         (void)hipGetLastError();      // (hipErrorNotReady of the query is not an error)
     }
     const int iters_max = ctx->opt.refresh_iters > 0 ? ctx->opt.refresh_iters : 16;
-    refresh_sequence(ctx, L, true, ctx->opt.refresh_warm_start != 0, nullptr, ctx->cpc, bound, least);
+    refresh_sequence(ctx, L, true, ctx->opt.refresh_warm_start != 0, nullptr, ctx->cpc, bound);
     L.residual(ctx->cpc / 32);
     ctx->refresh_seq++;
     ctx->fetch_last = -1;

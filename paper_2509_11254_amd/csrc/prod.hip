@@ -740,9 +740,10 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
 // would have filled.
 __global__ __launch_bounds__(kThreads) void thin_gram_kernel(const LayerDev* __restrict__ layers,
                                                              const int* __restrict__ ids, int role, int cp,
-                                                             int gate) {
+                                                             int gate, int flagged) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
+    if (flagged && L.status[1] == 0) return;
     const int len = side_len(L, side_of_role(L.transposed, role));
     const int ob = blockIdx.x;
     if (ob * BT >= len) return;
@@ -762,9 +763,9 @@ __global__ __launch_bounds__(kThreads) void thin_gram_kernel(const LayerDev* __r
     gram_tile_f64(otile, tw, BT, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2));
 }
 
-// gate: iteration gate of the refresh (-1: none)
+// gate: iteration gate of the refresh (-1: none); flagged: only the layers whose second-pass flag is set
 hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, int max_blocks, int role, int cp,
-                            int gate, hipStream_t st) {
+                            int gate, int flagged, hipStream_t st) {
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
     dim3 grid(max_blocks, n_ids), block(kThreads);
     const size_t lds = (size_t)BT * (cp + 1) * sizeof(float);
@@ -773,7 +774,7 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(thin_gram_kernel, grid, block, lds, st, layers, ids, role, cp, gate);
+    hipLaunchKernelGGL(thin_gram_kernel, grid, block, lds, st, layers, ids, role, cp, gate, flagged);
     return hipGetLastError();
 }
 

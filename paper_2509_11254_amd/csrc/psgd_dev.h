@@ -55,6 +55,12 @@ constexpr int kOneSlot = 1 << 30;
 // widths above this: the partial Gram matrices are added up by gram_sum_kernel, the factorisation is a launch of its own
 constexpr int kWideWidth = 32;
 
+// Narrow layers (width <= 16) whose thin matrix has at most 64 partial Gram matrices: every workgroup of the apply kernel
+// repeats the factorisation for itself.  Rows at 128 and at 32 per partial matrix:
+constexpr int kLocalCholMaxSlots = 64;
+constexpr int kLocalCholMaxRows = kLocalCholMaxSlots * kGramRows1;
+constexpr int kLocalGram32 = kLocalCholMaxSlots * 32;
+
 enum Side { SIDE_L = 0, SIDE_W = 1 };
 // Roles: the paper's P~ and Q (user buffers, leading dimension r) and the two wide internal
 // blocks of the subspace iteration (leading dimension wz).

@@ -62,21 +62,16 @@ hipError_t launch_pack(const LayerDev* layers, const int* ids, int n_ids, int ma
 }
 
 // --------------------------------------------------------------------------------------------
-// iterations the next refresh of these layers will run: the largest and the smallest per-layer count.  The host
-// fetches them asynchronously, stops launching iterations past the largest (they would find every gate closed) and
-// leaves out the second-pass launches of the iterations before the smallest (no layer has its last one there).
+// iterations the next refresh of these layers will run: the largest per-layer count.  The host fetches it asynchronously and
+// stops launching iterations past it (they would find every gate closed).
 // --------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void max_iterations_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
                                                             int n_ids, int mx, int* __restrict__ out) {
-    int k = 1, kmin = 255;
-    for (int i = threadIdx.x; i < n_ids; i += 64) {
-        const int ki = refresh_iterations(layers[ids[i]], mx);
-        k = max(k, ki);
-        kmin = min(kmin, ki);
-    }
+    int k = 1;
+    for (int i = threadIdx.x; i < n_ids; i += 64) k = max(k, refresh_iterations(layers[ids[i]], mx));
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { k = max(k, __shfl_xor(k, off)); kmin = min(kmin, __shfl_xor(kmin, off)); }
-    if (threadIdx.x == 0) out[0] = k | (min(kmin, k) << 16);     // largest count, and the smallest in the high half
+    for (int off = 32; off > 0; off >>= 1) k = max(k, __shfl_xor(k, off));
+    if (threadIdx.x == 0) out[0] = k;
 }
 
 hipError_t launch_max_iterations(const LayerDev* layers, const int* ids, int n_ids, int mx, int* out, hipStream_t st) {
@@ -110,10 +105,11 @@ __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ l
 // reading all of it.
 // --------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void gram_sum_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
-                                                            int role, int slot_rows, int gate) {
+                                                            int role, int slot_rows, int gate, int flagged) {
     __shared__ double part[4][64];
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;       // (the slots of a layer whose iteration is over hold what its Ritz step needs)
+    if (flagged && L.status[1] == 0) return;
     const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
     const int w = L.thin[role].width;
     const int ntri = (w * (w + 1)) / 2;
@@ -136,12 +132,13 @@ __global__ __launch_bounds__(kThreads) void gram_sum_kernel(const LayerDev* __re
     if (wv == 0 && e < ntri) g[0] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
 }
 
-// w: the widest of the layers' blocks; gate: iteration gate of the refresh (-1: none)
+// w: the widest of the layers' blocks; gate: iteration gate of the refresh (-1: none); flagged: only the layers whose
+// second-pass flag is set
 hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
-                           hipStream_t st) {
+                           int flagged, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const int ntri = (w * (w + 1)) / 2;
-    hipLaunchKernelGGL(gram_sum_kernel, dim3((ntri + 63) / 64, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows, gate);
+    hipLaunchKernelGGL(gram_sum_kernel, dim3((ntri + 63) / 64, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows, gate, flagged);
     return hipGetLastError();
 }
 
@@ -172,10 +169,12 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
 //   APPLY_PASS1  (upper-triangular tmat): flag set   -> also the partial Gram matrix of the result, and the
 //                                                       last workgroup to finish factorises their sum
 //                                         flag clear -> result is final: operand copies if cp > 0
+//   APPLY_PASS1_ONLY (the same)         : final + operand copies whatever the flag says: the second pass, if the flag asks
+//                                       for one, is run later on the result
 //   APPLY_PASS2  (upper-triangular tmat): flag clear -> nothing to do; else final + operand copies
 //   APPLY_RITZ   (full tmat)            : final + operand copies if cp > 0
 // --------------------------------------------------------------------------------------------
-enum ApplyMode { APPLY_PASS1 = 1, APPLY_PASS2 = 2, APPLY_RITZ = 3 };
+enum ApplyMode { APPLY_PASS1 = 1, APPLY_PASS2 = 2, APPLY_RITZ = 3, APPLY_PASS1_ONLY = 4 };
 
 // LDS bytes of the tmat block, the x tile and the result tile (what every mode needs), 16-byte rounded
 __host__ __device__ inline size_t apply_main_lds(int w_in, int w_out, int cp) {
@@ -193,7 +192,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restrict__ layers,
                                                          const int* __restrict__ ids, int src_role, int dst_role,
                                                          int mode, int cp, int gate, int a2gate, double tol2,
-                                                         int which) {
+                                                         int which, int slot_rows) {
     __shared__ int s_last;
     __shared__ int s_need2;
     const LayerDev& L = layers[ids[blockIdx.y]];
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
     const int n_valid_x = (min(len, i0 + kGramRows2) - i0) * w_in;          // elements that exist
     float4 xpre = make_float4(0.f, 0.f, 0.f, 0.f);
     bool have_pre = false;
-    if (SMALL && mode == APPLY_PASS1 && local_chol(L, src_role, 1)) {
+    if (SMALL && (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY) && local_chol(L, src_role, 1)) {
         // small factorisation repeated by every workgroup; the first one records the outcome.  The
         // workgroup's own rows are requested first so that their latency overlaps the factorisation.
         if (flat_x) {
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
             if (4 * (int)threadIdx.x < n_valid_x) xpre = *reinterpret_cast<const float4*>(X.ptr + xbase + 4 * threadIdx.x);
         }
         double* tml = reinterpret_cast<double*>(smem + main_lds);
-        chol_body<true>(L, src_role, tol2, 1, kGramRows1, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
+        chol_body<true>(L, src_role, tol2, 1, L.transposed ? kGramRows1 : slot_rows, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
                   tml, blockIdx.x == 0, &s_need2, scales_next(L, src_role, gate));
         __syncthreads();
         need2 = s_need2;
@@ -570,11 +569,13 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
 
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
+// slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
+// (the others: 128)
 // which: operand copies to leave when cp > 0 (1 = row-major, 2 = transposed, 3 = both; + 4: the row-major pieces go to
 // the layer's kept copies in fragment order where it has them -- the P~ of a compress step with a deferred residual)
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
-                        bool small, int which, hipStream_t st) {
+                        bool small, int which, int slot_rows, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     dim3 grid(max_lenP / kGramRows2, n_ids), block(kThreads);
     if (!small && w_in <= kApplyStreamMaxWidth && w_out <= w_in) {
@@ -598,7 +599,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
     }
     // w_in / w_out are upper bounds over the layers: sizes that grow with them cover every layer
     size_t lds = apply_main_lds(w_in, w_out, cp);
-    if (small && mode == APPLY_PASS1) {
+    if (small && (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY)) {
         if (chol_lds_bytes_upto(w_out) > lds) lds = chol_lds_bytes_upto(w_out);          // second-pass factorisation
         const int wl = w_in < kCholRegWidth ? w_in : kCholRegWidth;             // per-workgroup factorisation
         lds += (size_t)wl * wl * sizeof(double) + chol_lds_bytes_upto(wl);
@@ -609,7 +610,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, src_role, dst_role, mode, cp, gate, a2gate, tol2, which);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, src_role, dst_role, mode, cp, gate, a2gate, tol2, which, slot_rows);
     return hipGetLastError();
 }
 

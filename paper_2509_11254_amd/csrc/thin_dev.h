@@ -380,12 +380,11 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
 
 // Layers whose factorisation is cheap enough for every workgroup of the apply kernel to repeat it for
 // itself (one kernel boundary less): register path, and few partial Gram matrices to add up.
-constexpr int kLocalCholMaxSlots = 64;
 // local_ok: launch-wide permission (all layers of the launch are narrow), the same in every kernel of the chain
 __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
     const int len = side_len(L, side_of_role(L.transposed, role));
     return local_ok && L.thin[role].width <= kCholRegWidth &&
-           (len + kGramRows1 - 1) / kGramRows1 <= kLocalCholMaxSlots;
+           len <= kLocalCholMaxRows;
 }
 
 // Sums the partial Gram matrices of thin[role] (packed upper triangles, slots of `slot_rows` rows, fixed
