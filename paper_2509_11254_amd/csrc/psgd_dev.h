@@ -178,7 +178,8 @@ __device__ inline void divmod_small(int v, int d, int& q, int& r) {
 // kept: the layer's lzf[side] where the result is a factor of a compress step whose residual is deferred: the pieces of
 // the row-major copies then go there instead, in fragment order (frag_piece), for the layers that have such copies.
 // PLT: the plane count as a compile-time constant where the caller has it (0: from `planes`, all kMaxPlanes are formed)
-template <int PLT = 0>
+// NT: threads of the workgroup
+template <int PLT = 0, int NT = kThreads>
 __device__ inline void write_packs(const PackRef& K, int planes, const float* tile, int tw, int cp, int row0,
                                    int nrows, int lenP, int which = 3, bf16_t* const* kept = nullptr) {
     constexpr int NPL = PLT > 0 ? PLT : kMaxPlanes;
@@ -192,7 +193,7 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
         dn[k] = k < planes ? as_global(to_kept ? kept[k] : K.n[k]) : nullptr;
         dt[k] = k < planes ? as_global(K.t[k]) : nullptr;
     }
-    for (int v = t; (which & 1) && v < nrows * (cp / 8); v += kThreads) {
+    for (int v = t; (which & 1) && v < nrows * (cp / 8); v += NT) {
         int row, g8;
         if (to_kept) {
             // along the destination: piece v of the tile's run of whole fragments (row0, nrows: multiples of 32)
@@ -219,7 +220,7 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
     }
     // fragment-order copy: the tile's rows are (nrows / 16) * (cp / 32) whole fragments, one run of consecutive memory
     // per plane; thread v writes the v-th 16-byte piece of that run (row0 and nrows are multiples of 16)
-    for (int v = t; (which & 2) && v < cp * (nrows / 8); v += kThreads) {
+    for (int v = t; (which & 2) && v < cp * (nrows / 8); v += NT) {
         const int ln = v & 63, frag = v >> 6;
         int k16, nb;
         divmod_small(frag, cp >> 5, k16, nb);

@@ -567,6 +567,86 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
     }
 }
 
+// --------------------------------------------------------------------------------------------
+// The same product for blocks wider than the streaming kernel's.  Their tmat (205 KB at width 160) fits neither registers nor
+// LDS; apply_kernel stages 32 columns of it at a time behind barriers on four waves per 64 rows, and with 128 tiles of 64
+// rows (8192 x 128) that chain of round trips was all of its 45 us.  Here sixteen waves share a tile: wave (row group, column
+// group) walks every fourth 16-column tile of the result along the reduction index with the fragments of tmat loaded
+// straight from L2, four steps ahead.
+// --------------------------------------------------------------------------------------------
+constexpr int kApplyWideThreads = 1024;
+__global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const LayerDev* __restrict__ layers,
+                                                                       const int* __restrict__ ids, int src_role,
+                                                                       int dst_role, int mode, int cp, int gate, int w_in_max,
+                                                                       int w_out_max, int which) {
+    const LayerDev& L = layers[ids[blockIdx.y]];
+    if (!gate_open(L, gate)) return;
+    const int need2 = L.status[1];
+    if (mode == APPLY_PASS2 && !need2) return;
+    const bool do_gram = (mode == APPLY_PASS1) && need2;
+    const bool do_pack = !do_gram && cp > 0;
+    const int side = side_of_role(L.transposed, src_role);
+    const int len = side_len(L, side), lenP = side_lenP(L, side);
+    const int i0 = blockIdx.x * kGramRows2;
+    if (i0 >= (do_pack ? lenP : len)) return;
+    const ThinRef X = L.thin[src_role];
+    const ThinRef Y = L.thin[dst_role];
+    const int w_in = X.width, w_out = Y.width;
+    const bool upper = mode != APPLY_RITZ;
+    const int kpad = (w_in + 15) & ~15, n_ct = (w_out + 15) / 16;
+    const int xs = ((w_in_max + 15) & ~15) + 1;
+    const int wo16 = (w_out_max + 15) & ~15, ow = (cp > wo16 ? cp : wo16) + 1;
+    extern __shared__ __align__(16) unsigned char smem[];
+    float* sx = reinterpret_cast<float*>(smem);            // [64][xs]  x tile, zero beyond the matrix
+    float* so = sx + (size_t)kGramRows2 * xs;              // [64][ow]  result tile, zero beyond w_out
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
+    for (int i = wv; i < kGramRows2; i += kApplyWideThreads / 64) {
+        const bool in = i0 + i < len;
+        const PSGD_GLOBAL float* xr = as_global(X.ptr) + (int64_t)(in ? i0 + i : 0) * X.ld;
+        for (int c = lane; c < kpad; c += 64) sx[i * xs + c] = (in && c < w_in) ? xr[c] : 0.f;
+        for (int c = lane; c < ow; c += 64) so[i * ow + c] = 0.f;
+    }
+    __syncthreads();
+    const int rg = wv & 3, cg = wv >> 2;
+    const float* __restrict__ xa = sx + (16 * rg + li) * xs + lk;
+    const PSGD_GLOBAL double* __restrict__ tm = as_global(L.tmat);
+    for (int ct = cg; ct < n_ct; ct += 4) {
+        const int col = 16 * ct + li;
+        const int kend = upper ? min(kpad, 16 * (ct + 1)) : kpad;
+        const bool col_ok = col < w_in;
+        auto frag = [&](int k) {                           // (k + lk may pass the end: that row counts as zero)
+            const bool ok = col_ok && k + lk < w_in;
+            const double v = tm[ok ? (int64_t)(k + lk) * w_in + col : 0];
+            return ok ? v : 0.0;
+        };
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+        double b[4], bn[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = frag(4 * u);
+        for (int k = 0; k < kend; k += 16) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bn[u] = frag(k + 16 + 4 * u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xa[k + 4 * u], b[u], acc, 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) b[u] = bn[u];
+        }
+        if (col < w_out) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) so[(16 * rg + 4 * v + lk) * ow + col] = (float)acc[v];
+        }
+    }
+    __syncthreads();
+    const int rows_valid = min(len, i0 + kGramRows2) - i0;
+    for (int i = wv; i < rows_valid; i += kApplyWideThreads / 64) {
+        PSGD_GLOBAL float* yr = as_global(Y.ptr) + (int64_t)(i0 + i) * Y.ld;
+        for (int c = lane; c < w_out; c += 64) yr[c] = so[i * ow + c];
+    }
+    if (do_gram) gram_tile_f64(so, ow, kGramRows2, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
+    else if (do_pack) write_packs<0, kApplyWideThreads>(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
+}
+
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
@@ -595,6 +675,16 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kfn, dim3(per_layer, n_ids), block, lds, st, layers, ids, src_role, dst_role,
                            mode, cp, gate, w_out, which);
+        return hipGetLastError();
+    }
+    if (!small && w_out <= w_in) {
+        const int wi16 = (w_in + 15) & ~15, wo16 = (w_out + 15) & ~15;
+        const size_t lds = (size_t)kGramRows2 * (wi16 + 1 + (cp > wo16 ? cp : wo16) + 1) * sizeof(float);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(apply_wide_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(apply_wide_kernel, grid, dim3(kApplyWideThreads), lds, st, layers, ids, src_role, dst_role, mode, cp,
+                           gate, w_in, w_out, which);
         return hipGetLastError();
     }
     // w_in / w_out are upper bounds over the layers: sizes that grow with them cover every layer

@@ -9,6 +9,8 @@
 // Cholesky at step k equals (norm of column k's part orthogonal to the earlier columns / norm of
 // column k)^2; if it is <= rank_tol^2 the column is declared dependent and its P~ column is zero.
 #pragma once
+#include <type_traits>
+
 #include "psgd_dev.h"
 
 namespace psgd {
@@ -89,13 +91,51 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Value of v on lane `lane`, the same lane for the whole wavefront (a constant or a uniform value): two scalar
-// lane reads instead of the LDS-routed general shuffle, whose latency would sit on the critical path of every
-// step of the in-register factorisations below.  All lanes of the wave must be active.
-__device__ inline double bcast_lane(double v, int lane) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+// Value of v on lane I of each row of 16 lanes (a row broadcast on the data path: two moves, no scalar register in between.
+// Lane reads into scalar registers cost these factorisations 30 to 60 cycles per updated row, most of their time).
+template <int I> __device__ __forceinline__ double bcast_row(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + I, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + I, 0xf, 0xf, false);
     return __hiloint2double(hi, lo);
+}
+template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(static_cast<F&&>(f));
+    }
+}
+
+// Right-looking Cholesky A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
+// barriers: lane j of every row of 16 lanes holds column j of the matrix (x, the four rows of lanes hold the same) and column
+// j of an identity matrix (y), which the row operations turn into R^{-T}: y[i] on lane c ends up as T[c][i], T = R^{-1}, and
+// no separate inversion is needed.  A dependent column (flagged in badmask, or pivot not above tol2) makes row k of R the
+// k-th row of the identity and skips the update (multiplier 0).  Written without branches (selects): with branches the
+// compiler copies the whole register array at every merge point, which cost more than the arithmetic.
+template <int W>
+__device__ __forceinline__ void factor_in_registers(double (&x)[W], double (&y)[W], double tol2, int& badmask, double& min_piv) {
+    const int j = threadIdx.x & 15;
+    static_for<0, W>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        const double piv = bcast_row<k>(x[k]);
+        const bool dep = ((badmask >> k) & 1) || !(piv > tol2);
+        badmask |= dep ? (1 << k) : 0;
+        min_piv = (!dep && piv < min_piv) ? piv : min_piv;
+        const double rinv = rsqrt_nr(dep ? 1.0 : piv);
+        const double xk = dep ? (j == k ? 1.0 : 0.0) : x[k] * rinv;               // row k <- row k / R_kk
+        const double yk = dep ? y[k] : y[k] * rinv;
+        x[k] = xk;
+        y[k] = yk;
+        const double mx = dep ? 0.0 : xk, my = dep ? 0.0 : yk;
+        static_for<k + 1, W>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const double m = -bcast_row<i>(xk);                                   // row i <- row i - R[k][i] row k (on a lane
+            x[i] = __builtin_fma(m, mx, x[i]);                                    // j < i an entry below the diagonal: never read)
+            y[i] = __builtin_fma(m, my, y[i]);
+            // (an ordering point without an instruction: left alone the compiler collects the broadcasts of all steps at
+            // the front and spills)
+            asm volatile("" : "+v"(x[i]), "+v"(y[i]));
+        });
+    });
 }
 
 // Second-pass permission carried by a launch: -1 always, -2 never, else an iteration gate (kind 2).
@@ -105,66 +145,38 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
     return gate_open(L, a2gate);
 }
 
-// The factorisation for w <= 16 by one wavefront without LDS traffic or barriers: lane j < 16 holds column j
-// of the scaled matrix in registers, lane 16 + c holds column c of an identity matrix, and the steps
-// exchange values with cross-lane reads.  The row operations of the right-looking Cholesky A = R^T R turn
-// the identity columns into R^{-T}, so lane 16 + c ends up with row c of T = R^{-1} and no separate
-// inversion is needed.  g: the summed Gram matrix (packed upper triangle, LDS).  Same arithmetic and
-// outputs as the general path of chol_body.  W: compiled width (w <= W); rows and columns w .. W-1 are
-// those of an identity matrix.
+// The factorisation for w <= 16 by one wavefront (see factor_in_registers).  g: the summed Gram matrix (packed upper triangle,
+// LDS).  Same arithmetic and outputs as the general path of chol_body.  W: compiled width (w <= W); rows and columns
+// w .. W-1 are those of an identity matrix.
 template <int W>
 __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                            bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
-    const int j = threadIdx.x & 63;
-    const bool aug = j >= 16;                          // identity column c = j - 16
-    const int c = (j - 16) & 15;
-    const int jc = j < w ? j : 0;                      // matrix lanes >= w hold identity columns
+    const int c = threadIdx.x & 15;
+    const int jc = c < w ? c : 0;
     const double djj = g[tri_idx(jc, jc, w)];
     const double dsc_own = djj > kTinyNorm2 ? rsqrt_nr(djj) : 0.0;
-    const double dsc_row = __shfl(dsc_own, c < w ? c : 0);    // scaling of row c (used by lane 16 + c)
-    // a[i]: entry (i, j) of the scaled matrix, later of R; on lane 16 + c entry (i, c) of R^{-T}
-    double a[W];
+    double x[W], y[W];
     int badmask = 0;
-#pragma unroll
-    for (int i = 0; i < W; ++i) {
-        const double dsi = bcast_lane(dsc_own, i < w ? i : 0);
+    static_for<0, W>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const double dsi = bcast_row<i>(dsc_own);
         if (i < w && !(dsi > 0.0)) badmask |= 1 << i;
-        double x = (i == (aug ? c : j)) ? 1.0 : 0.0;
-        if (!aug && i < w && j < w && i <= j) x = g[tri_idx(i, jc, w)] * dsi * dsc_own;
-        a[i] = x;
-    }
+        y[i] = i == c ? 1.0 : 0.0;
+        x[i] = (i < w && c < w && i <= c) ? g[tri_idx(i < w ? i : 0, jc, w)] * dsi * dsc_own : y[i];
+    });
     double min_piv = 1.0;
-    // Written without branches (selects on the wave-uniform `dep`): with branches the compiler copies the whole
-    // register array at every merge point, which cost more than the arithmetic.  Rows k >= w are rows of the
-    // identity: pivot 1, multipliers 0, nothing changes.  A dependent column (pivot not above tol2) makes row k of
-    // R the k-th row of the identity and skips the update (multiplier 0).
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const double piv = bcast_lane(a[k], k);
-        const bool dep = ((badmask >> k) & 1) || !(piv > tol2);
-        badmask |= dep ? (1 << k) : 0;
-        min_piv = (!dep && piv < min_piv) ? piv : min_piv;
-        const double rinv = rsqrt_nr(dep ? 1.0 : piv);
-        const double ak = dep ? (aug ? a[k] : (j == k ? 1.0 : 0.0)) : a[k] * rinv;   // row k <- row k / R_kk
-        a[k] = ak;
-        const double mult = dep ? 0.0 : ak;
-#pragma unroll
-        for (int i = k + 1; i < W; ++i)
-            a[i] = __builtin_fma(-bcast_lane(ak, i), mult, a[i]);   // row i <- row i - R[k][i] row k  (on a matrix lane
-                                                                    // j < i an entry below the diagonal: never read)
+    factor_in_registers<W>(x, y, tol2, badmask, min_piv);
+    if (scale) {                                          // (uniform: every lane takes part in the broadcasts)
+        const double csc = next_scale(dsc_own);
+        static_for<0, W>([&](auto ic) { constexpr int i = decltype(ic)::value; y[i] *= bcast_row<i>(csc); });
     }
-    if (scale) {                                          // (uniform: every lane takes part in the lane reads)
-        const double csc_own = next_scale(dsc_own);
-#pragma unroll
-        for (int i = 0; i < W; ++i) a[i] *= bcast_lane(csc_own, i < w ? i : 0);
-    }
-    // lane 16 + c: row c of tmat = D T with the dependent columns zeroed
-    if (aug && j < 16 + w) {
+    // lane c: row c of tmat = D T with the dependent columns zeroed
+    if ((threadIdx.x & 63) < w) {
 #pragma unroll
         for (int i = 0; i < W; ++i)
-            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : a[i] * dsc_row;
+            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : y[i] * dsc_own;
     }
-    if (j == 0) {
+    if ((threadIdx.x & 63) == 0) {
         const int nbad = __popc(badmask & ((1 << w) - 1));
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
@@ -187,43 +199,25 @@ __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const doubl
     else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
 }
 
-// Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers (same scheme as above): factorises
-// the block `blk` (row-major, upper part), leaves T_JJ = R_JJ^{-1} (all 16 x 16 of it) in `tjj` and updates the
-// dependent-column flags and the smallest accepted pivot.  All 64 lanes of the wave call it.
+// Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers: factorises the block `blk` (row-major,
+// upper part), leaves T_JJ = R_JJ^{-1} (all 16 x 16 of it) in `tjj` and updates the dependent-column flags and the smallest
+// accepted pivot.  All 64 lanes of the wave call it.
 __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, double tol2, int* bad, double& min_piv) {
     constexpr int W = 16;
-    const int j = threadIdx.x & 63;
-    const bool aug = j >= 16;
-    const int c = (j - 16) & 15;
-    double x[W];
-    int badmask = 0;
+    const int c = threadIdx.x & 15, row = (threadIdx.x & 63) >> 4;
+    double x[W], y[W];
+    int badmask = (int)(__ballot(bad[c] != 0) & 0xffff);
 #pragma unroll
     for (int i = 0; i < W; ++i) {
-        if (bad[i]) badmask |= 1 << i;
-        double v = (i == (aug ? c : j)) ? 1.0 : 0.0;
-        if (!aug && i <= j) v = blk[16 * i + j];
-        x[i] = v;
+        y[i] = i == c ? 1.0 : 0.0;
+        x[i] = i <= c ? blk[16 * i + c] : 0.0;
     }
-    // (branch-free for the same reason as above)
+    factor_in_registers<W>(x, y, tol2, badmask, min_piv);
+    // lane c holds row c of T_JJ (each row of lanes writes a quarter of it)
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const double piv = bcast_lane(x[k], k);
-        const bool dep = ((badmask >> k) & 1) || !(piv > tol2);
-        badmask |= dep ? (1 << k) : 0;
-        min_piv = (!dep && piv < min_piv) ? piv : min_piv;
-        const double rinv = rsqrt_nr(dep ? 1.0 : piv);
-        const double xk = dep ? (aug ? x[k] : (j == k ? 1.0 : 0.0)) : x[k] * rinv;
-        x[k] = xk;
-        const double mult = dep ? 0.0 : xk;
-#pragma unroll
-        for (int i = k + 1; i < W; ++i) x[i] = __builtin_fma(-bcast_lane(xk, i), mult, x[i]);
-    }
-    // lane 16 + c holds row c of T_JJ
-    if (aug && j < 32) {
-#pragma unroll
-        for (int i = 0; i < W; ++i) tjj[kTjjStride * c + i] = x[i];
-    }
-    if (j < 16) bad[j] = (badmask >> j) & 1;
+    for (int i = 0; i < W; ++i)
+        if ((i >> 2) == row) tjj[kTjjStride * c + i] = y[i];
+    if (row == 0) bad[c] = (badmask >> c) & 1;
 }
 
 // Cholesky factorisation and inverse of its factor in one sweep over 16 x 16 blocks: the row operations that turn A into R
@@ -233,10 +227,10 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // on the fp64 matrix cores, blocks dealt to the waves.  W_IK lives where A_KI was (row K of A is finished by then), row J
 // of R in a buffer of its own, so one triangle of blocks holds everything; every operand is read row by row, 64 consecutive
 // doubles per instruction.
-// What bounds it is the chain of 16 steps inside each diagonal block (about 2 us): one wave updates and factorises block
-// J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.  One workgroup on a
-// 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion (packed triangle, five
-// barriers per block, spilling as a function call); 55 us now, 80 x 80 58 -> 27 us.
+// What bounds it is the chain of 16 steps inside each diagonal block (7200 cycles of the 10000 a block takes): one wave updates
+// and factorises block J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.
+// One workgroup on a 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion
+// (packed triangle, five barriers per block, spilling as a function call); 55 us now, 80 x 80 58 -> 27 us.
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
                                     unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv) {
@@ -250,39 +244,41 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
     const int t = threadIdx.x, nt = blockDim.x;
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), nw = nt >> 6, li = lane & 15, lk = lane >> 4;
     auto at = [&](int I, int K) { return a + (I * nbk - (I * (I - 1)) / 2 + (K - I)) * 256; };
-    // ---- blocks of the Gram matrix (256 threads per block, eight loads per thread in flight); identity in the padding
-    {
-        const int r = (t >> 4) & 15, c = t & 15, ng = nt >> 8;
-        for (int b0 = t >> 8; b0 < nblk; b0 += 8 * ng) {
-            double v[8];
-            int off[8];
+    // ---- blocks of the Gram matrix (256 threads per block, eight loads per thread in flight); identity in the padding.
+    // Which block is a scalar computation.
+    const int ng = nt >> 8, grp = __builtin_amdgcn_readfirstlane(t >> 8), er = (t >> 4) & 15, ec = t & 15;
+    auto decode = [&](int b, int& I, int& K) {
+        I = 0; K = b;
+        while (K >= nbk - I) { K -= nbk - I; ++I; }
+        K += I;
+    };
+    for (int b0 = grp; b0 < nblk; b0 += 8 * ng) {
+        double v[8], pad[8];
+        int off[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int b = min(b0 + u * ng, nblk - 1);
-                int K = b, I = 0;
-                while (K >= nbk - I) { K -= nbk - I; ++I; }
-                K += I;
-                const int i = 16 * I + r, j = 16 * K + c;
-                off[u] = (i <= j && j < w) ? tri_idx(i, j, w) : -1;
-                v[u] = off[u] >= 0 ? g[off[u]] : (i == j ? 1.0 : 0.0);
-            }
-            if (n_slots > 1) {
-                for (int s0 = 1; s0 < n_slots; s0 += 4) {
-                    double x[4][8];
-#pragma unroll
-                    for (int d = 0; d < 4; ++d)
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) x[d][u] = (s0 + d < n_slots && off[u] >= 0) ? g[(s0 + d) * sstr + off[u]] : 0.0;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d)
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) v[u] += x[d][u];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * r + c] = v[u];
+        for (int u = 0; u < 8; ++u) {
+            int I, K;
+            decode(min(b0 + u * ng, nblk - 1), I, K);
+            const int i = 16 * I + er, j = 16 * K + ec;
+            // (every lane loads: a conditional load is a branch, and eight of them run one after the other)
+            off[u] = (i <= j && j < w) ? tri_idx(i, j, w) : -1;
+            v[u] = g[max(off[u], 0)];
+            pad[u] = i == j ? 1.0 : 0.0;
         }
+        for (int s0 = 1; s0 < n_slots; s0 += 4) {
+            double x[4][8];
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[d][u] = g[min(s0 + d, n_slots - 1) * sstr + max(off[u], 0)];
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] += s0 + d < n_slots ? x[d][u] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * er + ec] = off[u] >= 0 ? v[u] : pad[u];
     }
     __syncthreads();
     for (int i = t; i < wp; i += nt) {
@@ -291,29 +287,59 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
         bad[i] = d > kTinyNorm2 ? 0 : 1;
     }
     __syncthreads();
-    {
-        // (four blocks of a thread at a time)
-        const int r = (t >> 4) & 15, c = t & 15, ng = nt >> 8;
-        for (int b0 = t >> 8; b0 < nblk; b0 += 4 * ng) {
-            double v[4];
+    for (int b0 = grp; b0 < nblk; b0 += 4 * ng) {
+        double v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int b = min(b0 + u * ng, nblk - 1);
-                int K = b, I = 0;
-                while (K >= nbk - I) { K -= nbk - I; ++I; }
-                v[u] = a[b * 256 + 16 * r + c] * (dsc[16 * I + r] * dsc[16 * (K + I) + c]);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * r + c] = v[u];
+        for (int u = 0; u < 4; ++u) {
+            const int b = min(b0 + u * ng, nblk - 1);
+            int I, K;
+            decode(b, I, K);
+            v[u] = a[b * 256 + 16 * er + ec] * (dsc[16 * I + er] * dsc[16 * K + ec]);
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * er + ec] = v[u];
     }
     __syncthreads();
     min_piv = 1.0;
-    if (wv == 0) chol_block16(a, tjj, tol2, bad, min_piv);
-    __syncthreads();
+    // trailing update of step J for block (I, K), K >= I > J of A or K <= J < I of W
+    auto update = [&](int J, int I, int K) {
+        double* blk = K >= I ? at(I, K) : at(K, I);
+        const double* __restrict__ ra = rj + I * 256;
+        const double* __restrict__ rb = K > J ? rj + K * 256 : at(K, J);
+        double av[4], bv[4];
+        doublex4 d;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { av[c] = -ra[16 * (4 * c + lk) + li]; bv[c] = rb[16 * (4 * c + lk) + li]; }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d[v] = K == J ? 0.0 : blk[16 * (4 * v + lk) + li];      // (K = J: W_IJ starts at zero)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) blk[16 * (4 * v + lk) + li] = d[v];
+    };
+#pragma unroll 1
     for (int J = 0; J < nbk; ++J) {
+        // ---- the rest of step J - 1: block (J, J) and its factorisation by wave 0, the other blocks by the other waves
+        if (wv == 0) {
+            if (J > 0) update(J - 1, J, J);
+            wave_sync();
+            chol_block16(at(J, J), tjj, tol2, bad + 16 * J, min_piv);
+        } else if (J > 0) {
+            // the blocks of rows I >= J one after the other, in each those of W (K < J), then those of A (K >= I)
+            int I = J, k = wv - 1, row = J + (nbk - I);
+#pragma unroll 1
+            for (;;) {
+                while (I < nbk && k >= row) { k -= row; ++I; --row; }
+                if (I >= nbk) break;
+                const int K = k < J ? k : I + (k - J);
+                if (I != J || K != I) update(J - 1, I, K);
+                k += nw - 1;
+            }
+        }
+        __syncthreads();
         // ---- panel
+#pragma unroll 1
         for (int K = wv; K < nbk; K += nw) {
             double* blk = K < J ? at(K, J) : at(J, K);
             doublex4 d = {0.0, 0.0, 0.0, 0.0};
@@ -336,39 +362,6 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
                 // T[i][j] = W[j][i], zero below the diagonal and in the columns of dependent vectors
                 if (i < w && j < w)
                     tm[(int64_t)i * w + j] = (K > J || dep) ? 0.0 : d[v] * dsc[i] * (scale ? next_scale(dsc[j]) : 1.0);
-            }
-        }
-        __syncthreads();
-        if (J + 1 == nbk) break;
-        // ---- trailing update; block (J + 1, J + 1) and its factorisation by wave 0
-        auto update = [&](int I, int K) {
-            double* blk = K >= I ? at(I, K) : at(K, I);
-            const double* __restrict__ ra = rj + I * 256;
-            const double* __restrict__ rb = K > J ? rj + K * 256 : at(K, J);
-            double av[4], bv[4];
-            doublex4 d;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { av[c] = -ra[16 * (4 * c + lk) + li]; bv[c] = rb[16 * (4 * c + lk) + li]; }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) d[v] = K == J ? 0.0 : blk[16 * (4 * v + lk) + li];      // (K = J: W_IJ starts at zero)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) blk[16 * (4 * v + lk) + li] = d[v];
-        };
-        if (wv == 0) {
-            update(J + 1, J + 1);
-            wave_sync();
-            chol_block16(at(J + 1, J + 1), tjj, tol2, bad + 16 * (J + 1), min_piv);
-        } else {
-            // the blocks of rows I > J one after the other, in each those of W (K <= J), then those of A (K >= I)
-            int I = J + 1, k = wv - 1, row = J + 1 + (nbk - I);
-            for (;;) {
-                while (I < nbk && k >= row) { k -= row; ++I; --row; }
-                if (I >= nbk) break;
-                const int K = k <= J ? k : I + (k - (J + 1));
-                if (I != J + 1 || K != I) update(I, K);
-                k += nw - 1;
             }
         }
         __syncthreads();

@@ -38,3 +38,31 @@ def test_ssp_step(r, rows, cols, dependent):
     assert orc.rel_fro(e, ml - out.delta_hat) <= 1e-4
     assert case.comp.status(0).rank_deficient == len(dep)
     assert all(np.all(p[:, j] == 0.0) for j in dep)
+
+
+# nearly dependent columns: the first CholeskyQR pass asks for the second; one tile of 64 rows, several, a ragged one, alone and
+# in a batch with layers that do not need it
+@pytest.mark.parametrize("r", [2, 8, 16, 24, 64])
+# (r at most half of the short side of the first layer: the close pair's pivot, 1e-8 (1 - r / n), stays above 1e-10, where
+# a column counts as dependent)
+@pytest.mark.parametrize("shapes", [[(160, 128)], [(1003, 136)], [(136, 1000)], [(1003, 136), (130, 128), (72, 512)]])
+def test_second_pass(r, shapes):
+    rng = np.random.default_rng(r)
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    case = Case(shapes, r, 1, synth.F32, lds=lds)
+    ms = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    qs = [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes]
+    qs[0][:, r - 1] = qs[0][:, 0] + np.float32(1e-4) * qs[0][:, r - 1]        # pivot about 1e-8
+    case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+    case.compress()
+    for l, (rows, cols) in enumerate(shapes):
+        p, q, e = case.outputs(l)
+        ml = ms[l].astype(np.float64)
+        if rows < cols:
+            ml, e = ml.T, e.T
+        out = orc.ssp_comp(qs[l].astype(np.float64), [ml])
+        # (p moves by cond(M Q) ~ 1e4 times the 1e-7 of the product where the columns are close; the rest is exact in p)
+        assert orc.rel_fro(p, out.p_tilde) <= (2e-2 if l == 0 else 1e-4), l
+        assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6, l
+        assert np.linalg.norm(q - ml.T @ p) <= 2e-6 * np.linalg.norm(ml), l
+        assert np.linalg.norm(e - (ml - p @ q.T)) <= 2e-6 * np.linalg.norm(ml), l
