@@ -241,16 +241,19 @@ bool form_row_env() {
 // up grow with the width, and the wide product kernels do not gain from more workgroups (4096 x 4096: the step at
 // r = 64 takes 0.325 ms with 1024 workgroups, 0.302 with 256; at r = 128 0.514 and 0.473; at r = 16 and 32 it is
 // the other way round).
-int split_target(bool form, int cp) {
+// Two per compute unit where their operand buffers fit its LDS twice (two planes up to width 128): 8192 x 8192 bf16 r = 128
+// 518 -> 497 us per step, 2048 x 6000 r = 100 237 -> 228; with three planes one fits, and 4096 x 4096 fp32 r = 128 takes 307 us
+// with 512 workgroups against 288.
+int split_target(bool form, int cp, int planes) {
     int target = target_tiles_env();
-    if (target == 0) target = cp >= 64 ? kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);
+    if (target == 0) target = cp >= 64 ? (planes == 2 && cp <= 128 ? 2 : 1) * kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);
     else if (!form && target > kTargetTilesPlain) target = target / 2;
     return target;
 }
 // (A launch that reaches three quarters of the target by itself is left whole: the forming pass of the 22 matrices of a
 // 1B-shaped model stored as the transpose, 968 workgroups, is 0.1 ms faster than in halves with their finish_kernel.)
-int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp) {
-    const int target = split_target(form, cp);
+int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int planes) {
+    const int target = split_target(form, cp, planes);
     if (4 * base_tiles >= 3 * target) return 1;
     int64_t s = (target + base_tiles - 1) / base_tiles;
     if (s > kMaxSplit) s = kMaxSplit;
@@ -267,7 +270,7 @@ int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp) {
 // r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 96 us; two 1B-shaped fp32 blocks at r = 16: row product of
 // the two matrices stored as the transpose (64 workgroups before) 101 -> 33 us, step 939 -> 865 us.
 template <class Tiles, class Chunks>
-void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, Tiles tiles, Chunks chunks,
+void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, int planes, Tiles tiles, Chunks chunks,
                  int Plan::*split) {
     int64_t base = 0, steps = 0;
     int most = 1;
@@ -277,7 +280,7 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
         most = std::max(most, (int)chunks(plan[l]));
     }
     if (base == 0) return;
-    const int s = choose_split(base, most, form, cp);
+    const int s = choose_split(base, most, form, cp, planes);
     if (s <= 1) return;
     // Steps per workgroup: with walks of one length as many pieces as choose_split says, with several lengths the fewest
     // steps that keep the launch within its target (pieces of one size run in whole rounds of the GPU: 608 of them where
@@ -290,7 +293,7 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
             for (int l : ids) n += (int64_t)tiles(plan[l]) * std::max<int64_t>(2, std::min<int64_t>((chunks(plan[l]) + q - 1) / q, kMaxSplit));
             return n;
         };
-        const int64_t target = split_target(form, cp);
+        const int64_t target = split_target(form, cp, planes);
         per = std::max<int64_t>(1, steps / target);
         while (per < most && total(per) > target) ++per;
     }
@@ -794,18 +797,18 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
         auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
         auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
-        plan_splits(c->plan, *ids, false, c->cpc, row_tiles, row_chunks, &Plan::split_row);
-        plan_splits(c->plan, *ids, false, c->cpc, col_tiles, col_chunks, &Plan::split_col);
-        plan_splits(c->plan, *ids, true, c->cpc, row_tiles, row_chunks, &Plan::split_row_f);
-        plan_splits(c->plan, *ids, true, c->cpc, col_tiles, col_chunks, &Plan::split_col_f);
+        plan_splits(c->plan, *ids, false, c->cpc, c->planes, row_tiles, row_chunks, &Plan::split_row);
+        plan_splits(c->plan, *ids, false, c->cpc, c->planes, col_tiles, col_chunks, &Plan::split_col);
+        plan_splits(c->plan, *ids, true, c->cpc, c->planes, row_tiles, row_chunks, &Plan::split_row_f);
+        plan_splits(c->plan, *ids, true, c->cpc, c->planes, col_tiles, col_chunks, &Plan::split_col_f);
         // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split), their
         // column products, and the row products of the layers stored with rows < cols
         auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
         auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
         auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
         auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
-        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, row_tiles_v2, row_chunks_v2, &Plan::split_row_v2);
-        plan_splits(c->plan, *ids, false, 32, col_tiles_v2, col_chunks_v2, &Plan::split_col_v2);
+        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, c->planes, row_tiles_v2, row_chunks_v2, &Plan::split_row_v2);
+        plan_splits(c->plan, *ids, false, 32, c->planes, col_tiles_v2, col_chunks_v2, &Plan::split_col_v2);
     }
     {
         int64_t m_bytes = 0, mt_bytes = 0;
@@ -1178,8 +1181,8 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     D.thin[ROLE_P].ptr = P;
     D.thin[ROLE_Q].ptr = Q;
     Plan one = p;
-    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz);
-    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz);
+    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->planes);
+    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->planes);
     one.split_row_f = one.split_row; one.split_col_f = one.split_col;      // (no forming pass in this call)
     D.split_row = one.split_row; D.split_col = one.split_col;
     D.split_row_f = one.split_row_f; D.split_col_f = one.split_col_f;
