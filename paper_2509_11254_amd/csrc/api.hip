@@ -559,15 +559,17 @@ struct Launcher {
     // layer's last iteration; that iteration only notes the need, see second_pass_deferred.  cp > 0: also leave the
     // split-bf16 operand copies of the result.
     enum Pass2 { PASS2_NEVER = 0, PASS2_ALWAYS = 1, PASS2_DEFERRED = 2 };
-    void prod_orth(bool p_like, bool form, int nb, int out_role, int w, double tol2, int cp, int kind, Pass2 pass2) {
-        const int g = gate < 0 ? -1 : gate_with_kind(gate, kind);
+    // if_asked (Y of the subspace iteration): only for the layers whose Z asked for it; the others' product leaves the operand
+    // copies, and the launches behind it find nothing to do.
+    void prod_orth(bool p_like, bool form, int nb, int out_role, int w, double tol2, int cp, int kind, Pass2 pass2, bool if_asked = false) {
+        const int g = gate < 0 ? -1 : gate_with_kind(gate, kind) | (if_asked ? kGateIfAsked : 0);
         const int a2 = pass2 == PASS2_ALWAYS ? -1 : (pass2 == PASS2_NEVER || gate < 0) ? -2 : gate_with_kind(gate, 2);
         // narrow blocks everywhere: the apply kernel factorises per workgroup and hands over to the second
         // factorisation itself; otherwise the second factorisation is a launch of its own
         const bool small = w <= 16;
         // (inside the iteration only products read the result: no row-major operand copies)
         const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_ROWMAJOR | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
-        prod(p_like, form, nb, out_role, EPI_GRAM, g, a2, tol2, w, small);
+        prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
             if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g, -2, 0, st));
@@ -678,15 +680,13 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
         // every layer runs its own number of iterations (decided on the device from the Ritz values of
         // its previous refresh); launches past that number find their gate closed and exit at once
         L.gate = make_gate(it, 0, iters, n_launch);
-        // Z = orth(M Y);  Y = M^T Z, orthonormalised in the first kOrthYIterations iterations only: the span, which is
-        // what the iteration is about, does not depend on it, and from then on the columns of Z have lined up with the
-        // singular vectors, so that those of M^T Z are nearly orthogonal (their norms are evened out on the way, see
-        // next_scale).  Saves the factorisation and the pass over the thin matrix, half of the serial chain between the
-        // products: 4096 x 4096 fp32 r = 8, 16 iterations, 1.29 -> 1.17 ms; 8192 x 8192 r = 128 15.9 -> 12.4 ms;
-        // the seven matrices of a 7B-shaped block in bf16 7.9 -> 7.0 ms; errors against 64 bits unchanged.
+        // Z = orth(M Y);  Y = M^T Z, orthonormalised in the first kOrthYIterations iterations, later only where the factor
+        // of Z says that it has to be (see Spread): the span, which is what the iteration is about, does not depend on it,
+        // and once the columns of Z have lined up with the singular vectors those of M^T Z are nearly orthogonal (their norms
+        // are evened out on the way, see next_scale).  The factorisation and the pass over the thin matrix are half of the
+        // serial chain between the products.
         L.prod_orth(true, form_first && it == 0, nbz, ROLE_ZP, wz, tol2, cpz, 0, Launcher::PASS2_DEFERRED);
-        if (it < kOrthYIterations) L.prod_orth(false, false, nbz, ROLE_ZQ, wz, tol2, cpz, 1, Launcher::PASS2_NEVER);
-        else L.prod(false, false, nbz, ROLE_ZQ, EPI_ITERATE);
+        L.prod_orth(false, false, nbz, ROLE_ZQ, wz, tol2, cpz, 1, Launcher::PASS2_NEVER, it >= kOrthYIterations);
     }
     L.gate = -1;
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)

@@ -45,7 +45,8 @@ template <int BIT, class V> __device__ inline void st_stream(PSGD_GLOBAL V* p, V
 
 constexpr int kStatusWords = 8 + 16 + 8; // per layer: 8 diagnostics and counters, one counter per Gram slot group,
                                          // then: [24] refreshes this layer has run in this workspace, [25] iterations
-                                         // its next refresh runs if its cut has no gap (see refresh_iterations)
+                                         // its next refresh runs if its cut has no gap (see refresh_iterations),
+                                         // [26] whether this iteration's Y is orthonormalised (see Spread)
 constexpr int kThreads = 256;      // 4 wavefronts of 64 lanes
 constexpr int kLenPad = 128;       // packed operand rows are padded (with zeros) to this multiple
 constexpr int kGramRows1 = 128;    // rows per partial Gram matrix written by a product's epilogue
@@ -66,8 +67,8 @@ enum Side { SIDE_L = 0, SIDE_W = 1 };
 // blocks of the subspace iteration (leading dimension wz).
 // what a product's epilogue does besides storing the thin result
 enum Epilogue { EPI_NONE = 0, EPI_GRAM = 1, EPI_PACK = 2, EPI_KIND_MASK = 3,
-                EPI_ITERATE = 3,     // Y = M^T Z of the subspace iteration: EPI_GRAM in a layer's last iteration, else only
-                                     // the transposed operand copies (see resolve_epilogue)
+                EPI_ITERATE = 3,     // Y = M^T Z of the subspace iteration: EPI_GRAM in a layer's last iteration and where Y
+                                     // is orthonormalised, else only the transposed operand copies (see resolve_epilogue)
                 EPI_KEEP_E = 16,     // flag: a FORM pass uses M but leaves E in place (M is formed again later)
                 EPI_KEPT = 32 };     // flag: EPI_PACK writes the kept copies (fragment order) in place of the row-major ones
 enum Role { ROLE_P = 0, ROLE_Q = 1, ROLE_ZP = 2, ROLE_ZQ = 3, ROLE_COUNT = 4 };
@@ -254,7 +255,9 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 // that was launched).  kind 1 marks the orthonormalisation of Y, which the last executed iteration skips because
 // the Rayleigh-Ritz step wants Y = M^T Z itself; kind 2 is open in the last executed iteration only (the second
 // CholeskyQR pass on Z, which the Rayleigh-Ritz step needs exact).
+// kGateIfAsked: besides, only for the layers whose last factorisation of Z asked for an orthonormalised Y (status[26]).
 constexpr int kMaxRefreshIterations = 255;
+constexpr int kGateIfAsked = 1 << 26;
 __host__ __device__ inline int make_gate(int iteration, int kind, int budget, int launched) {
     return iteration | kind << 8 | budget << 10 | launched << 18;
 }
@@ -277,7 +280,7 @@ __device__ inline bool gate_open(const LayerDev& L, int gate) {
     int k = refresh_iterations(L, mx);
     k = k < launched ? k : launched;
     if (kind == 2) return it == k - 1;
-    return it < k - kind;
+    return it < k - kind && (!(gate & kGateIfAsked) || L.status[26] != 0);
 }
 
 // What a product of the launch does with its result for this layer.  `copies`: the operand copies EPI_PACK leaves (1 =
@@ -286,12 +289,12 @@ __device__ inline int resolve_epilogue(const LayerDev& L, int epi_flags, int gat
     const int epi = epi_flags & EPI_KIND_MASK;
     copies = 3;
     if (epi != EPI_ITERATE) return epi;
-    if (!gate_open(L, gate_with_kind(gate, 1))) return EPI_GRAM;
+    if (!gate_open(L, gate_with_kind(gate, 1)) || L.status[26] != 0) return EPI_GRAM;
     copies = 2;
     return EPI_PACK;
 }
-// Whether the Z that a factorisation inside the subspace iteration orthonormalises is followed by a Y that is not
-// orthonormalised itself: from the second iteration on, except in the layer's last one.
+// Whether the Z that a factorisation inside the subspace iteration orthonormalises is followed by a Y that may be left as
+// it is: from the second iteration on, except in the layer's last one.
 constexpr int kOrthYIterations = 1;
 __device__ inline bool scales_next(const LayerDev& L, int role, int gate) {
     return gate >= 0 && role == ROLE_ZP && (gate & 0xff) >= kOrthYIterations && gate_open(L, gate_with_kind(gate, 1));

@@ -74,9 +74,8 @@ __device__ inline double rcp_nr(double x) {
 }
 
 // Power of two next to a column's scaling 1 / ||x||, kept within what fp32 can hold.  Z = X T columns multiplied by it
-// give Y = M^T Z columns of norm about 1 where X = M Y' did with a Y' of such columns: the subspace iteration then needs
-// no orthonormalised Y (its columns are as independent as Z's are once these have lined up with the singular vectors,
-// which one iteration from the warm start does), and nothing drifts out of range however small the gradients are.
+// give Y = M^T Z columns of norm about 1 where X = M Y' did with a Y' of such columns, so that a Y that is not
+// orthonormalised (see Spread) does not drift out of range however small the gradients are.
 __device__ inline double next_scale(double dsc) {
     if (!(dsc > 0.0)) return 1.0;
     const int e = __builtin_amdgcn_frexp_exp(dsc);
@@ -104,6 +103,57 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& 
         static_for<I + 1, N>(static_cast<F&&>(f));
     }
 }
+
+template <int CTRL> __device__ __forceinline__ int dpp_or(int other, int v) {
+    return __builtin_amdgcn_update_dpp(other, v, CTRL, 0xf, 0xf, false);
+}
+
+// What the factor R of X = Z R says about the Y = M^T Z that follows.  Left as it is, Y hands M M^T Z to the next
+// factorisation in place of M (orthonormal Y), and every ratio of singular values that Z mixes counts twice:
+//   - Columns out of order.  While a column of Z turns from a weak direction to one s times as strong, the pivot of the
+//     weak one is s^-4 in place of s^-2.  From s = 300 on that is below rank_tol^2 = 1e-10, and the column counts as
+//     dependent and is lost for the rest of the refresh.  A start block whose columns are sorted, or random, passes no
+//     such point; one with the strong directions last does.
+//   - Rounding along the leading vectors, 2^-17 or 2^-24 of sigma_1 (two or three operand planes), becomes
+//     (sigma_1 / sigma_j)^2 of that in X's column j: above its own norm where sigma_j / sigma_1 < 2^-8 or 2^-12.
+// So Y is orthonormalised in an iteration whose Z came with an R_jj more than 4 times an earlier one (or nearly: powers of
+// two), a pivot below 1e-2, or a smallest R_jj below 2^-11 (two planes 2^-7.5) of the largest column norm.
+// Model on 400 x 300 matrices, blocks of 16 and 40, 3 to 16 iterations, geometric spectra and outliers over a flat rest
+// with ratios of 1e2 to 3e4 in the block, sorted, random, permuted and ascending starts, against Y always orthonormal: no more
+// columns lost, sin(theta) within 7 times (at 5e-7; two planes 1.2 times).  Never orthonormal: up to 4 columns with
+// sin(theta) = 1 from a ratio of 5000 on.  The order at 32 in place of 4, or no limit on the pivots: 1e-4 in place of 4e-7.
+// In powers of two of squared norms; dependent columns do not count.
+struct Spread {
+    static constexpr int kNone = 1 << 20, kDisorder = 4;
+    static constexpr double kPivot = 1e-2;
+    int top = -kNone, low = kNone;      // largest column norm, smallest R_jj so far
+    int disorder = 0;
+    __device__ bool asks(int planes, double min_piv) const {
+        return low < kNone && (disorder || min_piv < kPivot || top - low > (planes == 3 ? 22 : 15));
+    }
+    // one column (norm: ||x_j||^2, rjj: R_jj^2)
+    __device__ void add(int norm, int rjj) {
+        disorder |= rjj - low > kDisorder;
+        low = min(low, rjj);
+        top = max(top, norm);
+    }
+    // the 16 columns of a block, one per lane of each row of 16 lanes (every lane of the wavefront ends up with the result)
+    __device__ __forceinline__ void add_block(int norm, int rjj, bool counts) {
+        int e = counts ? rjj : kNone, n = counts ? norm : -kNone;
+        int before = dpp_or<0x111>(kNone, e);                                     // smallest of the lanes before
+        before = min(before, dpp_or<0x111>(kNone, before));
+        before = min(before, dpp_or<0x112>(kNone, before));
+        before = min(before, dpp_or<0x114>(kNone, before));
+        before = min(before, dpp_or<0x118>(kNone, before));
+        n = max(n, dpp_or<0x111>(-kNone, n));
+        n = max(n, dpp_or<0x112>(-kNone, n));
+        n = max(n, dpp_or<0x114>(-kNone, n));
+        n = max(n, dpp_or<0x118>(-kNone, n));
+        disorder |= __ballot(counts && e - min(before, low) > kDisorder) != 0;
+        low = min(low, dpp_or<0x15f>(kNone, min(before, e)));                     // (lane 15 of the row)
+        top = max(top, dpp_or<0x15f>(-kNone, n));
+    }
+};
 
 // Right-looking Cholesky A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
 // barriers: lane j of every row of 16 lanes holds column j of the matrix (x, the four rows of lanes hold the same) and column
@@ -138,6 +188,16 @@ __device__ __forceinline__ void factor_in_registers(double (&x)[W], double (&y)[
     });
 }
 
+// Adds a factorised block's columns to `spread`: lane j's R_jj is x[j] / dsc (dsc = 1 / ||x_j||).
+template <int W>
+__device__ __forceinline__ void note_block(Spread& spread, const double (&x)[W], double dsc, bool counts) {
+    const int j = threadIdx.x & 15;
+    double rjj = 1.0;
+    static_for<0, W>([&](auto ic) { constexpr int i = decltype(ic)::value; rjj = j == i ? x[i] : rjj; });
+    const double norm = __builtin_amdgcn_rcp(counts ? dsc : 1.0);
+    spread.add_block(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp((rjj * norm) * (rjj * norm)), counts);
+}
+
 // Second-pass permission carried by a launch: -1 always, -2 never, else an iteration gate (kind 2).
 __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
     if (a2gate == -1) return true;
@@ -166,9 +226,11 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     });
     double min_piv = 1.0;
     factor_in_registers<W>(x, y, tol2, badmask, min_piv);
+    Spread spread;
     if (scale) {                                          // (uniform: every lane takes part in the broadcasts)
         const double csc = next_scale(dsc_own);
         static_for<0, W>([&](auto ic) { constexpr int i = decltype(ic)::value; y[i] *= bcast_row<i>(csc); });
+        note_block<W>(spread, x, dsc_own, c < w && !((badmask >> c) & 1));
     }
     // lane c: row c of tmat = D T with the dependent columns zeroed
     if ((threadIdx.x & 63) < w) {
@@ -184,6 +246,7 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
+                if (scale) L.status[26] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
@@ -201,8 +264,10 @@ __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const doubl
 
 // Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers: factorises the block `blk` (row-major,
 // upper part), leaves T_JJ = R_JJ^{-1} (all 16 x 16 of it) in `tjj` and updates the dependent-column flags and the smallest
-// accepted pivot.  All 64 lanes of the wave call it.
-__device__ __forceinline__ void chol_block16(const double* blk, double* tjj, double tol2, int* bad, double& min_piv) {
+// accepted pivot; with dsc (the block's 16 column scalings) also `spread` (columns from n_cols on are padding).  All 64 lanes
+// of the wave call it.
+__device__ __forceinline__ void chol_block16(const double* blk, double* tjj, double tol2, int* bad, double& min_piv,
+                                             const double* dsc, int n_cols, Spread& spread) {
     constexpr int W = 16;
     const int c = threadIdx.x & 15, row = (threadIdx.x & 63) >> 4;
     double x[W], y[W];
@@ -218,6 +283,7 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
     for (int i = 0; i < W; ++i)
         if ((i >> 2) == row) tjj[kTjjStride * c + i] = y[i];
     if (row == 0) bad[c] = (badmask >> c) & 1;
+    if (dsc) note_block<W>(spread, x, dsc[c], c < n_cols && !((badmask >> c) & 1));
 }
 
 // Cholesky factorisation and inverse of its factor in one sweep over 16 x 16 blocks: the row operations that turn A into R
@@ -233,7 +299,7 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // (packed triangle, five barriers per block, spilling as a function call); 55 us now, 80 x 80 58 -> 27 us.
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
-                                    unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv) {
+                                    unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread) {
     const int nbk = (w + 15) / 16, wp = 16 * nbk, nblk = (nbk * (nbk + 1)) / 2;
     double* a = reinterpret_cast<double*>(smem);          // blocks (I, K), K >= I, row by row, each [16][16]
     double* rj = a + nblk * 256;                          // [nbk] blocks: row J of R
@@ -324,7 +390,7 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
         if (wv == 0) {
             if (J > 0) update(J - 1, J, J);
             wave_sync();
-            chol_block16(at(J, J), tjj, tol2, bad + 16 * J, min_piv);
+            chol_block16(at(J, J), tjj, tol2, bad + 16 * J, min_piv, scale ? dsc + 16 * J : nullptr, w - 16 * J, spread);
         } else if (J > 0) {
             // the blocks of rows I >= J one after the other, in each those of W (K < J), then those of A (K >= I)
             int I = J, k = wv - 1, row = J + (nbk - I);
@@ -386,7 +452,8 @@ __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
 // Called by all threads of one workgroup per layer (256 or 1024: a multiple of 256 and a power of two); smem:
 // chol_lds_bytes(w), 8-byte aligned.
 // tm: where the w x w factor goes (the layer's tmat, or LDS of the caller); need2_out: optional LDS word
-// that receives the second-pass decision; write_status: whether this caller owns the layer's status words.
+// that receives the second-pass decision; write_status: whether this caller owns the layer's status words; scale: Z of the
+// subspace iteration, see scales_next (powers of two next to its columns' scaling, and whether Y is to be orthonormalised).
 // NARROW: compiled for widths <= 16 only (the register path; nothing else is generated).
 template <bool NARROW = false>
 __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
@@ -408,13 +475,14 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     const int t = threadIdx.x;
     const int nt = blockDim.x, nty = nt >> 4;             // threads, rows of the 16-wide thread grid
     const double* __restrict__ gram = L.gram;
-    auto outcome = [&](int nbad, double min_piv) {
+    auto outcome = [&](int nbad, double min_piv, const Spread& spread) {
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
         if (write_status) {
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
+                if (scale) L.status[26] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
@@ -424,8 +492,9 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
         if (chol_is_blocked(w)) {
             int nbad = 0;
             double min_piv = 1.0;
-            chol_blocked(gram, n_slots, sstr, w, tol2, scale, smem, tm, nbad, min_piv);
-            if (t == 0) outcome(nbad, min_piv);           // (wave 0 has factorised the diagonal blocks)
+            Spread spread;
+            chol_blocked(gram, n_slots, sstr, w, tol2, scale, smem, tm, nbad, min_piv, spread);
+            if (t == 0) outcome(nbad, min_piv, spread);   // (wave 0 has factorised the diagonal blocks)
             return;
         }
     }
@@ -529,6 +598,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     __syncthreads();
     // right-looking Cholesky, A = R^T R, R overwrites the strict upper triangle; 1 / R_kk goes to rdiag
     double min_piv = 1.0;
+    Spread spread;
     for (int k = 0; k < w; ++k) {
         // every thread reads the pivot itself; the pivot entry is never overwritten, so two barriers
         // per step are enough
@@ -542,6 +612,8 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
         } else {
             const double rinv = rsqrt_nr(piv);
             if (t == 0) rdiag[k] = rinv;
+            const double norm = __builtin_amdgcn_rcp(dsc[k]);
+            spread.add(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp(piv * (norm * norm)));
             for (int j = k + 1 + t; j < w; j += nt) a[kbase + j] *= rinv;
         }
         __syncthreads();
@@ -580,7 +652,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     if (t == 0) {
         int nbad = 0;
         for (int i = 0; i < w; ++i) nbad += bad[i];
-        outcome(nbad, min_piv);
+        outcome(nbad, min_piv, spread);
     }
 }
 

@@ -1,8 +1,10 @@
-"""The subspace iteration of the refresh, whose Y = M^T Z is not orthonormalised from the second iteration on: its
-columns are brought to a norm of about one by powers of two instead, at any scale of the gradients."""
+"""The subspace iteration of the refresh, whose Y = M^T Z is orthonormalised from the second iteration on only where the
+factor of Z asks for it: elsewhere its columns are brought to a norm of about one by powers of two, at any scale of the
+gradients."""
 import numpy as np
 import pytest
 
+from oracle import psgd_oracle as orc
 from paper_2509_11254_amd import synth
 from gpu_harness import Case
 from test_gpu_refresh_loops import _check_refreshed_step
@@ -36,3 +38,46 @@ def test_refresh_at_any_scale(rows, cols, r, rank, exponent):
         m, e = m.T, e.T
     # bounds of _check_refreshed_step: 1e-4 on the subspace, 2e-5 of ||M|| on the exact relations (measured: 1e-6, 1e-7)
     _check_refreshed_step(m, p, q, e, r, (rows, cols, r, exponent))
+
+
+# A start block that holds the leading right singular vectors in another order than that of their singular values: on the
+# way to the right one, columns of Z mix strong and weak directions (ratios up to 1e4 here), and none may be lost.  Block
+# widths 16 (factorised by the apply kernel), 32 (by finish_kernel), 40 (a launch of its own) and 184 (beyond the blocked
+# factorisation), split and unsplit products, both orientations, two and three operand planes; an outlier over a flat rest.
+@pytest.mark.parametrize("r,b", [(8, 16), (24, 32), (32, 40), (144, 184)])
+@pytest.mark.parametrize("rows,cols", [(400, 300), (300, 408)])
+@pytest.mark.parametrize("order", ["ascending", "permuted", "outlier"])
+@pytest.mark.parametrize("planes", [2, 3])
+def test_start_block_out_of_order(r, b, rows, cols, order, planes):
+    rng = np.random.default_rng(100 * r + rows)
+    n = min(rows, cols)
+    u, _ = np.linalg.qr(rng.standard_normal((rows, n)))
+    v, _ = np.linalg.qr(rng.standard_normal((cols, n)))
+    # (two planes carry 2^-17 of sigma_1: nothing asserted here lies below 1e-3)
+    if order == "outlier":
+        s = np.r_[1e4 if planes == 3 else 1e3, 1.0 + 2.0 * np.exp(-np.arange(n - 1) / (0.5 * r))]
+    else:
+        s = (1e-4 if planes == 3 else 1e-3) ** (np.arange(n) / b)
+    mat = ((u * s) @ v.T).astype(np.float32)
+    m = mat.astype(np.float64) if rows >= cols else mat.T.astype(np.float64)
+    left, sv, right = np.linalg.svd(m, full_matrices=False)
+    perm = rng.permutation(r) if order == "permuted" else np.arange(r)[::-1]
+    case = Case([(rows, cols)], r, 1, synth.F32, lds=[(cols + 7) // 8 * 8], refresh_iters=4, precision=planes)
+    case.upload([[mat]], [np.zeros((rows, cols), np.float32)], [right[:r].T[:, perm].astype(np.float32)])
+    case.compress(refresh=True)
+    p, q, e = case.outputs(0)
+    if rows < cols:
+        e = e.T
+    assert case.comp.status(0).rank_deficient == 0
+    nm = np.linalg.norm(m)
+    # bounds: fp32 storage and 2^-24 / 2^-17 products on the exact relations (as in _check_refreshed_step), the optimum of
+    # Eq. (6) to 1e-6 of ||M||^2
+    assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6
+    assert np.linalg.norm(q - m.T @ p) <= 2e-5 * nm
+    assert np.linalg.norm(e - (m - p @ q.T)) <= 2e-5 * nm
+    assert abs(np.sum(e ** 2) - np.sum(sv[r:] ** 2)) <= 1e-6 * nm ** 2
+    # The subspace, to what the products' rounding leaves of the r-th direction: the start holds the exact vectors in fp32, and
+    # an error of 2^-24 (2^-17) sigma_1 in M Y turns it by that over the gap of sigma_r to what is outside the block
+    if order != "outlier":
+        rounding = 2.0 ** (-24 if planes == 3 else -17) * np.sqrt(r)
+        assert orc.sin_theta_max(left[:, :r], p) <= max(4.0 * rounding * sv[0] / (sv[r - 1] - sv[r]), (sv[b] / sv[r - 1]) ** 6)
