@@ -215,6 +215,8 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
     const int n_valid_x = (min(len, i0 + kGramRows2) - i0) * w_in;          // elements that exist
     float4 xpre = make_float4(0.f, 0.f, 0.f, 0.f);
     bool have_pre = false;
+    // partial Gram matrices of the second pass: behind those of the first where other workgroups may still have to read these
+    double* gram2 = L.gram;
     if (SMALL && (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY) && local_chol(L, src_role, 1)) {
         // small factorisation repeated by every workgroup; the first one records the outcome.  The
         // workgroup's own rows are requested first so that their latency overlaps the factorisation.
@@ -223,7 +225,9 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
             if (4 * (int)threadIdx.x < n_valid_x) xpre = *reinterpret_cast<const float4*>(X.ptr + xbase + 4 * threadIdx.x);
         }
         double* tml = reinterpret_cast<double*>(smem + main_lds);
-        chol_body<true>(L, src_role, tol2, 1, L.transposed ? kGramRows1 : slot_rows, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
+        const int rows1 = L.transposed ? kGramRows1 : slot_rows;
+        gram2 += (int64_t)((len + rows1 - 1) / rows1) * ((w_in * (w_in + 1)) / 2);
+        chol_body<true>(L, src_role, tol2, 1, rows1, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
                   tml, blockIdx.x == 0, &s_need2, scales_next(L, src_role, gate));
         __syncthreads();
         need2 = s_need2;
@@ -340,10 +344,11 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
         }
     }
     if (do_gram) {
-        gram_tile_f64(so, ow, kGramRows2, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
+        gram_tile_f64(so, ow, kGramRows2, w_out, gram2 + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
         if (SMALL) {
             const int n_wg = (len + kGramRows2 - 1) / kGramRows2;
-            if (last_to_arrive(&L.status[7], n_wg, &s_last)) chol_body<true>(L, dst_role, tol2, 2, kGramRows2, false, smem, L.tmat);
+            if (last_to_arrive(&L.status[7], n_wg, &s_last))
+                chol_body<true>(L, dst_role, tol2, 2, kGramRows2, false, smem, L.tmat, true, nullptr, false, gram2);
         }
     } else if (do_pack) {
         write_packs(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);

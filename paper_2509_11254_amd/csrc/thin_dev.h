@@ -454,11 +454,12 @@ __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
 // tm: where the w x w factor goes (the layer's tmat, or LDS of the caller); need2_out: optional LDS word
 // that receives the second-pass decision; write_status: whether this caller owns the layer's status words; scale: Z of the
 // subspace iteration, see scales_next (powers of two next to its columns' scaling, and whether Y is to be orthonormalised).
+// gram_at: where the partial Gram matrices are (the layer's gram by default).
 // NARROW: compiled for widths <= 16 only (the register path; nothing else is generated).
 template <bool NARROW = false>
 __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
                                  unsigned char* smem, double* tm, bool write_status = true,
-                                 int* need2_out = nullptr, bool scale = false) {
+                                 int* need2_out = nullptr, bool scale = false, const double* gram_at = nullptr) {
     const int side = side_of_role(L.transposed, role);
     const int n_slots = (side_len(L, side) + slot_rows - 1) / slot_rows;      // (kOneSlot: one, the sum of all)
     const int w = L.thin[role].width;
@@ -474,7 +475,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     int* bad = reinterpret_cast<int*>(tcol + wp);         // [w] dependent-column flags
     const int t = threadIdx.x;
     const int nt = blockDim.x, nty = nt >> 4;             // threads, rows of the 16-wide thread grid
-    const double* __restrict__ gram = L.gram;
+    const double* __restrict__ gram = gram_at ? gram_at : L.gram;
     auto outcome = [&](int nbad, double min_piv, const Spread& spread) {
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;

@@ -66,3 +66,51 @@ def test_second_pass(r, shapes):
         assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6, l
         assert np.linalg.norm(q - ml.T @ p) <= 2e-6 * np.linalg.norm(ml), l
         assert np.linalg.norm(e - (ml - p @ q.T)) <= 2e-6 * np.linalg.norm(ml), l
+
+
+def _one_pass(x):
+    """One CholeskyQR pass on fp32 x as the library makes it (fp64 factor, fp32 result)."""
+    x = x.astype(np.float32).astype(np.float64)
+    d = 1.0 / np.linalg.norm(x, axis=0)
+    upper = np.linalg.cholesky((x * d).T @ (x * d)).T
+    return (x @ (d[:, None] * np.linalg.inv(upper))).astype(np.float32).astype(np.float64)
+
+
+# The second pass has to be made, by the layers that ask for it and by no other: pivots of 1e-12 (allowed by rank_tol) leave an
+# orthogonality error of 1e-5 to 1e-4 after the first.  Narrow layers with more workgroups than the GPU holds at a time, whose
+# factorisation every workgroup makes for itself: a late one reads the first pass's partial Gram matrices while the
+# early ones write those of the second.
+@pytest.mark.parametrize("shapes,r", [([(8192, 64)] * 48, 8), ([(2048, 64)] * 96, 16), ([(72, 8192), (8192, 64), (2048, 72)] * 12, 12),
+                                      ([(1003, 136), (136, 1000), (520, 72)], 24), ([(1003, 136), (136, 1000), (520, 72)], 64)])
+@pytest.mark.parametrize("which", ["all", "first"])
+def test_second_pass_is_made(shapes, r, which):
+    rng = np.random.default_rng(len(shapes) + r)
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    asks = [which == "all" or l == 0 for l in range(len(shapes))]
+    ms = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    plain = [np.linalg.qr(rng.standard_normal((min(s), r)))[0].astype(np.float32) for s in shapes]
+    close = [q.copy() for q in plain]
+    for q, a in zip(close, asks):
+        if a:
+            q[:, r - 1] = q[:, 0] + np.float32(1e-6) * q[:, r - 1]
+    worst = max(np.abs(z.T @ z - np.eye(r)).max() for z in [_one_pass((ms[0] if s[0] >= s[1] else ms[0].T) @ close[0]) for s in shapes[:1]])
+    assert worst > 4e-6                                              # (the bound below tells one pass from two)
+    out = {}
+    for name, qs in (("plain", plain), ("close", close)):
+        case = Case(shapes, r, 1, synth.F32, lds=lds, rank_tol=1e-7)
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+        case.compress()
+        out[name] = [case.outputs(l) for l in range(len(shapes))]
+    for l, (rows, cols) in enumerate(shapes):
+        p, q, e = out["close"][l]
+        if not asks[l]:
+            assert all(np.array_equal(a, b) for a, b in zip(out["close"][l], out["plain"][l])), l
+        ml = ms[l].astype(np.float64)
+        if rows < cols:
+            ml, e = ml.T, e.T
+        assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6, l
+        assert np.linalg.norm(q - ml.T @ p) <= 2e-6 * np.linalg.norm(ml), l
+        assert np.linalg.norm(e - (ml - p @ q.T)) <= 2e-6 * np.linalg.norm(ml), l
+        # (the first r - 1 columns do not know of the close pair)
+        first = orc.ssp_comp(close[l].astype(np.float64)[:, :r - 1], [ml]).p_tilde
+        assert orc.rel_fro(p[:, :r - 1], first) <= 1e-4, l
