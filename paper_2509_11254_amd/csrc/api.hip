@@ -82,6 +82,7 @@ struct Plan {            // host copy of what a layer needs
     int transposed;
     int rowsP, colsP;
     int m, n;
+    int wz = 0;                             // this layer's block width in the subspace iteration: at least r, at most n
     // reduction splits of this layer's products (see plan_splits)
     int split_row = 1, split_col = 1;       // prod_kernel, M read
     int split_row_f = 1, split_col_f = 1;   // prod_kernel, forming pass
@@ -103,7 +104,7 @@ struct psgd_ctx {
     Lists lists;
     int rmax = 0;
     int cpc = 0;     // packed width of the compress step: 32 * ceil(rmax / 32)
-    int wz = 0;      // block width of the subspace iteration (r + oversampling, multiple of 8)
+    int wz = 0;      // widest block of the subspace iteration (r + oversampling, multiple of 8), see Plan::wz
     int cpz = 0;     // its packed width: wz rounded up to a multiple of 32
     int cpmax = 0;   // max(cpc, cpz)
     int planes = 2;  // bf16 planes per fp32 operand of the MFMA products (2: 3 products, 3: 6 products)
@@ -197,22 +198,22 @@ LayerRegion layer_region(const psgd_ctx* c, const Plan& p) {
     const int lenP[2] = {p.rowsP, p.colsP};
     const int split[2] = {std::max(std::max(p.split_row, p.split_row_f), p.split_row_v2),
                           std::max(std::max(p.split_col, p.split_col_f), p.split_col_v2)};
-    for (int s = 0; s < 2; ++s) R.part[s] = take((size_t)split[s] * lenP[s] * c->wz * sizeof(float));
+    for (int s = 0; s < 2; ++s) R.part[s] = take((size_t)split[s] * lenP[s] * p.wz * sizeof(float));
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 2 * c->planes; ++k) R.pack[s][k] = take((size_t)lenP[s] * c->cpmax * sizeof(bf16_t));
     if (c->lazy && (!p.transposed || c->lazy_tr))
         for (int s = 0; s < 2; ++s)
             for (int k = 0; k < c->planes; ++k) R.lzf[s][k] = take((size_t)lenP[s] * c->cpc * sizeof(bf16_t));
     const int len[2] = {(int)p.d.rows, (int)p.d.cols};
-    for (int s = 0; s < 2; ++s) R.z[s] = take((size_t)len[s] * c->wz * sizeof(float));
-    const size_t w2 = (size_t)(c->wz + 2) * (c->wz + 2);
+    for (int s = 0; s < 2; ++s) R.z[s] = take((size_t)len[s] * p.wz * sizeof(float));
+    const size_t w2 = (size_t)(p.wz + 2) * (p.wz + 2);
     const int max_lenP = lenP[0] > lenP[1] ? lenP[0] : lenP[1];
     // one partial Gram matrix per 64 rows of the widest block, or per 32 and per 64 rows of a narrow P (the first pass of its
     // factorisation and, while that is being read, the second)
     const size_t tri = (size_t)p.d.r * (p.d.r + 1) / 2, pass12 = p.d.r <= 16 ? (size_t)(kGramRows2 / 32 + 1) * tri : 0;
     R.gram = take((size_t)(max_lenP / kGramRows2) * std::max(w2, pass12) * sizeof(double));
     R.tmat = take(w2 * sizeof(double));
-    R.eval = take((size_t)(c->wz + 2) * sizeof(double));
+    R.eval = take((size_t)(p.wz + 2) * sizeof(double));
     R.status = take(kStatusWords * sizeof(int));
     R.end = o;
     return R;
@@ -311,7 +312,7 @@ void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
     const LayerRegion R = layer_region(c, p);
     char* base = ws + c->off_layer[l];
     LayerDev L{};
-    L.rows = (int)p.d.rows; L.cols = (int)p.d.cols; L.ld = p.d.ld; L.r = p.d.r; L.wz = c->wz;
+    L.rows = (int)p.d.rows; L.cols = (int)p.d.cols; L.ld = p.d.ld; L.r = p.d.r; L.wz = p.wz;
     L.gdt = p.d.grad_dtype; L.n_workers = c->n_workers; L.transposed = p.transposed; L.planes = c->planes;
     L.rowsP = p.rowsP; L.colsP = p.colsP;
     L.split_row = p.split_row; L.split_col = p.split_col;
@@ -323,8 +324,8 @@ void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
     const int side_p = side_of_role(p.transposed, ROLE_P), side_q = side_of_role(p.transposed, ROLE_Q);
     L.thin[ROLE_P] = ThinRef{c->hP.empty() ? nullptr : c->hP[l], p.d.r, p.d.r};
     L.thin[ROLE_Q] = ThinRef{c->hQ.empty() ? nullptr : c->hQ[l], p.d.r, p.d.r};
-    L.thin[ROLE_ZP] = ThinRef{reinterpret_cast<float*>(base + R.z[side_p]), c->wz, c->wz};
-    L.thin[ROLE_ZQ] = ThinRef{reinterpret_cast<float*>(base + R.z[side_q]), c->wz, c->wz};
+    L.thin[ROLE_ZP] = ThinRef{reinterpret_cast<float*>(base + R.z[side_p]), p.wz, p.wz};
+    L.thin[ROLE_ZQ] = ThinRef{reinterpret_cast<float*>(base + R.z[side_q]), p.wz, p.wz};
     for (int s = 0; s < 2; ++s) {
         L.part[s] = reinterpret_cast<float*>(base + R.part[s]);
         for (int k = 0; k < c->planes; ++k) {
@@ -783,10 +784,13 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         int over = c->opt.refresh_oversample;
         if (over < 0) over = 8;
         if (c->opt.refresh_oversample < 0) over = rmax / 4 > 8 ? rmax / 4 : 8;
-        c->wz = (int)round_up(rmax + over, 8);
-        int nmin = c->plan[0].n;
-        for (auto& p : c->plan) if (p.n < nmin) nmin = p.n;
-        if (c->wz > nmin) c->wz = nmin;                                         // block no wider than the matrix
+        int nmin = c->plan[0].n, nmax = c->plan[0].n;
+        for (auto& p : c->plan) { nmin = std::min(nmin, p.n); nmax = std::max(nmax, p.n); }
+        // A block is no wider than its matrix.  One width for all layers where the smallest matrix has room for the largest
+        // rank; else each layer's own, the widest as wide as the kernels go if it has to be.
+        const int full = (int)round_up(rmax + over, 8);
+        c->wz = nmin >= rmax ? std::min(full, nmin) : std::min(std::min(full, nmax), kMaxWidth);
+        for (auto& p : c->plan) p.wz = std::min(c->wz, p.n);
         c->cpz = (int)round_up(c->wz, 32);
         c->cpmax = c->cpz > c->cpc ? c->cpz : c->cpc;
         if (c->cpmax > kMaxWidth) rc = PSGD_E_SHAPE;

@@ -106,7 +106,7 @@ struct LayerDev {
     int rows, cols;
     int64_t ld;
     int r;             // rank of the compressor
-    int wz;            // block width of the subspace iteration (multiple of 32, >= r)
+    int wz;            // block width of the subspace iteration (r <= wz <= min(rows, cols))
     int gdt;           // PSGD_F32 / PSGD_BF16
     int n_workers;
     int transposed;    // rows < cols: P~ is W-side

@@ -100,6 +100,22 @@ def test_workspace_and_algorithmic_bytes(lib):
     lib.psgd_destroy(c2)
 
 
+@pytest.mark.parametrize("r", [24, 64, 192])
+def test_a_small_layer_does_not_shrink_the_others_regions(lib, r):
+    """Block widths of the subspace iteration are capped by the matrix; a layer's partial sums, Gram and factor matrices have
+    to hold its own rank whatever the smallest matrix of the context is."""
+    def ws(layers):
+        opt = psgd.Options(0, 0, 1, 1, 0.0, 0, 0, 0, 0, 0)
+        rc, ctx = _init(lib, layers, opt=C.byref(opt))
+        assert rc == psgd.PSGD_OK
+        b = lib.psgd_workspace_bytes(ctx)
+        lib.psgd_destroy(ctx)
+        return b
+
+    big, small = (1024, 512, 0, r, psgd.PSGD_F32), (64, 8, 0, 4, psgd.PSGD_F32)
+    assert ws([big, small]) >= ws([big])
+
+
 def test_struct_layouts_match_the_header(tmp_path):
     """The ctypes mirrors of the ABI structs against the C compiler's view of include/psgd.h: sizes and the offset
     of every field, and the error codes the binding names."""

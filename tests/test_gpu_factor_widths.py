@@ -114,3 +114,39 @@ def test_second_pass_is_made(shapes, r, which):
         # (the first r - 1 columns do not know of the close pair)
         first = orc.ssp_comp(close[l].astype(np.float64)[:, :r - 1], [ml]).p_tilde
         assert orc.rel_fro(p[:, :r - 1], first) <= 1e-4, l
+
+
+# One context with ranks beyond the short side of its smallest matrices: every layer has its own block width in a refresh
+# (as many columns as the matrix has at most) and regions of its own size
+@pytest.mark.parametrize("shapes,ranks", [([(520, 264), (40, 8), (264, 1000), (24, 130)], [100, 4, 48, 20]),
+                                          ([(400, 24), (24, 400), (130, 200)], [3, 24, 60]),
+                                          ([(1000, 400), (16, 72)], [192, 16])])
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_batch_of_very_different_ranks(shapes, ranks, dtype):
+    rng = np.random.default_rng(ranks[0])
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    ms = []
+    for s in shapes:
+        k = min(s)
+        m = (rng.standard_normal((s[0], k)) * 0.99 ** np.arange(k) @ rng.standard_normal((k, s[1]))).astype(np.float32)
+        ms.append(synth.round_to_bf16(m) if dtype == synth.BF16 else m)
+    tol = {synth.F32: 1e-4, synth.BF16: 2e-2}[dtype]
+    case = Case(shapes, ranks, 1, dtype, lds=lds)
+    for refresh in (False, True, True):
+        qs = [rng.standard_normal((min(s), r)).astype(np.float32) for s, r in zip(shapes, ranks)]
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+        case.compress(refresh=refresh)
+        for l, ((rows, cols), r) in enumerate(zip(shapes, ranks)):
+            p, q, e = case.outputs(l)
+            ml = synth.gradient_as_f64(ms[l])
+            if rows < cols:
+                ml, e = ml.T, e.T
+            nm = np.linalg.norm(ml)
+            assert np.abs(p.T @ p - np.eye(r)).max() < 2e-5, (l, refresh)
+            assert np.linalg.norm(q - ml.T @ p) <= tol * nm, (l, refresh)
+            assert np.linalg.norm(e - (ml - p @ q.T)) <= tol * nm, (l, refresh)
+            if refresh:
+                tail = np.sum(np.linalg.svd(ml, compute_uv=False)[r:] ** 2)
+                assert abs(np.sum(e ** 2) - tail) <= 1e-4 * nm ** 2, (l, np.sum(e ** 2) / nm ** 2, tail / nm ** 2)
+            else:
+                assert orc.rel_fro(e, ml - orc.ssp_comp(qs[l].astype(np.float64), [ml]).delta_hat) <= 10 * tol or r == min(rows, cols), l
