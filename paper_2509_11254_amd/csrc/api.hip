@@ -241,8 +241,8 @@ bool form_row_env() {
 }
 
 // Reduction split of a launch with `base_tiles` output blocks.  cp: packed width of the thin operand.  At widths
-// of 64 and more one workgroup per compute unit is the target: the partial products that finish_kernel has to add
-// up grow with the width, and the wide product kernels do not gain from more workgroups (4096 x 4096: the step at
+// of 64 and more one workgroup per compute unit is the target with three planes: the partial products that finish_kernel has
+// to add up grow with the width, and the wide product kernels do not gain from more workgroups (4096 x 4096: the step at
 // r = 64 takes 0.325 ms with 1024 workgroups, 0.302 with 256; at r = 128 0.514 and 0.473; at r = 16 and 32 it is
 // the other way round).
 // Two per compute unit where their operand buffers fit its LDS twice (two planes up to width 128): 8192 x 8192 bf16 r = 128
@@ -254,11 +254,14 @@ int split_target(bool form, int cp, int planes) {
     else if (!form && target > kTargetTilesPlain) target = target / 2;
     return target;
 }
-// (A launch that reaches three quarters of the target by itself is left whole: the forming pass of the 22 matrices of a
-// 1B-shaped model stored as the transpose, 968 workgroups, is 0.1 ms faster than in halves with their finish_kernel.)
-int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int planes) {
+// A launch that does not reach the target by itself is split, although from three quarters of it on the split costs more
+// than it fills (25000 x 2048 fp32 r = 100, 196 workgroups of 256: 661 us per step in halves, 621 whole): the longer walks'
+// fp32 sums leave 1.4 to 1.7 times the error (E 6.2e-6 and 9.4e-6).  Left whole are launches of one orientation from three
+// quarters on where base_all, the batch's blocks of both orientations, reaches the target (the forming pass of the 22 matrices of
+// a 1B-shaped model stored as the transpose, 968 workgroups, is 0.1 ms faster than in halves with their finish_kernel).
+int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int planes, int64_t base_all) {
     const int target = split_target(form, cp, planes);
-    if (4 * base_tiles >= 3 * target) return 1;
+    if (base_tiles >= target || (4 * base_tiles >= 3 * target && base_all >= target)) return 1;
     int64_t s = (target + base_tiles - 1) / base_tiles;
     if (s > kMaxSplit) s = kMaxSplit;
     if (s > min_chunks) s = min_chunks;
@@ -268,28 +271,30 @@ int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int plan
 
 // Splits of one kind of product over the layers of one launch (a launch serves the layers of one orientation, and the
 // launches follow each other, so each has to fill the GPU by itself).  A layer has tiles(p) output blocks, each a walk over
-// chunks(p) steps; with fewer blocks than the target the walks are cut into pieces of about the same number of steps.
+// chunks(p) steps; with fewer blocks than the target the walks are cut into pieces of about the same number of steps, and
+// none into fewer pieces than an equal split of all would make (the longer the walk, the larger the error of its fp32 sum).
 // Either no layer of a launch is split or all are (their sums then all come from finish_kernel).
 // Measured against one split per batch, bounded by its shortest walk: eight small matrices of 64 x 24 to 1000 x 264, fp32,
 // r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 96 us; two 1B-shaped fp32 blocks at r = 16: row product of
-// the two matrices stored as the transpose (64 workgroups before) 101 -> 33 us, step 939 -> 865 us.
+// the two matrices stored as the transpose (64 workgroups before) 101 -> 33 us, step 939 -> 870 us.
 template <class Tiles, class Chunks>
 void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, int planes, Tiles tiles, Chunks chunks,
-                 int Plan::*split) {
-    int64_t base = 0, steps = 0;
-    int most = 1;
+                 bool both, int Plan::*split) {
+    int64_t base = 0, steps = 0, base_all = 0;
+    int most = 1, least = 1 << 30;
     for (int l : ids) {
         base += tiles(plan[l]);
         steps += (int64_t)tiles(plan[l]) * chunks(plan[l]);
         most = std::max(most, (int)chunks(plan[l]));
+        least = std::min(least, (int)chunks(plan[l]));
     }
     if (base == 0) return;
-    const int s = choose_split(base, most, form, cp, planes);
+    if (both) for (const Plan& p : plan) base_all += tiles(p);
+    const int s = choose_split(base, most, form, cp, planes, base_all);
     if (s <= 1) return;
     // Steps per workgroup: with walks of one length as many pieces as choose_split says, with several lengths the fewest
-    // steps that keep the launch within its target (pieces of one size run in whole rounds of the GPU: 608 of them where
-    // 512 fit at a time took longer than 576 of different lengths, the column product of the two blocks above 107 us
-    // against 92).
+    // steps that keep the launch within its target (before the equal split's number, whose pieces of the short walks end early
+    // and make room: the column product of the two blocks above 866 -> 870 us per step, error of Q 1.6e-7 -> 1.1e-7).
     int64_t per = 1;
     if (steps != base * most) {
         auto total = [&](int64_t q) {
@@ -301,8 +306,9 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
         per = std::max<int64_t>(1, steps / target);
         while (per < most && total(per) > target) ++per;
     }
+    const int equal = choose_split(base, least, form, cp, planes, base_all);
     for (int l : ids) {
-        const int64_t mine = steps == base * most ? s : (chunks(plan[l]) + per - 1) / per;
+        const int64_t mine = steps == base * most ? s : std::max<int64_t>(equal, (chunks(plan[l]) + per - 1) / per);
         plan[l].*split = (int)std::max<int64_t>(2, std::min<int64_t>(mine, kMaxSplit));
     }
 }
@@ -804,18 +810,18 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
         auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
         auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
-        plan_splits(c->plan, *ids, false, c->cpc, c->planes, row_tiles, row_chunks, &Plan::split_row);
-        plan_splits(c->plan, *ids, false, c->cpc, c->planes, col_tiles, col_chunks, &Plan::split_col);
-        plan_splits(c->plan, *ids, true, c->cpc, c->planes, row_tiles, row_chunks, &Plan::split_row_f);
-        plan_splits(c->plan, *ids, true, c->cpc, c->planes, col_tiles, col_chunks, &Plan::split_col_f);
+        plan_splits(c->plan, *ids, false, c->cpc, c->planes, row_tiles, row_chunks, true, &Plan::split_row);
+        plan_splits(c->plan, *ids, false, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col);
+        plan_splits(c->plan, *ids, true, c->cpc, c->planes, row_tiles, row_chunks, true, &Plan::split_row_f);
+        plan_splits(c->plan, *ids, true, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col_f);
         // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split), their
         // column products, and the row products of the layers stored with rows < cols
         auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
         auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
         auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
         auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
-        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, c->planes, row_tiles_v2, row_chunks_v2, &Plan::split_row_v2);
-        plan_splits(c->plan, *ids, false, 32, c->planes, col_tiles_v2, col_chunks_v2, &Plan::split_col_v2);
+        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, c->planes, row_tiles_v2, row_chunks_v2, false, &Plan::split_row_v2);
+        plan_splits(c->plan, *ids, false, 32, c->planes, col_tiles_v2, col_chunks_v2, false, &Plan::split_col_v2);
     }
     {
         int64_t m_bytes = 0, mt_bytes = 0;
@@ -1188,8 +1194,8 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     D.thin[ROLE_P].ptr = P;
     D.thin[ROLE_Q].ptr = Q;
     Plan one = p;
-    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->planes);
-    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->planes);
+    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->planes, 0);
+    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->planes, 0);
     one.split_row_f = one.split_row; one.split_col_f = one.split_col;      // (no forming pass in this call)
     D.split_row = one.split_row; D.split_col = one.split_col;
     D.split_row_f = one.split_row_f; D.split_col_f = one.split_col_f;

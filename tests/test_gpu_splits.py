@@ -56,3 +56,29 @@ def test_ssp_steps(shapes, r, dtype, lazy):
         case.comp.flush_residual(case.E)
     for l, (rw, cl) in enumerate(shapes):
         assert orc.rel_fro(logical(back(case.E[l], cl), rw, cl), e_or[l]) <= TOL[dtype], (l, rw, cl)
+
+
+def _first_layer_errors(shapes, r, seed=5):
+    """Errors of layer 0's P~ and Q after one step, against fp64 (relative Frobenius); layer 0 is the same for any shapes[1:]."""
+    rng = np.random.default_rng(seed)
+    rows, cols = shapes[0]
+    m = rng.standard_normal((rows, cols)).astype(np.float32)
+    q0 = rng.standard_normal((min(rows, cols), r)).astype(np.float32)
+    small = {s: rng.standard_normal(s).astype(np.float32) for s in dict.fromkeys(shapes)}
+    case = Case(shapes, r, 1, synth.F32)
+    case.upload([[m]] + [[small[s]] for s in shapes[1:]], [np.zeros(s, np.float32) for s in shapes],
+                [q0] + [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes[1:]])
+    case.compress()
+    p, q, _ = case.outputs(0)
+    m64 = m.astype(np.float64)
+    return orc.rel_fro(p, orc.ssp_comp(q0.astype(np.float64), [m64]).p_tilde), orc.rel_fro(q, m64.T @ p)
+
+
+# The error of an fp32 sum grows with the number of its terms.  A matrix's products are cut into no fewer pieces because its
+# batch comes near to filling the GPU (224 workgroups of 256, where 160 are cut in two), nor because it holds longer
+# matrices beside it; the same pieces give the same errors (a quarter is left for the orders of the sums).
+@pytest.mark.parametrize("fewer,more,r,which", [([(4096, 1024)] * 5, [(4096, 1024)] * 7, 100, 0),
+                                                ([(2048, 2048)] * 12, [(2048, 2048)] * 8 + [(5632, 2048)] * 4, 16, 1)], ids=["P", "Q"])
+def test_errors_do_not_depend_on_the_batch(fewer, more, r, which):
+    few, many = _first_layer_errors(fewer, r)[which], _first_layer_errors(more, r)[which]
+    assert many <= 1.25 * few, (few, many)
