@@ -115,7 +115,6 @@ struct psgd_ctx {
     double kernel_bytes[3] = {0.0, 0.0, 0.0};   // algorithmic bytes of the three streaming kernels of one SSP step
     int grad_kind = 0;                          // 1: every layer has fp32 gradients, 2: every layer bf16, 0: mixed
     bool nt_m = false;                          // the row-major layers' M is too large to be found in a cache again
-    bool nt_mt = false;                         // ... the M of the layers stored with rows < cols
     // XCD table of the forming pass on 32 x 256 tiles (see form_row_kernel): 16 rows of xstride ints; built when the
     // row-major layers are many enough to be dealt evenly to the 8 XCDs
     std::vector<int> hXtab, hXtabC;             // (forming pass; column-mode product: other tile counts)
@@ -275,8 +274,8 @@ int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int plan
 // none into fewer pieces than an equal split of all would make (the longer the walk, the larger the error of its fp32 sum).
 // Either no layer of a launch is split or all are (their sums then all come from finish_kernel).
 // Measured against one split per batch, bounded by its shortest walk: eight small matrices of 64 x 24 to 1000 x 264, fp32,
-// r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 96 us; two 1B-shaped fp32 blocks at r = 16: row product of
-// the two matrices stored as the transpose (64 workgroups before) 101 -> 33 us, step 939 -> 870 us.
+// r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 94 us; two 1B-shaped fp32 blocks at r = 16 939 -> 866 us (two
+// matrices of them are stored as the transpose, 32 workgroups of their row product).
 template <class Tiles, class Chunks>
 void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, int planes, Tiles tiles, Chunks chunks,
                  bool both, int Plan::*split) {
@@ -523,25 +522,23 @@ struct Launcher {
         else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
         else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
         else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, p_like ? (form ? norm.tiles_row_f : norm.tiles_row) : (form ? norm.tiles_col_f : norm.tiles_col), out_role, ef, gate, st));
-        // the row product of the layers stored with rows < cols (their Q): on 32 x 256 tiles as well, where finish_kernel
-        // or a plain set of operand copies completes it (22 matrices 2048 x 5632 of a 1B-shaped bf16 model at r = 32, not
-        // split: 275 us on prod_kernel's 128 x 64 tiles, 262 on these; two of them in fp32 at r = 16, split: 101 -> 33)
-        const bool t2 = !form && !p_like && n_tr > 0 && use_form_row && row_prod_supported(nb, ctx->planes) && (tr.split_row_v2 || epi == EPI_PACK);
-        if (t2) note(launch_row_prod(nb, ctx->planes, layers, ids_tr, n_tr, tr.tiles_row_v2, out_role, ef, gate, ctx->nt_mt ? 1 : 0, nullptr, 0, 0, st));
-        else note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, p_like ? (form ? tr.tiles_col_f : tr.tiles_col) : (form ? tr.tiles_row_f : tr.tiles_row), out_role, ef, gate, st));
+        // (the row product of the layers stored with rows < cols stays on 128 x 64 tiles: 990 x 3741 fp32 r = 6 72.8 us per step
+        // against 76.2 on 32 x 256 tiles, eight 2048 x 5632 r = 16 530 against 556, 22 of them in bf16 r = 32 1327 against 1358,
+        // four 4096 x 11008 r = 64 1015 against 1089; single long ones are up to 5 % faster there, 1024 x 100000 712 and 695)
+        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, p_like ? (form ? tr.tiles_col_f : tr.tiles_col) : (form ? tr.tiles_row_f : tr.tiles_row), out_role, ef, gate, st));
         prof_end(k);
         // split reductions are completed (and the epilogue run) by a second, small launch, whose last
         // workgroup per layer also factorises the Gram matrix; unsplit products need a launch for that
         const bool rv2 = v2 || r2;
         const bool split_n = n_norm > 0 && (rv2 ? norm.split_row_v2 : c2 ? norm.split_col_v2 : p_like ? (form ? norm.split_row_f : norm.split_row) : (form ? norm.split_col_f : norm.split_col));
-        const bool split_t = n_tr > 0 && (t2 ? tr.split_row_v2 : p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
+        const bool split_t = n_tr > 0 && (p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
         // Widths above kWideWidth: the partial Gram matrices are added up by a launch that spreads over the chip, and one
         // launch of the factorisation serves both orientations.
         const int ww = w > 0 ? w : 32 * nb;
         const bool wide = ww > kWideWidth;
         const int fin_gate = wide ? -2 : chol_gate;
         if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
-        if (split_t) note(launch_finish(p_like, t2 ? 2 : form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        if (split_t) note(launch_finish(p_like, form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
         // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
         // per 128 rows)
@@ -814,26 +811,26 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         plan_splits(c->plan, *ids, false, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col);
         plan_splits(c->plan, *ids, true, c->cpc, c->planes, row_tiles, row_chunks, true, &Plan::split_row_f);
         plan_splits(c->plan, *ids, true, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col_f);
-        // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split), their
-        // column products, and the row products of the layers stored with rows < cols
+        if (ids != &c->lists.norm) continue;
+        // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split) and their
+        // column products
         auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
         auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
         auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
         auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
-        plan_splits(c->plan, *ids, ids == &c->lists.norm, 32, c->planes, row_tiles_v2, row_chunks_v2, false, &Plan::split_row_v2);
+        plan_splits(c->plan, *ids, true, 32, c->planes, row_tiles_v2, row_chunks_v2, false, &Plan::split_row_v2);
         plan_splits(c->plan, *ids, false, 32, c->planes, col_tiles_v2, col_chunks_v2, false, &Plan::split_col_v2);
     }
     {
-        int64_t m_bytes = 0, mt_bytes = 0;
+        int64_t m_bytes = 0;
         bool f32 = false, b16 = false;
         for (auto& p : c->plan) {
             (p.d.grad_dtype == PSGD_F32 ? f32 : b16) = true;
-            (p.transposed ? mt_bytes : m_bytes) += p.d.rows * p.d.cols * 4;
+            if (!p.transposed) m_bytes += p.d.rows * p.d.cols * 4;
         }
         c->grad_kind = f32 && b16 ? 0 : (f32 ? 1 : 2);
         // M that the second pass can find in the 256 MB memory-side cache is stored with plain stores
         c->nt_m = m_bytes > ((int64_t)96 << 20);
-        c->nt_mt = mt_bytes > ((int64_t)96 << 20);
         if (const char* e = std::getenv("PSGD_NT_M")) c->nt_m = e[0] != '0';     // (measurement knob)
         // XCD table: the row-major layers (positions in the id list `norm`), largest first, each to the XCD with the
         // least work so far

@@ -44,8 +44,8 @@ template <int NB, int PL, int LAZY> constexpr size_t form_lds_bytes() {
 
 // The end of a row-mode product on 32-row blocks: the four waves' partial results (each over its quarter of every
 // step's reduction range) are added through LDS, and the block's 32 x cp result goes out -- as one of n_split partial
-// sums for finish_kernel, or as rows of the result, then with the block's partial Gram matrix (one slot per 32 rows) or
-// the operand copies of its rows if the launch asks for them.
+// sums for finish_kernel, or as rows of the result, then with the block's partial Gram matrix if the launch asks for
+// it (one slot per 32 rows).
 template <int NB>
 __device__ inline void row_epilogue(unsigned char* smem, const floatx16 (&acc)[NB], const LayerDev& L, int out_role,
                                     int epi_flags, int sp, int ob, int n_split) {
@@ -80,21 +80,16 @@ __device__ inline void row_epilogue(unsigned char* smem, const floatx16 (&acc)[N
         // written by one thread), from where this row block's partial Gram matrix is formed if the launch asks for
         // it: one slot per 32 rows here (epi_flags carries EPI_GRAM only where the factorisation that follows sums
         // 32-row slots)
-        const int epi = epi_flags & EPI_KIND_MASK;
-        const bool gram = epi == EPI_GRAM, pack = epi == EPI_PACK;
+        const bool gram = (epi_flags & EPI_KIND_MASK) == EPI_GRAM;
         for (int i = t; i < FR * cp; i += kThreads) {
             const int row = i / cp, col = i - row * cp;
             const float v = total(row, col);
-            if (gram || pack) red[row * RW + col] = v;
+            if (gram) red[row * RW + col] = v;
             if (col < T.width && row0 + row < L.rows) as_global(T.ptr)[(int64_t)(row0 + row) * T.ld + col] = v;
         }
         if (gram) {
             __syncthreads();
             gram_tile_f64(red, RW, FR, T.width, L.gram + (int64_t)ob * ((T.width * (T.width + 1)) / 2));
-        }
-        if (pack) {
-            __syncthreads();
-            write_packs(L.pack[SIDE_L], L.planes, red, RW, cp, row0, FR, L.rowsP, 3, (epi_flags & EPI_KEPT) ? L.lzf[SIDE_L] : nullptr);
         }
     }
 }
