@@ -476,6 +476,11 @@ struct Launcher {
     bool use_xtab = true;     // PSGD_XTAB=0 (environment, measurement knob): plain layer-by-layer launch order
     bool use_xtab_c = true;   // PSGD_XTAB_C=0 (likewise): the same for the column-mode product alone
 
+    // Whether the partial Gram matrices of a rows x w result are added up by a launch of their own, and the factorisation is
+    // another one (see kWideWidth, kSumSlots).
+    static bool sums_first(int w, int rows) {
+        return w > kWideWidth || (w > kCholRegWidth && rows > kSumSlots * kGramRows1);
+    }
     void note(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
     // event pair around one tagged launch group (only when profiling is on and pairs are left)
     int prof_begin(int tag) {
@@ -532,10 +537,10 @@ struct Launcher {
         const bool rv2 = v2 || r2;
         const bool split_n = n_norm > 0 && (rv2 ? norm.split_row_v2 : c2 ? norm.split_col_v2 : p_like ? (form ? norm.split_row_f : norm.split_row) : (form ? norm.split_col_f : norm.split_col));
         const bool split_t = n_tr > 0 && (p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
-        // Widths above kWideWidth: the partial Gram matrices are added up by a launch that spreads over the chip, and one
+        // Wide blocks, and long ones: the partial Gram matrices are added up by a launch that spreads over the chip, and one
         // launch of the factorisation serves both orientations.
         const int ww = w > 0 ? w : 32 * nb;
-        const bool wide = ww > kWideWidth;
+        const bool wide = sums_first(ww, p_like ? std::max(norm.longest, tr.longest) : std::max(norm.shortest_max, tr.shortest_max));
         const int fin_gate = wide ? -2 : chol_gate;
         if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         if (split_t) note(launch_finish(p_like, form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
@@ -588,7 +593,7 @@ struct Launcher {
     // launches that find nothing to do, where the second pass inside the iteration was one per iteration (the host does
     // not know which is a layer's last): 0.1 ms of a refresh with 16 iterations at widths above 16.
     void second_pass_deferred(int w, int cp, double tol2) {
-        const bool wide = w > kWideWidth;
+        const bool wide = sums_first(w, max_len());
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZP, cp, -1, 1, st));
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, -1, 1, st));
@@ -596,15 +601,16 @@ struct Launcher {
         for (int role : {ROLE_ZP, ROLE_ZQ})
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, st));
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZQ, cp, -1, 1, st));
-        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, -1, 1, st));
+        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, -1, 1, st));     // (as Jacobi expects them)
     }
     // the same CholeskyQR2 on a thin[out_role] that the caller supplied: its Gram slots come from a pass of their own
     void orth_given(int out_role, int w, double tol2, int cp) {
         const bool small = w <= 16;
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, 0, st));
-        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, 0, st));
-        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, w > kWideWidth ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
+        const bool wide = sums_first(w, max_len());
+        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, 0, st));
+        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
         if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));

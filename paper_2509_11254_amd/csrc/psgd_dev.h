@@ -55,6 +55,11 @@ constexpr int kGramRows2 = 64;     // rows per partial Gram matrix written by th
 constexpr int kOneSlot = 1 << 30;
 // widths above this: the partial Gram matrices are added up by gram_sum_kernel, the factorisation is a launch of its own
 constexpr int kWideWidth = 32;
+// ... and from this many 128-row slots on at widths above kCholRegWidth.  The last workgroup of finish_kernel needs 0.4 us per
+// slot for the sum, the two launches 8 us: 4096 x 512 r = 32 94.0 -> 85.2 us per step, 1024 x 16384 r = 24 193.7 -> 147.6,
+// 1024 x 100000 r = 32 1011 -> 695; with 4 to 8 slots the launches cost 1 to 2 us more than they save (128 x 512 r = 24 58.7 and 60.6).
+constexpr int kSumSlots = 12;
+constexpr int kCholRegWidth = 16;      // widths up to this are factorised by one wavefront in registers
 
 // Narrow layers (width <= 16) whose thin matrix has at most 64 partial Gram matrices: every workgroup of the apply kernel
 // repeats the factorisation for itself.  Rows at 128 and at 32 per partial matrix:

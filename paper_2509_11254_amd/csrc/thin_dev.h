@@ -20,7 +20,6 @@ namespace psgd {
 // status[1] is set and the pass-2 code (which exits at once otherwise) does its work.
 constexpr double kSecondPassPivot = 1e-6;
 constexpr int kCholMaxGroups = 8;
-constexpr int kCholRegWidth = 16;      // widths up to this are factorised by one wavefront in registers
 
 // slot groups that sum the partial Gram matrices side by side (all kThreads threads busy for small w)
 __host__ __device__ inline int chol_groups(int w) {

@@ -150,3 +150,38 @@ def test_batch_of_very_different_ranks(shapes, ranks, dtype):
                 assert abs(np.sum(e ** 2) - tail) <= 1e-4 * nm ** 2, (l, np.sum(e ** 2) / nm ** 2, tail / nm ** 2)
             else:
                 assert orc.rel_fro(e, ml - orc.ssp_comp(qs[l].astype(np.float64), [ml]).delta_hat) <= 10 * tol or r == min(rows, cols), l
+
+
+# widths factorised by finish_kernel up to 12 partial Gram matrices of 128 rows and by launches of their own beyond: both sides
+# of that line, in a batch on both, each orientation, in a step, its halves and a refresh
+@pytest.mark.parametrize("shapes", [[(1536, 72)], [(1544, 72)], [(72, 1537)], [(1000, 136), (136, 2000)], [(20000, 64), (64, 300)]])
+@pytest.mark.parametrize("op", ["step", "halves", "refresh"])
+@pytest.mark.parametrize("r", [17, 32])
+def test_many_partial_gram_matrices(shapes, op, r):
+    rng = np.random.default_rng(r + len(shapes))
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    # (refresh: singular values 0.8^i, so that the block of r columns is off by at most 0.8^32 = 8e-4 times the tangent of the
+    # start's angle, about 50, after 16 iterations: 2e-3 sigma_r^2 of energy, far below the 1e-4 ||M||^2 asked for)
+    decay = 0.8 if op == "refresh" else 0.95
+    ms = [((np.linalg.qr(rng.standard_normal((s[0], min(s))))[0] * decay ** np.arange(min(s))) @
+           np.linalg.qr(rng.standard_normal((s[1], min(s))))[0].T).astype(np.float32) for s in shapes]
+    qs = [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes]
+    case = Case(shapes, r, 1, synth.F32, lds=lds, refresh_oversample=0)
+    case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+    if op == "halves":
+        case.comp.compress_project(case.G, case.E, case.Q, case.P)
+        case.comp.compress_finish(case.E, case.Q, case.P)
+    else:
+        case.compress(refresh=op == "refresh")
+    for l, (rows, cols) in enumerate(shapes):
+        p, q, e = case.outputs(l)
+        ml = ms[l].astype(np.float64)
+        if rows < cols:
+            ml, e = ml.T, e.T
+        nm = np.linalg.norm(ml)
+        assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6, l
+        assert np.linalg.norm(q - ml.T @ p) <= 4e-6 * nm and np.linalg.norm(e - (ml - p @ q.T)) <= 4e-6 * nm, l
+        if op != "refresh":
+            assert orc.rel_fro(p, orc.ssp_comp(qs[l].astype(np.float64), [ml]).p_tilde) <= 1e-4, l
+        else:
+            assert abs(np.sum(e ** 2) - np.sum(np.linalg.svd(ml, compute_uv=False)[r:] ** 2)) <= 1e-4 * nm ** 2, l
