@@ -38,7 +38,7 @@ hipError_t launch_msgd(int nb, int planes, const LayerDev* layers, const int* id
 hipError_t launch_adam(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
                        float* const* m1s, float* const* m2s, float* const* xs, const float* coef, bool kept,
                        hipStream_t st);
-hipError_t launch_finish(bool colmode, int form, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
+hipError_t launch_finish(bool colmode, int kind, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st);
 hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, int max_blocks, int role, int cp,
@@ -83,10 +83,7 @@ struct Plan {            // host copy of what a layer needs
     int rowsP, colsP;
     int m, n;
     int wz = 0;                             // this layer's block width in the subspace iteration: at least r, at most n
-    // reduction splits of this layer's products (see plan_splits)
-    int split_row = 1, split_col = 1;       // prod_kernel, M read
-    int split_row_f = 1, split_col_f = 1;   // prod_kernel, forming pass
-    int split_row_v2 = 1, split_col_v2 = 1; // the kernels on 32 x 256 tiles
+    int split[SPLIT_KINDS][2] = {{1, 1}, {1, 1}, {1, 1}, {1, 1}};   // reduction splits of its products, as in LayerDev (see plan_splits)
 };
 
 struct Lists {
@@ -195,8 +192,9 @@ LayerRegion layer_region(const psgd_ctx* c, const Plan& p) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = (size_t)round_up((int64_t)(o + bytes), 256); return at; };
     const int lenP[2] = {p.rowsP, p.colsP};
-    const int split[2] = {std::max(std::max(p.split_row, p.split_row_f), p.split_row_v2),
-                          std::max(std::max(p.split_col, p.split_col_f), p.split_col_v2)};
+    int split[2] = {1, 1};
+    for (int m = 0; m < 2; ++m)
+        for (int k = 0; k < SPLIT_KINDS; ++k) split[m] = std::max(split[m], p.split[k][m]);
     for (int s = 0; s < 2; ++s) R.part[s] = take((size_t)split[s] * lenP[s] * p.wz * sizeof(float));
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 2 * c->planes; ++k) R.pack[s][k] = take((size_t)lenP[s] * c->cpmax * sizeof(bf16_t));
@@ -245,11 +243,12 @@ bool form_row_env() {
 // r = 64 takes 0.325 ms with 1024 workgroups, 0.302 with 256; at r = 128 0.514 and 0.473; at r = 16 and 32 it is
 // the other way round).
 // Two per compute unit where their operand buffers fit its LDS twice (two planes up to width 128): 8192 x 8192 bf16 r = 128
-// 518 -> 497 us per step, 2048 x 6000 r = 100 237 -> 228; with three planes one fits, and 4096 x 4096 fp32 r = 128 takes 307 us
-// with 512 workgroups against 288.
-int split_target(bool form, int cp, int planes) {
+// 534 -> 517 us per step, 2048 x 6000 r = 100 237 -> 228; with three planes one fits, and 4096 x 4096 fp32 r = 128 takes 307 us
+// with 512 workgroups against 288.  run: the width the products run at, wider than the step's cp in a refresh's iteration
+// (8192 x 8192 bf16 r = 128 at width 160: 6.38 ms with 512 workgroups, 6.18 with 256; 2048 x 8192 r = 104 4.52 and 4.36).
+int split_target(bool form, int cp, int run, int planes) {
     int target = target_tiles_env();
-    if (target == 0) target = cp >= 64 ? (planes == 2 && cp <= 128 ? 2 : 1) * kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);
+    if (target == 0) target = cp >= 64 ? (planes == 2 && run <= 128 ? 2 : 1) * kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);
     else if (!form && target > kTargetTilesPlain) target = target / 2;
     return target;
 }
@@ -258,8 +257,8 @@ int split_target(bool form, int cp, int planes) {
 // fp32 sums leave 1.4 to 1.7 times the error (E 6.2e-6 and 9.4e-6).  Left whole are launches of one orientation from three
 // quarters on where base_all, the batch's blocks of both orientations, reaches the target (the forming pass of the 22 matrices of
 // a 1B-shaped model stored as the transpose, 968 workgroups, is 0.1 ms faster than in halves with their finish_kernel).
-int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int planes, int64_t base_all) {
-    const int target = split_target(form, cp, planes);
+int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int run, int planes, int64_t base_all) {
+    const int target = split_target(form, cp, run, planes);
     if (base_tiles >= target || (4 * base_tiles >= 3 * target && base_all >= target)) return 1;
     int64_t s = (target + base_tiles - 1) / base_tiles;
     if (s > kMaxSplit) s = kMaxSplit;
@@ -277,8 +276,8 @@ int choose_split(int64_t base_tiles, int min_chunks, bool form, int cp, int plan
 // r = 8: products 115 -> 38 us, step with momentum SGD 163 -> 94 us; two 1B-shaped fp32 blocks at r = 16 939 -> 866 us (two
 // matrices of them are stored as the transpose, 32 workgroups of their row product).
 template <class Tiles, class Chunks>
-void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, int planes, Tiles tiles, Chunks chunks,
-                 bool both, int Plan::*split) {
+void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form, int cp, int run, int planes, Tiles tiles, Chunks chunks,
+                 bool both, SplitKind kind, int mode) {
     int64_t base = 0, steps = 0, base_all = 0;
     int most = 1, least = 1 << 30;
     for (int l : ids) {
@@ -289,7 +288,7 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
     }
     if (base == 0) return;
     if (both) for (const Plan& p : plan) base_all += tiles(p);
-    const int s = choose_split(base, most, form, cp, planes, base_all);
+    const int s = choose_split(base, most, form, cp, run, planes, base_all);
     if (s <= 1) return;
     // Steps per workgroup: with walks of one length as many pieces as choose_split says, with several lengths the fewest
     // steps that keep the launch within its target (before the equal split's number, whose pieces of the short walks end early
@@ -301,14 +300,14 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
             for (int l : ids) n += (int64_t)tiles(plan[l]) * std::max<int64_t>(2, std::min<int64_t>((chunks(plan[l]) + q - 1) / q, kMaxSplit));
             return n;
         };
-        const int64_t target = split_target(form, cp, planes);
+        const int64_t target = split_target(form, cp, run, planes);
         per = std::max<int64_t>(1, steps / target);
         while (per < most && total(per) > target) ++per;
     }
-    const int equal = choose_split(base, least, form, cp, planes, base_all);
+    const int equal = choose_split(base, least, form, cp, run, planes, base_all);
     for (int l : ids) {
         const int64_t mine = steps == base * most ? s : std::max<int64_t>(equal, (chunks(plan[l]) + per - 1) / per);
-        plan[l].*split = (int)std::max<int64_t>(2, std::min<int64_t>(mine, kMaxSplit));
+        plan[l].split[kind][mode] = (int)std::max<int64_t>(2, std::min<int64_t>(mine, kMaxSplit));
     }
 }
 
@@ -320,10 +319,7 @@ void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
     L.rows = (int)p.d.rows; L.cols = (int)p.d.cols; L.ld = p.d.ld; L.r = p.d.r; L.wz = p.wz;
     L.gdt = p.d.grad_dtype; L.n_workers = c->n_workers; L.transposed = p.transposed; L.planes = c->planes;
     L.rowsP = p.rowsP; L.colsP = p.colsP;
-    L.split_row = p.split_row; L.split_col = p.split_col;
-    L.split_row_f = p.split_row_f; L.split_col_f = p.split_col_f;
-    L.split_row_v2 = p.split_row_v2;
-    L.split_col_v2 = p.split_col_v2;
+    std::memcpy(L.split, p.split, sizeof(L.split));
     L.G = reinterpret_cast<const void* const*>(ws + c->off_gtab_s[slot]) + (size_t)l * c->n_workers;
     L.S = c->hE.empty() ? nullptr : c->hE[l];
     const int side_p = side_of_role(p.transposed, ROLE_P), side_q = side_of_role(p.transposed, ROLE_Q);
@@ -454,11 +450,9 @@ struct Launcher {
     int max_rows = 0, max_cols = 0, max_rowsP = 0, max_colsP = 0;
     int tiles_outer = 0;
     struct Geometry {       // of the layers of one orientation
-        int tiles_row = 0, tiles_col = 0, blocks_row = 0, blocks_col = 0;
-        int tiles_row_f = 0, tiles_col_f = 0;       // forming passes
-        int tiles_row_v2 = 0, tiles_col_v2 = 0;     // the kernels on 32 x 256 tiles
-        bool split_row = false, split_col = false, split_row_f = false, split_col_f = false, split_row_v2 = false,
-             split_col_v2 = false;                  // (all layers of a launch are split or none is)
+        int blocks[2] = {0, 0};                     // 128-row blocks of a row-mode / column-mode result
+        int tiles[SPLIT_KINDS][2] = {};             // workgroups per layer of a product
+        bool split[SPLIT_KINDS][2] = {};            // (all layers of a launch are split or none is)
         int longest = 0, shortest_max = 0;          // largest long side (P) and largest short side (Q)
     } norm, tr;
     int gram_rows_n = kGramRows1, gram_rows_t = kGramRows1;   // rows per Gram slot of the last product, per orientation
@@ -508,6 +502,8 @@ struct Launcher {
         const int k = prof_begin(p_like ? PSGD_PROF_SWEEP1 : PSGD_PROF_SWEEP2);
         const int ef = epi | (keep_e ? EPI_KEEP_E : 0) | (kept_packs && epi == EPI_PACK ? EPI_KEPT : 0);
         const bool onew = ctx->n_workers == 1;
+        const SplitKind kind = (SplitKind)split_kind(form, gate);      // (where prod_kernel runs)
+        const int mode_n = p_like ? 0 : 1, mode_t = 1 - mode_n;
         // forming pass on row-major layers at compress-step widths: the kernel built on 32 x 256 tiles
         // (never inside the gated part of the subspace iteration: its first product carries gate iteration 0,
         // which is open for every layer)
@@ -518,36 +514,36 @@ struct Launcher {
                               ? reinterpret_cast<const int*>(ws + ctx->off_xtab) : nullptr;
         // the same product on a matrix that is already formed (the refresh's iteration, further power steps)
         const bool r2 = !form && p_like && n_norm > 0 && use_form_row && row_prod_supported(nb, ctx->planes);
-        const bool gram32 = (v2 || r2) && !norm.split_row_v2 && epi == EPI_GRAM && chol_gate >= -1 && (!small || norm.longest <= kLocalGram32);
+        const bool gram32 = (v2 || r2) && !norm.split[SPLIT_V2][0] && epi == EPI_GRAM && chol_gate >= -1 && (!small || norm.longest <= kLocalGram32);
         // the second product on row-major layers at those widths likewise
         const bool c2 = !form && !p_like && n_norm > 0 && use_form_row && col_prod_supported(nb, ctx->planes);
         const int* xtab_c = (ctx->xstride > 0 && use_xtab && use_xtab_c && nb >= 2 && ids_norm == ids_all + ctx->n_layers)
                                 ? reinterpret_cast<const int*>(ws + ctx->off_xtab_c) : nullptr;
-        if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles_col_v2, out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
-        else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles_row_v2, out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, p_like ? (form ? norm.tiles_row_f : norm.tiles_row) : (form ? norm.tiles_col_f : norm.tiles_col), out_role, ef, gate, st));
+        if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][1], out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
+        else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
+        else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
+        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, norm.tiles[kind][mode_n], out_role, ef, gate, st));
         // (the row product of the layers stored with rows < cols stays on 128 x 64 tiles: 990 x 3741 fp32 r = 6 72.8 us per step
         // against 76.2 on 32 x 256 tiles, eight 2048 x 5632 r = 16 530 against 556, 22 of them in bf16 r = 32 1327 against 1358,
         // four 4096 x 11008 r = 64 1015 against 1089; single long ones are up to 5 % faster there, 1024 x 100000 712 and 695)
-        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, p_like ? (form ? tr.tiles_col_f : tr.tiles_col) : (form ? tr.tiles_row_f : tr.tiles_row), out_role, ef, gate, st));
+        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, tr.tiles[kind][mode_t], out_role, ef, gate, st));
         prof_end(k);
         // split reductions are completed (and the epilogue run) by a second, small launch, whose last
         // workgroup per layer also factorises the Gram matrix; unsplit products need a launch for that
         const bool rv2 = v2 || r2;
-        const bool split_n = n_norm > 0 && (rv2 ? norm.split_row_v2 : c2 ? norm.split_col_v2 : p_like ? (form ? norm.split_row_f : norm.split_row) : (form ? norm.split_col_f : norm.split_col));
-        const bool split_t = n_tr > 0 && (p_like ? (form ? tr.split_col_f : tr.split_col) : (form ? tr.split_row_f : tr.split_row));
+        const SplitKind kind_n = rv2 || c2 ? SPLIT_V2 : kind;
+        const bool split_n = n_norm > 0 && norm.split[kind_n][mode_n], split_t = n_tr > 0 && tr.split[kind][mode_t];
         // Wide blocks, and long ones: the partial Gram matrices are added up by a launch that spreads over the chip, and one
         // launch of the factorisation serves both orientations.
         const int ww = w > 0 ? w : 32 * nb;
         const bool wide = sums_first(ww, p_like ? std::max(norm.longest, tr.longest) : std::max(norm.shortest_max, tr.shortest_max));
         const int fin_gate = wide ? -2 : chol_gate;
-        if (split_n) note(launch_finish(!p_like, rv2 ? 2 : c2 ? 3 : (form ? 1 : 0), layers, ids_norm, n_norm, p_like ? norm.blocks_row : norm.blocks_col, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
-        if (split_t) note(launch_finish(p_like, form ? 1 : 0, layers, ids_tr, n_tr, p_like ? tr.blocks_col : tr.blocks_row, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        if (split_n) note(launch_finish(!p_like, kind_n, layers, ids_norm, n_norm, norm.blocks[mode_n], 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        if (split_t) note(launch_finish(p_like, kind, layers, ids_tr, n_tr, tr.blocks[mode_t], 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
         // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
         // per 128 rows)
-        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks_row, out_role, 32 * nb, gate, 0, st));
+        if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks[0], out_role, 32 * nb, gate, 0, st));
         gram_rows_n = gram32 ? 32 : split_n ? finish_rows(ww) : kGramRows1;
         gram_rows_t = split_t ? finish_rows(ww) : kGramRows1;
         if (chol_gate >= -1) {
@@ -645,15 +641,13 @@ void geometry(const Plan& p, Launcher& L) {
     const int rb = (int)((p.d.rows + 127) / 128), cb = (int)((p.d.cols + 127) / 128);
     mx(L.tiles_outer, rb * cb);
     Launcher::Geometry& g = p.transposed ? L.tr : L.norm;
-    mx(g.blocks_row, rb); mx(g.blocks_col, cb);
     mx(g.longest, p.m); mx(g.shortest_max, p.n);
-    mx(g.tiles_row, rb * p.split_row); mx(g.tiles_col, cb * p.split_col);
-    mx(g.tiles_row_f, rb * p.split_row_f); mx(g.tiles_col_f, cb * p.split_col_f);
-    mx(g.tiles_row_v2, (p.rowsP / 32) * p.split_row_v2);
-    mx(g.tiles_col_v2, ((p.colsP + 255) / 256) * p.split_col_v2);
-    g.split_row |= p.split_row > 1; g.split_col |= p.split_col > 1;
-    g.split_row_f |= p.split_row_f > 1; g.split_col_f |= p.split_col_f > 1;
-    g.split_row_v2 |= p.split_row_v2 > 1; g.split_col_v2 |= p.split_col_v2 > 1;
+    mx(g.blocks[0], rb); mx(g.blocks[1], cb);
+    for (int k = 0; k < SPLIT_KINDS; ++k) {
+        mx(g.tiles[k][0], (k == SPLIT_V2 ? p.rowsP / 32 : rb) * p.split[k][0]);
+        mx(g.tiles[k][1], (k == SPLIT_V2 ? (p.colsP + 255) / 256 : cb) * p.split[k][1]);
+        for (int m = 0; m < 2; ++m) g.split[k][m] |= p.split[k][m] > 1;
+    }
 }
 
 Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
@@ -813,10 +807,12 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
         auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
         auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
-        plan_splits(c->plan, *ids, false, c->cpc, c->planes, row_tiles, row_chunks, true, &Plan::split_row);
-        plan_splits(c->plan, *ids, false, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col);
-        plan_splits(c->plan, *ids, true, c->cpc, c->planes, row_tiles, row_chunks, true, &Plan::split_row_f);
-        plan_splits(c->plan, *ids, true, c->cpc, c->planes, col_tiles, col_chunks, true, &Plan::split_col_f);
+        plan_splits(c->plan, *ids, false, c->cpc, c->cpc, c->planes, row_tiles, row_chunks, true, SPLIT_M, 0);
+        plan_splits(c->plan, *ids, false, c->cpc, c->cpc, c->planes, col_tiles, col_chunks, true, SPLIT_M, 1);
+        plan_splits(c->plan, *ids, false, c->cpc, c->cpz, c->planes, row_tiles, row_chunks, true, SPLIT_ITER, 0);
+        plan_splits(c->plan, *ids, false, c->cpc, c->cpz, c->planes, col_tiles, col_chunks, true, SPLIT_ITER, 1);
+        plan_splits(c->plan, *ids, true, c->cpc, c->cpc, c->planes, row_tiles, row_chunks, true, SPLIT_FORM, 0);
+        plan_splits(c->plan, *ids, true, c->cpc, c->cpc, c->planes, col_tiles, col_chunks, true, SPLIT_FORM, 1);
         if (ids != &c->lists.norm) continue;
         // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split) and their
         // column products
@@ -824,8 +820,8 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
         auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
         auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
-        plan_splits(c->plan, *ids, true, 32, c->planes, row_tiles_v2, row_chunks_v2, false, &Plan::split_row_v2);
-        plan_splits(c->plan, *ids, false, 32, c->planes, col_tiles_v2, col_chunks_v2, false, &Plan::split_col_v2);
+        plan_splits(c->plan, *ids, true, 32, 32, c->planes, row_tiles_v2, row_chunks_v2, false, SPLIT_V2, 0);
+        plan_splits(c->plan, *ids, false, 32, 32, c->planes, col_tiles_v2, col_chunks_v2, false, SPLIT_V2, 1);
     }
     {
         int64_t m_bytes = 0;
@@ -866,8 +862,8 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
                     if (total[x] > xtiles) xtiles = total[x];
                 }
             };
-            build(c->hXtab, c->xtiles, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return (p.rowsP / 32) * p.split_row_v2; });
-            build(c->hXtabC, c->xtiles_c, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return ((p.colsP + 255) / 256) * p.split_col_v2; });
+            build(c->hXtab, c->xtiles, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return (p.rowsP / 32) * p.split[SPLIT_V2][0]; });
+            build(c->hXtabC, c->xtiles_c, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return ((p.colsP + 255) / 256) * p.split[SPLIT_V2][1]; });
         }
     }
     // workspace layout
@@ -1197,11 +1193,10 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     D.thin[ROLE_P].ptr = P;
     D.thin[ROLE_Q].ptr = Q;
     Plan one = p;
-    one.split_row = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->planes, 0);
-    one.split_col = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->planes, 0);
-    one.split_row_f = one.split_row; one.split_col_f = one.split_col;      // (no forming pass in this call)
-    D.split_row = one.split_row; D.split_col = one.split_col;
-    D.split_row_f = one.split_row_f; D.split_col_f = one.split_col_f;
+    // (every product of this call is one of the iteration)
+    one.split[SPLIT_ITER][0] = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->cpz, ctx->planes, 0);
+    one.split[SPLIT_ITER][1] = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->cpz, ctx->planes, 0);
+    std::memcpy(D.split, one.split, sizeof(D.split));
     D.part[0] = reinterpret_cast<float*>(ws + ctx->off_single_part[0]);
     D.part[1] = reinterpret_cast<float*>(ws + ctx->off_single_part[1]);
     ctx->hLayers[ctx->n_layers] = D;

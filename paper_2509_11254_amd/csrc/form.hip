@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kThreads, 2) void form_row_kernel(const LayerDev* _
     const int rows = L.rows, cols = L.cols;
     const bool store_m = !(epi_flags & EPI_KEEP_E);
     const int n_ob = L.rowsP / FR;                       // (row blocks past the end write the zeros of the padding)
-    const int n_split = L.split_row_v2;
+    const int n_split = L.split[SPLIT_V2][0];
     if (tile >= n_ob * n_split) return;
     const int sp = tile % n_split, ob = tile / n_split;
     const int row0 = ob * FR;
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kThreads, 2) void row_prod_kernel(const LayerDev* _
     const LayerDev& L = layers[ids[layer_pos]];
     if (!gate_open(L, gate)) return;
     const int n_ob = L.rowsP / FR;
-    const int n_split = L.split_row_v2;
+    const int n_split = L.split[SPLIT_V2][0];
     if (tile >= n_ob * n_split) return;
     const int sp = tile % n_split, ob = tile / n_split;
     const int row0 = ob * FR;
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(kThreads, ((PL == 2 && NB == 1) ? 3 : 2)) void col_
     int copies;
     const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const int n_cb = (L.colsP + CW - 1) / CW;
-    const int n_split = L.split_col_v2;
+    const int n_split = L.split[SPLIT_V2][1];
     if (tile >= n_cb * n_split) return;
     const int ob = tile % n_cb, sp = tile / n_cb;
     const int col0 = ob * CW;
@@ -941,7 +941,7 @@ static hipError_t launch_colprod_nb(const LayerDev* layers, const int* ids, int 
 // (width 96 with three planes: the fragments of a step and two tiles do not fit the registers)
 bool col_prod_supported(int nb, int planes) { return nb == 1 || nb == 2 || (nb == 3 && planes == 2); }
 
-// max_tiles: max over the layers of ceil(padded cols / 256) * split_col_v2; nt_s: read S with the non-temporal hint
+// max_tiles: max over the layers of ceil(padded cols / 256) * split[SPLIT_V2][1]; nt_s: read S with the non-temporal hint
 hipError_t launch_col_prod(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
                            int out_role, int epi, int gate, int nt_s, const int* xtab, int xstride, int xtiles,
                            hipStream_t st) {
@@ -1033,7 +1033,7 @@ bool form_row_supported(int nb, int planes, bool gbf, bool onew, bool lazy) {
 // fp32); onew: one worker; lazy: apply the owed residual on the way in (2: the kept Q is what the transposed operand
 // copies of the product hold, and is taken from those); nt_m: store M with the non-temporal hint
 // (matrices too large to be found in a cache by the second pass).  max_tiles: max over the layers of
-// (padded rows / 32) * split_row_v2.  xtab (device, nullable): the XCD table described in the kernel, 16 rows of
+// (padded rows / 32) * split[SPLIT_V2][0].  xtab (device, nullable): the XCD table described in the kernel, 16 rows of
 // xstride ints; xtiles: the largest tile total of an XCD.
 hipError_t launch_form_row(int nb, int planes, bool gbf, bool onew, int lazy, const LayerDev* layers, const int* ids,
                            int n_ids, int max_tiles, int out_role, int epi, int nt_m, const int* xtab, int xstride,

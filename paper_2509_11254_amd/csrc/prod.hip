@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
     const int out_len = COLMODE ? L.cols : L.rows;
     const int red_len = COLMODE ? L.rows : L.cols;
     const int n_ob = (out_len + BT - 1) / BT;
-    const int n_split = FORM ? (COLMODE ? L.split_col_f : L.split_row_f) : (COLMODE ? L.split_col : L.split_row);
+    const int n_split = L.split[split_kind(FORM, gate)][COLMODE ? 1 : 0];
     const int tile = blockIdx.x;
     if (tile >= n_ob * n_split) return;
     int ob, sp;
@@ -650,7 +650,7 @@ template <int FB>
 __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __restrict__ layers,
                                                           const int* __restrict__ ids, int colmode, int cp,
                                                           int out_role, int epi_flags, int gate, int chol_gate,
-                                                          int a2gate, double tol2, int local_ok, int form) {
+                                                          int a2gate, double tol2, int local_ok, int kind) {
     __shared__ int s_last;
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
@@ -658,10 +658,7 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
     const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const int out_side = colmode ? SIDE_W : SIDE_L;
     const int out_len = colmode ? L.cols : L.rows;
-    // form (whose partial sums): 0 = a product of prod_kernel that reads M, 1 = a forming pass of prod_kernel,
-    // 2 = a row-mode pass on 32 x 256 tiles (form_row_kernel, row_prod_kernel), 3 = col_prod_kernel
-    const int n_split = form == 2 ? L.split_row_v2 : form == 3 ? L.split_col_v2
-                        : form ? (colmode ? L.split_col_f : L.split_row_f) : (colmode ? L.split_col : L.split_row);
+    const int n_split = L.split[kind][colmode];      // (kind: SplitKind, whose partial sums)
     const int ob = blockIdx.x;
     const int out_lenP = side_lenP(L, out_side);
     if (n_split <= 1 || ob * FB >= out_lenP) return;      // (the operand copies' padding is written as well)
@@ -781,8 +778,8 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
 // Rows per workgroup and Gram slot.  w: widest block of the launch
 int finish_rows(int w) { return w > kWideWidth ? BT / 2 : BT; }
 
-// max_blocks: 128-row blocks of the longest result
-hipError_t launch_finish(bool colmode, int form, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
+// kind: SplitKind of the launch whose partial sums these are; max_blocks: 128-row blocks of the longest result
+hipError_t launch_finish(bool colmode, int kind, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st) {
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
@@ -797,7 +794,7 @@ hipError_t launch_finish(bool colmode, int form, const LayerDev* layers, const i
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, colmode ? 1 : 0, cp, out_role, epi, gate,
-                       chol_gate, a2gate, tol2, local_ok, form);
+                       chol_gate, a2gate, tol2, local_ok, kind);
     return hipGetLastError();
 }
 

@@ -107,6 +107,11 @@ struct PackRef {
     bf16_t* t[kMaxPlanes];
 };
 
+// Which of a layer's splits a product uses: a pass of prod_kernel over M, one inside the refresh's iteration, a forming pass
+// of it, or one of the kernels on 32 x 256 tiles (form_row_kernel, row_prod_kernel, col_prod_kernel).
+enum SplitKind { SPLIT_M = 0, SPLIT_ITER = 1, SPLIT_FORM = 2, SPLIT_V2 = 3, SPLIT_KINDS = 4 };
+__host__ __device__ inline int split_kind(bool form, int gate) { return form ? SPLIT_FORM : gate >= 0 ? SPLIT_ITER : SPLIT_M; }
+
 struct LayerDev {
     int rows, cols;
     int64_t ld;
@@ -117,13 +122,7 @@ struct LayerDev {
     int transposed;    // rows < cols: P~ is W-side
     int planes;        // 2 or 3 bf16 planes per fp32 operand (3 or 6 MFMA products per term)
     int rowsP, colsP;  // rows / cols rounded up to kLenPad
-    int split_row;     // k-splits of the row-mode product  (reduction over cols)
-    int split_col;     // k-splits of the column-mode product (reduction over rows)
-    int split_row_f;   // the same for the forming passes, which want about twice as many workgroups
-    int split_col_f;
-    int split_row_v2;  // k-splits of the row-mode forming pass on 32 x 256 tiles (form_row_kernel)
-    int split_col_v2;  // k-splits of the column-mode product on 32 x 256 tiles (col_prod_kernel)
-    int pad_[2];
+    int split[4][2];   // pieces of the products' reductions: [SplitKind][0 = row mode, over cols; 1 = column mode, over rows]
     const void* const* G;   // n_workers device pointers
     float* S;               // E on entry, M between the sweeps, E_{t+1} on exit
     ThinRef thin[ROLE_COUNT];

@@ -82,3 +82,31 @@ def _first_layer_errors(shapes, r, seed=5):
 def test_errors_do_not_depend_on_the_batch(fewer, more, r, which):
     few, many = _first_layer_errors(fewer, r)[which], _first_layer_errors(more, r)[which]
     assert many <= 1.25 * few, (few, many)
+
+
+# two planes at r = 112: the step's products run at width 128 and the refresh's iteration at 160, with other splits, in the
+# same context and, one after the other, on the same partial sums
+@pytest.mark.parametrize("shapes", [[(1000, 520)], [(520, 1000)], [(1000, 520), (264, 1496), (2056, 264)]])
+def test_step_and_refresh_at_different_widths(shapes):
+    rng = np.random.default_rng(len(shapes))
+    r, tol = 112, TOL[synth.BF16]
+    ms = [synth.round_to_bf16((np.linalg.qr(rng.standard_normal((s[0], min(s))))[0] * 0.97 ** np.arange(min(s)) @
+                               np.linalg.qr(rng.standard_normal((s[1], min(s))))[0].T).astype(np.float32)) for s in shapes]
+    case = Case(shapes, r, 1, synth.BF16)
+    for refresh in (False, True, False, True):
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes],
+                    [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes])
+        q0 = [back(q) for q in case.Q]
+        case.compress(refresh=refresh)
+        for l, (rows, cols) in enumerate(shapes):
+            p, q, e = case.outputs(l)
+            m = logical(synth.gradient_as_f64(ms[l]), rows, cols)
+            e = logical(e, rows, cols)
+            nm = np.linalg.norm(m)
+            assert np.abs(p.T @ p - np.eye(r)).max() < 2e-5, (l, refresh)
+            assert np.linalg.norm(q - m.T @ p) <= tol * nm and np.linalg.norm(e - (m - p @ q.T)) <= tol * nm, (l, refresh)
+            if refresh:
+                tail = np.sum(np.linalg.svd(m, compute_uv=False)[r:] ** 2)
+                assert abs(np.sum(e ** 2) - tail) <= 1e-4 * nm ** 2, l
+            else:
+                assert orc.rel_fro(p @ q.T, orc.ssp_comp(q0[l], [m]).delta_hat) <= tol, l
