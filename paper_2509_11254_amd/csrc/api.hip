@@ -84,6 +84,7 @@ struct Plan {            // host copy of what a layer needs
     int m, n;
     int wz = 0;                             // this layer's block width in the subspace iteration: at least r, at most n
     int split[SPLIT_KINDS][2] = {{1, 1}, {1, 1}, {1, 1}, {1, 1}};   // reduction splits of its products, as in LayerDev (see plan_splits)
+    int split_alone[2] = {1, 1};            // SPLIT_ITER of the layer by itself (psgd_refresh)
 };
 
 struct Lists {
@@ -123,7 +124,8 @@ struct psgd_ctx {
     static constexpr int kGSlots = 4;
     size_t off_layers_s[kGSlots] = {}, off_gtab_s[kGSlots] = {};
     size_t off_iters = 0;            // one int: most iterations any layer's next refresh will run
-    size_t off_ids = 0, off_outs = 0, off_moms = 0, off_m2s = 0, off_xs = 0, off_single_part[2] = {0, 0};
+    size_t off_ids = 0, off_outs = 0, off_moms = 0, off_m2s = 0, off_xs = 0;
+    size_t off_alone[2] = {0, 0};    // partial sums of psgd_refresh, which splits for one layer (a context of one: the layer's own)
     std::vector<size_t> off_layer;   // start of each layer's private region
     size_t ws_bytes = 0;
     // cached tables
@@ -182,6 +184,51 @@ int fail_hip(psgd_ctx* c, hipError_t e) {
         if (e__ != hipSuccess) return fail_hip(ctx, e__); \
     } while (0)
 
+// PSGD_FORM_ROW=0 (environment, measurement knob): forming passes use the 128 x 64 kernel everywhere
+bool form_row_env() {
+    static int v = -1;
+    if (v < 0) {
+        const char* e = std::getenv("PSGD_FORM_ROW");
+        v = (e && e[0] == '0') ? 0 : 1;
+    }
+    return v == 1;
+}
+
+// Whether a product of the row-major layers runs on 32 x 256 tiles (form_row_kernel, row_prod_kernel, col_prod_kernel) at
+// operand width 32 nb.  lazy: a forming pass that also applies the owed residual.
+bool on_wide_tiles(const psgd_ctx* c, bool p_like, bool form, int nb, bool lazy) {
+    if (!form_row_env()) return false;
+    if (!form) return p_like ? row_prod_supported(nb, c->planes) : col_prod_supported(nb, c->planes);
+    return p_like && c->grad_kind != 0 && form_row_supported(nb, c->planes, c->grad_kind == 2, c->n_workers == 1, lazy);
+}
+
+// Floats of partial sums per row of one side's result (0: rows, 1: columns) that the products of layer p can need: pieces
+// times width, the most over the launches of the compress-type calls (alone: those of psgd_refresh).
+int64_t part_width(const psgd_ctx* c, const Plan& p, int side, bool alone) {
+    int64_t most = 0;
+    auto launch = [&](bool p_like, bool form, bool iter, bool lazy) {
+        const int mode = p_like == (p.transposed == 0) ? 0 : 1;
+        if (mode != side) return;
+        const int nb = (iter ? c->cpz : c->cpc) / 32;
+        const int kind = !p.transposed && on_wide_tiles(c, p_like, form, nb, lazy) ? SPLIT_V2 : split_kind(form, iter ? 0 : -1);
+        const int split = alone && kind == SPLIT_ITER ? p.split_alone[mode] : p.split[kind][mode];
+        if (split > 1) most = std::max<int64_t>(most, (int64_t)split * (iter ? p.wz : p.d.r));
+    };
+    if (alone) {
+        launch(true, false, true, false);
+        launch(false, false, true, false);
+        return most;
+    }
+    for (bool iter : {false, true}) {
+        launch(true, true, iter, false);                              // M formed
+        if (c->lazy) launch(true, true, iter, true);
+        launch(true, false, iter, false);                             // M read (the step: further power iterations)
+        launch(false, false, iter, false);
+        if (c->reform_m && !iter) launch(false, true, iter, false);
+    }
+    return most;
+}
+
 struct LayerRegion {
     size_t part[2], pack[2][6], lzf[2][3], z[2], gram, tmat, eval, status, end;
 };
@@ -192,10 +239,11 @@ LayerRegion layer_region(const psgd_ctx* c, const Plan& p) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = (size_t)round_up((int64_t)(o + bytes), 256); return at; };
     const int lenP[2] = {p.rowsP, p.colsP};
-    int split[2] = {1, 1};
-    for (int m = 0; m < 2; ++m)
-        for (int k = 0; k < SPLIT_KINDS; ++k) split[m] = std::max(split[m], p.split[k][m]);
-    for (int s = 0; s < 2; ++s) R.part[s] = take((size_t)split[s] * lenP[s] * p.wz * sizeof(float));
+    for (int s = 0; s < 2; ++s) {
+        int64_t width = part_width(c, p, s, false);
+        if (c->n_layers == 1) width = std::max(width, part_width(c, p, s, true));      // (see off_alone)
+        R.part[s] = take((size_t)width * lenP[s] * sizeof(float));
+    }
     for (int s = 0; s < 2; ++s)
         for (int k = 0; k < 2 * c->planes; ++k) R.pack[s][k] = take((size_t)lenP[s] * c->cpmax * sizeof(bf16_t));
     if (c->lazy && (!p.transposed || c->lazy_tr))
@@ -225,16 +273,6 @@ int target_tiles_env() {
         if (v < 1) v = 0;
     }
     return v;
-}
-
-// PSGD_FORM_ROW=0 (environment, measurement knob): forming passes use the 128 x 64 kernel everywhere
-bool form_row_env() {
-    static int v = -1;
-    if (v < 0) {
-        const char* e = std::getenv("PSGD_FORM_ROW");
-        v = (e && e[0] == '0') ? 0 : 1;
-    }
-    return v == 1;
 }
 
 // Reduction split of a launch with `base_tiles` output blocks.  cp: packed width of the thin operand.  At widths
@@ -309,6 +347,78 @@ void plan_splits(std::vector<Plan>& plan, const std::vector<int>& ids, bool form
         const int64_t mine = steps == base * most ? s : std::max<int64_t>(equal, (chunks(plan[l]) + per - 1) / per);
         plan[l].split[kind][mode] = (int)std::max<int64_t>(2, std::min<int64_t>(mine, kMaxSplit));
     }
+}
+
+// The splits of all launches.  one_split: one number per kind of product for the whole context, bounded by its shortest walk
+// and planned for the fewer workgroups.
+void plan_all(psgd_ctx* c, bool one_split) {
+    auto row_tiles = [](const Plan& p) { return (int)((p.d.rows + 127) / 128); };
+    auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
+    auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
+    auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
+    auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
+    auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
+    auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
+    auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
+    std::vector<int> all(c->n_layers);
+    for (int l = 0; l < c->n_layers; ++l) all[l] = l;
+    auto plan = [&](const std::vector<int>& ids, SplitKind kind, int mode, bool form, int cp, int run, auto tiles, auto chunks) {
+        if (!one_split) {
+            plan_splits(c->plan, ids, form, cp, run, c->planes, tiles, chunks, kind != SPLIT_V2, kind, mode);
+            return;
+        }
+        int64_t base = 0;
+        int least = 1 << 30;
+        for (int l : ids) { base += tiles(c->plan[l]); least = std::min(least, chunks(c->plan[l])); }
+        const int s = base > 0 ? choose_split(base, least, form, cp, kMaxWidth, c->planes, 0) : 1;
+        for (int l : ids) c->plan[l].split[kind][mode] = s;
+    };
+    for (Plan& p : c->plan)
+        for (auto& k : p.split) k[0] = k[1] = 1;
+    for (const std::vector<int>* ids : {&c->lists.norm, &c->lists.tr}) {
+        const std::vector<int>& of = one_split ? all : *ids;
+        plan(of, SPLIT_M, 0, false, c->cpc, c->cpc, row_tiles, row_chunks);
+        plan(of, SPLIT_M, 1, false, c->cpc, c->cpc, col_tiles, col_chunks);
+        plan(of, SPLIT_ITER, 0, false, c->cpc, c->cpz, row_tiles, row_chunks);
+        plan(of, SPLIT_ITER, 1, false, c->cpc, c->cpz, col_tiles, col_chunks);
+        plan(of, SPLIT_FORM, 0, true, c->cpc, c->cpc, row_tiles, row_chunks);
+        plan(of, SPLIT_FORM, 1, true, c->cpc, c->cpc, col_tiles, col_chunks);
+    }
+    // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split) and their
+    // column products
+    plan(c->lists.norm, SPLIT_V2, 0, true, 32, 32, row_tiles_v2, row_chunks_v2);
+    plan(c->lists.norm, SPLIT_V2, 1, false, 32, 32, col_tiles_v2, col_chunks_v2);
+    for (Plan& p : c->plan) {
+        p.split_alone[0] = choose_split(row_tiles(p), row_chunks(p), false, c->cpz, one_split ? kMaxWidth : c->cpz, c->planes, 0);
+        p.split_alone[1] = choose_split(col_tiles(p), col_chunks(p), false, c->cpz, one_split ? kMaxWidth : c->cpz, c->planes, 0);
+    }
+}
+
+// Workspace layout for the planned splits: offsets and total.
+void lay_out(psgd_ctx* c) {
+    size_t o = 0;
+    auto take = [&](size_t bytes) { size_t at = o; o = (size_t)round_up((int64_t)(o + bytes), 256); return at; };
+    for (int k = 0; k < psgd_ctx::kGSlots; ++k) c->off_layers_s[k] = take((size_t)(c->n_layers + 1) * sizeof(LayerDev));
+    c->off_ids = take((3 * (size_t)c->n_layers + 1) * sizeof(int));
+    c->off_iters = take(psgd_ctx::kIterSlots * sizeof(int));
+    c->off_xtab = take((size_t)16 * c->xstride * sizeof(int) + 16);
+    c->off_xtab_c = take((size_t)16 * c->xstride * sizeof(int) + 16);
+    for (int k = 0; k < psgd_ctx::kGSlots; ++k) c->off_gtab_s[k] = take((size_t)c->n_layers * c->n_workers * sizeof(void*));
+    c->off_outs = take((size_t)c->n_layers * sizeof(void*));
+    c->off_moms = take((size_t)c->n_layers * sizeof(void*));
+    c->off_xs = take((size_t)c->n_layers * sizeof(void*));
+    c->off_m2s = take((size_t)c->n_layers * sizeof(void*));
+    for (int s = 0; s < 2 && c->n_layers > 1; ++s) {
+        size_t most = 0;
+        for (const Plan& p : c->plan) most = std::max(most, (size_t)part_width(c, p, s, true) * (s == 0 ? p.rowsP : p.colsP) * sizeof(float));
+        c->off_alone[s] = take(most);
+    }
+    c->off_layer.resize(c->n_layers);
+    for (int l = 0; l < c->n_layers; ++l) {
+        c->off_layer[l] = o;
+        o += layer_region(c, c->plan[l]).end;
+    }
+    c->ws_bytes = o;
 }
 
 void build_layer_dev(psgd_ctx* c, char* ws, int l, int slot, LayerDev* out) {
@@ -466,7 +576,6 @@ struct Launcher {
                               // the kept Q, which the pass then need not read
     bool kept_packs = false;  // compress step with a deferred residual: the row-major operand copies of its P~ and Q go
                               // to the kept copies (fragment order) in the layers that have them
-    bool use_form_row = true; // PSGD_FORM_ROW=0 (environment, measurement knob): the older 128 x 64 forming pass
     bool use_xtab = true;     // PSGD_XTAB=0 (environment, measurement knob): plain layer-by-layer launch order
     bool use_xtab_c = true;   // PSGD_XTAB_C=0 (likewise): the same for the column-mode product alone
 
@@ -507,16 +616,16 @@ struct Launcher {
         // forming pass on row-major layers at compress-step widths: the kernel built on 32 x 256 tiles
         // (never inside the gated part of the subspace iteration: its first product carries gate iteration 0,
         // which is open for every layer)
-        const bool v2 = form && p_like && n_norm > 0 && ctx->grad_kind != 0 && use_form_row &&
-                        form_row_supported(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form);
+        const bool on_wide = n_norm > 0 && on_wide_tiles(ctx, p_like, form, nb, lazy_form);
+        const bool v2 = on_wide && form;
         // (the XCD table pays where the thin operands are a large part of what a workgroup reads: width 64)
         const int* xtab = (ctx->xstride > 0 && use_xtab && nb >= 2 && ids_norm == ids_all + ctx->n_layers)
                               ? reinterpret_cast<const int*>(ws + ctx->off_xtab) : nullptr;
         // the same product on a matrix that is already formed (the refresh's iteration, further power steps)
-        const bool r2 = !form && p_like && n_norm > 0 && use_form_row && row_prod_supported(nb, ctx->planes);
+        const bool r2 = on_wide && !form && p_like;
         const bool gram32 = (v2 || r2) && !norm.split[SPLIT_V2][0] && epi == EPI_GRAM && chol_gate >= -1 && (!small || norm.longest <= kLocalGram32);
         // the second product on row-major layers at those widths likewise
-        const bool c2 = !form && !p_like && n_norm > 0 && use_form_row && col_prod_supported(nb, ctx->planes);
+        const bool c2 = on_wide && !form && !p_like;
         const int* xtab_c = (ctx->xstride > 0 && use_xtab && use_xtab_c && nb >= 2 && ids_norm == ids_all + ctx->n_layers)
                                 ? reinterpret_cast<const int*>(ws + ctx->off_xtab_c) : nullptr;
         if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][1], out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
@@ -660,7 +769,6 @@ Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
     L.ids_all = ids; L.ids_norm = ids + nl; L.ids_tr = ids + 2 * (size_t)nl;
     L.n_all = nl; L.n_norm = (int)ctx->lists.norm.size(); L.n_tr = (int)ctx->lists.tr.size();
     for (const Plan& p : ctx->plan) geometry(p, L);
-    L.use_form_row = form_row_env();
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab = v == 1; }
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB_C"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab_c = v == 1; }
     return L;
@@ -801,28 +909,6 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         c->lazy_tr = c->lazy && c->cpc == 32;
     }
     if (rc != PSGD_OK) { delete c; return rc; }
-    // reduction splits of the batched launches
-    for (const std::vector<int>* ids : {&c->lists.norm, &c->lists.tr}) {
-        auto row_tiles = [](const Plan& p) { return (int)((p.d.rows + 127) / 128); };
-        auto col_tiles = [](const Plan& p) { return (int)((p.d.cols + 127) / 128); };
-        auto row_chunks = [](const Plan& p) { return (int)((p.d.cols + 63) / 64); };
-        auto col_chunks = [](const Plan& p) { return (int)((p.d.rows + 63) / 64); };
-        plan_splits(c->plan, *ids, false, c->cpc, c->cpc, c->planes, row_tiles, row_chunks, true, SPLIT_M, 0);
-        plan_splits(c->plan, *ids, false, c->cpc, c->cpc, c->planes, col_tiles, col_chunks, true, SPLIT_M, 1);
-        plan_splits(c->plan, *ids, false, c->cpc, c->cpz, c->planes, row_tiles, row_chunks, true, SPLIT_ITER, 0);
-        plan_splits(c->plan, *ids, false, c->cpc, c->cpz, c->planes, col_tiles, col_chunks, true, SPLIT_ITER, 1);
-        plan_splits(c->plan, *ids, true, c->cpc, c->cpc, c->planes, row_tiles, row_chunks, true, SPLIT_FORM, 0);
-        plan_splits(c->plan, *ids, true, c->cpc, c->cpc, c->planes, col_tiles, col_chunks, true, SPLIT_FORM, 1);
-        if (ids != &c->lists.norm) continue;
-        // on 32 x 256 tiles: the forming pass of the row-major layers (and the row products that share its split) and their
-        // column products
-        auto row_tiles_v2 = [](const Plan& p) { return p.rowsP / 32; };
-        auto col_tiles_v2 = [](const Plan& p) { return (p.colsP + 255) / 256; };
-        auto row_chunks_v2 = [](const Plan& p) { return (int)((p.d.cols + 255) / 256); };
-        auto col_chunks_v2 = [](const Plan& p) { return (int)((p.d.rows + 31) / 32); };
-        plan_splits(c->plan, *ids, true, 32, 32, c->planes, row_tiles_v2, row_chunks_v2, false, SPLIT_V2, 0);
-        plan_splits(c->plan, *ids, false, 32, 32, c->planes, col_tiles_v2, col_chunks_v2, false, SPLIT_V2, 1);
-    }
     {
         int64_t m_bytes = 0;
         bool f32 = false, b16 = false;
@@ -834,11 +920,23 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         // M that the second pass can find in the 256 MB memory-side cache is stored with plain stores
         c->nt_m = m_bytes > ((int64_t)96 << 20);
         if (const char* e = std::getenv("PSGD_NT_M")) c->nt_m = e[0] != '0';     // (measurement knob)
+        const int n_norm = (int)c->lists.norm.size();
+        if (n_norm >= 32) c->xstride = n_norm + 2;
+        // The splits, and with them the workspace.  psgd_compress_static takes what fits its buffer with one split per kind of
+        // product, so a context keeps to those where only that fits.
+        plan_all(c, false);
+        lay_out(c);
+        if (c->ws_bytes > (size_t)PSGD_STATIC_WORKSPACE_BYTES) {
+            plan_all(c, true);
+            lay_out(c);
+            if (c->ws_bytes > (size_t)PSGD_STATIC_WORKSPACE_BYTES) {
+                plan_all(c, false);
+                lay_out(c);
+            }
+        }
         // XCD table: the row-major layers (positions in the id list `norm`), largest first, each to the XCD with the
         // least work so far
-        const int n_norm = (int)c->lists.norm.size();
         if (n_norm >= 32) {
-            c->xstride = n_norm + 2;
             // work = rows x cols decides the deal (the same for both kernels), tiles = what a layer launches
             auto build = [&](std::vector<int>& tab, int& xtiles, auto tiles_of) {
                 tab.assign((size_t)16 * c->xstride, 0);
@@ -866,29 +964,8 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
             build(c->hXtabC, c->xtiles_c, [&](int pos) { const Plan& p = c->plan[c->lists.norm[pos]]; return ((p.colsP + 255) / 256) * p.split[SPLIT_V2][1]; });
         }
     }
-    // workspace layout
-    size_t o = 0;
-    auto take = [&](size_t bytes) { size_t at = o; o = (size_t)round_up((int64_t)(o + bytes), 256); return at; };
-    for (int k = 0; k < psgd_ctx::kGSlots; ++k) c->off_layers_s[k] = take((size_t)(n_layers + 1) * sizeof(LayerDev));
-    c->off_ids = take((3 * (size_t)n_layers + 1) * sizeof(int));
-    c->off_iters = take(psgd_ctx::kIterSlots * sizeof(int));
-    c->off_xtab = take(c->hXtab.size() * sizeof(int) + 16);
-    c->off_xtab_c = take(c->hXtabC.size() * sizeof(int) + 16);
-    for (int k = 0; k < psgd_ctx::kGSlots; ++k) c->off_gtab_s[k] = take((size_t)n_layers * n_workers * sizeof(void*));
-    c->off_outs = take((size_t)n_layers * sizeof(void*));
-    c->off_moms = take((size_t)n_layers * sizeof(void*));
-    c->off_xs = take((size_t)n_layers * sizeof(void*));
-    c->off_m2s = take((size_t)n_layers * sizeof(void*));
-    int max_rowsP = 0, max_colsP = 0;
-    for (auto& p : c->plan) { if (p.rowsP > max_rowsP) max_rowsP = p.rowsP; if (p.colsP > max_colsP) max_colsP = p.colsP; }
-    c->off_single_part[0] = take((size_t)kMaxSplit * max_rowsP * c->wz * sizeof(float));
-    c->off_single_part[1] = take((size_t)kMaxSplit * max_colsP * c->wz * sizeof(float));
-    c->off_layer.resize(n_layers);
     double bytes = 0.0;
-    for (int l = 0; l < n_layers; ++l) {
-        c->off_layer[l] = o;
-        o += layer_region(c, c->plan[l]).end;
-        const Plan& p = c->plan[l];
+    for (const Plan& p : c->plan) {
         const double sg = p.d.grad_dtype == PSGD_BF16 ? 2.0 : 4.0;
         // two passes separated by the global QR: either M is stored between them (N*sg + 16 bytes
         // per element) or formed twice from the gradients (2*N*sg + 12); the smaller one counts
@@ -906,7 +983,6 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         c->kernel_bytes[1] += e * (c->reform_m ? nsg + 4.0 : 4.0) + thin;
         if (!deferred) c->kernel_bytes[2] += e * (c->reform_m ? nsg + 8.0 : 8.0) + thin;
     }
-    c->ws_bytes = o;
     c->algo_bytes = bytes;
     // host tables at their final capacity, so that no compute call allocates host memory either
     {
@@ -1194,11 +1270,10 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     D.thin[ROLE_Q].ptr = Q;
     Plan one = p;
     // (every product of this call is one of the iteration)
-    one.split[SPLIT_ITER][0] = choose_split((p.d.rows + 127) / 128, (int)((p.d.cols + 63) / 64), false, ctx->cpz, ctx->cpz, ctx->planes, 0);
-    one.split[SPLIT_ITER][1] = choose_split((p.d.cols + 127) / 128, (int)((p.d.rows + 63) / 64), false, ctx->cpz, ctx->cpz, ctx->planes, 0);
-    std::memcpy(D.split, one.split, sizeof(D.split));
-    D.part[0] = reinterpret_cast<float*>(ws + ctx->off_single_part[0]);
-    D.part[1] = reinterpret_cast<float*>(ws + ctx->off_single_part[1]);
+    for (int m = 0; m < 2; ++m) {
+        D.split[SPLIT_ITER][m] = one.split[SPLIT_ITER][m] = p.split_alone[m];
+        if (ctx->n_layers > 1) D.part[m] = reinterpret_cast<float*>(ws + ctx->off_alone[m]);
+    }
     ctx->hLayers[ctx->n_layers] = D;
     PSGD_TRY(launch_put(ws + ctx->off_layers_s[ctx->cur_slot] + (size_t)ctx->n_layers * sizeof(LayerDev), &D, sizeof(LayerDev), st));
     // this call rewrites the layer's iteration count: what the host knows about the next batched refresh is void

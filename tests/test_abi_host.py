@@ -100,6 +100,23 @@ def test_workspace_and_algorithmic_bytes(lib):
     lib.psgd_destroy(c2)
 
 
+# (layers, workers, oversample, m_policy, lazy_residual): contexts that psgd_compress_static takes with one split of the
+# reductions per kind of product
+@pytest.mark.parametrize("layers,n,over,policy,lazy", [
+    ([(2048, 2048, 0, 48, 1)], 1, -1, 0, 0), ([(4096, 1024, 0, 48, 1)], 1, -1, 0, 0), ([(1024, 2048, 0, 64, 0)], 1, -1, 0, 0),
+    ([(1024, 4096, 0, 48, 0)], 1, -1, 0, 0), ([(410, 6794, 6800, 37, 1)], 2, -1, 0, 0), ([(122, 8007, 8008, 47, 0)], 1, 0, 0, 1),
+    ([(2246, 2505, 2512, 60, 1)], 4, 0, 2, 0), ([(153, 306, 312, 9, 1), (507, 14397, 14400, 9, 1)], 1, -1, 0, 1),
+    ([(1334, 1608, 0, 53, 0)] * 3, 4, -1, 2, 0), ([(222, 1476, 1480, 103, 1)] * 3, 4, -1, 0, 0),
+    ([(271, 160, 160, 33, 1), (3450, 3313, 3320, 5, 1)], 1, -1, 0, 1), ([(1195, 3371, 3376, 38, 0)] * 2, 1, -1, 0, 0),
+    ([(376, 578, 584, 35, 0), (1051, 5177, 5184, 35, 0), (1051, 5177, 5184, 35, 0)], 1, -1, 2, 0)])
+def test_static_workspace_takes(lib, layers, n, over, policy, lazy):
+    opt = psgd.Options(0, over, 1, 1, 0.0, 0, policy, 0, lazy, 0)
+    rc, ctx = _init(lib, layers, n_workers=n, opt=C.byref(opt))
+    assert rc == psgd.PSGD_OK
+    assert lib.psgd_workspace_bytes(ctx) <= psgd.STATIC_WORKSPACE_BYTES
+    lib.psgd_destroy(ctx)
+
+
 @pytest.mark.parametrize("r", [24, 64, 192])
 def test_a_small_layer_does_not_shrink_the_others_regions(lib, r):
     """Block widths of the subspace iteration are capped by the matrix; a layer's partial sums, Gram and factor matrices have

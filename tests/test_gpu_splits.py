@@ -5,7 +5,7 @@ import pytest
 
 from oracle import psgd_oracle as orc
 from paper_2509_11254_amd import synth
-from gpu_harness import Case, back, logical, to_dev_grad
+from gpu_harness import Case, back, logical, to_dev_grad, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -110,3 +110,54 @@ def test_step_and_refresh_at_different_widths(shapes):
                 assert abs(np.sum(e ** 2) - tail) <= 1e-4 * nm ** 2, l
             else:
                 assert orc.rel_fro(p @ q.T, orc.ssp_comp(q0[l], [m]).delta_hat) <= tol, l
+
+
+# psgd_refresh splits for one layer: its partial sums are the layer's own region (a context of one layer) or one region for
+# all; between steps, on 32 x 256 tiles (r = 24) and at widths 128 and 160, one orientation and both
+@pytest.mark.parametrize("shapes", [[(1000, 264)], [(264, 2056)], [(1000, 264), (264, 2056), (520, 520)]])
+@pytest.mark.parametrize("r,dtype", [(24, synth.F32), (100, synth.F32), (112, synth.BF16)])
+def test_refresh_of_single_layers_between_steps(shapes, r, dtype):
+    torch = torch_mod()
+    rng = np.random.default_rng(r + len(shapes))
+    ms = []
+    for s in shapes:
+        m = (np.linalg.qr(rng.standard_normal((s[0], min(s))))[0] * 0.95 ** np.arange(min(s)) @
+             np.linalg.qr(rng.standard_normal((s[1], min(s))))[0].T).astype(np.float32)
+        ms.append(synth.round_to_bf16(m) if dtype == synth.BF16 else m)
+    case = Case(shapes, r, 1, dtype)
+    for _ in range(2):
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes],
+                    [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes])
+        q0 = [back(q) for q in case.Q]
+        case.compress()
+        for l, (rows, cols) in enumerate(shapes):
+            m = logical(synth.gradient_as_f64(ms[l]), rows, cols)
+            p, q, _ = case.outputs(l)
+            assert orc.rel_fro(p @ q.T, orc.ssp_comp(q0[l], [m]).delta_hat) <= TOL[dtype], l
+        for l, (rows, cols) in enumerate(shapes):
+            m = logical(synth.gradient_as_f64(ms[l]), rows, cols)
+            dense = torch.from_numpy(np.ascontiguousarray(logical(m, rows, cols)).astype(np.float32)).cuda()
+            p, q = torch.zeros((max(rows, cols), r), device="cuda"), torch.zeros((min(rows, cols), r), device="cuda")
+            case.comp.refresh(l, dense, p, q)
+            p, q, nm = back(p), back(q), np.linalg.norm(m)
+            assert np.abs(p.T @ p - np.eye(r)).max() < 2e-5, l
+            assert np.linalg.norm(q - m.T @ p) <= 2e-5 * nm, l
+            tail = np.sum(np.linalg.svd(m, compute_uv=False)[r:] ** 2)
+            assert abs(np.linalg.norm(m - p @ q.T) ** 2 - tail) <= 1e-4 * nm ** 2, l
+
+
+# psgd_compress_static in a context whose workspace fits the built-in one only with its sums as they are planned there
+@pytest.mark.parametrize("shapes,r", [([(1024, 4096)], 48), ([(2048, 2048)], 48), ([(1334, 1608)] * 3, 53)])
+def test_static_step_equals_step(shapes, r):
+    torch = torch_mod()
+    rng = np.random.default_rng(r)
+    ms = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    qs = [rng.standard_normal((min(s), r)).astype(np.float32) for s in shapes]
+    out = []
+    for static in (False, True):
+        case = Case(shapes, r, 1, synth.F32)
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+        (case.comp.compress_static if static else case.comp.compress)(case.G, case.E, case.Q, case.P)
+        torch.cuda.synchronize()
+        out.append([case.outputs(l) for l in range(len(shapes))])
+    assert all(np.array_equal(a, b) for x, y in zip(*out) for a, b in zip(x, y))
