@@ -81,3 +81,42 @@ def test_start_block_out_of_order(r, b, rows, cols, order, planes):
     if order != "outlier":
         rounding = 2.0 ** (-24 if planes == 3 else -17) * np.sqrt(r)
         assert orc.sin_theta_max(left[:, :r], p) <= max(4.0 * rounding * sv[0] / (sv[r - 1] - sv[r]), (sv[b] / sv[r - 1]) ** 6)
+
+
+# The second CholeskyQR pass on Z, made once after the iteration for the layers that ask for it (Z <- Z T, Y <- Y T, the Gram
+# matrix of Y anew): one iteration from a start block with two columns 1e-6 apart, whose pivot of 1e-12 leaves an
+# orthogonality error of 1e-5 to 1e-2 after the first pass.  Block widths 16, 32, 56 and 120; alone, and in a batch with
+# layers that do not ask and keep their bits.
+@pytest.mark.parametrize("r", [8, 20, 40, 96])
+@pytest.mark.parametrize("shapes", [[(400, 300)], [(300, 408)], [(2000, 264), (300, 408), (400, 300), (264, 1800)]])
+def test_second_pass_after_the_iteration(r, shapes):
+    rng = np.random.default_rng(r + len(shapes))
+    lds = [(c + 7) // 8 * 8 for _, c in shapes]
+    ms = [rng.standard_normal(s).astype(np.float32) for s in shapes]
+    plain = [np.linalg.qr(rng.standard_normal((min(s), r)))[0].astype(np.float32) for s in shapes]
+    close = [q.copy() for q in plain]
+    close[0][:, r - 1] = close[0][:, 0] + np.float32(1e-6) * close[0][:, r - 1]
+    # one pass on the warm columns in fp64, stored in fp32: what the bound below has to tell from two
+    x = ((ms[0] if shapes[0][0] >= shapes[0][1] else ms[0].T) @ close[0]).astype(np.float64)
+    d = 1.0 / np.linalg.norm(x, axis=0)
+    z = (x @ (d[:, None] * np.linalg.inv(np.linalg.cholesky((x * d).T @ (x * d)).T))).astype(np.float32).astype(np.float64)
+    assert np.abs(z.T @ z - np.eye(r)).max() > 4e-6
+    out = {}
+    for name, qs in (("plain", plain), ("close", close)):
+        case = Case(shapes, r, 1, synth.F32, lds=lds, rank_tol=1e-7, refresh_iters=1)
+        case.upload([[m] for m in ms], [np.zeros(s, np.float32) for s in shapes], qs)
+        case.compress(refresh=True)
+        out[name] = [case.outputs(l) for l in range(len(shapes))]
+    for l, (rows, cols) in enumerate(shapes):
+        if l > 0:
+            assert all(np.array_equal(a, b) for a, b in zip(out["close"][l], out["plain"][l])), l
+        p, q, e = out["close"][l]
+        m = ms[l].astype(np.float64)
+        if rows < cols:
+            m, e = m.T, e.T
+        assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6, l
+        assert np.linalg.norm(q - m.T @ p) <= 2e-6 * np.linalg.norm(m), l
+        assert np.linalg.norm(e - (m - p @ q.T)) <= 2e-6 * np.linalg.norm(m), l
+        # Ritz vectors: Q = M^T P~ has orthogonal columns in falling order (H = Y^T Y of the Y that goes with the final Z)
+        h = q.T @ q
+        assert np.abs(h - np.diag(np.diag(h))).max() <= 4e-6 * h[0, 0] and np.all(np.diff(np.diag(h)) <= 4e-6 * h[0, 0]), l
