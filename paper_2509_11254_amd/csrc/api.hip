@@ -1432,7 +1432,7 @@ int psgd_status(psgd_ctx* ctx, void* workspace, void* stream, int layer, psgd_la
     PSGD_TRY(hipMemcpy(raw, ws + ctx->off_layer[layer] + R.status, sizeof(raw), hipMemcpyDeviceToHost));
     out->rank_deficient = raw[0];
     out->refresh_iters_next = raw[4];
-    out->refresh_iters_no_gap = raw[25] < 2 ? 2 : raw[25];
+    out->refresh_iters_no_gap = raw[9] < 2 ? 2 : raw[9];
     std::memcpy(&out->sigma_max, &raw[2], sizeof(float));
     std::memcpy(&out->sigma_r, &raw[3], sizeof(float));
     return PSGD_OK;

@@ -43,10 +43,7 @@ template <int BIT, class V> __device__ inline void st_stream(PSGD_GLOBAL V* p, V
     if constexpr ((PSGD_NT_MASK & BIT) != 0) __builtin_nontemporal_store(v, p); else *p = v;
 }
 
-constexpr int kStatusWords = 8 + 16 + 8; // per layer: 8 diagnostics and counters, one counter per Gram slot group,
-                                         // then: [24] refreshes this layer has run in this workspace, [25] iterations
-                                         // its next refresh runs if its cut has no gap (see refresh_iterations),
-                                         // [26] whether this iteration's Y is orthonormalised (see Spread)
+constexpr int kStatusWords = 16;   // per layer, see LayerDev::status
 constexpr int kThreads = 256;      // 4 wavefronts of 64 lanes
 constexpr int kLenPad = 128;       // packed operand rows are padded (with zeros) to this multiple
 constexpr int kGramRows1 = 128;    // rows per partial Gram matrix written by a product's epilogue
@@ -134,10 +131,11 @@ struct LayerDev {
                             // row block of the producer
     double* tmat;           // [wmax*wmax] small factor applied from the right
     double* eval;           // [wmax]
-    int* status;            // [kStatusWords] : rank_deficient, second-pass-needed flag, sigma_max bits, sigma_r bits,
-                            //       iterations the next refresh needs (0 = not known yet), Jacobi sweeps of the last
-                            //       refresh, arrival counters of the two kernels that hand over to the
-                            //       factorisation, then the arrival counters of the Gram slot groups
+    int* status;            // [kStatusWords] : 0 rank_deficient, 1 second-pass-needed flag, 2 sigma_max bits, 3 sigma_r bits,
+                            //       4 iterations the next refresh needs (0 = not known yet), 5 Jacobi sweeps of the last
+                            //       refresh, 6 and 7 arrival counters of finish_kernel and apply_kernel, 8 refreshes this
+                            //       layer has run in this workspace, 9 iterations its next refresh runs if its cut has no
+                            //       gap (see refresh_iterations), 10 whether this iteration's Y is orthonormalised (see Spread)
 };
 
 __host__ __device__ inline int side_of_role(int transposed, int role) {
@@ -254,12 +252,12 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 // its spectrum needs to converge, from the Ritz values of its last refresh) when that is within the budget; and
 // otherwise -- the cut is then too close to a cluster of singular values to converge across in the budget, and the
 // members of such a cluster compress almost equally well -- the count that keeps the compression error within a
-// tenth of 1e-4 ||M||^2 of the optimum (status[25]), at least 2, at most the budget.  k never exceeds the number of launched iterations (the host may launch fewer than the budget when
+// tenth of 1e-4 ||M||^2 of the optimum (status[9]), at least 2, at most the budget.  k never exceeds the number of launched iterations (the host may launch fewer than the budget when
 // it knows an upper bound of the counts; should that bound be out of date, a layer's last iteration is still one
 // that was launched).  kind 1 marks the orthonormalisation of Y, which the last executed iteration skips because
-// the Rayleigh-Ritz step wants Y = M^T Z itself; kind 2 is open in the last executed iteration only (the second
-// CholeskyQR pass on Z, which the Rayleigh-Ritz step needs exact).
-// kGateIfAsked: besides, only for the layers whose last factorisation of Z asked for an orthonormalised Y (status[26]).
+// the Rayleigh-Ritz step wants Y = M^T Z itself; kind 2 is open in the last executed iteration only (there the
+// factorisation of Z may ask for the second CholeskyQR pass, which is made after the iteration: the Rayleigh-Ritz step needs Z exact).
+// kGateIfAsked: besides, only for the layers whose last factorisation of Z asked for an orthonormalised Y (status[10]).
 constexpr int kMaxRefreshIterations = 255;
 constexpr int kGateIfAsked = 1 << 26;
 __host__ __device__ inline int make_gate(int iteration, int kind, int budget, int launched) {
@@ -269,11 +267,11 @@ __host__ __device__ inline int gate_with_kind(int gate, int kind) { return (gate
 // iterations the layer's next refresh runs when the budget is mx
 __device__ inline int refresh_iterations(const LayerDev& L, int mx) {
     int k = L.status[4];
-    if (k <= 0 || L.status[24] < 2) k = mx;
+    if (k <= 0 || L.status[8] < 2) k = mx;
     else if (k > mx) {
         // no gap to converge across within the budget: as many iterations as the error bound of Lemma 2 needs
-        // (status[25], see jacobi_kernel), at least 2, at most the budget
-        const int ke = L.status[25] < 2 ? 2 : L.status[25];
+        // (status[9], see jacobi_kernel), at least 2, at most the budget
+        const int ke = L.status[9] < 2 ? 2 : L.status[9];
         k = mx < ke ? mx : ke;
     }
     return k;
@@ -284,7 +282,7 @@ __device__ inline bool gate_open(const LayerDev& L, int gate) {
     int k = refresh_iterations(L, mx);
     k = k < launched ? k : launched;
     if (kind == 2) return it == k - 1;
-    return it < k - kind && (!(gate & kGateIfAsked) || L.status[26] != 0);
+    return it < k - kind && (!(gate & kGateIfAsked) || L.status[10] != 0);
 }
 
 // What a product of the launch does with its result for this layer.  `copies`: the operand copies EPI_PACK leaves (1 =
@@ -293,7 +291,7 @@ __device__ inline int resolve_epilogue(const LayerDev& L, int epi_flags, int gat
     const int epi = epi_flags & EPI_KIND_MASK;
     copies = 3;
     if (epi != EPI_ITERATE) return epi;
-    if (!gate_open(L, gate_with_kind(gate, 1)) || L.status[26] != 0) return EPI_GRAM;
+    if (!gate_open(L, gate_with_kind(gate, 1)) || L.status[10] != 0) return EPI_GRAM;
     copies = 2;
     return EPI_PACK;
 }

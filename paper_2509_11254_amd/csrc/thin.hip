@@ -163,72 +163,67 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
 
 // --------------------------------------------------------------------------------------------
 // apply: thin[dst] (len x w_out) <- thin[src] (len x w_in) * tmat[:, :w_out]   (fp64 accumulate);
-// w_in and w_out are the widths of the two thin matrices, tmat is w_in x w_in row-major.
+// w_in and w_out are the widths of the two thin matrices, tmat is w_in x w_in row-major.  One kernel for launches whose
+// layers are all narrow (width <= 16, in place), one for widths up to 96, one beyond.
 // In place (dst == src) is allowed: a workgroup reads its 64 rows completely before writing them.
 // Fused follow-ups, chosen by `mode` and the layer's second-pass flag:
-//   APPLY_PASS1  (upper-triangular tmat): flag set   -> also the partial Gram matrix of the result, and the
-//                                                       last workgroup to finish factorises their sum
+//   APPLY_PASS1  (upper-triangular tmat): flag set   -> also the partial Gram matrix of the result (the narrow kernel's last
+//                                                       workgroup to finish factorises their sum)
 //                                         flag clear -> result is final: operand copies if cp > 0
 //   APPLY_PASS1_ONLY (the same)         : final + operand copies whatever the flag says: the second pass, if the flag asks
 //                                       for one, is run later on the result
 //   APPLY_PASS2  (upper-triangular tmat): flag clear -> nothing to do; else final + operand copies
-//   APPLY_RITZ   (full tmat)            : final + operand copies if cp > 0
+//   APPLY_RITZ   (full tmat)            : final + operand copies if cp > 0 (not in the narrow kernel)
 // --------------------------------------------------------------------------------------------
 enum ApplyMode { APPLY_PASS1 = 1, APPLY_PASS2 = 2, APPLY_RITZ = 3, APPLY_PASS1_ONLY = 4 };
 
-// LDS bytes of the tmat block, the x tile and the result tile (what every mode needs), 16-byte rounded
-__host__ __device__ inline size_t apply_main_lds(int w_in, int w_out, int cp) {
-    const int ow = (cp > w_out ? cp : w_out) + 1;
-    const int kpad = (w_in + 3) & ~3;
-    const size_t b = (size_t)kGramRows2 * (ow + w_in + 1) * sizeof(float) + (size_t)kpad * 32 * sizeof(double);
+// LDS bytes of the narrow kernel's x tile and result tile, 16-byte rounded
+__host__ __device__ inline size_t apply_main_lds(int w, int cp) {
+    const int ow = (cp > 16 ? cp : 16) + 1;
+    const size_t b = (size_t)kGramRows2 * (ow + w + 1) * sizeof(float);
     return (b + 15) & ~(size_t)15;
 }
 
-// SMALL: the variant for launches whose layers are all narrow (width <= 16) -- it carries the per-workgroup
-// factorisation and the hand-over to the second-pass factorisation, which cost registers the plain variant
-// (wide blocks, where the kernel is a streaming pass and wants occupancy) does without; there the
-// second-pass factorisation is a launch of its own.
-template <bool SMALL>
+// Narrow layers (width <= 16).  It carries the per-workgroup factorisation of the first pass and the hand-over to that of the
+// second.  ITER: inside the subspace iteration, where a factorisation also notes what its successor needs (see Spread); the
+// step's launches are 0.4 us shorter without that code.
+template <bool ITER>
 __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restrict__ layers,
-                                                         const int* __restrict__ ids, int src_role, int dst_role,
-                                                         int mode, int cp, int gate, int a2gate, double tol2,
-                                                         int which, int slot_rows) {
+                                                         const int* __restrict__ ids, int role, int mode, int cp,
+                                                         int gate, int a2gate, double tol2, int which, int slot_rows) {
     __shared__ int s_last;
     __shared__ int s_need2;
     const LayerDev& L = layers[ids[blockIdx.y]];
-    if (!gate_open(L, gate)) return;
-    const int side = side_of_role(L.transposed, src_role);
+    if (ITER && !gate_open(L, gate)) return;
+    const int side = side_of_role(L.transposed, role);
     const int len = side_len(L, side), lenP = side_lenP(L, side);
     const int i0 = blockIdx.x * kGramRows2;
     if (i0 >= lenP) return;
-    const ThinRef X = L.thin[src_role];
-    const ThinRef Y = L.thin[dst_role];
-    const int w_in = X.width, w_out = Y.width;
+    const ThinRef X = L.thin[role];
+    const int w = X.width;
     extern __shared__ __align__(16) unsigned char smem[];
-    const size_t main_lds = apply_main_lds(w_in, w_out, cp);
+    const size_t main_lds = apply_main_lds(w, cp);
     const double* __restrict__ tm = L.tmat;
     int need2;
-    // x tile (64 x w_in): one contiguous block of the thin matrix when ld == width (always the case for the
-    // library's own buffers and for P, Q), fetched with 16-byte loads over the flat range
-    const bool flat_x = X.ld == w_in && (w_in & 3) == 0;
-    const int64_t xbase = (int64_t)i0 * X.ld;
-    const int n_valid_x = (min(len, i0 + kGramRows2) - i0) * w_in;          // elements that exist
-    float4 xpre = make_float4(0.f, 0.f, 0.f, 0.f);
-    bool have_pre = false;
+    const int t = threadIdx.x;
+    // x tile (64 x w): one contiguous block of the thin matrix when ld == width (always the case for the
+    // library's own buffers and for P, Q), fetched with one 16-byte load per thread over the flat range
+    const bool flat_x = X.ld == w && (w & 3) == 0;
+    const int n_valid = (min(len, i0 + kGramRows2) - i0) * w;               // elements that exist
+    floatx4 xpre = {0.f, 0.f, 0.f, 0.f};
     // partial Gram matrices of the second pass: behind those of the first where other workgroups may still have to read these
     double* gram2 = L.gram;
-    if (SMALL && (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY) && local_chol(L, src_role, 1)) {
+    const int ntri = (w * (w + 1)) / 2;
+    const bool local = (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY) && local_chol(L, role, 1);
+    if (local) {
         // small factorisation repeated by every workgroup; the first one records the outcome.  The
         // workgroup's own rows are requested first so that their latency overlaps the factorisation.
-        if (flat_x) {
-            have_pre = true;
-            if (4 * (int)threadIdx.x < n_valid_x) xpre = *reinterpret_cast<const float4*>(X.ptr + xbase + 4 * threadIdx.x);
-        }
+        if (flat_x && 4 * t < n_valid) xpre = *reinterpret_cast<const PSGD_GLOBAL floatx4*>(as_global(X.ptr) + (int64_t)i0 * X.ld + 4 * t);
         double* tml = reinterpret_cast<double*>(smem + main_lds);
         const int rows1 = L.transposed ? kGramRows1 : slot_rows;
-        gram2 += (int64_t)((len + rows1 - 1) / rows1) * ((w_in * (w_in + 1)) / 2);
-        chol_body<true>(L, src_role, tol2, 1, rows1, allow2_of(L, a2gate), smem + main_lds + w_in * w_in * sizeof(double),
-                  tml, blockIdx.x == 0, &s_need2, scales_next(L, src_role, gate));
+        gram2 += (int64_t)((len + rows1 - 1) / rows1) * ntri;
+        chol_body<true>(L, role, tol2, 1, rows1, allow2_of(L, a2gate), smem + main_lds + w * w * sizeof(double),
+                        tml, blockIdx.x == 0, &s_need2, ITER && scales_next(L, role, gate));
         __syncthreads();
         need2 = s_need2;
         tm = tml;
@@ -239,127 +234,75 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
     const bool do_gram = (mode == APPLY_PASS1) && need2;
     const bool do_pack = !do_gram && cp > 0;
     if (i0 >= (do_pack ? lenP : len)) return;
-    const bool upper = mode != APPLY_RITZ;
-    const int ow = (cp > w_out ? cp : w_out) + 1;     // stride of the output tile (zero padded to cp)
-    // The product runs on the fp64 matrix cores (v_mfma_f64_16x16x4_f64): wave v owns rows 16v..16v+15
-    // of the 64-row tile and walks the 16-column tiles of the result.  A operand = x (fp32 in LDS,
-    // widened per use), B operand = a block of tmat columns staged in LDS.
-    const int xs = w_in + 1;                                         // row stride of the x tile
-    const int kpad = (w_in + 3) & ~3;                                // reduction length padded to the MFMA k
-    const int cbw = 32;                                              // output columns per pass
-    double* st = reinterpret_cast<double*>(smem);                    // [kpad][cbw] block of tmat columns
-    float* sx = reinterpret_cast<float*>(st + (size_t)kpad * cbw);    // [64][xs]  x tile
-    float* so = sx + (size_t)kGramRows2 * xs;                        // [64][ow]  result tile
-    const int t = threadIdx.x;
+    const int ow = (cp > 16 ? cp : 16) + 1;           // stride of the result tile (zero padded to cp)
+    const int xs = w + 1;                             // row stride of the x tile
+    float* sx = reinterpret_cast<float*>(smem);       // [64][xs]  x tile
+    float* so = sx + (size_t)kGramRows2 * xs;         // [64][ow]  result tile
     const int tx = t & 63, ty = t >> 6;
-    {
-        const float inv_w = 1.0f / (float)w_in;
-        if (flat_x) {
-            // up to eight 16-byte loads per thread in flight before the first LDS store (w_in <= 128 in one go)
-            for (int f0 = 0; f0 < kGramRows2 * w_in; f0 += 32 * kThreads) {
-                floatx4 xv[8];
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const int f = f0 + 4 * (d * kThreads + t);
-                    xv[d] = floatx4{0.f, 0.f, 0.f, 0.f};
-                    if (have_pre && f == 4 * t) xv[d] = floatx4{xpre.x, xpre.y, xpre.z, xpre.w};
-                    else if (f < n_valid_x) xv[d] = *reinterpret_cast<const PSGD_GLOBAL floatx4*>(as_global(X.ptr) + xbase + f);
-                }
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const int f = f0 + 4 * (d * kThreads + t);
-                    if (f >= kGramRows2 * w_in) continue;
-                    int row = (int)(((float)f + 0.5f) * inv_w);
-                    int c = f - row * w_in;
-                    if (c < 0) { --row; c += w_in; } else if (c >= w_in) { ++row; c -= w_in; }
-                    float* dd = sx + row * xs + c;
-                    dd[0] = xv[d].x; dd[1] = xv[d].y; dd[2] = xv[d].z; dd[3] = xv[d].w;
-                }
-            }
-        } else {
-            for (int i = ty; i < kGramRows2; i += 4) {
-                const bool in = i0 + i < len;
-                const float* __restrict__ xr = X.ptr + (int64_t)(in ? i0 + i : 0) * X.ld;
-                for (int c = tx; c < w_in; c += 64) sx[i * xs + c] = in ? xr[c] : 0.f;
-            }
-        }
-        for (int e = t; e < kGramRows2 * ow; e += kThreads) so[e] = 0.f;
-    }
-    const int li = tx & 15, lk = tx >> 4;                             // MFMA lane: row/column index, k index
-    for (int cb = 0; cb < w_out; cb += cbw) {
-        __syncthreads();
-        const int jmax = upper ? min(cb + cbw, w_in) : w_in;          // below-diagonal entries of tmat are zero
-        const int jpad = (jmax + 3) & ~3;
-        // block of tmat -> LDS; eight loads per thread are issued before their LDS stores so that they are
-        // in flight together (a load-store-load-store chain costs a round trip to L2 per row)
-        for (int e0 = 0; e0 < jpad * cbw; e0 += 8 * kThreads) {
-            double tv[8];
-#pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                const int e = e0 + d * kThreads + t;
-                const int j = e / cbw, c = e % cbw;             // cbw is a power of two
-                tv[d] = (e < jpad * cbw && j < w_in && cb + c < w_in) ? tm[(int64_t)j * w_in + cb + c] : 0.0;
-            }
-#pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                const int e = e0 + d * kThreads + t;
-                if (e < jpad * cbw) st[e] = tv[d];
-            }
-        }
-        __syncthreads();
-        const float* __restrict__ xa = sx + (16 * ty + li) * xs + lk;
-        for (int ct = 0; ct < cbw / 16 && cb + 16 * ct < w_out; ++ct) {
-            doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-            const int kend = upper ? min(jpad, (cb + 16 * ct + 16 + 3) & ~3) : jpad;
-            const double* __restrict__ sb = st + lk * cbw + 16 * ct + li;
-            for (int k = 0; k < kend; k += 4) {
-                const double a = (k + lk < w_in) ? (double)xa[k] : 0.0;
-                const double b = sb[k * cbw];
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-            }
-            const int col = cb + 16 * ct + li;
-            if (col < w_out) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) so[(16 * ty + 4 * v + lk) * ow + col] = (float)acc[v];
-            }
-        }
-    }
-    __syncthreads();
-    if (Y.ld == w_out && (w_out & 3) == 0) {
-        // contiguous result block: 16-byte stores (rows past the end are cut off)
-        const int n_valid = (min(len, i0 + kGramRows2) - i0) * w_out;
-        const float inv_w = 1.0f / (float)w_out;
-        for (int f = 4 * t; f < n_valid; f += 4 * kThreads) {
+    const float inv_w = 1.0f / (float)w;
+    if (flat_x) {
+        if (!local && 4 * t < n_valid) xpre = *reinterpret_cast<const PSGD_GLOBAL floatx4*>(as_global(X.ptr) + (int64_t)i0 * X.ld + 4 * t);
+        const int f = 4 * t;
+        if (f < kGramRows2 * w) {
             int row = (int)(((float)f + 0.5f) * inv_w);
-            int c = f - row * w_out;
-            if (c < 0) { --row; c += w_out; } else if (c >= w_out) { ++row; c -= w_out; }
-            const float* __restrict__ sr = so + row * ow + c;
-            *reinterpret_cast<float4*>(Y.ptr + (int64_t)i0 * Y.ld + f) = make_float4(sr[0], sr[1], sr[2], sr[3]);
+            int c = f - row * w;
+            if (c < 0) { --row; c += w; } else if (c >= w) { ++row; c -= w; }
+            float* dd = sx + row * xs + c;
+            dd[0] = xpre.x; dd[1] = xpre.y; dd[2] = xpre.z; dd[3] = xpre.w;
         }
     } else {
         for (int i = ty; i < kGramRows2; i += 4) {
-            if (i0 + i >= len) break;
-            float* __restrict__ yr = Y.ptr + (int64_t)(i0 + i) * Y.ld;
-            for (int c = tx; c < w_out; c += 64) yr[c] = so[i * ow + c];
+            const bool in = i0 + i < len;
+            const float* __restrict__ xr = X.ptr + (int64_t)(in ? i0 + i : 0) * X.ld;
+            if (tx < w) sx[i * xs + tx] = in ? xr[tx] : 0.f;
         }
     }
-    if (do_gram) {
-        gram_tile_f64(so, ow, kGramRows2, w_out, gram2 + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
-        if (SMALL) {
-            const int n_wg = (len + kGramRows2 - 1) / kGramRows2;
-            if (last_to_arrive(&L.status[7], n_wg, &s_last))
-                chol_body<true>(L, dst_role, tol2, 2, kGramRows2, false, smem, L.tmat, true, nullptr, false, gram2);
+    for (int e = t; e < kGramRows2 * ow; e += kThreads) so[e] = 0.f;
+    // The product runs on the fp64 matrix cores (v_mfma_f64_16x16x4_f64): wave v owns rows 16v..16v+15 of the tile.
+    // A operand = x (fp32 in LDS, widened per use), B operand = tmat; lane: row / column index li, k index lk.
+    const int li = tx & 15, lk = tx >> 4;
+    double b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) b[u] = (4 * u + lk < w && li < w) ? tm[(4 * u + lk) * w + li] : 0.0;
+    __syncthreads();
+    const float* __restrict__ xa = sx + (16 * ty + li) * xs + lk;
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (4 * u < w) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(4 * u + lk < w ? (double)xa[4 * u] : 0.0, b[u], acc, 0, 0, 0);
+    if (li < w) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) so[(16 * ty + 4 * v + lk) * ow + li] = (float)acc[v];
+    }
+    __syncthreads();
+    if (flat_x) {
+        // contiguous result block: one 16-byte store per thread (rows past the end are cut off)
+        const int f = 4 * t;
+        if (f < n_valid) {
+            int row = (int)(((float)f + 0.5f) * inv_w);
+            int c = f - row * w;
+            if (c < 0) { --row; c += w; } else if (c >= w) { ++row; c -= w; }
+            const float* __restrict__ sr = so + row * ow + c;
+            *reinterpret_cast<PSGD_GLOBAL floatx4*>(as_global(X.ptr) + (int64_t)i0 * X.ld + f) = floatx4{sr[0], sr[1], sr[2], sr[3]};
         }
+    } else {
+        for (int i = ty; i < kGramRows2 && i0 + i < len; i += 4)
+            if (tx < w) X.ptr[(int64_t)(i0 + i) * X.ld + tx] = so[i * ow + tx];
+    }
+    if (do_gram) {
+        gram_tile_f64(so, ow, kGramRows2, w, gram2 + (int64_t)blockIdx.x * ntri);
+        const int n_wg = (len + kGramRows2 - 1) / kGramRows2;
+        if (last_to_arrive(&L.status[7], n_wg, &s_last))
+            chol_body<true>(L, role, tol2, 2, kGramRows2, false, smem, L.tmat, true, nullptr, false, gram2);
     } else if (do_pack) {
         write_packs(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
     }
 }
 
 // --------------------------------------------------------------------------------------------
-// The same product for blocks up to 96 wide that are not `small`, as a streaming pass: at these widths the kernel above
-// spends its time on latency, not bytes -- a workgroup stages a block of tmat per 32 output columns from L2 behind
-// barriers, and its 66 KB of LDS let two workgroups run per compute unit (config 4, 1.58 M rows of width 64: 0.70 ms
-// for 1.6 GB of traffic).  Here a workgroup keeps the part of tmat it needs in LDS for its whole life -- per
+// The same product for blocks up to 96 wide, as a streaming pass: with a block of tmat staged per 32 output columns from L2
+// behind barriers and 66 KB of LDS per workgroup it spent its time on latency, not bytes (224 matrices, 1.58 M rows of width
+// 64: 0.70 ms for 1.6 GB of traffic).  Here a workgroup keeps the part of tmat it needs in LDS for its whole life -- per
 // 16-column tile of the result only the rows above the diagonal block when tmat is triangular -- and walks over
 // many 64-row tiles of its layer; the rows of the next tile are requested before the MFMA phase of the current one.
 // --------------------------------------------------------------------------------------------
@@ -574,8 +517,8 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
 
 // --------------------------------------------------------------------------------------------
 // The same product for blocks wider than the streaming kernel's.  Their tmat (205 KB at width 160) fits neither registers nor
-// LDS; apply_kernel stages 32 columns of it at a time behind barriers on four waves per 64 rows, and with 128 tiles of 64
-// rows (8192 x 128) that chain of round trips was all of its 45 us.  Here sixteen waves share a tile: wave (row group, column
+// LDS; staged 32 columns at a time behind barriers on four waves per 64 rows, with 128 tiles of 64 rows (8192 x 128), that
+// chain of round trips was all of 45 us.  Here sixteen waves share a tile: wave (row group, column
 // group) walks every fourth 16-column tile of the result along the reduction index with the fragments of tmat loaded
 // straight from L2, four steps ahead.
 // --------------------------------------------------------------------------------------------
@@ -662,8 +605,9 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, int slot_rows, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
+    if (w_out > w_in || (small && (w_in > kCholRegWidth || w_out != w_in || src_role != dst_role || mode == APPLY_RITZ))) return hipErrorInvalidValue;
     dim3 grid(max_lenP / kGramRows2, n_ids), block(kThreads);
-    if (!small && w_in <= kApplyStreamMaxWidth && w_out <= w_in) {
+    if (!small && w_in <= kApplyStreamMaxWidth) {
         // a few rounds of workgroups over the whole launch, each walking several tiles of its layer
         // (config 4, width 64: 0.54 ms with one round of 512 workgroups, 0.43 with four, 0.42 with eight, 0.45 with 16)
         int per_layer = (8 * 512 + n_ids - 1) / n_ids;
@@ -682,7 +626,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                            mode, cp, gate, w_out, which);
         return hipGetLastError();
     }
-    if (!small && w_out <= w_in) {
+    if (!small) {
         const int wi16 = (w_in + 15) & ~15, wo16 = (w_out + 15) & ~15;
         const size_t lds = (size_t)kGramRows2 * (wi16 + 1 + (cp > wo16 ? cp : wo16) + 1) * sizeof(float);
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(apply_wide_kernel),
@@ -692,20 +636,19 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                            gate, w_in, w_out, which);
         return hipGetLastError();
     }
-    // w_in / w_out are upper bounds over the layers: sizes that grow with them cover every layer
-    size_t lds = apply_main_lds(w_in, w_out, cp);
-    if (small && (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY)) {
-        if (chol_lds_bytes_upto(w_out) > lds) lds = chol_lds_bytes_upto(w_out);          // second-pass factorisation
-        const int wl = w_in < kCholRegWidth ? w_in : kCholRegWidth;             // per-workgroup factorisation
-        lds += (size_t)wl * wl * sizeof(double) + chol_lds_bytes_upto(wl);
+    // (w_in: upper bound over the layers, every size here grows with it)
+    size_t lds = apply_main_lds(w_in, cp);
+    if (mode == APPLY_PASS1 || mode == APPLY_PASS1_ONLY) {
+        if (chol_lds_bytes_upto(w_in) > lds) lds = chol_lds_bytes_upto(w_in);           // second-pass factorisation
+        lds += (size_t)w_in * w_in * sizeof(double) + chol_lds_bytes_upto(w_in);        // per-workgroup factorisation
     }
-    auto kfn = small ? apply_kernel<true> : apply_kernel<false>;
+    auto kfn = gate >= 0 ? apply_kernel<true> : apply_kernel<false>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, src_role, dst_role, mode, cp, gate, a2gate, tol2, which, slot_rows);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, src_role, mode, cp, gate, a2gate, tol2, which, slot_rows);
     return hipGetLastError();
 }
 
@@ -1073,9 +1016,9 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             if (rho < 0.999) k_next = (rho <= 1e-12) ? 2 : (int)ceil(log(1e-5) / log(rho)) + 1;
         }
         L.status[4] = max(2, min(255, k_next));
-        L.status[25] = s_ke;
+        L.status[9] = s_ke;
         L.status[5] = sweeps;
-        L.status[24] = min(L.status[24] + 1, 1 << 20);
+        L.status[8] = min(L.status[8] + 1, 1 << 20);
     }
 }
 

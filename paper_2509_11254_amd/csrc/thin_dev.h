@@ -245,7 +245,7 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
-                if (scale) L.status[26] = spread.asks(L.planes, min_piv) ? 1 : 0;
+                if (scale) L.status[10] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
@@ -482,7 +482,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
-                if (scale) L.status[26] = spread.asks(L.planes, min_piv) ? 1 : 0;
+                if (scale) L.status[10] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
