@@ -46,9 +46,9 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
 hipError_t launch_pack(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int role_a, int role_b,
                        int cp, int which, hipStream_t st);
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows, int gate, int a2gate, int local_ok, hipStream_t st);
-hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
-                           int flagged, hipStream_t st);
+                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, hipStream_t st);
+hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows_n, int slot_rows_t,
+                           int gate, int flagged, hipStream_t st);
 int finish_rows(int w);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
@@ -656,17 +656,20 @@ struct Launcher {
         gram_rows_n = gram32 ? 32 : split_n ? finish_rows(ww) : kGramRows1;
         gram_rows_t = split_t ? finish_rows(ww) : kGramRows1;
         if (chol_gate >= -1) {
-            // (the many 32-row slots are added up before at any width)
-            if (wide || (gram32 && !small)) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, chol_gate, 0, st));
+            // (the many 32-row slots are added up before at any width; the launches for an orthonormal Y that only a few
+            // layers ask for are kept few: there the factorisation adds the slots up itself)
+            // (up to 2048 rows: 70 matrices of 400 x 400 to 1072 x 400 bf16 r = 37 3.45 -> 3.35 ms, 4096 x 4096 r = 112 4.47 -> 4.66)
+            const bool few = wide && chol_gate >= 0 && (chol_gate & kGateIfAsked) && std::max(norm.shortest_max, tr.shortest_max) <= 2048;
+            if (wide && !few) note(launch_gram_sum(layers, ids_all, n_all, ww, out_role, gram_rows_n, gram_rows_t, chol_gate, 0, st));
+            else if (gram32 && !small) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, gram_rows_t, chol_gate, 0, st));
             if (wide) {
-                note(launch_gram_sum(layers, ids_tr, n_tr, ww, out_role, gram_rows_t, chol_gate, 0, st));
-                note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, kOneSlot, chol_gate, a2gate, 0, st));
+                note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, few ? gram_rows_n : kOneSlot, few ? gram_rows_t : kOneSlot, chol_gate, a2gate, 0, st));
             } else {
                 // (not where the apply kernel factorises every layer for itself)
                 const bool local_n = small && (p_like ? norm.longest : norm.shortest_max) <= kLocalCholMaxRows;
                 const bool local_t = small && (p_like ? tr.longest : tr.shortest_max) <= kLocalCholMaxRows;
-                if (!split_n && !local_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
-                if (!split_t && !local_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
+                if (!split_n && !local_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, 0, chol_gate, a2gate, small ? 1 : 0, st));
+                if (!split_t && !local_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, 0, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
             }
         }
     }
@@ -689,7 +692,7 @@ struct Launcher {
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, g, -2, 0, st));
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, g, -2, 0, st));
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
         }
     }
@@ -701,12 +704,12 @@ struct Launcher {
         const bool wide = sums_first(w, max_len());
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZP, cp, -1, 1, st));
-        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, -1, 1, st));
-        note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, -1, -2, 0, st));
+        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, kGramRows1, -1, 1, st));
+        note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -2, 0, st));
         for (int role : {ROLE_ZP, ROLE_ZQ})
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, st));
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZQ, cp, -1, 1, st));
-        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, -1, 1, st));     // (as Jacobi expects them)
+        if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, kGramRows1, -1, 1, st));     // (as Jacobi expects them)
     }
     // the same CholeskyQR2 on a thin[out_role] that the caller supplied: its Gram slots come from a pass of their own
     void orth_given(int out_role, int w, double tol2, int cp) {
@@ -714,10 +717,10 @@ struct Launcher {
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, 0, st));
         const bool wide = sums_first(w, max_len());
-        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, -1, 0, st));
-        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
+        if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, kGramRows1, -1, 0, st));
+        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
-        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, -1, -2, 0, st));
+        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
     void residual(int nb, bool form = false) {
@@ -806,10 +809,7 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     L.gate = -1;
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)
     const bool wide = wz > kWideWidth;
-    if (wide) {
-        L.note(launch_gram_sum(L.layers, L.ids_norm, L.n_norm, wz, ROLE_ZQ, L.gram_rows_n, -1, 0, L.st));
-        L.note(launch_gram_sum(L.layers, L.ids_tr, L.n_tr, wz, ROLE_ZQ, L.gram_rows_t, -1, 0, L.st));
-    }
+    if (wide) L.note(launch_gram_sum(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, L.gram_rows_n, L.gram_rows_t, -1, 0, L.st));
     L.second_pass_deferred(wz, cpz, tol2);
     L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,

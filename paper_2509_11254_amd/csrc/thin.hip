@@ -87,29 +87,31 @@ hipError_t launch_max_iterations(const LayerDev* layers, const int* ids, int n_i
 template <int NT>
 __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ layers,
                                                   const int* __restrict__ ids, int role, double tol2,
-                                                  int pass, int slot_rows, int gate, int a2gate,
+                                                  int pass, int slot_rows_n, int slot_rows_t, int gate, int a2gate,
                                                   int local_ok) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
     if (pass == 2 && L.status[1] == 0) return;
     if (pass == 1 && local_chol(L, role, local_ok)) return;       // the apply kernel factorises for itself
     extern __shared__ __align__(16) unsigned char smem[];
-    chol_body(L, role, tol2, pass, slot_rows, allow2_of(L, a2gate), smem, L.tmat, true, nullptr,
+    chol_body(L, role, tol2, pass, L.transposed ? slot_rows_t : slot_rows_n, allow2_of(L, a2gate), smem, L.tmat, true, nullptr,
               pass == 1 && scales_next(L, role, gate));
 }
 
 // --------------------------------------------------------------------------------------------
-// gram sum: the partial Gram matrices of thin[role] (one per slot_rows rows) added up, fixed order, the sum left in the first
+// gram sum: the partial Gram matrices of thin[role] (one per slot_rows_n rows in the layers stored with rows >= cols, per
+// slot_rows_t in the others) added up, fixed order, the sum left in the first
 // slot.  A workgroup owns 64 entries and its four waves every fourth slot each, 16 loads in flight per thread: the sum of
 // 64 slots of width 160 (6.6 MB) is a microsecond-scale pass over the chip instead of the factorisation's one workgroup
 // reading all of it.
 // --------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void gram_sum_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
-                                                            int role, int slot_rows, int gate, int flagged) {
+                                                            int role, int slot_rows_n, int slot_rows_t, int gate, int flagged) {
     __shared__ double part[4][64];
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;       // (the slots of a layer whose iteration is over hold what its Ritz step needs)
     if (flagged && L.status[1] == 0) return;
+    const int slot_rows = L.transposed ? slot_rows_t : slot_rows_n;
     const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
     const int w = L.thin[role].width;
     const int ntri = (w * (w + 1)) / 2;
@@ -134,18 +136,18 @@ __global__ __launch_bounds__(kThreads) void gram_sum_kernel(const LayerDev* __re
 
 // w: the widest of the layers' blocks; gate: iteration gate of the refresh (-1: none); flagged: only the layers whose
 // second-pass flag is set
-hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int gate,
-                           int flagged, hipStream_t st) {
+hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows_n, int slot_rows_t,
+                           int gate, int flagged, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const int ntri = (w * (w + 1)) / 2;
-    hipLaunchKernelGGL(gram_sum_kernel, dim3((ntri + 63) / 64, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows, gate, flagged);
+    hipLaunchKernelGGL(gram_sum_kernel, dim3((ntri + 63) / 64, n_ids), dim3(kThreads), 0, st, layers, ids, role, slot_rows_n, slot_rows_t, gate, flagged);
     return hipGetLastError();
 }
 
 // Widths above 32 get 512 threads: the panels and trailing updates of the blocked factorisation are dealt to the waves
 // (1024 threads halve the registers a thread may hold, and measured slower).
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows, int gate, int a2gate, int local_ok, hipStream_t st) {
+                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const bool wide = w > 32;
     dim3 grid(1, n_ids), block(wide ? 512 : kThreads);
@@ -156,7 +158,7 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, tol2, pass, slot_rows, gate, a2gate,
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, tol2, pass, slot_rows_n, slot_rows_t, gate, a2gate,
                        local_ok);
     return hipGetLastError();
 }

@@ -115,15 +115,17 @@ template <int CTRL> __device__ __forceinline__ int dpp_or(int other, int v) {
 //     such point; one with the strong directions last does.
 //   - Rounding along the leading vectors, 2^-17 or 2^-24 of sigma_1 (two or three operand planes), becomes
 //     (sigma_1 / sigma_j)^2 of that in X's column j: above its own norm where sigma_j / sigma_1 < 2^-8 or 2^-12.
-// So Y is orthonormalised in an iteration whose Z came with an R_jj more than 4 times an earlier one (or nearly: powers of
-// two), a pivot below 1e-2, or a smallest R_jj below 2^-11 (two planes 2^-7.5) of the largest column norm.
+// So Y is orthonormalised in an iteration whose Z came with a column norm ||x_j|| more than 16 times an earlier R_ii (or
+// nearly: powers of two), a pivot below 1e-2, or a smallest R_jj below 2^-11 (two planes 2^-7.5) of the largest column norm.
 // Model on 400 x 300 matrices, blocks of 16 and 40, 3 to 16 iterations, geometric spectra and outliers over a flat rest
 // with ratios of 1e2 to 3e4 in the block, sorted, random, permuted and ascending starts, against Y always orthonormal: no more
-// columns lost, sin(theta) within 7 times (at 5e-7; two planes 1.2 times).  Never orthonormal: up to 4 columns with
-// sin(theta) = 1 from a ratio of 5000 on.  The order at 32 in place of 4, or no limit on the pivots: 1e-4 in place of 4e-7.
+// columns lost, sin(theta) within 7 times (at 3e-7; two planes 1.1 times).  Never orthonormal: up to 4 columns with
+// sin(theta) = 1 from a ratio of 5000 on; no limit on the pivots: 1e-4 in place of 4e-7.  R_jj in place of ||x_j|| misses
+// columns that have just been passed on to an earlier one (5e-5 in place of 6e-7) unless the limit is 4, and then refreshes of
+// an error-feedback run ask once each on average, where now one in eight does.
 // In powers of two of squared norms; dependent columns do not count.
 struct Spread {
-    static constexpr int kNone = 1 << 20, kDisorder = 4;
+    static constexpr int kNone = 1 << 20, kDisorder = 8;
     static constexpr double kPivot = 1e-2;
     int top = -kNone, low = kNone;      // largest column norm, smallest R_jj so far
     int disorder = 0;
@@ -132,23 +134,24 @@ struct Spread {
     }
     // one column (norm: ||x_j||^2, rjj: R_jj^2)
     __device__ void add(int norm, int rjj) {
-        disorder |= rjj - low > kDisorder;
+        disorder |= norm - low > kDisorder;
         low = min(low, rjj);
         top = max(top, norm);
     }
     // the 16 columns of a block, one per lane of each row of 16 lanes (every lane of the wavefront ends up with the result)
     __device__ __forceinline__ void add_block(int norm, int rjj, bool counts) {
-        int e = counts ? rjj : kNone, n = counts ? norm : -kNone;
+        const int e = counts ? rjj : kNone;
+        int n = counts ? norm : -kNone;
         int before = dpp_or<0x111>(kNone, e);                                     // smallest of the lanes before
         before = min(before, dpp_or<0x111>(kNone, before));
         before = min(before, dpp_or<0x112>(kNone, before));
         before = min(before, dpp_or<0x114>(kNone, before));
         before = min(before, dpp_or<0x118>(kNone, before));
+        disorder |= __ballot(n - min(before, low) > kDisorder) != 0;
         n = max(n, dpp_or<0x111>(-kNone, n));
         n = max(n, dpp_or<0x112>(-kNone, n));
         n = max(n, dpp_or<0x114>(-kNone, n));
         n = max(n, dpp_or<0x118>(-kNone, n));
-        disorder |= __ballot(counts && e - min(before, low) > kDisorder) != 0;
         low = min(low, dpp_or<0x15f>(kNone, min(before, e)));                     // (lane 15 of the row)
         top = max(top, dpp_or<0x15f>(-kNone, n));
     }
