@@ -94,8 +94,9 @@ typedef struct {
                                    within 1e-5 ||M||^2 of the optimum of Eq. (6) by the same Ritz values, at
                                    least 2, at most the maximum                                         */
     int32_t refresh_oversample; /* extra block columns beyond r; negative = default max(8, r/4); the
-                                   block width r + oversample is rounded up to a multiple of 8 and
-                                   capped at n                                                       */
+                                   block width r + oversample (r: the largest of the context) is rounded
+                                   up to a multiple of 8 and capped at the smallest n of the context, or,
+                                   where that is below the largest r, at 192 and at each layer's own n   */
     int32_t refresh_warm_start; /* 1: psgd_compress_refresh starts from span(Q_{t-1}) plus random
                                    columns; 0: random start.  Default 1.                             */
     uint32_t seed;              /* seed of the counter-based generator for the random start      */

@@ -298,7 +298,7 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // What bounds it is the chain of 16 steps inside each diagonal block (7200 cycles of the 10000 a block takes): one wave updates
 // and factorises block J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.
 // One workgroup on a 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion
-// (packed triangle, five barriers per block, spilling as a function call); 55 us now, 80 x 80 58 -> 27 us.
+// (packed triangle, five barriers per block, spilling as a function call); 74 us now (128 x 128: 59), 80 x 80 58 -> 32 us.
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
                                     unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread) {

@@ -41,7 +41,8 @@ def test_ssp_step(r, rows, cols, dependent):
 
 
 # nearly dependent columns: the first CholeskyQR pass asks for the second; one tile of 64 rows, several, a ragged one, alone and
-# in a batch with layers that do not need it
+# in a batch with layers that do not need it (that the second pass leaves a right result; that it is made, and by whom, is
+# test_second_pass_is_made's)
 @pytest.mark.parametrize("r", [2, 8, 16, 24, 64])
 # (r at most half of the short side of the first layer: the close pair's pivot, 1e-8 (1 - r / n), stays above 1e-10, where
 # a column counts as dependent)
