@@ -31,11 +31,11 @@ hipError_t launch_row_prod(int nb, int planes, const LayerDev* layers, const int
                            hipStream_t st);
 bool row_prod_supported(int nb, int planes);
 hipError_t launch_outer(int nb, int planes, bool decomp, bool form, bool kept, const LayerDev* layers, const int* ids,
-                        int n_ids, int max_tiles, void* const* outs, int out_bf16, hipStream_t st);
+                        int n_ids, int max_tiles, int rpw, void* const* outs, int out_bf16, hipStream_t st);
 hipError_t launch_max_iterations(const LayerDev* layers, const int* ids, int n_ids, int mx, int* out, hipStream_t st);
-hipError_t launch_msgd(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
+hipError_t launch_msgd(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles, int rpw,
                        float* const* moms, float* const* xs, float mu, float eta, bool kept, hipStream_t st);
-hipError_t launch_adam(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
+hipError_t launch_adam(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles, int rpw,
                        float* const* m1s, float* const* m2s, float* const* xs, const float* coef, bool kept,
                        hipStream_t st);
 hipError_t launch_finish(bool colmode, int kind, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
@@ -133,7 +133,7 @@ struct psgd_ctx {
     void* outs_ws = nullptr;     // workspace that holds the current table of decompress outputs
     void* msgd_ws = nullptr;     // ... and of the momentum and weight buffers of psgd_decompress_msgd / _adam
     void* m2_ws = nullptr;       // ... and of the second-moment buffers of psgd_decompress_adam
-    void* factors_ws = nullptr;  // workspace whose row-major operand copies are the P~, Q of the last compress call
+    void* factors_ws = nullptr;  // workspace whose outer-product operand copies are the P~, Q of the last compress call
     bool factors_kept = false;   // ... a call with a deferred residual: in the layers that defer they are the kept copies
     bool tables_valid = false;
     std::vector<const void*> hG;                       // the caller's current table
@@ -558,7 +558,11 @@ struct Launcher {
     int n_all, n_norm, n_tr;
     // geometry maxima over the layers addressed by this launcher
     int max_rows = 0, max_cols = 0, max_rowsP = 0, max_colsP = 0;
-    int tiles_outer = 0;
+    // 128 x 128 tiles of an outer product: of all layers, and workgroups of the layer with the most of them at 4, 8, 16 and 32
+    // blocks of 32 rows each
+    int64_t tiles_all = 0;
+    static constexpr int kOuterGroups = 4;
+    int tiles_rg[kOuterGroups] = {};
     struct Geometry {       // of the layers of one orientation
         int blocks[2] = {0, 0};                     // 128-row blocks of a row-mode / column-mode result
         int tiles[SPLIT_KINDS][2] = {};             // workgroups per layer of a product
@@ -574,8 +578,8 @@ struct Launcher {
     bool lazy_form = false;   // the forming pass of the row-major layers also applies their pending residual
     bool lazy_share = false;  // ... and the transposed operand copies of Q_{t-1} are what the step before left: they hold
                               // the kept Q, which the pass then need not read
-    bool kept_packs = false;  // compress step with a deferred residual: the row-major operand copies of its P~ and Q go
-                              // to the kept copies (fragment order) in the layers that have them
+    bool kept_packs = false;  // compress step with a deferred residual: the outer-product operand copies of its P~ and Q
+                              // are the kept ones in the layers that have them
     bool use_xtab = true;     // PSGD_XTAB=0 (environment, measurement knob): plain layer-by-layer launch order
     bool use_xtab_c = true;   // PSGD_XTAB_C=0 (likewise): the same for the column-mode product alone
 
@@ -597,9 +601,9 @@ struct Launcher {
     int max_len() const { return max_rows > max_cols ? max_rows : max_cols; }
     int max_lenP() const { return max_rowsP > max_colsP ? max_rowsP : max_colsP; }
 
-    // operand copies of caller-supplied thin matrices: the transposed ones for a product, the row-major ones for an
+    // operand copies of caller-supplied thin matrices: the transposed ones for a product, the others for an
     // outer-product kernel
-    enum { PACK_ROWMAJOR = 1, PACK_TRANSPOSED = 2 };
+    enum { PACK_OUTER = 1, PACK_TRANSPOSED = 2 };
     void pack(int role, int cp, int which, int role_b = -1) {
         note(launch_pack(layers, ids_all, n_all, max_lenP(), role, role_b, cp, which, st));
     }
@@ -687,8 +691,8 @@ struct Launcher {
         // narrow blocks everywhere: the apply kernel factorises per workgroup and hands over to the second
         // factorisation itself; otherwise the second factorisation is a launch of its own
         const bool small = w <= 16;
-        // (inside the iteration only products read the result: no row-major operand copies)
-        const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_ROWMAJOR | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
+        // (inside the iteration only products read the result: no outer-product copies)
+        const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_OUTER | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
@@ -723,9 +727,24 @@ struct Launcher {
         if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
+    // 32-row blocks per workgroup of the outer-product kernels and the grid that goes with them.  Four blocks, one per wave, and the
+    // column operand staged for one tile, up to nb * planes = 6.  Wider operands leave a compute unit room for two such
+    // workgroups (nb * planes = 8) or one, which stages, multiplies and stores one after the other: there 8 or 16 waves
+    // share one staged operand and walk down 8 to 32 blocks, as many as still give every compute unit a workgroup
+    // (8192 x 8192 r = 128, four blocks and 32: three planes residual 194 -> 133 us, decompress 153 -> 99, momentum SGD 266 -> 223;
+    // two planes 128 -> 120, 72 -> 56 into bf16; 4096 x 4096 three planes 49 -> 38.  2048 x 2048, 64 tiles too few: 12.4 and 15.1.
+    // nb * planes = 6, 7B-shaped block: residual 311 against 343, Adam 910 and 935)
+    int outer_log_groups(int nb) const {
+        if (nb * ctx->planes < kOuterManyWaves) return 0;
+        int i = kOuterGroups - 1;
+        while (i > 0 && (tiles_all >> i) < 256) --i;
+        return i;
+    }
+    int outer_rows(int nb) const { return 4 << outer_log_groups(nb); }
+    int outer_tiles(int nb) const { return tiles_rg[outer_log_groups(nb)]; }
     void residual(int nb, bool form = false) {
         const int k = prof_begin(PSGD_PROF_RESIDUAL);
-        note(launch_outer(nb, ctx->planes, false, form, false, layers, ids_all, n_all, tiles_outer, nullptr, 0, st));
+        note(launch_outer(nb, ctx->planes, false, form, false, layers, ids_all, n_all, outer_tiles(nb), outer_rows(nb), nullptr, 0, st));
         prof_end(k);
     }
     // deferred residual: the layers that defer keep their operands; the others (stored with rows < cols, at
@@ -734,14 +753,14 @@ struct Launcher {
     void residual_deferred(int nb) {
         if (ctx->lazy_tr) return;
         const int k = prof_begin(PSGD_PROF_RESIDUAL);
-        note(launch_outer(nb, ctx->planes, false, false, false, layers, ids_tr, n_tr, tiles_outer, nullptr, 0, st));
+        note(launch_outer(nb, ctx->planes, false, false, false, layers, ids_tr, n_tr, outer_tiles(nb), outer_rows(nb), nullptr, 0, st));
         prof_end(k);
     }
     // E <- M - (kept P~)(kept Q)^T for the layers that defer: what the deferred residual still owes
     void residual_owed(int nb) {
         const int k = prof_begin(PSGD_PROF_RESIDUAL);
-        if (ctx->lazy_tr) note(launch_outer(nb, ctx->planes, false, false, true, layers, ids_all, n_all, tiles_outer, nullptr, 0, st));
-        else note(launch_outer(nb, ctx->planes, false, false, true, layers, ids_norm, n_norm, tiles_outer, nullptr, 0, st));
+        if (ctx->lazy_tr) note(launch_outer(nb, ctx->planes, false, false, true, layers, ids_all, n_all, outer_tiles(nb), outer_rows(nb), nullptr, 0, st));
+        else note(launch_outer(nb, ctx->planes, false, false, true, layers, ids_norm, n_norm, outer_tiles(nb), outer_rows(nb), nullptr, 0, st));
         prof_end(k);
     }
 };
@@ -751,7 +770,8 @@ void geometry(const Plan& p, Launcher& L) {
     mx(L.max_rows, (int)p.d.rows); mx(L.max_cols, (int)p.d.cols);
     mx(L.max_rowsP, p.rowsP); mx(L.max_colsP, p.colsP);
     const int rb = (int)((p.d.rows + 127) / 128), cb = (int)((p.d.cols + 127) / 128);
-    mx(L.tiles_outer, rb * cb);
+    L.tiles_all += (int64_t)rb * cb;
+    for (int i = 0; i < Launcher::kOuterGroups; ++i) mx(L.tiles_rg[i], ((rb + (1 << i) - 1) >> i) * cb);
     Launcher::Geometry& g = p.transposed ? L.tr : L.norm;
     mx(g.longest, p.m); mx(g.shortest_max, p.n);
     mx(g.blocks[0], rb); mx(g.blocks[1], cb);
@@ -1323,16 +1343,16 @@ int psgd_decompress(psgd_ctx* ctx, void* workspace, void* stream, const float* c
     ctx->outs_ws = workspace;
     Launcher L = batch_launcher(ctx, workspace, st);
     const int cp = ctx->cpc, nb = cp / 32;
-    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_ROWMAJOR, ROLE_Q);
+    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_OUTER, ROLE_Q);
     // (factors of a compress call with a deferred residual: the layers that defer hold them as their kept copies)
     const bool kept = packed && ctx->factors_kept;
     const int n_kept = !kept ? 0 : ctx->lazy_tr ? L.n_all : L.n_norm;
     const int* ids_kept = ctx->lazy_tr ? L.ids_all : L.ids_norm;
     void* const* outs = reinterpret_cast<void* const*>(ws + ctx->off_outs);
     const int obf = out_dtype == PSGD_BF16 ? 1 : 0;
-    if (n_kept > 0) L.note(launch_outer(nb, ctx->planes, true, false, true, L.layers, ids_kept, n_kept, L.tiles_outer, outs, obf, st));
-    if (!kept) L.note(launch_outer(nb, ctx->planes, true, false, false, L.layers, L.ids_all, L.n_all, L.tiles_outer, outs, obf, st));
-    else if (!ctx->lazy_tr) L.note(launch_outer(nb, ctx->planes, true, false, false, L.layers, L.ids_tr, L.n_tr, L.tiles_outer, outs, obf, st));
+    if (n_kept > 0) L.note(launch_outer(nb, ctx->planes, true, false, true, L.layers, ids_kept, n_kept, L.outer_tiles(nb), L.outer_rows(nb), outs, obf, st));
+    if (!kept) L.note(launch_outer(nb, ctx->planes, true, false, false, L.layers, L.ids_all, L.n_all, L.outer_tiles(nb), L.outer_rows(nb), outs, obf, st));
+    else if (!ctx->lazy_tr) L.note(launch_outer(nb, ctx->planes, true, false, false, L.layers, L.ids_tr, L.n_tr, L.outer_tiles(nb), L.outer_rows(nb), outs, obf, st));
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;
 }
@@ -1359,15 +1379,15 @@ int psgd_decompress_msgd(psgd_ctx* ctx, void* workspace, void* stream, const flo
     ctx->msgd_ws = workspace;
     Launcher L = batch_launcher(ctx, workspace, st);
     const int cp = ctx->cpc, nb = cp / 32;
-    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_ROWMAJOR, ROLE_Q);
+    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_OUTER, ROLE_Q);
     const bool kept = packed && ctx->factors_kept;      // (see psgd_decompress)
     const int n_kept = !kept ? 0 : ctx->lazy_tr ? L.n_all : L.n_norm;
     const int* ids_kept = ctx->lazy_tr ? L.ids_all : L.ids_norm;
     float* const* dm = reinterpret_cast<float* const*>(ws + ctx->off_moms);
     float* const* dx = reinterpret_cast<float* const*>(ws + ctx->off_xs);
-    if (n_kept > 0) L.note(launch_msgd(nb, ctx->planes, L.layers, ids_kept, n_kept, L.tiles_outer, dm, dx, mu, eta, true, st));
-    if (!kept) L.note(launch_msgd(nb, ctx->planes, L.layers, L.ids_all, L.n_all, L.tiles_outer, dm, dx, mu, eta, false, st));
-    else if (!ctx->lazy_tr) L.note(launch_msgd(nb, ctx->planes, L.layers, L.ids_tr, L.n_tr, L.tiles_outer, dm, dx, mu, eta, false, st));
+    if (n_kept > 0) L.note(launch_msgd(nb, ctx->planes, L.layers, ids_kept, n_kept, L.outer_tiles(nb), L.outer_rows(nb), dm, dx, mu, eta, true, st));
+    if (!kept) L.note(launch_msgd(nb, ctx->planes, L.layers, L.ids_all, L.n_all, L.outer_tiles(nb), L.outer_rows(nb), dm, dx, mu, eta, false, st));
+    else if (!ctx->lazy_tr) L.note(launch_msgd(nb, ctx->planes, L.layers, L.ids_tr, L.n_tr, L.outer_tiles(nb), L.outer_rows(nb), dm, dx, mu, eta, false, st));
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;
 }
@@ -1408,16 +1428,16 @@ int psgd_decompress_adam(psgd_ctx* ctx, void* workspace, void* stream, const flo
                            (float)((double)eta * (double)weight_decay)};
     Launcher L = batch_launcher(ctx, workspace, st);
     const int cp = ctx->cpc, nb = cp / 32;
-    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_ROWMAJOR, ROLE_Q);
+    if (!packed) L.pack(ROLE_P, cp, Launcher::PACK_OUTER, ROLE_Q);
     const bool kept = packed && ctx->factors_kept;      // (see psgd_decompress)
     const int n_kept = !kept ? 0 : ctx->lazy_tr ? L.n_all : L.n_norm;
     const int* ids_kept = ctx->lazy_tr ? L.ids_all : L.ids_norm;
     float* const* d1 = reinterpret_cast<float* const*>(ws + ctx->off_moms);
     float* const* d2 = reinterpret_cast<float* const*>(ws + ctx->off_m2s);
     float* const* dx = reinterpret_cast<float* const*>(ws + ctx->off_xs);
-    if (n_kept > 0) L.note(launch_adam(nb, ctx->planes, L.layers, ids_kept, n_kept, L.tiles_outer, d1, d2, dx, coef, true, st));
-    if (!kept) L.note(launch_adam(nb, ctx->planes, L.layers, L.ids_all, L.n_all, L.tiles_outer, d1, d2, dx, coef, false, st));
-    else if (!ctx->lazy_tr) L.note(launch_adam(nb, ctx->planes, L.layers, L.ids_tr, L.n_tr, L.tiles_outer, d1, d2, dx, coef, false, st));
+    if (n_kept > 0) L.note(launch_adam(nb, ctx->planes, L.layers, ids_kept, n_kept, L.outer_tiles(nb), L.outer_rows(nb), d1, d2, dx, coef, true, st));
+    if (!kept) L.note(launch_adam(nb, ctx->planes, L.layers, L.ids_all, L.n_all, L.outer_tiles(nb), L.outer_rows(nb), d1, d2, dx, coef, false, st));
+    else if (!ctx->lazy_tr) L.note(launch_adam(nb, ctx->planes, L.layers, L.ids_tr, L.n_tr, L.outer_tiles(nb), L.outer_rows(nb), d1, d2, dx, coef, false, st));
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;
 }

@@ -58,6 +58,9 @@ constexpr int kWideWidth = 32;
 constexpr int kSumSlots = 12;
 constexpr int kCholRegWidth = 16;      // widths up to this are factorised by one wavefront in registers
 
+// blocks of 32 columns times operand planes from which on the workgroups of the outer-product kernels have more than four waves
+constexpr int kOuterManyWaves = 8;
+
 // Narrow layers (width <= 16) whose thin matrix has at most 64 partial Gram matrices: every workgroup of the apply kernel
 // repeats the factorisation for itself.  Rows at 128 and at 32 per partial matrix:
 constexpr int kLocalCholMaxSlots = 64;
@@ -72,7 +75,7 @@ enum Epilogue { EPI_NONE = 0, EPI_GRAM = 1, EPI_PACK = 2, EPI_KIND_MASK = 3,
                 EPI_ITERATE = 3,     // Y = M^T Z of the subspace iteration: EPI_GRAM in a layer's last iteration and where Y
                                      // is orthonormalised, else only the transposed operand copies (see resolve_epilogue)
                 EPI_KEEP_E = 16,     // flag: a FORM pass uses M but leaves E in place (M is formed again later)
-                EPI_KEPT = 32 };     // flag: EPI_PACK writes the kept copies (fragment order) in place of the row-major ones
+                EPI_KEPT = 32 };     // flag: EPI_PACK writes the kept copies in place of the working ones (PackRef::n)
 enum Role { ROLE_P = 0, ROLE_Q = 1, ROLE_ZP = 2, ROLE_ZQ = 3, ROLE_COUNT = 4 };
 
 struct ThinRef {
@@ -84,7 +87,9 @@ struct ThinRef {
 // Split-bf16 operand copies of one thin matrix X (len x width), zero padded to lenP x cp.
 // X is written as a sum of `planes` bf16 numbers, plane 0 the rounded value and each further plane
 // the rounded remainder: two planes carry 16 mantissa bits (|error| <= 2^-17 |x|), three carry 24.
-//   n[k] : [lenP][cp]   row-major      (A/B operand of the rank-r outer product)
+//   n[k] : the A and B operand of the rank-r outer products (reduction over cp), in fragment order (frag_piece).  (Row-major, a
+//          wavefront's fragment was 32 segments of 32 bytes: residual of a 7B-shaped block r = 64 309 -> 278 us, of a 1B-shaped
+//          one r = 32 in fp32 76 -> 66.)
 //   t[k] : the B operand of the tall-skinny products (reduction over len) in the register layout of
 //          v_mfma_f32_32x32x16_bf16: [lenP / 16][cp / 32][64 lanes][8], lane li + 32 lg of block (k16, nb) holding
 //          X[16 k16 + 8 lg .. + 7][32 nb + li].  One MFMA B fragment of a wavefront is 1 KB of consecutive memory,
@@ -166,6 +171,7 @@ __device__ inline void divmod_small(int v, int d, int& q, int& r) {
         case 6: q = v / 6; break;
         case 4: q = v / 4; break;
         case 8: q = v / 8; break;
+        case 10: q = v / 10; break;
         case 12: q = v / 12; break;
         case 16: q = v / 16; break;
         case 20: q = v / 20; break;
@@ -176,10 +182,10 @@ __device__ inline void divmod_small(int v, int d, int& q, int& r) {
 }
 
 // Operand copies of `nrows` finished rows held as an fp32 LDS tile [nrows][tw] (columns >= cp unused,
-// nrows and row0 multiples of 16); global rows row0 .. row0 + nrows - 1.  All threads of the workgroup take part.
-// which: 1 = the row-major copies only, 2 = the transposed ones only, 3 = both.
-// kept: the layer's lzf[side] where the result is a factor of a compress step whose residual is deferred: the pieces of
-// the row-major copies then go there instead, in fragment order (frag_piece), for the layers that have such copies.
+// nrows and row0 multiples of 32); global rows row0 .. row0 + nrows - 1.  All threads of the workgroup take part.
+// which: 1 = the outer-product copies (n) only, 2 = the transposed ones (t) only, 3 = both.
+// kept: the layer's lzf[side] where the result is a factor of a compress step whose residual is deferred: the outer-product
+// copies then go there instead, for the layers that have such copies.
 // PLT: the plane count as a compile-time constant where the caller has it (0: from `planes`, all kMaxPlanes are formed)
 // NT: threads of the workgroup
 template <int PLT = 0, int NT = kThreads>
@@ -197,17 +203,10 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
         dt[k] = k < planes ? as_global(K.t[k]) : nullptr;
     }
     for (int v = t; (which & 1) && v < nrows * (cp / 8); v += NT) {
-        int row, g8;
-        if (to_kept) {
-            // along the destination: piece v of the tile's run of whole fragments (row0, nrows: multiples of 32)
-            int blk, ks;
-            divmod_small(v >> 6, cp >> 4, blk, ks);
-            row = 32 * blk + (v & 31);
-            g8 = 2 * ks + ((v >> 5) & 1);
-        } else {
-            divmod_small(v, cp / 8, row, g8);
-        }
-        const int c0 = 8 * g8;
+        // along the destination: piece v of the tile's run of whole fragments (row0, nrows: multiples of 32)
+        int blk, ks;
+        divmod_small(v >> 6, cp >> 4, blk, ks);
+        const int row = 32 * blk + (v & 31), c0 = 16 * ks + 8 * ((v >> 5) & 1);
         bf16x8 o[NPL];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -216,7 +215,7 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 #pragma unroll
             for (int k = 0; k < NPL; ++k) o[k][u] = q[k];
         }
-        const int64_t off = to_kept ? frag_piece(row0 + row, g8, cp) * 8 : (int64_t)(row0 + row) * cp + c0;
+        const int64_t off = frag_piece(row0, 0, cp) * 8 + 8 * v;
 #pragma unroll
         for (int k = 0; k < NPL; ++k)
             if (k < planes) *reinterpret_cast<PSGD_GLOBAL bf16x8*>(dn[k] + off) = o[k];
@@ -286,7 +285,7 @@ __device__ inline bool gate_open(const LayerDev& L, int gate) {
 }
 
 // What a product of the launch does with its result for this layer.  `copies`: the operand copies EPI_PACK leaves (1 =
-// row-major, 2 = transposed, 3 = both; 2: nothing else of the result is read, its rows are not stored either).
+// outer-product, 2 = transposed, 3 = both; 2: nothing else of the result is read, its rows are not stored either).
 __device__ inline int resolve_epilogue(const LayerDev& L, int epi_flags, int gate, int& copies) {
     const int epi = epi_flags & EPI_KIND_MASK;
     copies = 3;

@@ -9,9 +9,9 @@
 namespace psgd {
 
 // --------------------------------------------------------------------------------------------
-// pack: thin fp32 (len x width, ld) -> split-bf16 operand copies, row-major and transposed.
+// pack: thin fp32 (len x width, ld) -> split-bf16 operand copies (PackRef).
 // --------------------------------------------------------------------------------------------
-// grid.z walks the roles to pack (role_a, then role_b when two are asked for); which: 1 = row-major copies (what
+// grid.z walks the roles to pack (role_a, then role_b when two are asked for); which: 1 = outer-product copies (what
 // the outer-product kernels read), 2 = transposed copies (what the products read), 3 = both
 __global__ __launch_bounds__(kThreads) void pack_kernel(const LayerDev* __restrict__ layers,
                                                         const int* __restrict__ ids, int role_a, int role_b,
@@ -601,8 +601,8 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
 // (the others: 128)
-// which: operand copies to leave when cp > 0 (1 = row-major, 2 = transposed, 3 = both; + 4: the row-major pieces go to
-// the layer's kept copies in fragment order where it has them -- the P~ of a compress step with a deferred residual)
+// which: operand copies to leave when cp > 0 (1 = outer-product, 2 = transposed, 3 = both; + 4: the outer-product ones are
+// the layer's kept copies where it has them -- the P~ of a compress step with a deferred residual)
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, int slot_rows, hipStream_t st) {
