@@ -38,7 +38,7 @@ hipError_t launch_msgd(int nb, int planes, const LayerDev* layers, const int* id
 hipError_t launch_adam(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles, int rpw,
                        float* const* m1s, float* const* m2s, float* const* xs, const float* coef, bool kept,
                        hipStream_t st);
-hipError_t launch_finish(bool colmode, int kind, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
+hipError_t launch_finish(bool p_like, int kind_n, int kind_t, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st);
 hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, int max_blocks, int role, int cp,
@@ -651,8 +651,13 @@ struct Launcher {
         const int ww = w > 0 ? w : 32 * nb;
         const bool wide = sums_first(ww, p_like ? std::max(norm.longest, tr.longest) : std::max(norm.shortest_max, tr.shortest_max));
         const int fin_gate = wide ? -2 : chol_gate;
-        if (split_n) note(launch_finish(!p_like, kind_n, layers, ids_norm, n_norm, norm.blocks[mode_n], 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
-        if (split_t) note(launch_finish(p_like, kind, layers, ids_tr, n_tr, tr.blocks[mode_t], 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        if (split_n || split_t) {
+            // (one launch for both orientations where both are split)
+            const int* ids = split_n && split_t ? ids_all : split_n ? ids_norm : ids_tr;
+            const int n_ids = split_n && split_t ? n_all : split_n ? n_norm : n_tr;
+            const int most = std::max(split_n ? norm.blocks[mode_n] : 0, split_t ? tr.blocks[mode_t] : 0);
+            note(launch_finish(p_like, kind_n, kind, layers, ids, n_ids, most, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+        }
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
         // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
         // per 128 rows)

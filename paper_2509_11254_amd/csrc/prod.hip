@@ -211,21 +211,37 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
 
 // Epilogue on a complete ROWS x cp output tile held in LDS as fp32 [ROWS][tw]: store the rows of the
 // thin result, then either the partial Gram matrix of these rows (fp64, upper triangle, slot = block
-// index) or the split-bf16 operand copies of the rows.  Called by all threads of the workgroup.
-template <int ROWS>
+// index) or the split-bf16 operand copies of the rows.  Called by all NT threads of the workgroup.
+template <int ROWS, int NT = kThreads>
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
                                      int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
-                                     int copies = 3) {
+                                     int copies = 3, double* red = nullptr) {
     const int t = threadIdx.x;
     const int w = T.width;
-    for (int e = t; copies != 2 && e < ROWS * w; e += kThreads) {
-        const int row = e / w, col = e % w;
-        if (ob * ROWS + row < out_len) as_global(T.ptr)[(int64_t)(ob * ROWS + row) * T.ld + col] = otile[row * tw + col];
+    if (copies != 2) {
+        PSGD_GLOBAL float* dst = as_global(T.ptr) + (int64_t)ob * ROWS * T.ld;
+        const int n_rows = min(ROWS, out_len - ob * ROWS);
+        const float inv_w = 1.0f / (float)w;
+        if (T.ld == w && (w & 3) == 0) {
+            // one run of memory: 16 bytes per thread (no integer division: the quotient is off by one at most)
+            for (int e = 4 * t; e < n_rows * w; e += 4 * NT) {
+                int row = (int)(((float)e + 0.5f) * inv_w);
+                int c = e - row * w;
+                if (c < 0) { --row; c += w; } else if (c >= w) { ++row; c -= w; }
+                const float* sr = otile + row * tw + c;
+                *reinterpret_cast<PSGD_GLOBAL floatx4*>(dst + e) = floatx4{sr[0], sr[1], sr[2], sr[3]};
+            }
+        } else {
+            for (int e = t; e < n_rows * w; e += NT) {
+                const int row = e / w, col = e % w;
+                dst[(int64_t)row * T.ld + col] = otile[row * tw + col];
+            }
+        }
     }
     if (epi == EPI_GRAM) {
-        gram_tile_f64(otile, tw, ROWS, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2));
+        gram_tile_f64<NT>(otile, tw, ROWS, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2), red);
     } else if (epi == EPI_PACK) {
-        write_packs(L.pack[out_side], L.planes, otile, tw, cp, ob * ROWS, ROWS, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
+        write_packs<0, NT>(L.pack[out_side], L.planes, otile, tw, cp, ob * ROWS, ROWS, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
     }
 }
 
@@ -640,25 +656,29 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
 // Gram matrix); the partials are added in split order, so the result is deterministic.
 // FB = 128 for narrow blocks.  Above width 32 the kernel is a pass over [split][width][rows] floats and the fp64 MFMAs of the
-// Gram matrix, with no more workgroups than row blocks: 64 rows each give it twice as many (8192 x 160, four partial sums:
-// 57 -> 20 us, of which the smaller register need without the factorisation's code is a part).
+// Gram matrix, with no more workgroups than row blocks: 64 rows each give it twice as many, of 512 threads.
+// It waits for memory, not for bandwidth: a thread requests 16 pieces of 16 bytes at a time, four items of up to four
+// partial sums or two of eight, where it has one item 8 or 32 (sums past the last are requested as the last one again, and not added).
+// One launch serves both orientations (p_like: the result is on the long side; kind_n, kind_t: SplitKind of the launches whose
+// partial sums these are).
 // chol_gate >= -1: the last workgroup to finish a layer goes on to factorise the sum of the partial Gram
 // matrices (first CholeskyQR pass) if that gate is open, unless the layer is one where the apply kernel
 // does that for itself; -2: no factorisation follows, or one in a launch of its own.
 static_assert(BT == kGramRows1, "one partial Gram matrix per output block of a product");
-template <int FB>
-__global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __restrict__ layers,
-                                                          const int* __restrict__ ids, int colmode, int cp,
-                                                          int out_role, int epi_flags, int gate, int chol_gate,
-                                                          int a2gate, double tol2, int local_ok, int kind) {
+template <int FB, int NT>
+__global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__ layers,
+                                                    const int* __restrict__ ids, int p_like, int cp,
+                                                    int out_role, int epi_flags, int gate, int chol_gate,
+                                                    int a2gate, double tol2, int local_ok, int kind_n, int kind_t) {
     __shared__ int s_last;
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
     int copies;
     const int epi = resolve_epilogue(L, epi_flags, gate, copies);
+    const int colmode = (p_like != 0) == (L.transposed != 0);
     const int out_side = colmode ? SIDE_W : SIDE_L;
     const int out_len = colmode ? L.cols : L.rows;
-    const int n_split = L.split[kind][colmode];      // (kind: SplitKind, whose partial sums)
+    const int n_split = L.split[L.transposed ? kind_t : kind_n][colmode];
     const int ob = blockIdx.x;
     const int out_lenP = side_lenP(L, out_side);
     if (n_split <= 1 || ob * FB >= out_lenP) return;      // (the operand copies' padding is written as well)
@@ -667,46 +687,41 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
     float* otile = reinterpret_cast<float*>(smem);    // [FB][cp + 1]
     const int tw = cp + 1;
     const int t = threadIdx.x;
-    for (int e = t; e < FB * cp; e += kThreads) otile[(e / cp) * tw + e % cp] = 0.f;
-    __syncthreads();
+    // (the columns beyond the width; the others are written below)
+    for (int row = t / 32; row < FB; row += NT / 32)
+        for (int c = T.width + t % 32; c < cp; c += 32) otile[row * tw + c] = 0.f;
     const int64_t plane = (int64_t)out_lenP * T.width;
     const PSGD_GLOBAL float* __restrict__ src = as_global(L.part[out_side]) + (int64_t)ob * FB;
-    // U items per thread at a time (two where a thread has several: 16 loads of 16 bytes in flight at a split of 8;
-    // four spill), eight splits per batch.  Every sum runs in split order.
-    auto reduce_items = [&](auto u_tag, int first, int last) {
-        constexpr int U = decltype(u_tag)::value;
-        for (int item0 = first + t; item0 < last; item0 += U * kThreads) {
+    // U items of D partial sums per thread at a time.  Every sum runs in split order.
+    auto reduce_items = [&](auto u_tag, auto d_tag) {
+        constexpr int U = decltype(u_tag)::value, D = decltype(d_tag)::value;
+        const int n_items = T.width * (FB / 4);
+        for (int item0 = t; item0 < n_items; item0 += U * NT) {
             const PSGD_GLOBAL float* sc[U];
             float4 sum[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int item = item0 + u * kThreads < last ? item0 + u * kThreads : item0;     // (clamped: a valid address)
+                const int item = item0 + u * NT < n_items ? item0 + u * NT : item0;     // (clamped: a valid address)
                 sc[u] = src + (int64_t)(item / (FB / 4)) * out_lenP + 4 * (item % (FB / 4));
                 sum[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
-            int s2 = 0;
-            for (; s2 + 8 <= n_split; s2 += 8) {
-                float4 x[U][8];
+            for (int s2 = 0; s2 < n_split; s2 += D) {
+                float4 x[U][D];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                for (int d = 0; d < D; ++d)
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) x[u][d] = ld_f32x4(sc[u] + (s2 + d) * plane);
+                    for (int u = 0; u < U; ++u) x[u][d] = ld_f32x4(sc[u] + min(s2 + d, n_split - 1) * plane);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                for (int d = 0; d < D; ++d)
+                    if (s2 + d < n_split) {
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) { sum[u].x += x[u][d].x; sum[u].y += x[u][d].y; sum[u].z += x[u][d].z; sum[u].w += x[u][d].w; }
-            }
-            for (; s2 < n_split; ++s2) {
-                float4 x[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) x[u] = ld_f32x4(sc[u] + s2 * plane);
-#pragma unroll
-                for (int u = 0; u < U; ++u) { sum[u].x += x[u].x; sum[u].y += x[u].y; sum[u].z += x[u].z; sum[u].w += x[u].w; }
+                        for (int u = 0; u < U; ++u) { sum[u].x += x[u][d].x; sum[u].y += x[u][d].y; sum[u].z += x[u][d].z; sum[u].w += x[u][d].w; }
+                    }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int item = item0 + u * kThreads;
-                if (item >= last) continue;
+                const int item = item0 + u * NT;
+                if (item >= n_items) continue;
                 const int col = item / (FB / 4), r4 = 4 * (item % (FB / 4));
                 otile[(r4 + 0) * tw + col] = sum[u].x;
                 otile[(r4 + 1) * tw + col] = sum[u].y;
@@ -715,13 +730,20 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const LayerDev* __rest
             }
         }
     };
-    {
-        const int n_items = T.width * (FB / 4);
-        if (n_items >= 2 * kThreads) reduce_items(std::integral_constant<int, 2>{}, 0, n_items);
-        else reduce_items(std::integral_constant<int, 1>{}, 0, n_items);
+    using one = std::integral_constant<int, 1>;
+    using two = std::integral_constant<int, 2>;
+    using four = std::integral_constant<int, 4>;
+    using eight = std::integral_constant<int, 8>;
+    if (T.width * (FB / 4) >= 2 * NT) {
+        if (n_split <= 4) reduce_items(four{}, four{}); else reduce_items(two{}, eight{});
+    } else if (FB == BT && n_split > 8) {
+        reduce_items(one{}, std::integral_constant<int, 32>{});
+    } else {
+        reduce_items(one{}, eight{});
     }
     __syncthreads();
-    tile_epilogue<FB>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+    double* red = FB == BT && T.width <= 16 ? reinterpret_cast<double*>(smem + (((size_t)FB * tw * sizeof(float) + 7) & ~(size_t)7)) : nullptr;
+    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red);
     // (FB = 64 is for widths whose factorisation is a launch of its own)
     if constexpr (FB == BT) {
         if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && gate_open(L, chol_gate)) {
@@ -778,23 +800,24 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
 // Rows per workgroup and Gram slot.  w: widest block of the launch
 int finish_rows(int w) { return w > kWideWidth ? BT / 2 : BT; }
 
-// kind: SplitKind of the launch whose partial sums these are; max_blocks: 128-row blocks of the longest result
-hipError_t launch_finish(bool colmode, int kind, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
+// max_blocks: 128-row blocks of the longest result of the launch's layers
+hipError_t launch_finish(bool p_like, int kind_n, int kind_t, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st) {
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
     const int fb = finish_rows(w > 0 ? w : cp);
-    dim3 grid(max_blocks * (BT / fb), n_ids), block(kThreads);
-    auto kfn = fb == BT ? finish_kernel<BT> : finish_kernel<BT / 2>;
+    dim3 grid(max_blocks * (BT / fb), n_ids), block(fb == BT ? kThreads : 2 * kThreads);
+    auto kfn = fb == BT ? finish_kernel<BT, kThreads> : finish_kernel<BT / 2, 2 * kThreads>;
     size_t lds = (size_t)fb * (cp + 1) * sizeof(float);
+    if (fb == BT) lds += 8 + (kThreads / 64) * 256 * sizeof(double);            // (layers of widths up to 16: see gram_tile_f64)
     if (chol_gate >= -1 && chol_lds_bytes_upto(w) > lds) lds = chol_lds_bytes_upto(w);
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, colmode ? 1 : 0, cp, out_role, epi, gate,
-                       chol_gate, a2gate, tol2, local_ok, kind);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, p_like ? 1 : 0, cp, out_role, epi, gate,
+                       chol_gate, a2gate, tol2, local_ok, kind_n, kind_t);
     return hipGetLastError();
 }
 

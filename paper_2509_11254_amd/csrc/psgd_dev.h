@@ -309,20 +309,45 @@ __host__ __device__ inline int tri_idx(int i, int j, int w) { return i * w - (i 
 // Partial Gram matrix of a tile of finished rows on the fp64 matrix cores:
 //   g[tri_idx(i, j, w)] = sum_rows tile[row][i] * tile[row][j]   for i <= j < w   (packed upper triangle)
 // tile is fp32 in LDS, [nrows][tw], nrows a multiple of 4, columns up to the next multiple of 16 of w
-// readable (zero padded).  The 16 x 16 blocks (bi <= bj) are dealt to the four waves of the workgroup;
+// readable (zero padded).  The 16 x 16 blocks (bi <= bj) are dealt to the waves of the workgroup (NT threads);
 // v_mfma_f64_16x16x4_f64 takes A = tile^T (lane: column, k: row) and B = tile.
-__device__ inline void gram_tile_f64(const float* tile, int tw, int nrows, int w, double* __restrict__ g_generic) {
+// red (w <= 16, where there is one block): LDS scratch of NT / 64 x 256 doubles; the waves then take a share of the rows each, and
+// their sums are added in wave order.
+template <int NT = kThreads>
+__device__ inline void gram_tile_f64(const float* tile, int tw, int nrows, int w, double* __restrict__ g_generic, double* red = nullptr) {
     PSGD_GLOBAL double* __restrict__ g = as_global(g_generic);
+    constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
     const int nt = (w + 15) / 16;
+    if (red && nt == 1) {
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+        const float* __restrict__ pa = tile + lk * tw + li;
+#pragma unroll 4
+        for (int k0 = 4 * wv; k0 < nrows; k0 += 4 * NW) {
+            const double x = (double)pa[k0 * tw];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wv * 256 + 64 * v + lane] = acc[v];
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            const int i = 4 * wv + lk;                     // (entry 64 v + lane of a wave's block: row 4 v + lk, column li)
+            double sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) sum += red[q * 256 + threadIdx.x];
+            if (i <= li && li < w) g[tri_idx(i, li, w)] = sum;
+        }
+        return;
+    }
     int p = 0;
     for (int bi = 0; bi < nt; ++bi)
         for (int bj = bi; bj < nt; ++bj, ++p) {
-            if ((p & 3) != wv) continue;
+            if (p % NW != wv) continue;
             doublex4 acc = {0.0, 0.0, 0.0, 0.0};
             const float* __restrict__ pa = tile + lk * tw + 16 * bi + li;
             const float* __restrict__ pb = tile + lk * tw + 16 * bj + li;
+#pragma unroll 4
             for (int k0 = 0; k0 < nrows; k0 += 4)
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)pa[k0 * tw], (double)pb[k0 * tw], acc, 0, 0, 0);
             const int j = 16 * bj + li;
