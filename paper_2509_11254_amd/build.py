@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpsgd.so")
 CEIL_LIB = os.path.join(HERE, "libpsgd_ceilings.so")      # plain streaming kernels for `bench.py --ceilings`
-SOURCES = ["api.hip", "prod.hip", "form.hip", "residual.hip", "thin.hip"]
+SOURCES = ["api.hip", "prod.hip", "form.hip", "residual.hip", "thin.hip", "tiny.hip"]
 CEIL_SOURCE = "ceilings.hip"
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-sanitize",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

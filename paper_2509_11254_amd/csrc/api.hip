@@ -57,6 +57,11 @@ hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, 
                              int src_role, int warm, uint32_t seed, hipStream_t st);
 hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st);
+bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays);
+size_t tiny_lds_bytes(int64_t rows, int64_t cols);
+hipError_t launch_tiny_step(const LayerDev* layers, const int* ids, int n_ids, size_t lds, double tol2, hipStream_t st);
+hipError_t launch_tiny_iterate(const LayerDev* layers, const int* ids, int n_ids, size_t lds, double tol2, int iters, int warm,
+                               uint32_t seed, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t n_bytes, hipStream_t st);
 hipError_t launch_put(void* dst, const void* src_host, size_t bytes, hipStream_t st);
 hipError_t launch_clear_status(const LayerDev* layers, const int* ids, int n_ids, hipStream_t st);
@@ -133,7 +138,10 @@ struct psgd_ctx {
     void* outs_ws = nullptr;     // workspace that holds the current table of decompress outputs
     void* msgd_ws = nullptr;     // ... and of the momentum and weight buffers of psgd_decompress_msgd / _adam
     void* m2_ws = nullptr;       // ... and of the second-moment buffers of psgd_decompress_adam
-    void* factors_ws = nullptr;  // workspace whose outer-product operand copies are the P~, Q of the last compress call
+// every layer's step (plain, one power iteration) or refresh runs in one workgroup that holds M in LDS (tiny.hip)
+    bool tiny_step = false, tiny_refresh = false;
+    size_t tiny_lds = 0;
+        void* factors_ws = nullptr;  // workspace whose outer-product operand copies are the P~, Q of the last compress call
     bool factors_kept = false;   // ... a call with a deferred residual: in the layers that defer they are the kept copies
     bool tables_valid = false;
     std::vector<const void*> hG;                       // the caller's current table
@@ -816,10 +824,12 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     const int n_launch = launch_iters > 0 && launch_iters < iters ? launch_iters : iters;
     const double tol2 = tol2_of(ctx);
     L.prof_mute = true;
-    L.note(launch_init_block(L.layers, L.ids_all, L.n_all, L.max_len(), wz, ROLE_ZQ, ROLE_Q, warm ? 1 : 0,
+    const bool tiny = ctx->tiny_refresh && form_first;
+    if (tiny) L.note(launch_tiny_iterate(L.layers, L.ids_all, L.n_all, ctx->tiny_lds, tol2, iters, warm ? 1 : 0, ctx->opt.seed, L.st));
+    if (!tiny) L.note(launch_init_block(L.layers, L.ids_all, L.n_all, L.max_len(), wz, ROLE_ZQ, ROLE_Q, warm ? 1 : 0,
                              ctx->opt.seed, L.st));
-    L.pack(ROLE_ZQ, cpz, Launcher::PACK_TRANSPOSED);
-    for (int it = 0; it < n_launch; ++it) {
+    if (!tiny) L.pack(ROLE_ZQ, cpz, Launcher::PACK_TRANSPOSED);
+    for (int it = 0; it < n_launch && !tiny; ++it) {
         // every layer runs its own number of iterations (decided on the device from the Ritz values of
         // its previous refresh); launches past that number find their gate closed and exit at once
         L.gate = make_gate(it, 0, iters, n_launch);
@@ -835,8 +845,8 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)
     const bool wide = wz > kWideWidth;
     if (wide) L.note(launch_gram_sum(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, L.gram_rows_n, L.gram_rows_t, -1, 0, L.st));
-    L.second_pass_deferred(wz, cpz, tol2);
-    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide ? kOneSlot : kGramRows1, sigma_out, L.st));
+    if (!tiny) L.second_pass_deferred(wz, cpz, tol2);
+    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide || tiny ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
                         final_cp, -1, -2, 0.0, false, 3, 0, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZQ, ROLE_Q, APPLY_RITZ,
@@ -931,6 +941,13 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         c->cpmax = c->cpz > c->cpc ? c->cpz : c->cpc;
         if (c->cpmax > kMaxWidth) rc = PSGD_E_SHAPE;
         if (c->lazy && c->cpc > 128) rc = PSGD_E_SHAPE;
+        c->tiny_step = !c->lazy && !c->reform_m && c->opt.power_iters <= 1;
+        c->tiny_refresh = true;
+        for (const auto& p : c->plan) {
+            c->tiny_step = c->tiny_step && tiny_fits(p.d.rows, p.d.cols, p.d.r, n_workers + 1);
+            c->tiny_refresh = c->tiny_refresh && tiny_fits(p.d.rows, p.d.cols, p.wz, 1);
+            c->tiny_lds = std::max(c->tiny_lds, tiny_lds_bytes(p.d.rows, p.d.cols));
+        }
         c->lazy_tr = c->lazy && c->cpc == 32;
     }
     if (rc != PSGD_OK) { delete c; return rc; }
@@ -1074,6 +1091,16 @@ int psgd_compress(psgd_ctx* ctx, void* workspace, void* stream, const void* cons
     ctx->factors_ws = nullptr;
     Launcher L = batch_launcher(ctx, workspace, st);
     const int cp = ctx->cpc, nb = cp / 32;
+    if (ctx->tiny_step) {
+        // (Q_{t-1} from the caller's buffers: where they are promised to be untouched they hold what the copies do)
+        const int k = L.prof_begin(PSGD_PROF_SWEEP1);
+        L.note(launch_tiny_step(L.layers, L.ids_all, L.n_all, ctx->tiny_lds, tol2_of(ctx), st));
+        L.prof_end(k);
+        if (L.err != hipSuccess) return fail_hip(ctx, L.err);
+        ctx->factors_ws = workspace;
+        ctx->factors_kept = false;
+        return PSGD_OK;
+    }
     if (!q_in_place) L.pack(ROLE_Q, cp, Launcher::PACK_TRANSPOSED);
     // P = M Q_{t-1} (M formed on the way and, unless it is formed again below, stored over E);
     // P~ = QR(P), operand copies of P~;  Q_t = M^T P~, operand copies of Q_t;  K times (Eq. (8)), K = 1 by default
@@ -1231,6 +1258,12 @@ int psgd_compress_refresh(psgd_ctx* ctx, void* workspace, void* stream, const vo
     ctx->refresh_seq++;
     ctx->fetch_last = -1;
     if (capturing) ctx->iters_gen++;
+    if (ctx->tiny_refresh) {                          // (its one launch knows the counts)
+        if (L.err != hipSuccess) return fail_hip(ctx, L.err);
+        ctx->factors_ws = workspace;
+        ctx->factors_kept = false;
+        return PSGD_OK;
+    }
     // fetch the bound for the next one (pinned words and events are created on first use; without them every
     // refresh simply launches the whole budget)
     if (!capturing && !ctx->fetch_ready && !ctx->fetch_failed) {

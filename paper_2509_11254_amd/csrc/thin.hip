@@ -655,14 +655,8 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
 }
 
 // --------------------------------------------------------------------------------------------
-// start block of the subspace iteration: columns [0, n_copy) from thin[src_role] (warm start),
-// the others uniform in (-1, 1) from a counter-based hash of (seed, layer, row, column).
+// start block of the subspace iteration: columns [0, n_copy) from thin[src_role] (warm start), the others from start_value.
 // --------------------------------------------------------------------------------------------
-__device__ inline uint32_t mix32(uint32_t x) {
-    x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
-    return x;
-}
-
 __global__ __launch_bounds__(kThreads) void init_block_kernel(const LayerDev* __restrict__ layers,
                                                               const int* __restrict__ ids, int dst_role,
                                                               int src_role, int warm, uint32_t seed) {
@@ -680,9 +674,7 @@ __global__ __launch_bounds__(kThreads) void init_block_kernel(const LayerDev* __
         if (c < n_copy) {
             v = X.ptr[(int64_t)i * X.ld + c];
         } else {
-            uint32_t h = mix32(seed ^ mix32((uint32_t)lid * 0x9e3779b9u + 0x85ebca6bu));
-            h = mix32(h ^ mix32((uint32_t)i + 0x632be5abu) ^ mix32((uint32_t)c * 0xc2b2ae35u + 0x27d4eb2fu));
-            v = (float)(h >> 8) * (2.0f / 16777216.0f) - 1.0f;
+            v = start_value(seed, lid, i, c);
         }
         Y.ptr[(int64_t)i * Y.ld + c] = v;
     }
@@ -1045,8 +1037,8 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     v_rows = v_rows > n ? n : v_rows;
     const size_t lds = jacobi_lds_bytes(w, v_rows);
     const int n_blocks = ((n / 2) * (n / 2 + 1)) / 2;
-    // 256 threads for narrow blocks (the rounds are latency-bound there), else 1024.  (With three to five blocks
-    // per thread the kernel spills a few registers; 512 threads with twice the registers measured slower.)
+    // 256 threads for narrow blocks (the rounds are latency-bound there; one wavefront at width 12: 56 -> 67 us), else 1024.  (With
+    // three to five blocks per thread the kernel spills a few registers; 512 threads with twice the registers measured slower.)
     const int threads = w <= 48 ? 256 : 1024;
     dim3 grid((n + v_rows - 1) / v_rows, n_ids), block(threads);
     const int per_thread = (n_blocks + threads - 1) / threads;

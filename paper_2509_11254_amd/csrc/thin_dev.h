@@ -200,6 +200,18 @@ __device__ __forceinline__ void note_block(Spread& spread, const double (&x)[W],
     spread.add_block(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp((rjj * norm) * (rjj * norm)), counts);
 }
 
+// Start block of the subspace iteration beyond the columns of the warm start: uniform in (-1, 1) from a counter-based hash of
+// (seed, layer, row, column).
+__device__ inline uint32_t mix32(uint32_t x) {
+    x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
+    return x;
+}
+__device__ inline float start_value(uint32_t seed, int layer, int i, int c) {
+    uint32_t h = mix32(seed ^ mix32((uint32_t)layer * 0x9e3779b9u + 0x85ebca6bu));
+    h = mix32(h ^ mix32((uint32_t)i + 0x632be5abu) ^ mix32((uint32_t)c * 0xc2b2ae35u + 0x27d4eb2fu));
+    return (float)(h >> 8) * (2.0f / 16777216.0f) - 1.0f;
+}
+
 // Second-pass permission carried by a launch: -1 always, -2 never, else an iteration gate (kind 2).
 __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
     if (a2gate == -1) return true;
@@ -212,7 +224,8 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
 // w .. W-1 are those of an identity matrix.
 template <int W>
 __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                           bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
+                                           bool allow2, double* tm, bool write_status, int* need2_out, bool scale,
+                                           int* asks_out) {
     const int c = threadIdx.x & 15;
     const int jc = c < w ? c : 0;
     const double djj = g[tri_idx(jc, jc, w)];
@@ -244,6 +257,7 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
         const int nbad = __popc(badmask & ((1 << w) - 1));
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
+        if (scale && asks_out) *asks_out = spread.asks(L.planes, min_piv) ? 1 : 0;
         if (write_status) {
             if (pass == 1) {
                 L.status[0] = nbad;
@@ -256,12 +270,14 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     }
 }
 
+// asks_out: optional LDS word that receives, with `scale`, whether Y is to be orthonormalised (also status[10])
 __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                         bool allow2, double* tm, bool write_status, int* need2_out, bool scale) {
-    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
-    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
-    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
-    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
+                                         bool allow2, double* tm, bool write_status, int* need2_out, bool scale,
+                                         int* asks_out = nullptr) {
+    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
+    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
+    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
+    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
 }
 
 // Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers: factorises the block `blk` (row-major,
