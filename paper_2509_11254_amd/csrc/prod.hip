@@ -14,6 +14,7 @@
 // first, with v_mfma_f32_32x32x16_bf16.
 // The S tile goes global -> registers (coalesced 16-byte loads, summed over workers) -> LDS in the
 // k-contiguous layout the MFMA A operand wants; the thin operand arrives pre-split and transposed.
+#include <algorithm>
 #include <type_traits>
 
 #include "thin_dev.h"
@@ -653,6 +654,233 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
     tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
+// The products that only read M from kWideProd blocks of 32 columns on.  A workgroup of prod_kernel has a compute unit (nearly) to
+// itself there, and its four waves first split and stage, then multiply.  Here an element of M is read by the one wave that
+// multiplies it, 128 bytes of a row at a time by loads that write to LDS directly, into a buffer of the wave's own; it is split
+// in registers, in the layout of the A operand.  The thin operand is double-buffered, by loads of the same kind (its copies
+// are in fragment order, so a fragment is 1 KB of consecutive memory on both sides).  Eight waves: the halves h take 32 of a
+// chunk's 64 reduction steps each, one barrier per chunk, and add their sums at the end (half as long: error of E against 64
+// bits 3.1e-5 -> 2.2e-5 in a refresh of 8192 x 8192 fp32 r = 128); the two waves of a SIMD multiply and split in turn.
+// Per launch, prod_kernel and this: 8192 x 8192 width 160, three planes, 163 -> 121 us either way (1.06 PFLOP/s of plane products; a
+// library product of 8192^3 in bf16 reaches 1.2), 7B-shaped block width 96, two planes, rows 241 -> 220 us.  With M straight
+// to registers 127 to 130 and 288: a load of 32 rows takes 16 bytes of each, and the lines are fetched again.  Not below
+// kWideProd: blocks of 1B shape, r = 16 and 32, 1 % slower than prod_kernel, several of whose workgroups share a compute unit.
+constexpr int kWideThreads = 512;
+constexpr int kWideProd = 3;
+template <int NB, int PL> constexpr int wide_operand_elems() { return PL * (BK / 16) * NB * 512; }      // one chunk of the thin operand
+// chunks of M in LDS: two where they fit a compute unit's 160 KB, and where one workgroup per compute unit is all there is
+constexpr int kWideTile = BT * BK * 4;
+template <int NB, int PL> constexpr int wide_stages() {
+    const int operand = 2 * 2 * wide_operand_elems<NB, PL>();
+    return operand + kWideTile <= 80 * 1024 ? 1 : operand + 2 * kWideTile <= 160 * 1024 ? 2 : 1;
+}
+template <int NB, int PL> constexpr size_t wide_lds_bytes() {
+    return std::max((size_t)(2 * 2 * wide_operand_elems<NB, PL>() + wide_stages<NB, PL>() * kWideTile), (size_t)BT * (32 * NB + 1) * sizeof(float));
+}
+
+#define PSGD_LDS __attribute__((address_space(3)))
+// chunk ch of the thin operand to LDS, a fragment per wave and load
+template <int NB, int PL>
+__device__ __forceinline__ void wide_load_b(const PSGD_GLOBAL bf16_t* x0, const PSGD_GLOBAL bf16_t* x1, const PSGD_GLOBAL bf16_t* x2,
+                                            PSGD_LDS bf16_t* dst, int ch, int wv, int lane) {
+    constexpr int PF = (BK / 16) * NB, FRAGS = PL * PF;      // fragments per plane, in all
+#pragma unroll
+    for (int j = 0; j < (FRAGS + 7) / 8; ++j) {
+        const int f = wv + 8 * j;
+        if (8 * j + 8 <= FRAGS || f < FRAGS) {
+            const int k = f / PF, fi = f - k * PF;
+            const PSGD_GLOBAL bf16_t* src = (k == 0 ? x0 : PL == 3 && k == 1 ? x1 : x2) + ((int64_t)ch * PF + fi) * 512 + lane * 8;
+            __builtin_amdgcn_global_load_lds((const PSGD_GLOBAL void*)src, (PSGD_LDS void*)(dst + f * 512), 16, 0, 0);
+        }
+    }
+}
+// a wave's 32 x 32 elements of M from (r0, c0) on to LDS, row by row of 128 bytes, eight whole rows per load.  SWZ: 16-byte piece c
+// of row r is at place c ^ (r & 7) of its row, so that lanes which read one piece of 32 rows spread over all banks.
+// Pieces outside the matrix are replaced by others inside it (the caller drops them).
+template <bool SWZ>
+__device__ __forceinline__ void wide_load_a(const PSGD_GLOBAL float* S, int64_t ld, int r0, int c0, int rows, int cols, PSGD_LDS float* dst,
+                                            int lane) {
+    const int lr = lane >> 3, piece = (lane & 7) ^ (SWZ ? lr : 0);
+    const int c = c0 + 4 * piece < cols ? c0 + 4 * piece : 0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const PSGD_GLOBAL float* src = S + (int64_t)min(r0 + 8 * p + lr, rows - 1) * ld + c;
+        __builtin_amdgcn_global_load_lds((const PSGD_GLOBAL void*)src, (PSGD_LDS void*)(dst + 256 * p), 16, 0, 0);
+    }
+}
+
+template <int NB, int PL, bool COLMODE>
+__global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
+                                                                    int cp, int out_role, int epi_flags, int gate) {
+    const LayerDev& L = layers[ids[blockIdx.y]];
+    if (!gate_open(L, gate)) return;
+    int copies;
+    const int epi = resolve_epilogue(L, epi_flags, gate, copies);
+    const int out_side = COLMODE ? SIDE_W : SIDE_L;
+    const int out_len = COLMODE ? L.cols : L.rows;
+    const int red_len = COLMODE ? L.rows : L.cols;
+    const int n_ob = (out_len + BT - 1) / BT;
+    const int n_split = L.split[split_kind(false, gate)][COLMODE ? 1 : 0];
+    const int tile = blockIdx.x;
+    if (tile >= n_ob * n_split) return;
+    const int ob = COLMODE ? tile % n_ob : tile / n_split, sp = COLMODE ? tile / n_ob : tile % n_split;
+    const int n_chunks = (red_len + BK - 1) / BK;
+    const int cps = (n_chunks + n_split - 1) / n_split;
+    const int ch0 = sp * cps;
+    const int n_loc = min(n_chunks, ch0 + cps) - ch0;
+    // (each row block starts its walk at a chunk of its own, see prod_kernel)
+    const int rot = (COLMODE || n_loc <= 0) ? 0 : ((ob & 7) * (n_loc >> 3) + 2 * (ob >> 3) + (int)blockIdx.y) % n_loc;
+    auto chunk_at = [&](int it) { const int c = it + rot; return ch0 + (c >= n_loc ? c - n_loc : c); };
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int BUF = wide_operand_elems<NB, PL>(), BPL = BUF / PL, STAGES = wide_stages<NB, PL>();
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rg = wv & 3, h = wv >> 2;
+    const int li = lane & 31, lg = lane >> 5;
+
+    const PackRef& X = L.pack[COLMODE ? SIDE_L : SIDE_W];
+    PSGD_LDS bf16_t* const b_lds = (PSGD_LDS bf16_t*)smem;   // two buffers of PL planes of [BK / 16][NB] fragments
+    const PSGD_GLOBAL bf16_t* const xt[3] = {as_global(X.t[0]), as_global(X.t[1]), as_global(X.t[PL - 1])};
+    const PSGD_GLOBAL float* const S = as_global(L.S);
+    const int64_t ld = L.ld;
+    const int rows = L.rows, cols = L.cols, tile0 = ob * BT + 32 * rg;
+    PSGD_LDS float* const a_lds = (PSGD_LDS float*)(b_lds + 2 * BUF) + STAGES * 1024 * wv;       // this wave's STAGES buffers
+    auto load_a = [=](int it) {
+        const int k0 = chunk_at(it) * BK + 32 * h;
+        wide_load_a<!COLMODE>(S, ld, COLMODE ? k0 : tile0, COLMODE ? tile0 : k0, rows, cols, a_lds + (STAGES == 2 ? (it & 1) * 1024 : 0), lane);
+    };
+
+    floatx16 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
+    if (n_loc > 0) {
+        load_a(0);
+        wide_load_b<NB, PL>(xt[0], xt[1], xt[2], b_lds, chunk_at(0), wv, lane);
+        asm volatile("" ::: "memory");
+        if (STAGES == 2 && n_loc > 1) load_a(1);
+    }
+    for (int it = 0; it < n_loc; ++it) {
+        // This chunk has arrived, for every wave, and nobody reads the thin operand's other buffer any more.  (Loads complete in
+        // the order of their issue; with two stages the next chunk's four, issued last, stay in flight, which __syncthreads
+        // would wait for.)
+        if (STAGES == 2 && it + 1 < n_loc) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        // reduction steps 32 h + 16 s + 8 lg .. + 7 (s = 0, 1) of the chunk of this lane's row or column
+        float x[2][8];
+        const PSGD_LDS float* al = a_lds + (STAGES == 2 ? (it & 1) * 1024 : 0);
+        if constexpr (!COLMODE) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const floatx4 v = *reinterpret_cast<const PSGD_LDS floatx4*>(al + 32 * li + 4 * ((4 * (p >> 1) + 2 * lg + (p & 1)) ^ (li & 7)));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[p >> 1][4 * (p & 1) + u] = v[u];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[s][u] = al[(16 * s + 8 * lg + u) * 32 + li];
+        }
+        const int k0 = chunk_at(it) * BK + 32 * h;
+        if (tile0 + 32 > out_len || k0 + 32 > red_len) {
+            const int n_in = tile0 + li < out_len ? red_len - k0 - 8 * lg : 0;
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[s][u] = 16 * s + u < n_in ? x[s][u] : 0.f;
+        }
+        if (it + 1 < n_loc) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (this wave's reads of the buffer that is loaded next)
+            wide_load_b<NB, PL>(xt[0], xt[1], xt[2], b_lds + ((it + 1) & 1) * BUF, chunk_at(it + 1), wv, lane);
+            asm volatile("" ::: "memory");
+            if (it + STAGES < n_loc) load_a(it + STAGES);
+        }
+        bf16x8 av[2][PL];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                bf16_t q[PL];
+                split_planes<PL>(x[s][u], q);
+#pragma unroll
+                for (int k = 0; k < PL; ++k) av[s][k][u] = q[k];
+            }
+        const PSGD_LDS bf16_t* bb = b_lds + (it & 1) * BUF + 2 * h * NB * 512 + lane * 8;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                bf16x8 bv[PL];
+#pragma unroll
+                for (int k = 0; k < PL; ++k) bv[k] = *reinterpret_cast<const PSGD_LDS bf16x8*>(bb + k * BPL + (s * NB + nb) * 512);
+                // smallest products first
+#pragma unroll
+                for (int sum = 2 * (PL - 1); sum >= 0; --sum)
+#pragma unroll
+                    for (int ka = 0; ka < PL; ++ka) {
+                        const int kb = sum - ka;
+                        if (kb >= 0 && kb < PL && keep_term<PL>(ka, kb))
+                            acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[s][ka], bv[kb], acc[nb], 0, 0, 0);
+                    }
+            }
+    }
+    // the halves' sums: wave (rg, 0) ends up with the first NH blocks, wave (rg, 1) with the others
+    constexpr int NH = (NB + 1) / 2;
+    floatx4* ex = reinterpret_cast<floatx4*>(smem);          // [NB][4 rg][4][64]
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+        if ((nb < NH) != (h == 0)) {
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq)
+                ex[((nb * 4 + rg) * 4 + vq) * 64 + lane] = floatx4{acc[nb][4 * vq], acc[nb][4 * vq + 1], acc[nb][4 * vq + 2], acc[nb][4 * vq + 3]};
+        }
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+        if ((nb < NH) == (h == 0)) {
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                const floatx4 o = ex[((nb * 4 + rg) * 4 + vq) * 64 + lane];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[nb][4 * vq + u] += o[u];
+            }
+        }
+    const int out_lenP = side_lenP(L, out_side);
+    const ThinRef T = L.thin[out_role];
+    if (n_split > 1) {
+        // one of n_split partial sums, [split][column][row] (see prod_kernel)
+        const int64_t plane = (int64_t)out_lenP * T.width;
+        PSGD_GLOBAL float* __restrict__ dst = as_global(L.part[out_side]) + sp * plane + (int64_t)ob * BT + 32 * rg + 4 * lg;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int col = 32 * nb + li;
+            if ((nb < NH) == (h == 0) && col < T.width) {
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq)
+                    *reinterpret_cast<PSGD_GLOBAL floatx4*>(dst + (int64_t)col * out_lenP + 8 * vq) =
+                        floatx4{acc[nb][4 * vq], acc[nb][4 * vq + 1], acc[nb][4 * vq + 2], acc[nb][4 * vq + 3]};
+            }
+        }
+        return;
+    }
+    __syncthreads();
+    float* otile = reinterpret_cast<float*>(smem);           // [BT][cp + 1]
+    const int tw = cp + 1;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+        if ((nb < NH) == (h == 0)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) otile[(32 * rg + 8 * (v >> 2) + 4 * lg + (v & 3)) * tw + 32 * nb + li] = acc[nb][v];
+        }
+    __syncthreads();
+    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+}
+
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
 // Gram matrix); the partials are added in split order, so the result is deterministic.
 // FB = 128 for narrow blocks.  Above width 32 the kernel is a pass over [split][width][rows] floats and the fp64 MFMAs of the
@@ -857,8 +1085,15 @@ static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, const
             return hipErrorInvalidValue;
         }
     } else if (form && onew) { if (colmode) PSGD_LAUNCH(true, true, false, true); else PSGD_LAUNCH(false, true, false, true); }
-    else if (colmode) { if (form) PSGD_LAUNCH(true, true); else PSGD_LAUNCH(true, false); }
-    else              { if (form) PSGD_LAUNCH(false, true); else PSGD_LAUNCH(false, false); }
+    else if (form) { if (colmode) PSGD_LAUNCH(true, true); else PSGD_LAUNCH(false, true); }
+    else if constexpr (NB >= kWideProd && wide_lds_bytes<NB, PL>() <= 160 * 1024) {
+        constexpr size_t bytes = wide_lds_bytes<NB, PL>();
+        auto kfn = colmode ? wide_prod_kernel<NB, PL, true> : wide_prod_kernel<NB, PL, false>;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kfn, grid, dim3(kWideThreads), bytes, st, layers, ids, cp, out_role, epi, gate);
+    }
+    else { if (colmode) PSGD_LAUNCH(true, false); else PSGD_LAUNCH(false, false); }
 #undef PSGD_LAUNCH
     return hipGetLastError();
 }
