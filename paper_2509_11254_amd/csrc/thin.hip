@@ -747,25 +747,69 @@ __device__ inline int jacobi_pos0(int j, int n) {
     return j < half ? 2 * j : 2 * (n - 1 - j) + 1;
 }
 
-// Rotation that annihilates the off-diagonal entry of slot k's 2 x 2 diagonal block (H is stored by position);
-// also notes which columns of V the slot holds in round rd.
-__device__ inline void jacobi_rotation(const double* a, int n, int rd, int k, double* cs, int* pq) {
-    const int half = n / 2;
-    const double app = a[sym_idx(2 * k, 2 * k, n)], aqq = a[sym_idx(2 * k + 1, 2 * k + 1, n)];
-    const double apq = a[sym_idx(2 * k, 2 * k + 1, n)];
-    double c = 1.0, sn = 0.0;
+// position before the tournament's step of the player that ends up at position x (inverse of jacobi_next_pos)
+__device__ inline int jacobi_prev_pos(int x, int n) {
+    const int half = n / 2, k = x >> 1;
+    if (x == 0 || n <= 2) return x;
+    if (x & 1) return k == 0 ? 2 : x - 2;                   // bottom[k] <- bottom[k - 1], bottom[0] <- top[1]
+    return k == half - 1 ? x + 1 : x + 2;                   // top[k] <- top[k + 1], the last one <- bottom[half - 1]
+}
+
+// Rotation that annihilates apq of a 2 x 2 diagonal block
+__device__ inline void jacobi_angle(double app, double apq, double aqq, double& c, double& sn) {
+    c = 1.0;
+    sn = 0.0;
     if (fabs(apq) > 1e-300 && apq * apq > 1e-36 * fabs(app * aqq)) {
         // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)), tau = (aqq - app) / (2 apq), written with one division
-        // (square root and quotient from the hardware estimates with Newton steps: this sits on the critical path
-        // of every round.  b^2 is a normal number by the test above.)
+        // (square root and quotient from the hardware estimates with Newton steps; b^2 is a normal number by the test above)
         const double d = aqq - app, b = 2.0 * apq;
         const double h2 = __builtin_fma(d, d, b * b);
         const double tt = (d >= 0.0 ? b : -b) * rcp_nr(fabs(d) + h2 * rsqrt_nr(h2));
         c = rsqrt_nr(__builtin_fma(tt, tt, 1.0));
         sn = tt * c;
     }
+}
+// J^T A J for the off-diagonal block (slot k1) x (slot k2) ...
+__device__ inline void jacobi_rotate(double c1, double s1, double c2, double s2, double app, double apq, double aqp, double aqq, double (&o)[4]) {
+    // rows: (top, bottom) <- (c1 top - s1 bottom, s1 top + c1 bottom)
+    const double rpp = c1 * app - s1 * aqp, rpq = c1 * apq - s1 * aqq;
+    const double rqp = s1 * app + c1 * aqp, rqq = s1 * apq + c1 * aqq;
+    // columns: likewise with slot k2's rotation
+    o[0] = c2 * rpp - s2 * rpq;
+    o[1] = s2 * rpp + c2 * rpq;
+    o[2] = c2 * rqp - s2 * rqq;
+    o[3] = s2 * rqp + c2 * rqq;
+}
+// ... and for a diagonal one (upper part)
+__device__ inline void jacobi_rotate_diag(double c, double s, double app, double apq, double aqq, double& opp, double& opq, double& oqq) {
+    opp = c * c * app - 2.0 * c * s * apq + s * s * aqq;
+    opq = (c * c - s * s) * apq + c * s * (app - aqq);
+    oqq = s * s * app + 2.0 * c * s * apq + c * c * aqq;
+}
+__device__ inline void jacobi_note(double c, double sn, int n, int rd, int k, double* cs, int* pq) {
+    const int half = n / 2;
     cs[k] = c; cs[half + k] = sn;
-    pq[k] = jacobi_top(k, rd, n); pq[half + k] = jacobi_bottom(k, rd, n);
+    pq[k] = jacobi_top(k, rd, n); pq[half + k] = jacobi_bottom(k, rd, n);      // the columns of V the slot holds in round rd
+}
+// Slot k's rotation of round rd from the H of that round (stored by position)
+__device__ inline void jacobi_rotation(const double* a, int n, int rd, int k, double* cs, int* pq) {
+    double c, sn;
+    jacobi_angle(a[sym_idx(2 * k, 2 * k, n)], a[sym_idx(2 * k, 2 * k + 1, n)], a[sym_idx(2 * k + 1, 2 * k + 1, n)], c, sn);
+    jacobi_note(c, sn, n, rd, k, cs, pq);
+}
+// Slot k's rotation of round rd from the H and the rotations (cs0) of the round before, n >= 4: pt, pb are the positions its two
+// players have in that round, in two different slots
+__device__ inline void jacobi_rotation_ahead(const double* a, int n, int rd, int k, int pt, int pb, const double* cs0, double* cs, int* pq) {
+    const int half = n / 2, kt = pt >> 1, kb = pb >> 1;
+    const double ct = cs0[kt], st = cs0[half + kt], cb = cs0[kb], sb = cs0[half + kb];
+    double p0, p1, p2, q0, q1, q2, o[4], c, sn;
+    jacobi_rotate_diag(ct, st, a[sym_idx(2 * kt, 2 * kt, n)], a[sym_idx(2 * kt, 2 * kt + 1, n)], a[sym_idx(2 * kt + 1, 2 * kt + 1, n)], p0, p1, p2);
+    jacobi_rotate_diag(cb, sb, a[sym_idx(2 * kb, 2 * kb, n)], a[sym_idx(2 * kb, 2 * kb + 1, n)], a[sym_idx(2 * kb + 1, 2 * kb + 1, n)], q0, q1, q2);
+    jacobi_rotate(ct, st, cb, sb, a[sym_idx(2 * kt, 2 * kb, n)], a[sym_idx(2 * kt, 2 * kb + 1, n)],
+                  a[sym_idx(2 * kt + 1, 2 * kb, n)], a[sym_idx(2 * kt + 1, 2 * kb + 1, n)], o);
+    const double top_row = pb & 1 ? o[1] : o[0], bottom_row = pb & 1 ? o[3] : o[2];
+    jacobi_angle(pt & 1 ? p2 : p0, pt & 1 ? bottom_row : top_row, pb & 1 ? q2 : q0, c, sn);
+    jacobi_note(c, sn, n, rd, k, cs, pq);
 }
 
 // grid = (slices, layers): every workgroup of a layer repeats the (deterministic) iteration on H and
@@ -774,14 +818,18 @@ __device__ inline void jacobi_rotation(const double* a, int n, int rd, int k, do
 // H is stored by POSITION in the tournament, not by matrix index: the 2 x 2 block (slot k1) x (slot k2) sits at
 // the same LDS addresses in every round, is rotated by the two slots' rotations, and its four entries are written
 // to where the tournament moves their row and column players.  Source and destination addresses of a thread's
-// blocks are therefore computed once; a round is: read and rotate (registers) | barrier | write | barrier | the
-// next rotations from the diagonal blocks, and V <- V J on the columns the slots hold | barrier.
+// blocks are therefore computed once; a round is: read and rotate (registers), and beside it the next round's
+// rotations, which the last threads work out from the same entries for themselves | barrier | write, and V <- V J on the
+// columns the slots hold | barrier.  (The rotations after the write, behind a barrier of their own, were a quarter of a
+// narrow round and a tenth of a wide one: width 160 2.49 -> 2.22 ms, width 80 570 -> 510 us at the same sweeps.)
 // V stays indexed by matrix index.
-// NBLK: 2 x 2 blocks of H per thread, at least (w/2)(w/2 + 1)/2 over the workgroup's threads.
+// NBLK: 2 x 2 blocks of H per thread, at least (w/2)(w/2 + 1)/2 over the h_threads first threads of the workgroup, which update H.
+// The others have nothing to do but the rotations: beside blocks of their own they would be the last at the barrier (width
+// 160: 2.45 ms).
 template <int NBLK>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
-                                                      int slot_rows, float* __restrict__ sigma_out) {
+                                                      int slot_rows, int h_threads, float* __restrict__ sigma_out) {
     __shared__ int s_ke;
     __shared__ double s_sum;
     const LayerDev& L = layers[ids[blockIdx.y]];
@@ -833,11 +881,11 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
         const int total = (half * (half + 1)) / 2;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) {
-            const int e = t + b * nt;
+            const int e = t + b * h_threads;
             bk[b] = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) adr[b][q] = 0;
-            if (e < total) {
+            if (t < h_threads && e < total) {
                 const int dk = e / half, k1 = e - dk * half;
                 int k2 = k1 + dk;
                 k2 -= k2 >= half ? half : 0;
@@ -854,6 +902,9 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             }
         }
     }
+    // the slot whose rotations this thread works out a round ahead (-1: none)
+    const int slot = nt - 1 - t < half ? nt - 1 - t : -1;
+    const int prev_top = slot < 0 ? 0 : jacobi_prev_pos(2 * slot, n), prev_bottom = slot < 0 ? 0 : jacobi_prev_pos(2 * slot + 1, n);
     __syncthreads();
     int cur = 0, sweeps = 0;
     for (int sweep = 0; sweep < kJacobiMaxSweeps; ++sweep) {
@@ -880,6 +931,8 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             const double* cs = csb + cur * n;
             const int* pq = pqb + cur * n;
             // H <- J^T H J on this thread's blocks: rows by slot k1's rotation, columns by slot k2's
+            if (slot >= 0 && rd + 1 < n - 1)
+                jacobi_rotation_ahead(a, n, rd + 1, slot, prev_top, prev_bottom, cs, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             double o[NBLK][4];
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
@@ -890,20 +943,10 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
                 const double aqp = a[adr[b][2] & 0xffffu], aqq = a[adr[b][3] & 0xffffu];
                 if (k1 == k2) {
                     // (aqp is apq here)
-                    o[b][0] = c1 * c1 * app - 2.0 * c1 * s1 * apq + s1 * s1 * aqq;
-                    o[b][1] = (c1 * c1 - s1 * s1) * apq + c1 * s1 * (app - aqq);
+                    jacobi_rotate_diag(c1, s1, app, apq, aqq, o[b][0], o[b][1], o[b][3]);
                     o[b][2] = 0.0;
-                    o[b][3] = s1 * s1 * app + 2.0 * c1 * s1 * apq + c1 * c1 * aqq;
                 } else {
-                    const double c2 = cs[k2], s2 = cs[half + k2];
-                    // rows: (top, bottom) <- (c1 top - s1 bottom, s1 top + c1 bottom)
-                    const double rpp = c1 * app - s1 * aqp, rpq = c1 * apq - s1 * aqq;
-                    const double rqp = s1 * app + c1 * aqp, rqq = s1 * apq + c1 * aqq;
-                    // columns: likewise with slot k2's rotation
-                    o[b][0] = c2 * rpp - s2 * rpq;
-                    o[b][1] = s2 * rpp + c2 * rpq;
-                    o[b][2] = c2 * rqp - s2 * rqq;
-                    o[b][3] = s2 * rqp + c2 * rqq;
+                    jacobi_rotate(c1, s1, cs[k2], cs[half + k2], app, apq, aqp, aqq, o[b]);
                 }
             }
             __syncthreads();
@@ -916,9 +959,6 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
                 if (!diag) a[adr[b][2] >> 16] = o[b][2];
                 a[adr[b][3] >> 16] = o[b][3];
             }
-            __syncthreads();
-            // the next round's rotations (from the updated H) while the other waves finish V <- V J
-            if (rd + 1 < n - 1 && t < half) jacobi_rotation(a, n, rd + 1, t, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             for (int i = ty; i < nv; i += tyw)
                 for (int k = tx; k < half; k += txw) {
                     const int p = pq[k], q = pq[half + k];
@@ -1041,8 +1081,10 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     // three to five blocks per thread the kernel spills a few registers; 512 threads with twice the registers measured slower.)
     const int threads = w <= 48 ? 256 : 1024;
     dim3 grid((n + v_rows - 1) / v_rows, n_ids), block(threads);
-    const int per_thread = (n_blocks + threads - 1) / threads;
-    void (*kfn)(const LayerDev*, const int*, int, int, int, float*) = nullptr;
+    int h_threads = threads - 64 * ((n / 2 + 63) / 64);
+    if (n_blocks > 5 * h_threads) h_threads = threads;
+    const int per_thread = (n_blocks + h_threads - 1) / h_threads;
+    void (*kfn)(const LayerDev*, const int*, int, int, int, int, float*) = nullptr;
     switch (per_thread) {
         case 1: kfn = jacobi_kernel<1>; break;
         case 2: kfn = jacobi_kernel<2>; break;
@@ -1057,7 +1099,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, sigma_out);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, h_threads, sigma_out);
     return hipGetLastError();
 }
 
