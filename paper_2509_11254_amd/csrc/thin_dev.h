@@ -157,45 +157,66 @@ struct Spread {
     }
 };
 
-// Right-looking Cholesky A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
-// barriers: lane j of every row of 16 lanes holds column j of the matrix (x, the four rows of lanes hold the same) and column
-// j of an identity matrix (y), which the row operations turn into R^{-T}: y[i] on lane c ends up as T[c][i], T = R^{-1}, and
-// no separate inversion is needed.  A dependent column (flagged in badmask, or pivot not above tol2) makes row k of R the
-// k-th row of the identity and skips the update (multiplier 0).  Written without branches (selects): with branches the
-// compiler copies the whole register array at every merge point, which cost more than the arithmetic.
-template <int W>
-__device__ __forceinline__ void factor_in_registers(double (&x)[W], double (&y)[W], double tol2, int& badmask, double& min_piv) {
-    const int j = threadIdx.x & 15;
-    static_for<0, W>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        const double piv = bcast_row<k>(x[k]);
-        const bool dep = ((badmask >> k) & 1) || !(piv > tol2);
-        badmask |= dep ? (1 << k) : 0;
-        min_piv = (!dep && piv < min_piv) ? piv : min_piv;
-        const double rinv = rsqrt_nr(dep ? 1.0 : piv);
-        const double xk = dep ? (j == k ? 1.0 : 0.0) : x[k] * rinv;               // row k <- row k / R_kk
-        const double yk = dep ? y[k] : y[k] * rinv;
-        x[k] = xk;
-        y[k] = yk;
-        const double mx = dep ? 0.0 : xk, my = dep ? 0.0 : yk;
-        static_for<k + 1, W>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            const double m = -bcast_row<i>(xk);                                   // row i <- row i - R[k][i] row k (on a lane
-            x[i] = __builtin_fma(m, mx, x[i]);                                    // j < i an entry below the diagonal: never read)
-            y[i] = __builtin_fma(m, my, y[i]);
-            // (an ordering point without an instruction: left alone the compiler collects the broadcasts of all steps at
-            // the front and spills)
-            asm volatile("" : "+v"(x[i]), "+v"(y[i]));
-        });
+// value of v on lane (row of lanes, I + row of lanes) of the caller's row of lanes
+template <int I> __device__ __forceinline__ double bcast_by_row(double v) {
+    int lo = 0, hi = 0;
+    static_for<0, 4>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        lo = __builtin_amdgcn_update_dpp(lo, __double2loint(v), 0x150 + I + r, 1 << r, 0xf, false);
+        hi = __builtin_amdgcn_update_dpp(hi, __double2hiint(v), 0x150 + I + r, 1 << r, 0xf, false);
     });
+    return __hiloint2double(hi, lo);
 }
 
-// Adds a factorised block's columns to `spread`: lane j's R_jj is x[j] / dsc (dsc = 1 / ||x_j||).
+// Right-looking Cholesky A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
+// barriers.  x and y are 16 x 16 matrices in the accumulator layout of v_mfma_f64_16x16x4_f64 (x[v]: row 4 v + (lane >> 4),
+// column lane & 15), x the matrix (upper part) and y an identity, which the row operations turn into R^{-T}: y[v] ends up as
+// T[column][row], T = R^{-1}, and no separate inversion is needed.  Step k scales row k, which one row of lanes holds, and
+// takes its multiples off the rows below with one MFMA each for x and y, the other rows of lanes supplying zeros: what bounds
+// the chain is the square root and one MFMA, not the up to 15 row updates of 2 moves and 2 FMAs each.
+// (As row updates: refresh of 256 x 128 fp32 r = 4 306 us, 274 now; of 4096 x 4096 r = 8 1145 and 1123; of a 7B-shaped block
+// 6.3 and 6.1 ms.)
+// A dependent column (flagged in badmask, or pivot not above tol2) makes row k of R the k-th row of the identity and skips
+// the update.  rjj: R_jj of column j = lane & 15 (of the columns that are not dependent).  badmask, min_piv and rjj are the same in all
+// rows of lanes.  Selects, not branches: at every merge point the compiler would copy the register array.
 template <int W>
-__device__ __forceinline__ void note_block(Spread& spread, const double (&x)[W], double dsc, bool counts) {
-    const int j = threadIdx.x & 15;
-    double rjj = 1.0;
-    static_for<0, W>([&](auto ic) { constexpr int i = decltype(ic)::value; rjj = j == i ? x[i] : rjj; });
+__device__ __forceinline__ void factor_in_registers(doublex4& x, doublex4& y, double tol2, int& badmask, double& min_piv, double& rjj) {
+    const int j = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+    int bad = badmask;
+    double low = min_piv, diag = 1.0;
+    static_for<0, W>([&](auto kc) {
+        constexpr int k = decltype(kc)::value, v = k >> 2, r = k & 3;
+        const bool own = q == r;
+        const double piv = bcast_row<k>(x[v]);                                    // (means the pivot in row r of lanes only)
+        const bool dep = ((bad >> k) & 1) || !(piv > tol2);
+        const bool go = own && !dep;
+        bad |= own && dep ? (1 << k) : 0;
+        low = (go && piv < low) ? piv : low;
+        const double rinv = rsqrt_nr(go ? piv : 1.0);
+        const double xk = go ? x[v] * rinv : 0.0, yk = go ? y[v] * rinv : 0.0;
+        diag = go && j == k ? xk : diag;
+        x[v] = own ? (dep ? (j == k ? 1.0 : 0.0) : xk) : x[v];
+        y[v] = go ? yk : y[v];
+        if constexpr (k + 1 < W) {
+            const double m = j > k ? -xk : 0.0;
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(m, xk, x, 0, 0, 0);
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(m, yk, y, 0, 0, 0);
+        }
+    });
+    // every row of lanes knows its own steps: together
+    badmask = 0;
+    min_piv = 1.0;
+    static_for<0, 4>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        badmask |= __builtin_amdgcn_readlane(bad, 16 * r);
+        const double p = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(low), 16 * r), __builtin_amdgcn_readlane(__double2loint(low), 16 * r));
+        min_piv = p < min_piv ? p : min_piv;
+    });
+    rjj = __shfl(diag, 16 * (j & 3) + j);
+}
+
+// Adds a factorised block's columns to `spread`: lane j's R_jj is rjj / dsc (dsc = 1 / ||x_j||).
+__device__ __forceinline__ void note_block(Spread& spread, double rjj, double dsc, bool counts) {
     const double norm = __builtin_amdgcn_rcp(counts ? dsc : 1.0);
     spread.add_block(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp((rjj * norm) * (rjj * norm)), counts);
 }
@@ -226,32 +247,34 @@ template <int W>
 __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                            bool allow2, double* tm, bool write_status, int* need2_out, bool scale,
                                            int* asks_out) {
-    const int c = threadIdx.x & 15;
+    const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
     const int jc = c < w ? c : 0;
     const double djj = g[tri_idx(jc, jc, w)];
     const double dsc_own = djj > kTinyNorm2 ? rsqrt_nr(djj) : 0.0;
-    double x[W], y[W];
-    int badmask = 0;
-    static_for<0, W>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        const double dsi = bcast_row<i>(dsc_own);
-        if (i < w && !(dsi > 0.0)) badmask |= 1 << i;
-        y[i] = i == c ? 1.0 : 0.0;
-        x[i] = (i < w && c < w && i <= c) ? g[tri_idx(i < w ? i : 0, jc, w)] * dsi * dsc_own : y[i];
+    int badmask = (int)(__ballot(c < w && !(dsc_own > 0.0)) & 0xffff);
+    doublex4 x, y;
+    static_for<0, 4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const int i = 4 * v + q;
+        const double dsi = bcast_by_row<4 * v>(dsc_own);
+        y[v] = i == c ? 1.0 : 0.0;
+        x[v] = (i < w && c < w && i <= c) ? g[tri_idx(i < w ? i : 0, jc, w)] * dsi * dsc_own : y[v];
     });
-    double min_piv = 1.0;
-    factor_in_registers<W>(x, y, tol2, badmask, min_piv);
+    double min_piv = 1.0, rjj;
+    factor_in_registers<W>(x, y, tol2, badmask, min_piv, rjj);
     Spread spread;
     if (scale) {                                          // (uniform: every lane takes part in the broadcasts)
         const double csc = next_scale(dsc_own);
-        static_for<0, W>([&](auto ic) { constexpr int i = decltype(ic)::value; y[i] *= bcast_row<i>(csc); });
-        note_block<W>(spread, x, dsc_own, c < w && !((badmask >> c) & 1));
+        static_for<0, 4>([&](auto vc) { constexpr int v = decltype(vc)::value; y[v] *= bcast_by_row<4 * v>(csc); });
+        note_block(spread, rjj, dsc_own, c < w && !((badmask >> c) & 1));
     }
-    // lane c: row c of tmat = D T with the dependent columns zeroed
-    if ((threadIdx.x & 63) < w) {
+    // lane (q, c): entries 4 v + q of row c of tmat = D T with the dependent columns zeroed
+    if (c < w) {
 #pragma unroll
-        for (int i = 0; i < W; ++i)
-            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : y[i] * dsc_own;
+        for (int v = 0; v < W / 4; ++v) {
+            const int i = 4 * v + q;
+            if (i < w) tm[(int64_t)c * w + i] = ((badmask >> i) & 1) ? 0.0 : y[v] * dsc_own;
+        }
     }
     if ((threadIdx.x & 63) == 0) {
         const int nbad = __popc(badmask & ((1 << w) - 1));
@@ -286,22 +309,23 @@ __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const doubl
 // of the wave call it.
 __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, double tol2, int* bad, double& min_piv,
                                              const double* dsc, int n_cols, Spread& spread) {
-    constexpr int W = 16;
-    const int c = threadIdx.x & 15, row = (threadIdx.x & 63) >> 4;
-    double x[W], y[W];
+    const int c = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+    doublex4 x, y;
     int badmask = (int)(__ballot(bad[c] != 0) & 0xffff);
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-        y[i] = i == c ? 1.0 : 0.0;
-        x[i] = i <= c ? blk[16 * i + c] : 0.0;
+    for (int v = 0; v < 4; ++v) {
+        const int i = 4 * v + q;
+        y[v] = i == c ? 1.0 : 0.0;
+        x[v] = i <= c ? blk[16 * i + c] : 0.0;
     }
-    factor_in_registers<W>(x, y, tol2, badmask, min_piv);
-    // lane c holds row c of T_JJ (each row of lanes writes a quarter of it)
+    double piv = 1.0, rjj;
+    factor_in_registers<16>(x, y, tol2, badmask, piv, rjj);
+    min_piv = piv < min_piv ? piv : min_piv;
+    // lane (q, c) holds entries 4 v + q of row c of T_JJ
 #pragma unroll
-    for (int i = 0; i < W; ++i)
-        if ((i >> 2) == row) tjj[kTjjStride * c + i] = y[i];
-    if (row == 0) bad[c] = (badmask >> c) & 1;
-    if (dsc) note_block<W>(spread, x, dsc[c], c < n_cols && !((badmask >> c) & 1));
+    for (int v = 0; v < 4; ++v) tjj[kTjjStride * c + 4 * v + q] = y[v];
+    if (q == 0) bad[c] = (badmask >> c) & 1;
+    if (dsc) note_block(spread, rjj, dsc[c], c < n_cols && !((badmask >> c) & 1));
 }
 
 // Cholesky factorisation and inverse of its factor in one sweep over 16 x 16 blocks: the row operations that turn A into R
@@ -311,10 +335,11 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // on the fp64 matrix cores, blocks dealt to the waves.  W_IK lives where A_KI was (row K of A is finished by then), row J
 // of R in a buffer of its own, so one triangle of blocks holds everything; every operand is read row by row, 64 consecutive
 // doubles per instruction.
-// What bounds it is the chain of 16 steps inside each diagonal block (7200 cycles of the 10000 a block takes): one wave updates
+// What bounds it is the chain of 16 steps inside each diagonal block (see factor_in_registers): one wave updates
 // and factorises block J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.
 // One workgroup on a 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion
-// (packed triangle, five barriers per block, spilling as a function call); 74 us now (128 x 128: 59), 80 x 80 58 -> 32 us.
+// (packed triangle, five barriers per block, spilling as a function call); 74 us in one sweep with row updates in the diagonal
+// blocks (128 x 128: 59; 80 x 80 58 -> 32 us), less since those are MFMAs.
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
                                     unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread) {
