@@ -17,7 +17,7 @@
 
 namespace psgd {
 hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers,
-                       const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, hipStream_t st);
+                       const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st);
 hipError_t launch_form_row(int nb, int planes, bool gbf, bool onew, int lazy, const LayerDev* layers, const int* ids,
                            int n_ids, int max_tiles, int out_role, int epi, int nt_m, const int* xtab, int xstride,
                            int xtiles, hipStream_t st);
@@ -118,6 +118,7 @@ struct psgd_ctx {
     double kernel_bytes[3] = {0.0, 0.0, 0.0};   // algorithmic bytes of the three streaming kernels of one SSP step
     int grad_kind = 0;                          // 1: every layer has fp32 gradients, 2: every layer bf16, 0: mixed
     bool nt_m = false;                          // the row-major layers' M is too large to be found in a cache again
+    bool nt_read = false;                       // ... the M of all layers
     // XCD table of the forming pass on 32 x 256 tiles (see form_row_kernel): 16 rows of xstride ints; built when the
     // row-major layers are many enough to be dealt evenly to the 8 XCDs
     std::vector<int> hXtab, hXtabC;             // (forming pass; column-mode product: other tile counts)
@@ -138,10 +139,10 @@ struct psgd_ctx {
     void* outs_ws = nullptr;     // workspace that holds the current table of decompress outputs
     void* msgd_ws = nullptr;     // ... and of the momentum and weight buffers of psgd_decompress_msgd / _adam
     void* m2_ws = nullptr;       // ... and of the second-moment buffers of psgd_decompress_adam
-// every layer's step (plain, one power iteration) or refresh runs in one workgroup that holds M in LDS (tiny.hip)
+    // every layer's step (plain, one power iteration) or refresh runs in one workgroup that holds M in LDS (tiny.hip)
     bool tiny_step = false, tiny_refresh = false;
     size_t tiny_lds = 0;
-        void* factors_ws = nullptr;  // workspace whose outer-product operand copies are the P~, Q of the last compress call
+    void* factors_ws = nullptr;  // workspace whose outer-product operand copies are the P~, Q of the last compress call
     bool factors_kept = false;   // ... a call with a deferred residual: in the layers that defer they are the kept copies
     bool tables_valid = false;
     std::vector<const void*> hG;                       // the caller's current table
@@ -643,11 +644,11 @@ struct Launcher {
         if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][1], out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
         else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
         else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, norm.tiles[kind][mode_n], out_role, ef, gate, st));
+        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, norm.tiles[kind][mode_n], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
         // (the row product of the layers stored with rows < cols stays on 128 x 64 tiles: 990 x 3741 fp32 r = 6 72.8 us per step
         // against 76.2 on 32 x 256 tiles, eight 2048 x 5632 r = 16 530 against 556, 22 of them in bf16 r = 32 1327 against 1358,
         // four 4096 x 11008 r = 64 1015 against 1089; single long ones are up to 5 % faster there, 1024 x 100000 712 and 695)
-        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, tr.tiles[kind][mode_t], out_role, ef, gate, st));
+        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, tr.tiles[kind][mode_t], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
         prof_end(k);
         // split reductions are completed (and the epilogue run) by a second, small launch, whose last
         // workgroup per layer also factorises the Gram matrix; unsplit products need a launch for that
@@ -952,15 +953,16 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
     }
     if (rc != PSGD_OK) { delete c; return rc; }
     {
-        int64_t m_bytes = 0;
+        int64_t m_bytes = 0, tr_bytes = 0;
         bool f32 = false, b16 = false;
         for (auto& p : c->plan) {
             (p.d.grad_dtype == PSGD_F32 ? f32 : b16) = true;
-            if (!p.transposed) m_bytes += p.d.rows * p.d.cols * 4;
+            (p.transposed ? tr_bytes : m_bytes) += p.d.rows * p.d.cols * 4;
         }
         c->grad_kind = f32 && b16 ? 0 : (f32 ? 1 : 2);
         // M that the second pass can find in the 256 MB memory-side cache is stored with plain stores
         c->nt_m = m_bytes > ((int64_t)96 << 20);
+        c->nt_read = m_bytes + tr_bytes > ((int64_t)96 << 20);
         if (const char* e = std::getenv("PSGD_NT_M")) c->nt_m = e[0] != '0';     // (measurement knob)
         const int n_norm = (int)c->lists.norm.size();
         if (n_norm >= 32) c->xstride = n_norm + 2;

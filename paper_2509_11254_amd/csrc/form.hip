@@ -938,8 +938,8 @@ static hipError_t launch_colprod_nb(const LayerDev* layers, const int* ids, int 
     return hipGetLastError();
 }
 
-// (width 96 with three planes: the fragments of a step and two tiles do not fit the registers)
-bool col_prod_supported(int nb, int planes) { return nb == 1 || nb == 2 || (nb == 3 && planes == 2); }
+// (width 96 with two planes: 7B-shaped block 223 us, in wide_prod_kernel 181)
+bool col_prod_supported(int nb, int) { return nb == 1 || nb == 2; }
 
 // max_tiles: max over the layers of ceil(padded cols / 256) * split[SPLIT_V2][1]; nt_s: read S with the non-temporal hint
 hipError_t launch_col_prod(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
@@ -950,7 +950,6 @@ hipError_t launch_col_prod(int nb, int planes, const LayerDev* layers, const int
                                     : launch_colprod_nb<1, 3>(layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, xtab, xstride, xtiles, st);
     if (nb == 2) return planes == 2 ? launch_colprod_nb<2, 2>(layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, xtab, xstride, xtiles, st)
                                     : launch_colprod_nb<2, 3>(layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, xtab, xstride, xtiles, st);
-    if (nb == 3 && planes == 2) return launch_colprod_nb<3, 2>(layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, xtab, xstride, xtiles, st);
     return hipErrorInvalidValue;
 }
 

@@ -662,8 +662,8 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
 // chunk's 64 reduction steps each, one barrier per chunk, and add their sums at the end (half as long: error of E against 64
 // bits 3.1e-5 -> 2.2e-5 in a refresh of 8192 x 8192 fp32 r = 128); the two waves of a SIMD multiply and split in turn.
 // Per launch, prod_kernel and this: 8192 x 8192 width 160, three planes, 163 -> 121 us either way (1.06 PFLOP/s of plane products; a
-// library product of 8192^3 in bf16 reaches 1.2), 7B-shaped block width 96, two planes, rows 241 -> 220 us.  With M straight
-// to registers 127 to 130 and 288: a load of 32 rows takes 16 bytes of each, and the lines are fetched again.  Not below
+// library product of 8192^3 in bf16 reaches 1.2), 7B-shaped block width 96, two planes, rows 241 -> 203 us and
+// columns (col_prod_kernel) 223 -> 181, of which 20 to 40 is the non-temporal hint.  With M straight to registers 127 to 130 and 288: a load of 32 rows takes 16 bytes of each, and the lines are fetched again.  Not below
 // kWideProd: blocks of 1B shape, r = 16 and 32, 1 % slower than prod_kernel, several of whose workgroups share a compute unit.
 constexpr int kWideThreads = 512;
 constexpr int kWideProd = 3;
@@ -697,7 +697,8 @@ __device__ __forceinline__ void wide_load_b(const PSGD_GLOBAL bf16_t* x0, const 
 // a wave's 32 x 32 elements of M from (r0, c0) on to LDS, row by row of 128 bytes, eight whole rows per load.  SWZ: 16-byte piece c
 // of row r is at place c ^ (r & 7) of its row, so that lanes which read one piece of 32 rows spread over all banks.
 // Pieces outside the matrix are replaced by others inside it (the caller drops them).
-template <bool SWZ>
+// AUX: cache policy (2: non-temporal)
+template <bool SWZ, int AUX>
 __device__ __forceinline__ void wide_load_a(const PSGD_GLOBAL float* S, int64_t ld, int r0, int c0, int rows, int cols, PSGD_LDS float* dst,
                                             int lane) {
     const int lr = lane >> 3, piece = (lane & 7) ^ (SWZ ? lr : 0);
@@ -705,13 +706,13 @@ __device__ __forceinline__ void wide_load_a(const PSGD_GLOBAL float* S, int64_t 
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const PSGD_GLOBAL float* src = S + (int64_t)min(r0 + 8 * p + lr, rows - 1) * ld + c;
-        __builtin_amdgcn_global_load_lds((const PSGD_GLOBAL void*)src, (PSGD_LDS void*)(dst + 256 * p), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const PSGD_GLOBAL void*)src, (PSGD_LDS void*)(dst + 256 * p), 16, 0, AUX);
     }
 }
 
 template <int NB, int PL, bool COLMODE>
 __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
-                                                                    int cp, int out_role, int epi_flags, int gate) {
+                                                                    int cp, int out_role, int epi_flags, int gate, int nt_s) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
     int copies;
@@ -747,7 +748,10 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
     PSGD_LDS float* const a_lds = (PSGD_LDS float*)(b_lds + 2 * BUF) + STAGES * 1024 * wv;       // this wave's STAGES buffers
     auto load_a = [=](int it) {
         const int k0 = chunk_at(it) * BK + 32 * h;
-        wide_load_a<!COLMODE>(S, ld, COLMODE ? k0 : tile0, COLMODE ? tile0 : k0, rows, cols, a_lds + (STAGES == 2 ? (it & 1) * 1024 : 0), lane);
+        const int r0 = COLMODE ? k0 : tile0, c0 = COLMODE ? tile0 : k0;
+        PSGD_LDS float* dst = a_lds + (STAGES == 2 ? (it & 1) * 1024 : 0);
+        if (nt_s) wide_load_a<!COLMODE, 2>(S, ld, r0, c0, rows, cols, dst, lane);
+        else wide_load_a<!COLMODE, 0>(S, ld, r0, c0, rows, cols, dst, lane);
     };
 
     floatx16 acc[NB];
@@ -1057,7 +1061,7 @@ size_t prod_lds_bytes(int nb, int planes, bool lazy = false) {
 
 template <int NB, int PL>
 static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers, const int* ids,
-                            int n_ids, int max_tiles, int out_role, int epi, int gate, hipStream_t st) {
+                            int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st) {
     if (n_ids <= 0 || max_tiles <= 0) return hipSuccess;
     dim3 grid(max_tiles, n_ids), block(kThreads);
     const size_t lds = prod_lds_bytes(NB, PL, lazy);
@@ -1091,7 +1095,7 @@ static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, const
         auto kfn = colmode ? wide_prod_kernel<NB, PL, true> : wide_prod_kernel<NB, PL, false>;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kfn, grid, dim3(kWideThreads), bytes, st, layers, ids, cp, out_role, epi, gate);
+        hipLaunchKernelGGL(kfn, grid, dim3(kWideThreads), bytes, st, layers, ids, cp, out_role, epi, gate, nt_s);
     }
     else { if (colmode) PSGD_LAUNCH(true, false); else PSGD_LAUNCH(false, false); }
 #undef PSGD_LAUNCH
@@ -1101,12 +1105,13 @@ static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, const
 // nb = width / 32 of the thin operand (1..6); planes = 2 or 3 bf16 planes per operand.
 // lazy: the forming pass also applies the pending rank-r correction (row mode, form, nb <= 4).
 // onew: every layer of the launch has one worker (forming passes only; ignored otherwise).
+// nt_s: read M with the non-temporal hint (products from width 96 on that only read it)
 hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers,
-                       const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, hipStream_t st) {
+                       const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st) {
 #define PSGD_CASE(N)                                                                                          \
     case N:                                                                                                   \
-        return planes == 2 ? launch_nb<N, 2>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, st) \
-                           : launch_nb<N, 3>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, st);
+        return planes == 2 ? launch_nb<N, 2>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st) \
+                           : launch_nb<N, 3>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st);
     switch (nb) {
         PSGD_CASE(1) PSGD_CASE(2) PSGD_CASE(3) PSGD_CASE(4) PSGD_CASE(5) PSGD_CASE(6)
         default: return hipErrorInvalidValue;
