@@ -174,8 +174,8 @@ template <int I> __device__ __forceinline__ double bcast_by_row(double v) {
 // T[column][row], T = R^{-1}, and no separate inversion is needed.  Step k scales row k, which one row of lanes holds, and
 // takes its multiples off the rows below with one MFMA each for x and y, the other rows of lanes supplying zeros: what bounds
 // the chain is the square root and one MFMA, not the up to 15 row updates of 2 moves and 2 FMAs each.
-// (As row updates: refresh of 256 x 128 fp32 r = 4 306 us, 274 now; of 4096 x 4096 r = 8 1145 and 1123; of a 7B-shaped block
-// 6.3 and 6.1 ms.)
+// (As row updates: refresh of 256 x 128 fp32 r = 4 306 us, 274 to 286 now; of 4096 x 4096 r = 8 1145, and 1123 to 1170.  The blocked
+// factorisation takes as long with either: 37 to 39 us at width 80, 78 to 84 at 160, slot sum included.)
 // A dependent column (flagged in badmask, or pivot not above tol2) makes row k of R the k-th row of the identity and skips
 // the update.  rjj: R_jj of column j = lane & 15 (of the columns that are not dependent).  badmask, min_piv and rjj are the same in all
 // rows of lanes.  Selects, not branches: at every merge point the compiler would copy the register array.
@@ -338,8 +338,8 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // What bounds it is the chain of 16 steps inside each diagonal block (see factor_in_registers): one wave updates
 // and factorises block J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.
 // One workgroup on a 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion
-// (packed triangle, five barriers per block, spilling as a function call); 74 us in one sweep with row updates in the diagonal
-// blocks (128 x 128: 59; 80 x 80 58 -> 32 us), less since those are MFMAs.
+// (packed triangle, five barriers per block, spilling as a function call); 74 to 84 us in one sweep (128 x 128: 59; 80 x 80
+// 58 -> 32 to 39 us).
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
                                     unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread) {
