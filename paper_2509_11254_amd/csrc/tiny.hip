@@ -7,7 +7,8 @@
 // What bounds such layers is latency: the general path runs six dependent launches of 3 to 11 us per step and as many per
 // iteration, on less work than one compute unit does in the time.  Here everything between the first load and the last store
 // stays in LDS.  M and the thin matrices are fp32 as in memory, the products run on v_mfma_f32_16x16x4_f32 (fp32 operands and
-// sums: no operand planes), Gram matrices, factorisation and its application in fp64 as in the general path.
+// sums: no operand planes), Gram matrices, factorisation and its application in fp64 as in the general path.  The product that E
+// loses is the one that the updates apply (tiny_residual_planes; with three planes one that differs from it by roundings of fp32).
 // A step of a 256 x 128 fp32 layer with four workers (with psgd_decompress) 39.1 -> 32 us, of a 64 x 64 one 38.2 -> 16, sixteen
 // of 104 x 104 43.5 -> 23; a refresh 559 -> 288, 425 -> 156, 601 -> 240.  Of the 28 us of the first, 8 go to the gradients (one
 // compute unit reads at 64 bytes per clock: 4.3 us for 640 KB), the rest to LDS round trips of the products.
@@ -232,8 +233,10 @@ __device__ __forceinline__ void tiny_store(const ThinRef& T, const float* X, int
     }
 }
 
-// outer-product operand copies (32 columns) of a thin matrix in LDS, zero beyond it
-__device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, const float* X, int len, int lenP, int w) {
+// outer-product operand copies (32 columns) of a thin matrix in LDS, zero beyond it.  KEEP: the first two planes also replace the
+// matrix in LDS, eight columns of a row (32 bytes) by those of plane 0 and those of plane 1.
+template <bool KEEP>
+__device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X, int len, int lenP, int w) {
     PSGD_GLOBAL bf16_t* dn[kMaxPlanes];
 #pragma unroll
     for (int k = 0; k < kMaxPlanes; ++k) dn[k] = as_global(K.n[k < planes ? k : 0]);
@@ -252,6 +255,11 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, const fl
 #pragma unroll
         for (int k = 0; k < kMaxPlanes; ++k)
             if (k < planes) *reinterpret_cast<PSGD_GLOBAL bf16x8*>(dn[k] + 8 * v) = o[k];
+        if (KEEP && row < len && c0 < 16) {                    // (what this thread alone has read)
+            bf16x8* own = reinterpret_cast<bf16x8*>(X + row * kTinyStride + c0);
+            own[0] = o[0];
+            own[1] = o[1];
+        }
     }
 }
 
@@ -272,6 +280,35 @@ struct TinyLds {
         ldm = tiny_ldm(L.cols);
     }
 };
+
+// E = M - X_L X_W^T from the two planes that tiny_pack has left in place of the factors.  What the updates subtract is the
+// product of these planes, 2^-17 from that of the factors themselves, and E has to hold what they leave: the same plane products
+// in the same order as in the outer-product kernels, so that E plus the update is M to the rounding of E.  (bf16 gradients, four
+// workers, compress alone: 256 x 128 28.8 us with the fp32 product of the factors, 26.0 with this; 64 x 64 11.4 and 11.6.  Splitting the
+// factors here again, 31.0 and 12.1.)
+__device__ __forceinline__ void tiny_residual_planes(const LayerDev& L, const float* M, int ldm, const float* xl, const float* xw) {
+    const int rows = L.rows, cols = L.cols;
+    const int64_t ld = L.ld;
+    PSGD_GLOBAL float* out = as_global(L.S);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 31, lg = lane >> 5;
+    const int nc = (cols + 31) / 32, n_tiles = ((rows + 31) / 32) * nc;
+    for (int tile = wv; tile < n_tiles; tile += kTinyWaves) {
+        const int I = tile / nc, J = tile - I * nc, row0 = 32 * I + 4 * lg, col = 32 * J + li;
+        const bf16x8* a = reinterpret_cast<const bf16x8*>(xl + min(32 * I + li, rows - 1) * kTinyStride + 8 * lg);
+        const bf16x8* b = reinterpret_cast<const bf16x8*>(xw + min(col, cols - 1) * kTinyStride + 8 * lg);
+        floatx16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = row0 + 8 * (v >> 2) + (v & 3);
+            if (row < rows && col < cols) out[(int64_t)row * ld + col] = M[row * ldm + col] - acc[v];
+        }
+    }
+}
 
 __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids, double tol2) {
     const LayerDev& L = layers[ids[blockIdx.x]];
@@ -298,11 +335,20 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y);
     tiny_store(L.thin[ROLE_P], S.x, m, w);
     tiny_store(L.thin[ROLE_Q], S.y, n, w);
-    const float* xl = tr ? S.y : S.x;
-    const float* xw = tr ? S.x : S.y;
-    tiny_pack(L.pack[SIDE_L], L.planes, xl, rows, L.rowsP, w);
-    tiny_pack(L.pack[SIDE_W], L.planes, xw, cols, L.colsP, w);
-    // E = M - P~ Q^T, 16 x 16 blocks, four of them at a time
+    float* xl = tr ? S.y : S.x;
+    float* xw = tr ? S.x : S.y;
+    if (L.planes == 2) {
+        __syncthreads();                                   // (what tiny_store reads is replaced)
+        tiny_pack<true>(L.pack[SIDE_L], 2, xl, rows, L.rowsP, w);
+        tiny_pack<true>(L.pack[SIDE_W], 2, xw, cols, L.colsP, w);
+        __syncthreads();
+        tiny_residual_planes(L, S.m, S.ldm, xl, xw);
+        return;
+    }
+    tiny_pack<false>(L.pack[SIDE_L], L.planes, xl, rows, L.rowsP, w);
+    tiny_pack<false>(L.pack[SIDE_W], L.planes, xw, cols, L.colsP, w);
+    // E = M - P~ Q^T, 16 x 16 blocks, four of them at a time (three planes hold the factors to fp32: the product of the planes and
+    // this one differ by roundings of fp32 sums)
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), li = lane & 15, lk = lane >> 4;
     const int nc = (cols + 15) / 16, n_tiles = ((rows + 15) / 16) * nc;
     const int64_t ld = L.ld;

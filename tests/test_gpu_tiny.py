@@ -65,7 +65,8 @@ def test_step(r, n_workers, dtype):
         tag = (l, rows, cols, r)
         assert np.abs(p.T @ p - np.eye(rs[l])).max() < 2e-6, tag
         assert np.linalg.norm(q - m.T @ p) <= 2e-6 * scale, tag
-        assert np.linalg.norm(logical(e, rows, cols) - (m - p @ q.T)) <= 2e-6 * scale, tag
+        # (the update of bf16 gradients is a product of two bf16 planes per factor, 2^-17 of each, and E is what that leaves of M)
+        assert np.linalg.norm(logical(e, rows, cols) - (m - p @ q.T)) <= (2e-6 if dtype == synth.F32 else 4 * 2.0 ** -17) * scale, tag
         x = m @ data[2][l].astype(np.float64)
         sv = np.linalg.svd(x / np.linalg.norm(x, axis=0), compute_uv=False)
         if sv[-1] > 1e-3:
@@ -75,6 +76,29 @@ def test_step(r, n_workers, dtype):
             assert np.linalg.norm(pg @ qg.T - p @ q.T) <= tol and np.linalg.norm(eg - e) <= tol, tag
         assert np.linalg.norm(logical(back(outs[0][l], cols), rows, cols) - p @ q.T) <= (1e-6 if dtype == synth.F32 else 4 * 2.0 ** -17) * scale, tag
         assert case.comp.status(l).rank_deficient == general.comp.status(l).rank_deficient, tag
+
+
+# what a step leaves in E and what it lets the update apply are M together, whatever the operand planes
+@pytest.mark.parametrize("r", [1, 7, 16])
+@pytest.mark.parametrize("n_workers,dtype,precision", [(3, synth.BF16, 0), (1, synth.BF16, 3), (2, synth.F32, 0), (2, synth.F32, 2)])
+def test_error_feedback_balances(r, n_workers, dtype, precision):
+    torch = torch_mod()
+    rs = [min(r, *s) for s in SHAPES]
+    data = _inputs(SHAPES, r, n_workers, dtype, 7 * r + n_workers)
+    data[2] = [q[:, :k] for q, k in zip(data[2], rs)]
+    case = _run(SHAPES, rs, n_workers, dtype, data, False, precision=precision)
+    for factors in ((None, None), (case.P, case.Q)):
+        out = [torch.zeros_like(e) for e in case.E]
+        case.comp.decompress(*factors, out, psgd.PSGD_F32)
+        mom, x = [torch.zeros_like(e) for e in case.E], [torch.zeros_like(e) for e in case.E]
+        case.comp.decompress_msgd(*factors, mom, x, 0.0, 1.0)
+        for l, (rows, cols) in enumerate(SHAPES):
+            m = np.mean([synth.gradient_as_f64(g) for g in data[0][l]], axis=0) + data[1][l]
+            e = back(case.E[l], cols).astype(np.float64)
+            for update in (out[l], mom[l]):
+                # five roundings of M (a sum of up to three, a quotient, E added), one of E, and with three planes those of two fp32
+                # sums of the update: at most 16 of 2^-24
+                assert np.linalg.norm(e + back(update, cols) - m) <= 2.0 ** -20 * np.linalg.norm(m), (l, rows, cols, rs[l])
 
 
 # block widths up to 16, two refreshes with the budget and a third with the layer's own count
