@@ -818,15 +818,16 @@ __device__ inline void jacobi_rotation_ahead(const double* a, int n, int rd, int
 // H is stored by POSITION in the tournament, not by matrix index: the 2 x 2 block (slot k1) x (slot k2) sits at
 // the same LDS addresses in every round, is rotated by the two slots' rotations, and its four entries are written
 // to where the tournament moves their row and column players.  Source and destination addresses of a thread's
-// blocks are therefore computed once; a round is: read and rotate (registers), and beside it the next round's
-// rotations, which the last threads work out from the same entries for themselves | barrier | write, and V <- V J on the
-// columns the slots hold | barrier.  (The rotations after the write, behind a barrier of their own, were a quarter of a
-// narrow round and a tenth of a wide one: width 160 2.49 -> 2.22 ms, width 80 570 -> 510 us at the same sweeps.)
+// blocks are therefore computed once.  A round in two orders:
+//   AHEAD   read and rotate (registers), and beside it the next round's rotations, which the last threads work out from the same
+//           entries for themselves | barrier | write, and V <- V J on the columns the slots hold | barrier
+//   else    read and rotate | barrier | write | barrier | the next round's rotations from the new diagonal blocks, while the other
+//           waves run V <- V J | barrier
+// The second hides the rotations behind the update of V where that is long, and leaves all threads to H (see launch_jacobi).
 // V stays indexed by matrix index.
 // NBLK: 2 x 2 blocks of H per thread, at least (w/2)(w/2 + 1)/2 over the h_threads first threads of the workgroup, which update H.
-// The others have nothing to do but the rotations: beside blocks of their own they would be the last at the barrier (width
-// 160: 2.45 ms).
-template <int NBLK>
+// With AHEAD the others have nothing to do but the rotations: beside blocks of their own they would be the last at the barrier.
+template <int NBLK, bool AHEAD>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
                                                       int slot_rows, int h_threads, float* __restrict__ sigma_out) {
@@ -881,11 +882,11 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
         const int total = (half * (half + 1)) / 2;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) {
-            const int e = t + b * h_threads;
+            const int e = t + b * (AHEAD ? h_threads : nt);
             bk[b] = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) adr[b][q] = 0;
-            if (t < h_threads && e < total) {
+            if ((!AHEAD || t < h_threads) && e < total) {
                 const int dk = e / half, k1 = e - dk * half;
                 int k2 = k1 + dk;
                 k2 -= k2 >= half ? half : 0;
@@ -902,8 +903,8 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             }
         }
     }
-    // the slot whose rotations this thread works out a round ahead (-1: none)
-    const int slot = nt - 1 - t < half ? nt - 1 - t : -1;
+    // (AHEAD) the slot whose rotations this thread works out (-1: none)
+    const int slot = AHEAD && nt - 1 - t < half ? nt - 1 - t : -1;
     const int prev_top = slot < 0 ? 0 : jacobi_prev_pos(2 * slot, n), prev_bottom = slot < 0 ? 0 : jacobi_prev_pos(2 * slot + 1, n);
     __syncthreads();
     int cur = 0, sweeps = 0;
@@ -931,7 +932,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             const double* cs = csb + cur * n;
             const int* pq = pqb + cur * n;
             // H <- J^T H J on this thread's blocks: rows by slot k1's rotation, columns by slot k2's
-            if (slot >= 0 && rd + 1 < n - 1)
+            if (AHEAD && slot >= 0 && rd + 1 < n - 1)
                 jacobi_rotation_ahead(a, n, rd + 1, slot, prev_top, prev_bottom, cs, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             double o[NBLK][4];
 #pragma unroll
@@ -958,6 +959,10 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
                 a[adr[b][1] >> 16] = o[b][1];
                 if (!diag) a[adr[b][2] >> 16] = o[b][2];
                 a[adr[b][3] >> 16] = o[b][3];
+            }
+            if constexpr (!AHEAD) {
+                __syncthreads();
+                if (rd + 1 < n - 1 && t < half) jacobi_rotation(a, n, rd + 1, t, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             }
             for (int i = ty; i < nv; i += tyw)
                 for (int k = tx; k < half; k += txw) {
@@ -1081,16 +1086,21 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     // three to five blocks per thread the kernel spills a few registers; 512 threads with twice the registers measured slower.)
     const int threads = w <= 48 ? 256 : 1024;
     dim3 grid((n + v_rows - 1) / v_rows, n_ids), block(threads);
-    int h_threads = threads - 64 * ((n / 2 + 63) / 64);
-    if (n_blocks > 5 * h_threads) h_threads = threads;
+    // Rotations ahead or not.  One layer, us per sweep at the same number of sweeps, otherwise and ahead: width 48 48.0 and 42.5, 64 61
+    // and 57, 80 96.5 and 88.5, 112 163 and 142, 128 205 and 192, 144 301 and 260, 152 352 and 341; from 160 on the threads that are
+    // left for H hold a block more each, 160 357 and 367, 176 536 and 675.  With more than 16 rows of V per workgroup their
+    // update hides the rotations: width 80, 80 rows (256 layers) 183 and 198; 96, 24 rows 146 and 158; 128, 16 rows 262 and 257, 32
+    // rows 273 and 306.  Up to width 48 it is ahead with any number of rows (48, 48 rows 84 and 79).
+    const bool ahead = w <= 48 || (w <= 152 && v_rows <= 16);
+    const int h_threads = ahead ? threads - 64 * ((n / 2 + 63) / 64) : threads;
     const int per_thread = (n_blocks + h_threads - 1) / h_threads;
     void (*kfn)(const LayerDev*, const int*, int, int, int, int, float*) = nullptr;
     switch (per_thread) {
-        case 1: kfn = jacobi_kernel<1>; break;
-        case 2: kfn = jacobi_kernel<2>; break;
-        case 3: kfn = jacobi_kernel<3>; break;
-        case 4: kfn = jacobi_kernel<4>; break;
-        case 5: kfn = jacobi_kernel<5>; break;
+        case 1: kfn = ahead ? jacobi_kernel<1, true> : jacobi_kernel<1, false>; break;
+        case 2: kfn = ahead ? jacobi_kernel<2, true> : jacobi_kernel<2, false>; break;
+        case 3: kfn = ahead ? jacobi_kernel<3, true> : jacobi_kernel<3, false>; break;
+        case 4: kfn = ahead ? jacobi_kernel<4, true> : jacobi_kernel<4, false>; break;
+        case 5: kfn = ahead ? nullptr : jacobi_kernel<5, false>; break;
         default: break;
     }
     if (!kfn) return hipErrorInvalidValue;

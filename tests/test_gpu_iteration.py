@@ -120,3 +120,24 @@ def test_second_pass_after_the_iteration(r, shapes):
         # Ritz vectors: Q = M^T P~ has orthogonal columns in falling order (H = Y^T Y of the Y that goes with the final Z)
         h = q.T @ q
         assert np.abs(h - np.diag(np.diag(h))).max() <= 4e-6 * h[0, 0] and np.all(np.diff(np.diag(h)) <= 4e-6 * h[0, 0]), l
+
+
+# The Rayleigh-Ritz step's rotations, worked out a round ahead or behind the update: widths on both sides of the rule (48, 152 and 160; odd;
+# more blocks than threads), with few rows of the eigenvectors per workgroup (one layer) and with many (a batch)
+@pytest.mark.parametrize("w,n_layers", [(48, 64), (57, 1), (57, 90), (104, 36), (104, 43), (152, 1), (152, 28), (160, 1), (160, 20), (176, 1)])
+def test_ritz_step_of_any_width(w, n_layers):
+    rng = np.random.default_rng(100 * w + n_layers)
+    rows, cols, r = 240, 57 if w == 57 else 200, w - 8
+    u, _ = np.linalg.qr(rng.standard_normal((rows, cols)))
+    v, _ = np.linalg.qr(rng.standard_normal((cols, cols)))
+    s = 0.97 ** np.arange(cols)
+    s[r:] *= 0.3                                                # a gap at the cut
+    mats = [((u[rng.permutation(rows)] * s) @ v.T).astype(np.float32) for _ in range(n_layers)]
+    case = Case([(rows, cols)] * n_layers, r, 1, synth.F32, lds=[(cols + 7) // 8 * 8] * n_layers, refresh_oversample=8)
+    case.upload([[x] for x in mats], [np.zeros((rows, cols), np.float32)] * n_layers,
+                [rng.standard_normal((cols, r)).astype(np.float32) for _ in mats])
+    case.compress(refresh=True)
+    for l in {0, n_layers // 2, n_layers - 1}:
+        _check_refreshed_step(mats[l].astype(np.float64), *case.outputs(l), r, (w, n_layers, l))
+        st = case.comp.status(l)
+        assert abs(st.sigma_max - 1.0) < 1e-5 and abs(st.sigma_r - s[r - 1]) < 1e-5, (w, l, st.sigma_max, st.sigma_r)
