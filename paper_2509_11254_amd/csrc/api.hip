@@ -57,7 +57,7 @@ hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, 
                              int src_role, int warm, uint32_t seed, hipStream_t st);
 hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st);
-bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays);
+bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays, bool refresh);
 size_t tiny_lds_bytes(int64_t rows, int64_t cols);
 hipError_t launch_tiny_step(const LayerDev* layers, const int* ids, int n_ids, size_t lds, double tol2, hipStream_t st);
 hipError_t launch_tiny_iterate(const LayerDev* layers, const int* ids, int n_ids, size_t lds, double tol2, int iters, int warm,
@@ -945,8 +945,8 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         c->tiny_step = !c->lazy && !c->reform_m && c->opt.power_iters <= 1;
         c->tiny_refresh = true;
         for (const auto& p : c->plan) {
-            c->tiny_step = c->tiny_step && tiny_fits(p.d.rows, p.d.cols, p.d.r, n_workers + 1);
-            c->tiny_refresh = c->tiny_refresh && tiny_fits(p.d.rows, p.d.cols, p.wz, 1);
+            c->tiny_step = c->tiny_step && tiny_fits(p.d.rows, p.d.cols, p.d.r, n_workers + 1, false);
+            c->tiny_refresh = c->tiny_refresh && tiny_fits(p.d.rows, p.d.cols, p.wz, n_workers + 1, true);
             c->tiny_lds = std::max(c->tiny_lds, tiny_lds_bytes(p.d.rows, p.d.cols));
         }
         c->lazy_tr = c->lazy && c->cpc == 32;

@@ -1090,7 +1090,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     // and 57, 80 96.5 and 88.5, 112 163 and 142, 128 205 and 192, 144 301 and 260, 152 352 and 341; from 160 on the threads that are
     // left for H hold a block more each, 160 357 and 367, 176 536 and 675.  With more than 16 rows of V per workgroup their
     // update hides the rotations: width 80, 80 rows (256 layers) 183 and 198; 96, 24 rows 146 and 158; 128, 16 rows 262 and 257, 32
-    // rows 273 and 306.  Up to width 48 it is ahead with any number of rows (48, 48 rows 84 and 79).
+    // rows 273 and 306 (the other way round: 80, 40 rows 146 and 142).  Up to width 48 it is ahead with any number of rows (48, 48 rows 84 and 79).
     const bool ahead = w <= 48 || (w <= 152 && v_rows <= 16);
     const int h_threads = ahead ? threads - 64 * ((n / 2 + 63) / 64) : threads;
     const int per_thread = (n_blocks + h_threads - 1) / h_threads;

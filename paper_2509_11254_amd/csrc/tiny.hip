@@ -22,7 +22,7 @@ constexpr int kTinyStride = 16;                        // floats per row of a th
 constexpr int kTinyGramWaves = 4;                      // waves that share the rows of a Gram matrix
 constexpr size_t kTinyScratch = kTinyGramWaves * 256 * sizeof(double);
 constexpr size_t kTinyLds = 160 * 1024;
-constexpr int64_t kTinyElements = 400000;
+constexpr int64_t kTinyStepElements = 400000, kTinyRefreshElements = 2400000, kTinyRefreshAlways = 8192;
 
 // Row stride of M in LDS: whole 16-byte pieces, an odd number of them, so that 16 rows times 4 columns (the A operand of M Y) lie
 // in 64 different banks
@@ -43,10 +43,16 @@ __host__ __device__ inline TinyLayout tiny_layout(int rows, int cols) {
     t.end = t.flags + 16;
     return t;
 }
-// Whether a layer's step fits (r: widest thin matrix of it).  n_arrays: matrices of its size that the step reads, over which one
-// compute unit must not take longer than the general path's launches (256 x 128: 18 matrices 46.7 us against 46.1, 6 29 against 39)
-bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays) {
-    if (r > kCholRegWidth || n_arrays * rows * cols > kTinyElements || rows * cols > (int64_t)(kTinyLds / sizeof(float))) return false;
+// Whether a layer's step, or refresh, fits (r: widest thin matrix of it).  n_arrays: gradients and E, which one compute unit reads at
+// 0.08 to 0.1 ns per element: not longer than the general path's launches take.  256 x 128 fp32, us: step, 8 workers 33 against 41, 11
+// workers 42.4 and 42.8.  A refresh has more launches to save, and a general launch over a matrix of kTinyRefreshAlways elements is
+// one or two workgroups, which take as long per worker: 256 x 128 at two iterations, 64 workers 309 against 350, 96 398 and 398, 128
+// 481 and 440 (bf16 96 379 and 390, 128 456 and 386); 200 x 160 96 403 and 429, 128 491 and 472; 128 x 128 256 workers 566 and 616;
+// 64 x 64 301 and 578.  Not the number of layers, one workgroup each: 256 x 128, one worker, step of 1, 256, 4096 layers 26,
+// 37, 599 against 37, 102, 1250, refreshes at two iterations 170, 259, 2600 against 365, 812, 8250; 64 x 64 10, 13, 178 against 36, 65, 522.
+bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays, bool refresh) {
+    if (r > kCholRegWidth || rows * cols > (int64_t)(kTinyLds / sizeof(float))) return false;
+    if (refresh ? n_arrays * (rows * cols - kTinyRefreshAlways) > kTinyRefreshElements : n_arrays * rows * cols > kTinyStepElements) return false;
     return tiny_layout((int)rows, (int)cols).end <= kTinyLds;
 }
 

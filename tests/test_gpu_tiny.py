@@ -122,6 +122,16 @@ def test_refresh(r, n_workers, dtype):
             _check_refreshed_step(m, p, q, logical(e, rows, cols), rs[l], (t, l, rows, cols, r))
 
 
+# the most workers whose gradients one workgroup reads, and one more (the general path)
+@pytest.mark.parametrize("rows,cols,n_workers", [(256, 128, 96), (256, 128, 97), (128, 256, 97), (64, 24, 260)])
+def test_refresh_of_many_workers(rows, cols, n_workers):
+    data = _inputs([(rows, cols)], 4, n_workers, synth.F32, n_workers)
+    case = _run([(rows, cols)], [4], n_workers, synth.F32, data, True)
+    m = np.mean([g.astype(np.float64) for g in data[0][0]], axis=0) + data[1][0]
+    p, q, e = case.outputs(0)
+    _check_refreshed_step(logical(m, rows, cols), p, q, logical(e, rows, cols), 4, (rows, cols, n_workers))
+
+
 # a start block out of order (the factorisation of Z asks for an orthonormal Y), one with two columns 1e-6 apart (the second
 # CholeskyQR pass), and columns that depend on each other
 @pytest.mark.parametrize("rows,cols", [(200, 150), (150, 200)])
