@@ -417,7 +417,7 @@ def run_workload(name, args, primary):
 
     # ---- roofline of the dominant kernel: the first streaming pass (reads N gradients + E, writes M; with the
     # deferred residual also the kept factors of the step before).  Event pairs recorded inside the timed region;
-    # the SSP-only loop is the fallback when the timed region held no SSP step.
+    # the SSP-only loop is the fallback when the timed region held no SSP step.  (Small layers: the one launch of the whole step.)
     mode = "lazy" if lazy else "plain"
     s1_ms, s1_n = prof["sweep1"] if prof["sweep1"][1] > 0 else per_kernel[mode]["sweep1"]
     per_launch_ms = s1_ms / max(1, s1_n)

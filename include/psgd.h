@@ -262,7 +262,9 @@ double psgd_algorithmic_bytes(const psgd_ctx *ctx);
 
 /* Algorithmic HBM bytes of one launch of a streaming kernel of psgd_compress over all layers, under the
  * context's m_policy (tag = PSGD_PROF_SWEEP1 / _SWEEP2 / _RESIDUAL): matrix bytes read and written + the
- * packed thin operands.  What a measured kernel duration is divided into for the roofline. */
+ * packed thin operands.  What a measured kernel duration is divided into for the roofline.  Where psgd_compress is one
+ * launch (see psgd_compress), SWEEP1 is that launch, with all that the step reads and writes; SWEEP2 and RESIDUAL are then
+ * those of psgd_compress_finish. */
 double psgd_kernel_bytes(const psgd_ctx *ctx, int tag);
 
 /* Plain device copy kernel (dst <- src, n_bytes multiple of 16) used to calibrate profiler counters
@@ -271,7 +273,7 @@ int psgd_copy_bytes(void *stream, void *dst, const void *src, size_t n_bytes);
 
 /* Timing of the three streaming kernels of psgd_compress with HIP event pairs recorded on the
  * caller's stream around each launch: tag 0 = first pass (M formed, P = M Q), tag 1 = second pass
- * (Q = M^T P~), tag 2 = residual.  psgd_profile_enable allocates max_records event pairs (0 turns
+ * (Q = M^T P~), tag 2 = residual; where psgd_compress is one launch, tag 0 = the whole step.  psgd_profile_enable allocates max_records event pairs (0 turns
  * timing off and frees them); once they are used up further launches are not timed.
  * psgd_profile_read waits for the recorded events, adds the elapsed milliseconds and the number of
  * records per tag into total_ms[0..n_tags) / count[0..n_tags) (host arrays), and resets the pool. */

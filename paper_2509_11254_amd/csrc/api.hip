@@ -1023,7 +1023,13 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         // product's own fragments: q_resident, row-major layers)
         const double kept_q = 4.0 * (double)p.d.cols * 32.0 * ((p.d.r + 31) / 32);
         const bool shared_q = deferred && c->opt.q_resident == 1 && !p.transposed;
-        c->kernel_bytes[0] += e * (nsg + 4.0 + (c->reform_m ? 0.0 : 4.0)) + thin * (deferred ? 2.0 : 1.0) - (shared_q ? kept_q : 0.0);
+        if (c->tiny_step) {
+            // (one launch: gradients, E and Q read; E, P~, Q and the operand copies of both written.  The other tags are the launches of
+            // psgd_compress_finish)
+            c->kernel_bytes[0] += e * (nsg + 8.0) + 4.0 * (p.m + 2.0 * p.n) * p.d.r + 64.0 * c->planes * (p.rowsP + p.colsP);
+        } else {
+            c->kernel_bytes[0] += e * (nsg + 4.0 + (c->reform_m ? 0.0 : 4.0)) + thin * (deferred ? 2.0 : 1.0) - (shared_q ? kept_q : 0.0);
+        }
         c->kernel_bytes[1] += e * (c->reform_m ? nsg + 4.0 : 4.0) + thin;
         if (!deferred) c->kernel_bytes[2] += e * (c->reform_m ? nsg + 8.0 : 8.0) + thin;
     }

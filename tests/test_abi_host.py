@@ -163,3 +163,13 @@ def test_struct_layouts_match_the_header(tmp_path):
                                                       psgd.PSGD_E_HIP, psgd.PSGD_E_NOMEM, psgd.PSGD_E_CAPTURE,
                                                       psgd.PSGD_E_TOO_LARGE]
     assert int(out["static_ws"]) == psgd.STATIC_WORKSPACE_BYTES
+
+
+def test_kernel_bytes_of_a_one_launch_step():
+    """256 x 128 fp32, r = 4, four workers: the step's one launch reads four gradients, E and Q and writes E, P~, Q and their operand
+    copies (three planes, 32 columns, lengths padded to 128); the same layer with a deferred residual has its passes."""
+    comp = psgd.Compressor([(256, 128, 4, psgd.PSGD_F32)], 4, allocate=False)
+    matrix, thin, copies = 4 * 256 * 128, 4 * 4, 3 * 2 * 32 * (256 + 128)
+    assert comp.kernel_bytes("sweep1") == 6 * matrix + thin * (128 + 256 + 128) + copies
+    lazy = psgd.Compressor([(256, 128, 4, psgd.PSGD_F32)], 4, lazy_residual=True, allocate=False)
+    assert lazy.kernel_bytes("sweep1") > 6 * matrix and lazy.kernel_bytes("residual") == 0
