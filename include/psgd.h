@@ -106,7 +106,8 @@ typedef struct {
     int32_t precision;          /* bf16 planes per fp32 operand of the matrix-core products: 2 = three
                                    products per term (16 mantissa bits), 3 = six products (24 bits,
                                    fp32-faithful); 0 = default: 3 if any layer has fp32 gradients,
-                                   else 2                                                            */
+                                   else 2.  The products of small layers (see psgd_compress) do without
+                                   planes, the updates' P~ Q^T has them in every case                 */
     int32_t m_policy;           /* where M = mean G + E lives between the passes of an SSP step: 1 = stored
                                    over E by the first pass, 2 = formed again from G and E by every pass
                                    (E is only written by the residual; fewer bytes never, equal bytes for
@@ -121,7 +122,8 @@ typedef struct {
                                    operand copies of P~_t and Q_t aside in the workspace, and the forming pass of
                                    the next psgd_compress subtracts their product on the way (same arithmetic:
                                    E_{t+1} is rounded to fp32 before it enters M_{t+1}).  P~, Q and every later
-                                   result are those of the immediate form; the E buffers hold E_{t+1} only after
+                                   result are those of the immediate form (of small layers to the precision of
+                                   the planes, see psgd_compress); the E buffers hold E_{t+1} only after
                                    psgd_flush_residual (psgd_compress_refresh settles it by itself).  Saves the
                                    8 bytes per element of the residual pass.  Not with m_policy = 2; r <= 128.
                                    0 = default: immediate residual                                        */
@@ -169,7 +171,12 @@ int psgd_workspace_reset(psgd_ctx *ctx);
  *   E[l] <- M - P~ Q[l]^T;  P[l] <- P~.
  * G: n_layers*n_workers read-only device pointers (layer-major), element type grad_dtype.
  * E: n_layers fp32 buffers rows x cols (ld), updated in place.  Q: n x r fp32, in Q_{t-1}, out Q_t.
- * P: m x r fp32, out.  Errors: INVALID_ARG (null table or entry), ALIGN (pointer alignment), HIP. */
+ * P: m x r fp32, out.  Errors: INVALID_ARG (null table or entry), ALIGN (pointer alignment), HIP.
+ * Small layers: where every layer of the context has r <= 16, fits a compute unit's LDS with its thin matrices (256 x 128 does) and has
+ * at most 400000 elements in its gradients and E, and with the default m_policy, power_iters and residual, the step is one
+ * launch and its two products are formed from fp32 operands, not from bf16 planes.  P~ and Q then differ from those of the
+ * other forms of the step (deferred residual, the two halves, m_policy = 2) by the planes' 2^-17 where there are two of them, by
+ * roundings of fp32 where there are three.  E is what the updates leave of M in every form. */
 int psgd_compress(psgd_ctx *ctx, void *workspace, void *stream, const void *const *G,
                   float *const *E, float *const *Q, float *const *P);
 
@@ -196,7 +203,7 @@ int psgd_compress_static(psgd_ctx *ctx, void *stream, const void *const *G, floa
  *   -- the caller averages P over the workers (an all-reduce) and hands every worker the mean --
  *   finish:  P[l] <- P~ = QR(P[l]);  Q[l] <- M^(i)T P~;  E[l] <- e^(i)_{t+1} = M^(i) - P~ Q[l]^T.
  *   -- the caller averages Q over the workers: Q_t --
- * With one worker, project followed by finish is psgd_compress.  Same buffers, layouts and errors as psgd_compress;
+ * With one worker, project followed by finish is psgd_compress (of small layers to the precision of the planes, see there).  Same buffers, layouts and errors as psgd_compress;
  * INVALID_ARG with lazy_residual, m_policy = 2 or power_iters > 1 (the halves assume M stored over E once). */
 int psgd_compress_project(psgd_ctx *ctx, void *workspace, void *stream, const void *const *G,
                           float *const *E, float *const *Q, float *const *P);
