@@ -25,11 +25,11 @@ bool form_row_supported(int nb, int planes, bool gbf, bool onew, bool lazy);
 hipError_t launch_col_prod(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
                            int out_role, int epi, int gate, int nt_s, const int* xtab, int xstride, int xtiles,
                            hipStream_t st);
-bool col_prod_supported(int nb, int planes);
+bool col_prod_supported(int nb);
 hipError_t launch_row_prod(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
                            int out_role, int epi, int gate, int nt_s, const int* xtab, int xstride, int xtiles,
                            hipStream_t st);
-bool row_prod_supported(int nb, int planes);
+bool row_prod_supported(int nb);
 hipError_t launch_outer(int nb, int planes, bool decomp, bool form, bool kept, const LayerDev* layers, const int* ids,
                         int n_ids, int max_tiles, int rpw, void* const* outs, int out_bf16, hipStream_t st);
 hipError_t launch_max_iterations(const LayerDev* layers, const int* ids, int n_ids, int mx, int* out, hipStream_t st);
@@ -207,7 +207,7 @@ bool form_row_env() {
 // operand width 32 nb.  lazy: a forming pass that also applies the owed residual.
 bool on_wide_tiles(const psgd_ctx* c, bool p_like, bool form, int nb, bool lazy) {
     if (!form_row_env()) return false;
-    if (!form) return p_like ? row_prod_supported(nb, c->planes) : col_prod_supported(nb, c->planes);
+    if (!form) return p_like ? row_prod_supported(nb) : col_prod_supported(nb);
     return p_like && c->grad_kind != 0 && form_row_supported(nb, c->planes, c->grad_kind == 2, c->n_workers == 1, lazy);
 }
 
@@ -289,10 +289,13 @@ int target_tiles_env() {
 // to add up grow with the width, and the wide product kernels do not gain from more workgroups (4096 x 4096: the step at
 // r = 64 takes 0.325 ms with 1024 workgroups, 0.302 with 256; at r = 128 0.514 and 0.473; at r = 16 and 32 it is
 // the other way round).
-// Two per compute unit where their operand buffers fit its LDS twice (two planes up to width 128): 8192 x 8192 bf16 r = 128
-// 534 -> 517 us per step, 2048 x 6000 r = 100 237 -> 228; with three planes one fits, and 4096 x 4096 fp32 r = 128 takes 307 us
-// with 512 workgroups against 288.  run: the width the products run at, wider than the step's cp in a refresh's iteration
-// (8192 x 8192 bf16 r = 128 at width 160: 6.38 ms with 512 workgroups, 6.18 with 256; 2048 x 8192 r = 104 4.52 and 4.36).
+// Two per compute unit with two planes up to width 128: where a compute unit has room for two (the forming pass, and the products
+// that only read M up to width 96), and at width 128 also for the latter, of which one fits, for their shorter walks.  8192 x 8192 bf16
+// r = 128, us per step with 512 and 256 of them: 413 and 399, 4096 x 4096 216 and 203, 8192 x 2048 r = 110 208 and 194, but four
+// 4096 x 4096 438 and 464, three 11008 x 4096 r = 100 873 and 884, the 14 matrices of two 1B-shaped blocks 751 and 765, and with 256
+// the error of Q is up to a tenth larger (3.99e-7 and 4.03e-7, 4.46e-7 and 4.92e-7).  With three planes one fits, and 4096 x 4096
+// fp32 r = 128 took 307 us with 512 workgroups against 288.  run: the width the products run at, wider than the step's cp in a
+// refresh's iteration (8192 x 8192 bf16 r = 128 at width 160: 6.38 ms with 512 workgroups, 6.18 with 256; 2048 x 8192 r = 104 4.52 and 4.36).
 int split_target(bool form, int cp, int run, int planes) {
     int target = target_tiles_env();
     if (target == 0) target = cp >= 64 ? (planes == 2 && run <= 128 ? 2 : 1) * kTargetTilesWide : (form ? kTargetTiles : kTargetTilesPlain);

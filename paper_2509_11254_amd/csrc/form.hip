@@ -939,7 +939,7 @@ static hipError_t launch_colprod_nb(const LayerDev* layers, const int* ids, int 
 }
 
 // (width 96 with two planes: 7B-shaped block 223 us, in wide_prod_kernel 181)
-bool col_prod_supported(int nb, int) { return nb == 1 || nb == 2; }
+bool col_prod_supported(int nb) { return nb == 1 || nb == 2; }
 
 // max_tiles: max over the layers of ceil(padded cols / 256) * split[SPLIT_V2][1]; nt_s: read S with the non-temporal hint
 hipError_t launch_col_prod(int nb, int planes, const LayerDev* layers, const int* ids, int n_ids, int max_tiles,
@@ -971,7 +971,7 @@ static hipError_t launch_rowprod_nb(const LayerDev* layers, const int* ids, int 
 
 // (not at width 96: every 32 rows fetch the thin operand again, 12 bytes from L2 per 4 bytes of S with two planes,
 // and the pass is L2-bound there: 7.1 ms on the 7B-shaped set against 6.4 for prod_kernel's 128-row tiles)
-bool row_prod_supported(int nb, int planes) { (void)planes; return nb == 1 || nb == 2; }
+bool row_prod_supported(int nb) { return nb == 1 || nb == 2; }
 
 // thin[out_role] = S X on row-major layers, S read only.  max_tiles, xtab, xstride, xtiles as for launch_form_row;
 // gate: iteration gate of the refresh (-1: none)
