@@ -125,7 +125,8 @@ typedef struct {
                                    result are those of the immediate form (of small layers to the precision of
                                    the planes, see psgd_compress); the E buffers hold E_{t+1} only after
                                    psgd_flush_residual (psgd_compress_refresh settles it by itself).  Saves the
-                                   8 bytes per element of the residual pass.  Not with m_policy = 2; r <= 128.
+                                   8 bytes per element of the residual pass (small layers, see psgd_compress, are
+                                   faster without it).  Not with m_policy = 2; r <= 128.
                                    0 = default: immediate residual                                        */
     int32_t q_resident;         /* 1: the caller promises not to write the Q buffers between one compress-type call
                                    on a workspace and the next psgd_compress on it (a single-GPU loop; not a
