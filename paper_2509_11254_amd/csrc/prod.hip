@@ -212,13 +212,45 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
 
 // Epilogue on a complete ROWS x cp output tile held in LDS as fp32 [ROWS][tw]: store the rows of the
 // thin result, then either the partial Gram matrix of these rows (fp64, upper triangle, slot = block
-// index) or the split-bf16 operand copies of the rows.  Called by all NT threads of the workgroup.
+// index) or the split-bf16 operand copies of the rows.  shift: subtract that multiple of the rows being replaced first.
+// Called by all NT threads of the workgroup.
 template <int ROWS, int NT = kThreads>
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
-                                     int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
-                                     int copies = 3, double* red = nullptr) {
+                                     int out_lenP, int cp, int epi, float* otile, int tw, bool kept = false,
+                                     int copies = 3, double* red = nullptr, double shift = 0.0) {
     const int t = threadIdx.x;
     const int w = T.width;
+    if (shift != 0.0) {
+        // the rows hold what they are replaced by, the Z of the iteration before (see iteration_shift)
+        const PSGD_GLOBAL float* old = as_global(T.ptr) + (int64_t)ob * ROWS * T.ld;
+        const int n_rows = min(ROWS, out_len - ob * ROWS);
+        const float inv_w = 1.0f / (float)w;
+        if (T.ld == w && (w & 3) == 0) {
+            for (int e0 = 4 * t; e0 < n_rows * w; e0 += 16 * NT) {
+                floatx4 z[4];
+#pragma unroll
+                for (int d = 0; d < 4; ++d) z[d] = *reinterpret_cast<const PSGD_GLOBAL floatx4*>(old + (e0 + 4 * d * NT < n_rows * w ? e0 + 4 * d * NT : e0));
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const int e = e0 + 4 * d * NT;
+                    if (e >= n_rows * w) continue;
+                    int row = (int)(((float)e + 0.5f) * inv_w);
+                    int c = e - row * w;
+                    if (c < 0) { --row; c += w; } else if (c >= w) { ++row; c -= w; }
+                    float* o = otile + row * tw + c;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[q] = (float)((double)o[q] - shift * (double)z[d][q]);
+                }
+            }
+        } else {
+            for (int e = t; e < n_rows * w; e += NT) {
+                const int row = e / w, col = e % w;
+                float& o = otile[row * tw + col];
+                o = (float)((double)o - shift * (double)old[(int64_t)row * T.ld + col]);
+            }
+        }
+        __syncthreads();
+    }
     if (copies != 2) {
         PSGD_GLOBAL float* dst = as_global(T.ptr) + (int64_t)ob * ROWS * T.ld;
         const int n_rows = min(ROWS, out_len - ob * ROWS);
@@ -651,7 +683,7 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
             otile[row * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+    tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, nullptr, FORM ? 0.0 : iteration_shift(L, out_role, gate));
 }
 
 // The products that only read M from kWideProd blocks of 32 columns on.  A workgroup of prod_kernel has a compute unit (nearly) to
@@ -882,7 +914,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
             for (int v = 0; v < 16; ++v) otile[(32 * rg + 8 * (v >> 2) + 4 * lg + (v & 3)) * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
+    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, nullptr, iteration_shift(L, out_role, gate));
 }
 
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
@@ -896,15 +928,16 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
 // chol_gate >= -1: the last workgroup to finish a layer goes on to factorise the sum of the partial Gram
 // matrices (first CholeskyQR pass) if that gate is open, unless the layer is one where the apply kernel
 // does that for itself; -2: no factorisation follows, or one in a launch of its own.
+// ITER: inside the subspace iteration (gate >= 0), with its shift and notes.
 static_assert(BT == kGramRows1, "one partial Gram matrix per output block of a product");
-template <int FB, int NT>
+template <int FB, int NT, bool ITER>
 __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__ layers,
                                                     const int* __restrict__ ids, int p_like, int cp,
                                                     int out_role, int epi_flags, int gate, int chol_gate,
                                                     int a2gate, double tol2, int local_ok, int kind_n, int kind_t) {
     __shared__ int s_last;
     const LayerDev& L = layers[ids[blockIdx.y]];
-    if (!gate_open(L, gate)) return;
+    if (ITER && !gate_open(L, gate)) return;
     int copies;
     const int epi = resolve_epilogue(L, epi_flags, gate, copies);
     const int colmode = (p_like != 0) == (L.transposed != 0);
@@ -975,13 +1008,13 @@ __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__
     }
     __syncthreads();
     double* red = FB == BT && T.width <= 16 ? reinterpret_cast<double*>(smem + (((size_t)FB * tw * sizeof(float) + 7) & ~(size_t)7)) : nullptr;
-    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red);
+    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red, ITER ? iteration_shift(L, out_role, gate) : 0.0);
     // (FB = 64 is for widths whose factorisation is a launch of its own)
     if constexpr (FB == BT) {
-        if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && gate_open(L, chol_gate)) {
+        if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && (!ITER || gate_open(L, chol_gate))) {
             const int n_wg = (out_len + FB - 1) / FB;      // = number of Gram slots
             if (last_to_arrive(&L.status[6], n_wg, &s_last))
-                chol_body(L, out_role, tol2, 1, FB, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, scales_next(L, out_role, chol_gate));
+                chol_body(L, out_role, tol2, 1, FB, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, ITER ? iteration_notes(L, out_role, chol_gate) : 0, nullptr, chol_gate & 0xff);
         }
     }
 }
@@ -1039,7 +1072,8 @@ hipError_t launch_finish(bool p_like, int kind_n, int kind_t, const LayerDev* la
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
     const int fb = finish_rows(w > 0 ? w : cp);
     dim3 grid(max_blocks * (BT / fb), n_ids), block(fb == BT ? kThreads : 2 * kThreads);
-    auto kfn = fb == BT ? finish_kernel<BT, kThreads> : finish_kernel<BT / 2, 2 * kThreads>;
+    auto kfn = fb == BT ? (gate >= 0 ? finish_kernel<BT, kThreads, true> : finish_kernel<BT, kThreads, false>)
+                        : (gate >= 0 ? finish_kernel<BT / 2, 2 * kThreads, true> : finish_kernel<BT / 2, 2 * kThreads, false>);
     size_t lds = (size_t)fb * (cp + 1) * sizeof(float);
     if (fb == BT) lds += 8 + (kThreads / 64) * 256 * sizeof(double);            // (layers of widths up to 16: see gram_tile_f64)
     if (chol_gate >= -1 && chol_lds_bytes_upto(w) > lds) lds = chol_lds_bytes_upto(w);

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ l
     if (pass == 1 && local_chol(L, role, local_ok)) return;       // the apply kernel factorises for itself
     extern __shared__ __align__(16) unsigned char smem[];
     chol_body(L, role, tol2, pass, L.transposed ? slot_rows_t : slot_rows_n, allow2_of(L, a2gate), smem, L.tmat, true, nullptr,
-              pass == 1 && scales_next(L, role, gate));
+              pass == 1 ? iteration_notes(L, role, gate) : 0, nullptr, gate & 0xff);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
         const int rows1 = L.transposed ? kGramRows1 : slot_rows;
         gram2 += (int64_t)((len + rows1 - 1) / rows1) * ntri;
         chol_body<true>(L, role, tol2, 1, rows1, allow2_of(L, a2gate), smem + main_lds + w * w * sizeof(double),
-                        tml, blockIdx.x == 0, &s_need2, ITER && scales_next(L, role, gate));
+                        tml, blockIdx.x == 0, &s_need2, ITER ? iteration_notes(L, role, gate) : 0, nullptr, gate & 0xff);
         __syncthreads();
         need2 = s_need2;
         tm = tml;
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const LayerDev* __restr
         gram_tile_f64(so, ow, kGramRows2, w, gram2 + (int64_t)blockIdx.x * ntri);
         const int n_wg = (len + kGramRows2 - 1) / kGramRows2;
         if (last_to_arrive(&L.status[7], n_wg, &s_last))
-            chol_body<true>(L, role, tol2, 2, kGramRows2, false, smem, L.tmat, true, nullptr, false, gram2);
+            chol_body<true>(L, role, tol2, 2, kGramRows2, false, smem, L.tmat, true, nullptr, 0, gram2);
     } else if (do_pack) {
         write_packs(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
     }
@@ -830,7 +830,7 @@ __device__ inline void jacobi_rotation_ahead(const double* a, int n, int rd, int
 template <int NBLK, bool AHEAD>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
-                                                      int slot_rows, int h_threads, float* __restrict__ sigma_out) {
+                                                      int slot_rows, int h_threads, int budget, float* __restrict__ sigma_out) {
     __shared__ int s_ke;
     __shared__ double s_sum;
     const LayerDev& L = layers[ids[blockIdx.y]];
@@ -1003,8 +1003,8 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
     const int r = L.r;
     // Iterations for a cut without a gap (see refresh_iterations).  Where the count that the subspace needs is out of
     // reach, what is asked of the step is its error (Lemma 2 / Eq. (6): ||M - P~ P~^T M||^2 = sum_{i > r} sigma_i^2
-    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= (theta_b / theta_i)^k after k
-    // iterations from any start (theta: Ritz values = squared singular value estimates), costs at most
+    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= rho^3 (rho / (2 - rho))^(k - 3), rho = theta_b / theta_i,
+    // after k iterations from any start (theta: Ritz values = squared singular value estimates; three of them are not shifted), costs at most
     // sin^2(theta_i) (theta_i - theta_b) on top of the optimum: the directions well above the cut cost nothing after
     // two iterations, the ones in the cluster at the cut have little to lose.  The count is the smallest k for which
     // the sum of these is below 1e-5 of ||M||^2 >= sum of the Ritz values: a tenth of the 1e-4 the step is held to,
@@ -1023,7 +1023,10 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             double part = 0.0;
             for (int i = t; i < r; i += nt) {
                 const double li = L.eval[i];
-                if (lb > 0.0 && li > lb) part += pow(lb / li, 2.0 * k) * (li - lb);
+                if (lb > 0.0 && li > lb) {
+                    const double rho = lb / li;
+                    part += pow(rho, 2.0 * k) * pow(2.0 - rho, -2.0 * max(k - kPlainIterations, 0)) * (li - lb);
+                }
             }
             if (part > 0.0) atomicAdd(&s_sum, part);
             __syncthreads();
@@ -1043,19 +1046,28 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
         if (k == r - 1) L.status[3] = __float_as_int(sg);
     }
     if (t == 0) {
-        // The iteration contracts the error of the leading r-dimensional subspace by about
-        // rho = (theta_b / theta_r)^2 per step (theta = Ritz values, the smallest one of the block standing
-        // in for sigma_{b+1}); the next refresh of this layer needs as many steps as 1e-5 takes (a tenth of
+        // The iteration contracts the error of the leading r-dimensional subspace by about rho = theta_b / theta_r per plain
+        // step and rho / (2 - rho) per shifted one (theta = Ritz values, the smallest one of the block standing
+        // in for sigma_{b+1}^2); the next refresh of this layer needs as many steps as 1e-5 takes (a tenth of
         // the 1e-4 bar on the subspace), plus one.  (Error feedback drives M towards rho = 1: what is not
-        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)
+        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)  A cut counts as one
+        // without a gap where plain steps would be more than the option asks for: of 7B-shaped layers in such a run most need
+        // 17 to 25 plain steps or 12 to 14 shifted ones, and their error needs 4 or 5 (a block of them 6.0 ms per refresh, 6.5
+        // with as many as converge).
         int k_next = 255;
         const double lr = L.eval[r - 1], lb = L.eval[w - 1];
         if (w > r && lr > 0.0 && lb >= 0.0) {
             const double rho = lb / lr;
-            if (rho < 0.999) k_next = (rho <= 1e-12) ? 2 : (int)ceil(log(1e-5) / log(rho)) + 1;
+            if (rho < 0.999) {
+                const double plain = log(fmax(rho, 1e-12)), left = log(1e-5) - kPlainIterations * plain;
+                const int unshifted = rho <= 1e-12 ? 2 : (int)ceil(log(1e-5) / plain) + 1;
+                k_next = left >= 0.0 || unshifted > budget ? unshifted
+                                                           : kPlainIterations + (int)ceil(left / (plain - log(2.0 - rho))) + 1;
+            }
         }
         L.status[4] = max(2, min(255, k_next));
         L.status[9] = s_ke;
+        L.status[11] = 0;
         L.status[5] = sweeps;
         L.status[8] = min(L.status[8] + 1, 1 << 20);
     }
@@ -1067,7 +1079,8 @@ size_t jacobi_lds_bytes(int w, int v_rows) {
 }
 
 // slot_rows: rows per partial Gram matrix of thin[role] (kOneSlot: gram_sum_kernel has added them up)
-hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
+// budget: iterations that the option refresh_iters asks for
+hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int budget, float* sigma_out,
                          hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const int n = (w + 1) & ~1;
@@ -1094,7 +1107,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
     const bool ahead = w <= 48 || (w <= 152 && v_rows <= 16);
     const int h_threads = ahead ? threads - 64 * ((n / 2 + 63) / 64) : threads;
     const int per_thread = (n_blocks + h_threads - 1) / h_threads;
-    void (*kfn)(const LayerDev*, const int*, int, int, int, int, float*) = nullptr;
+    void (*kfn)(const LayerDev*, const int*, int, int, int, int, int, float*) = nullptr;
     switch (per_thread) {
         case 1: kfn = ahead ? jacobi_kernel<1, true> : jacobi_kernel<1, false>; break;
         case 2: kfn = ahead ? jacobi_kernel<2, true> : jacobi_kernel<2, false>; break;
@@ -1109,7 +1122,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, h_threads, sigma_out);
+    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, h_threads, budget, sigma_out);
     return hipGetLastError();
 }
 

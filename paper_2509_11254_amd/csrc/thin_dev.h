@@ -31,6 +31,7 @@ __host__ __device__ inline int chol_groups(int w) {
 // beside them and the vectors fit a workgroup's 160 KB, i.e. up to 11 blocks = 176; beyond that a packed triangle without
 // blocking.
 constexpr int kCholMaxBlocks = 11;
+constexpr int kMaxWaveColumns = 3;     // columns of the widest block per lane of one wave
 constexpr int kTjjStride = 17;         // row stride of the diagonal block's inverse (doubles)
 __host__ __device__ inline bool chol_is_blocked(int w) { return w > kCholRegWidth && (w + 15) / 16 <= kCholMaxBlocks; }
 // LDS bytes chol_body needs
@@ -221,6 +222,45 @@ __device__ __forceinline__ void note_block(Spread& spread, double rjj, double ds
     spread.add_block(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp((rjj * norm) * (rjj * norm)), counts);
 }
 
+// The state behind the shift of the subspace iteration (see iteration_shift): in the layer's eval and status words, or in the
+// registers of the wave that factorises (scale: of column lane & 15).
+struct IterationState {
+    double c = 0.0, scale = 1.0;
+    int shifted = 0, asks = 0, ends = 0;
+    bool shifts = false;                // this iteration's product is shifted by c / 2
+};
+constexpr double kLargest = 1e300;
+// minimum over the 16 lanes of a row of lanes; over the wave
+__device__ inline double min_lane16(double v) {
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) v = fmin(v, __shfl_xor(v, d));
+    return v;
+}
+__device__ inline double min_wave(double v) {
+    v = min_lane16(v);
+    v = fmin(v, __shfl_xor(v, 16));
+    return fmin(v, __shfl_xor(v, 32));
+}
+// What a factorisation tells the next iterations, by one wave.  low, low_r: smallest growth of all columns and of the first r
+// (NOTE_FIRST_Y: smallest R_jj^2).  Called before status[10] is rewritten.
+__device__ inline void note_iteration(const LayerDev& L, int note, int it, double low, double low_r, bool dependent, bool asks, IterationState* own) {
+    const bool first_y = (note & NOTE_FIRST_Y) != 0, shifts = (note & NOTE_SHIFTS) != 0;
+    const double c0 = own ? own->c : L.eval[L.wz], x = shifts ? 0.5 * c0 : 0.0;
+    const int shifted = first_y ? 0 : (own ? own->shifted : L.status[12]) + (x > 0.0 ? 1 : 0);
+    const double c = dependent ? 0.0 : first_y ? low : shifts ? x + low : c0;
+    const int ends = shifts && !dependent && !asks ? converged_after(L.planes, min(L.rows, L.cols), it, c, x + low_r, shifted) : 0;
+    if (own) {
+        own->c = c;
+        own->shifted = shifted;
+        own->asks = asks ? 1 : 0;
+        own->ends = ends;
+    } else if ((threadIdx.x & 63) == 0) {
+        L.eval[L.wz] = c;
+        L.status[12] = shifted;
+        if (ends > 0) L.status[11] = ends;
+    }
+}
+
 // Start block of the subspace iteration beyond the columns of the warm start: uniform in (-1, 1) from a counter-based hash of
 // (seed, layer, row, column).
 __device__ inline uint32_t mix32(uint32_t x) {
@@ -245,8 +285,8 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
 // w .. W-1 are those of an identity matrix.
 template <int W>
 __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                           bool allow2, double* tm, bool write_status, int* need2_out, bool scale,
-                                           int* asks_out) {
+                                           bool allow2, double* tm, bool write_status, int* need2_out, int note,
+                                           int it, IterationState* own) {
     const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
     const int jc = c < w ? c : 0;
     const double djj = g[tri_idx(jc, jc, w)];
@@ -263,10 +303,23 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     double min_piv = 1.0, rjj;
     factor_in_registers<W>(x, y, tol2, badmask, min_piv, rjj);
     Spread spread;
-    if (scale) {                                          // (uniform: every lane takes part in the broadcasts)
-        const double csc = next_scale(dsc_own);
+    const bool good = c < w && !((badmask >> c) & 1);
+    const double csc = next_scale(dsc_own);
+    if (note & NOTE_SCALE) {                              // (uniform: every lane takes part in the broadcasts)
         static_for<0, 4>([&](auto vc) { constexpr int v = decltype(vc)::value; y[v] *= bcast_by_row<4 * v>(csc); });
-        note_block(spread, rjj, dsc_own, c < w && !((badmask >> c) & 1));
+        note_block(spread, rjj, dsc_own, good);
+    }
+    if (note && (write_status || own)) {
+        // (own: the caller keeps the state in registers, lane c column c's)
+        const double norm = rjj * __builtin_amdgcn_rcp(good ? dsc_own : 1.0);
+        const double prev = own ? own->scale : (note & NOTE_SHIFTS) ? L.eval[jc] : 1.0;
+        const double grew = good ? (note & NOTE_FIRST_Y ? norm * norm : norm / prev) : kLargest;
+        note_iteration(L, note, it, min_lane16(grew), min_lane16(c < L.r ? grew : kLargest), (badmask & ((1 << w) - 1)) != 0,
+                       (note & NOTE_SCALE) && spread.asks(L.planes, min_piv), own);
+        if (note & NOTE_SCALE) {
+            if (own) own->scale = csc;
+            else if ((threadIdx.x & 63) < w) L.eval[jc] = csc;
+        }
     }
     // lane (q, c): entries 4 v + q of row c of tmat = D T with the dependent columns zeroed
     if (c < w) {
@@ -280,12 +333,11 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
         const int nbad = __popc(badmask & ((1 << w) - 1));
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
-        if (scale && asks_out) *asks_out = spread.asks(L.planes, min_piv) ? 1 : 0;
         if (write_status) {
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
-                if (scale) L.status[10] = spread.asks(L.planes, min_piv) ? 1 : 0;
+                if (note & NOTE_SCALE) L.status[10] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
@@ -293,14 +345,14 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     }
 }
 
-// asks_out: optional LDS word that receives, with `scale`, whether Y is to be orthonormalised (also status[10])
+// note: see IterationNote (it: the iteration); own: the iteration's state where the caller keeps it
 __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
-                                         bool allow2, double* tm, bool write_status, int* need2_out, bool scale,
-                                         int* asks_out = nullptr) {
-    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
-    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
-    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
-    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, scale, asks_out);
+                                         bool allow2, double* tm, bool write_status, int* need2_out, int note, int it = 0,
+                                         IterationState* own = nullptr) {
+    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
+    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
+    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
+    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
 }
 
 // Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers: factorises the block `blk` (row-major,
@@ -341,8 +393,10 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // (packed triangle, five barriers per block, spilling as a function call); 74 to 84 us in one sweep (128 x 128: 59; 80 x 80
 // 58 -> 32 to 39 us).
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
+// growth(inverse R_jj of the scaled matrix, column scaling, column dependent): called by wave 0 at the end, for column j = lane + 64 u.
+template <class Growth>
 __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_slots, int64_t sstr, int w, double tol2, bool scale,
-                                    unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread) {
+                                    unsigned char* smem, double* __restrict__ tm, int& nbad, double& min_piv, Spread& spread, Growth&& growth) {
     const int nbk = (w + 15) / 16, wp = 16 * nbk, nblk = (nbk * (nbk + 1)) / 2;
     double* a = reinterpret_cast<double*>(smem);          // blocks (I, K), K >= I, row by row, each [16][16]
     double* rj = a + nblk * 256;                          // [nbk] blocks: row J of R
@@ -476,8 +530,10 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
         __syncthreads();
     }
     nbad = 0;
-    if (wv == 0)
+    if (wv == 0) {
         for (int i0 = 0; i0 < w; i0 += 64) nbad += __popcll(__ballot(i0 + lane < w && bad[i0 + lane] != 0));
+        growth([&](int j) { return at(j >> 4, j >> 4)[17 * (j & 15)]; }, dsc, bad);
+    }
 }
 
 // Layers whose factorisation is cheap enough for every workgroup of the apply kernel to repeat it for
@@ -495,14 +551,14 @@ __device__ inline bool local_chol(const LayerDev& L, int role, int local_ok) {
 // Called by all threads of one workgroup per layer (256 or 1024: a multiple of 256 and a power of two); smem:
 // chol_lds_bytes(w), 8-byte aligned.
 // tm: where the w x w factor goes (the layer's tmat, or LDS of the caller); need2_out: optional LDS word
-// that receives the second-pass decision; write_status: whether this caller owns the layer's status words; scale: Z of the
-// subspace iteration, see scales_next (powers of two next to its columns' scaling, and whether Y is to be orthonormalised).
+// that receives the second-pass decision; write_status: whether this caller owns the layer's status words; note, it: iteration_notes
+// of the subspace iteration.
 // gram_at: where the partial Gram matrices are (the layer's gram by default).
 // NARROW: compiled for widths <= 16 only (the register path; nothing else is generated).
 template <bool NARROW = false>
 __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double tol2, int pass, int slot_rows, bool allow2,
                                  unsigned char* smem, double* tm, bool write_status = true,
-                                 int* need2_out = nullptr, bool scale = false, const double* gram_at = nullptr) {
+                                 int* need2_out = nullptr, int note = 0, const double* gram_at = nullptr, int it = 0) {
     const int side = side_of_role(L.transposed, role);
     const int n_slots = (side_len(L, side) + slot_rows - 1) / slot_rows;      // (kOneSlot: one, the sum of all)
     const int w = L.thin[role].width;
@@ -519,7 +575,32 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     const int t = threadIdx.x;
     const int nt = blockDim.x, nty = nt >> 4;             // threads, rows of the 16-wide thread grid
     const double* __restrict__ gram = gram_at ? gram_at : L.gram;
+    const bool scale = (note & NOTE_SCALE) != 0;
+    // (wave 0) the growth of its columns, and what follows from it; the scales of the iteration before are requested at the start
+    double prev[kMaxWaveColumns];
+    if constexpr (!NARROW) {
+#pragma unroll
+        for (int u = 0; u < kMaxWaveColumns; ++u) prev[u] = t < 64 && (note & NOTE_SHIFTS) ? as_global(L.eval)[min(t + 64 * u, w - 1)] : 1.0;
+    }
+    double low = kLargest, low_r = kLargest;
+    auto growth = [&](auto&& inverse_of, const double* dsc, const int* bad) {
+        if (note == 0) return;
+#pragma unroll
+        for (int u = 0; u < kMaxWaveColumns; ++u) {
+            const int j = t + 64 * u;
+            if (j >= w) continue;
+            if (!bad[j]) {
+                const double norm = 1.0 / (inverse_of(j) * dsc[j]), grew = note & NOTE_FIRST_Y ? norm * norm : norm / prev[u];
+                low = fmin(low, grew);
+                if (j < L.r) low_r = fmin(low_r, grew);
+            }
+            if (scale) as_global(L.eval)[j] = next_scale(dsc[j]);
+        }
+        low = min_wave(low);
+        low_r = min_wave(low_r);
+    };
     auto outcome = [&](int nbad, double min_piv, const Spread& spread) {
+        if (note && write_status) note_iteration(L, note, it, low, low_r, nbad > 0, scale && spread.asks(L.planes, min_piv), nullptr);
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
         if (write_status) {
@@ -537,7 +618,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
             int nbad = 0;
             double min_piv = 1.0;
             Spread spread;
-            chol_blocked(gram, n_slots, sstr, w, tol2, scale, smem, tm, nbad, min_piv, spread);
+            chol_blocked(gram, n_slots, sstr, w, tol2, scale, smem, tm, nbad, min_piv, spread, growth);
             if (t == 0) outcome(nbad, min_piv, spread);   // (wave 0 has factorised the diagonal blocks)
             return;
         }
@@ -623,7 +704,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     }
     __syncthreads();
     if (w <= kCholRegWidth) {
-        if (t < 64) chol_in_registers(L, a, w, tol2, pass, allow2, tm, write_status, need2_out, scale);
+        if (t < 64) chol_in_registers(L, a, w, tol2, pass, allow2, tm, write_status, need2_out, note, it);
         return;
     }
     if constexpr (NARROW) return;
@@ -693,6 +774,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
             tm[(int64_t)i * w + j] = v * dsc[i] * (scale ? next_scale(dsc[j]) : 1.0);
         }
     }
+    if (t < 64) growth([&](int j) { return rdiag[j]; }, dsc, bad);
     if (t == 0) {
         int nbad = 0;
         for (int i = 0; i < w; ++i) nbad += bad[i];

@@ -121,7 +121,12 @@ __device__ __forceinline__ void tiny_form(const LayerDev& L, float* M, int ldm) 
 // X (m x w) = A Y, A(i, k) = M[i si + k sk] (m x n), Y (n x w): a wave per 16 rows, the operands of the next 16 steps of the reduction
 // requested before the products of these.  fp32 sums run over 16 steps, their sums in pairs are fp64: with fp32 sums over a quarter of
 // the reduction the result was 8 % further from 64 bits than that of the split operands' longer accumulators.
-__device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X) {
+// fine: fp64 sums of single accumulators of 8 steps, for the last two products of a refresh.  One that ends when it has converged leaves its columns
+// less settled, which the Rayleigh-Ritz step makes up for with another rounding of both factors (error of E against 64 bits 6.3e-7
+// after 16 iterations, 6.8e-7 after 7, and 6.4e-7 with these sums; in all products they take 3 % longer).
+// shift: X <- A Y - shift X
+__device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X, double shift = 0.0,
+                                         bool fine = false) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
     int oa[4];
 #pragma unroll
@@ -148,7 +153,12 @@ __device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, 
             c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[2], bc[2], c1, 0, 0, 0);
             c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[1], bc[1], c0, 0, 0, 0);
             c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[3], bc[3], c1, 0, 0, 0);
-            if ((k0 & 16) || k0 + 16 >= n16) {
+            if (fine) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[v] += (double)c0[v] + (double)c1[v];
+                c0 = zero;
+                c1 = zero;
+            } else if ((k0 & 16) || k0 + 16 >= n16) {
                 const floatx4 c = c0 + c1;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sum[v] += (double)c[v];
@@ -166,7 +176,10 @@ __device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * tile + 4 * lk + v;
-            if (row < m) X[row * kTinyStride + li] = (float)sum[v];       // (columns from w on: zero)
+            if (row >= m) continue;
+            float& x = X[row * kTinyStride + li];
+            if (shift != 0.0) sum[v] -= shift * (double)x;
+            x = (float)sum[v];                             // (columns from w on: zero)
         }
     }
     __syncthreads();
@@ -271,8 +284,8 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X
 
 struct TinyLds {
     float *m, *x, *y;
-    double *tm, *gram;
-    int *need2, *asks;
+    double *tm, *gram, *shift;
+    int *need2, *asks_ends;                                // asks_ends: IterationState::asks + 2 ends
     int ldm;
     __device__ TinyLds(const LayerDev& L, unsigned char* smem) {
         const TinyLayout t = tiny_layout(L.rows, L.cols);
@@ -282,7 +295,8 @@ struct TinyLds {
         tm = reinterpret_cast<double*>(smem + t.tm);
         gram = reinterpret_cast<double*>(smem + t.gram);
         need2 = reinterpret_cast<int*>(smem + t.flags);
-        asks = need2 + 1;
+        asks_ends = need2 + 1;
+        shift = reinterpret_cast<double*>(smem + t.flags + 8);
         ldm = tiny_ldm(L.cols);
     }
 };
@@ -332,7 +346,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x);
     for (int pass = 1; pass <= 2; ++pass) {
         tiny_gram(S.x, m, w, reinterpret_cast<double*>(S.y), S.gram);
-        if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1, S.tm, true, S.need2, false);
+        if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1, S.tm, true, S.need2, 0);
         __syncthreads();
         const bool again = *S.need2 != 0;
         tiny_apply(S.x, m, w, S.tm);
@@ -398,7 +412,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
     extern __shared__ __align__(16) unsigned char smem[];
     const TinyLds S(L, smem);
     const int tr = L.transposed, rows = L.rows, cols = L.cols, m = tr ? cols : rows, n = tr ? rows : cols, w = L.wz, t = threadIdx.x;
-    const int k_iters = refresh_iterations(L, iters);      // (read before anything is stored)
+    int k_iters = refresh_iterations(L, iters);            // (read before anything is stored)
     {
         const ThinRef Q = L.thin[ROLE_Q];
         const PSGD_GLOBAL float* q = as_global(Q.ptr);
@@ -411,24 +425,42 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
     if (L.gdt == 0) tiny_form<false, true>(L, S.m, S.ldm); else tiny_form<true, true>(L, S.m, S.ldm);
     __syncthreads();
     const int sl = tr ? 1 : S.ldm, ss = tr ? S.ldm : 1;
+    IterationState state;                                  // (wave 0's)
+    double shift = 0.0;
+    bool asked = false;
 #pragma unroll 1
     for (int it = 0; it < k_iters; ++it) {
-        const bool last = it == k_iters - 1;
-        tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x);
+        const bool last = it == k_iters - 1, may_shift = it > kOrthYIterations && !last && !asked;
+        tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x, may_shift ? shift : 0.0, last);
 #pragma unroll 1
         for (int pass = 1; pass <= 2; ++pass) {
             tiny_gram(S.x, m, w, reinterpret_cast<double*>(S.y), S.gram);
-            if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, !last && it >= kOrthYIterations, S.asks);
+            if (t < 64) {
+                const int note = pass == 2 || last || it < kOrthYIterations ? 0 : may_shift ? NOTE_SCALE | NOTE_SHIFTS : NOTE_SCALE;
+                chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, note, it, &state);
+                if (note && t == 0) { *S.asks_ends = state.asks + 2 * state.ends; *S.shift = 0.5 * state.c; }
+            }
             __syncthreads();
             const bool again = *S.need2 != 0;
             tiny_apply(S.x, m, w, S.tm);
             if (!again) break;
         }
-        tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y);
-        if (!last && (it < kOrthYIterations || *S.asks != 0)) {
+        if (it >= kOrthYIterations && !last) {
+            asked = (*S.asks_ends & 1) != 0;
+            const int ends = *S.asks_ends >> 1;
+            if (ends > 0 && ends < k_iters) k_iters = ends;
+            shift = *S.shift;
+        }
+        tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y, 0.0, last);
+        if (!last && (it < kOrthYIterations || asked)) {
+            // (the Gram scratch overwrites Z: the next product is not shifted)
             tiny_gram(S.y, n, w, reinterpret_cast<double*>(S.x), S.gram);
-            if (t < 64) chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, false);
+            if (t < 64) {
+                chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, it == 0 ? NOTE_FIRST_Y : 0, it, &state);
+                if (it == 0 && t == 0) *S.shift = 0.5 * state.c;
+            }
             __syncthreads();
+            if (it == 0) shift = *S.shift;
             tiny_apply(S.y, n, w, S.tm);
         }
     }

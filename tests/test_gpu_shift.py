@@ -1,0 +1,101 @@
+"""The shift of the refresh's subspace iteration and the end of an iteration that has converged, against the same iteration
+without either in fp64."""
+import numpy as np
+import pytest
+
+from oracle import psgd_oracle as orc
+from paper_2509_11254_amd import synth
+from gpu_harness import Case
+
+pytestmark = pytest.mark.gpu
+
+SEED = 11
+
+
+def _spectrum_matrix(rng, rows, cols, s):
+    k = len(s)
+    u, _ = np.linalg.qr(rng.standard_normal((rows, k)))
+    v, _ = np.linalg.qr(rng.standard_normal((cols, k)))
+    return ((u * s) @ v.T).astype(np.float32)
+
+
+def _plain_excess(m, start, r, iters):
+    """What `iters` iterations Z = orth(M Y), Y = M^T Z and the Rayleigh-Ritz step leave above the optimum of Eq. (6)."""
+    y = start
+    for _ in range(iters):
+        z, _ = np.linalg.qr(m @ y)
+        y = m.T @ z
+    theta = np.linalg.svd(y, compute_uv=False)
+    return np.sum(np.linalg.svd(m, compute_uv=False)[:r] ** 2) - np.sum(theta[:r] ** 2)
+
+
+# No gap at the cut: the (fewer) shifted iterations leave no more than 16 without shift.  Block widths 16 (in one launch; with
+# the factorisation in the apply kernel), 24 (by finish_kernel), 40, 96, 160 (a launch of its own) and 184 (not blocked);
+# both orientations, odd sizes, products split and, in a batch, not
+@pytest.mark.parametrize("rows,cols,r,b,n_layers", [(200, 150, 8, 16, 1), (150, 200, 8, 16, 1), (520, 333, 8, 16, 1), (333, 520, 8, 16, 1),
+                                                    (520, 400, 8, 16, 70), (640, 333, 16, 24, 1), (500, 408, 32, 40, 1), (408, 500, 32, 40, 1),
+                                                    (500, 408, 32, 40, 70), (700, 512, 76, 96, 1), (512, 700, 76, 96, 1),
+                                                    (900, 640, 128, 160, 1), (640, 520, 144, 184, 1)])
+@pytest.mark.parametrize("planes", [2, 3])
+def test_no_gap(rows, cols, r, b, n_layers, planes):
+    rng = np.random.default_rng(rows + 7 * r)
+    n = min(rows, cols)
+    # falls by a twentieth from the r-th value to the one after the block, and on at that rate
+    s = 0.95 ** (np.arange(n) / (b - r))
+    mats = [_spectrum_matrix(rng, rows, cols, s) for _ in range(min(n_layers, 2))]
+    mats = [mats[l % len(mats)] for l in range(n_layers)]
+    warm = [rng.standard_normal((n, r)).astype(np.float32) for _ in range(min(n_layers, 2))]
+    warm = [warm[l % len(warm)] for l in range(n_layers)]
+    case = Case([(rows, cols)] * n_layers, r, 1, synth.F32, lds=[(cols + 7) // 8 * 8] * n_layers, precision=planes, seed=SEED)
+    case.upload([[x] for x in mats], [np.zeros((rows, cols), np.float32)] * n_layers, warm)
+    case.compress(refresh=True)
+    for l in {0, n_layers - 1}:
+        m = mats[l].astype(np.float64)
+        m = m if rows >= cols else m.T
+        p, q, e = case.outputs(l)
+        norm2 = np.sum(m ** 2)
+        start = np.concatenate([warm[l].astype(np.float64), orc.counter_uniform(SEED, l, n, b)[:, r:]], axis=1)
+        plain, fewer = _plain_excess(m, start, r, 16), _plain_excess(m, start, r, 14)
+        tail = np.sum(np.linalg.svd(m, compute_uv=False)[r:] ** 2)
+        excess = np.sum(e ** 2) - tail
+        print(rows, cols, r, "excess / ||M||^2", excess / norm2, "plain, 16 iterations", plain / norm2, "14", fewer / norm2)
+        # E = M - P~ Q^T is off by 2^-17 (three planes 2^-24) of ||M|| in directions of its own: 2^-16 ||M|| ||E|| at most
+        slack = 2.0 ** (-22 if planes == 3 else -16) * norm2
+        assert fewer > 1.1 * plain
+        assert excess <= 1.05 * plain + slack
+        assert np.abs(p.T @ p - np.eye(r)).max() < 2e-6
+        assert np.linalg.norm(q - m.T @ p) <= 2e-5 * np.sqrt(norm2)
+        assert case.comp.status(l).rank_deficient == 0
+
+
+# A gap that the iteration crosses long before its budget ends, from a random start: the subspace is what fp32 products leave
+# of it.  Also where the columns after the gap have nothing to line up with (rank r, dependent columns: no shift) and where one
+# direction stands far above the rest.
+@pytest.mark.parametrize("rows,cols,r,n_layers", [(200, 150, 8, 1), (640, 333, 8, 1), (333, 640, 8, 70), (500, 408, 32, 1), (700, 512, 76, 1)])
+@pytest.mark.parametrize("kind", ["gap", "close_gap", "rank", "outlier"])
+def test_ends_when_converged(rows, cols, r, n_layers, kind):
+    rng = np.random.default_rng(rows + 7 * r)
+    n = min(rows, cols)
+    s = np.linspace(2.0, 1.0, n)
+    if kind == "rank":
+        s = s[:r]
+    else:
+        s[r:] *= 0.3 if kind == "close_gap" else 0.1
+        if kind == "outlier":
+            s[0] = 100.0
+    mat = _spectrum_matrix(rng, rows, cols, s)
+    m = mat.astype(np.float64) if rows >= cols else mat.T.astype(np.float64)
+    u, sv, _ = np.linalg.svd(m, full_matrices=False)
+    case = Case([(rows, cols)] * n_layers, r, 1, synth.F32, lds=[(cols + 7) // 8 * 8] * n_layers, seed=SEED)
+    case.upload([[mat]] * n_layers, [np.zeros((rows, cols), np.float32)] * n_layers, [rng.standard_normal((n, r)).astype(np.float32)] * n_layers)
+    for _ in range(2):
+        case.compress(refresh=True)
+        for l in {0, n_layers - 1}:
+            p, q, e = case.outputs(l)
+            e = e if rows >= cols else e.T
+            # rounding of 2^-24 sigma_1 per product, over the gap sigma_r - sigma_{r+1}
+            bound = 64 * 2.0 ** -24 * sv[0] / (sv[r - 1] - (sv[r] if r < len(sv) else 0.0))
+            assert orc.sin_theta_max(u[:, :r], p) <= bound, (kind, l)
+            assert np.linalg.norm(e - (m - p @ q.T)) <= 2e-6 * np.linalg.norm(m)
+        for x in case.E:
+            x.zero_()
