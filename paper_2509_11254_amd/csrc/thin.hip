@@ -693,10 +693,8 @@ hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, 
 
 // --------------------------------------------------------------------------------------------
 // Rayleigh-Ritz: eigen-decomposition of the w x w Gram matrix H = Y^T Y (Y = M^T Z, Z orthonormal)
-// by cyclic two-sided Jacobi in fp64 with a round-robin ordering (w/2 disjoint rotations per round).
-// One workgroup per layer.  One copy of each entry of the symmetric H is kept in LDS (layout: sym_idx); in a round the 2 x 2 blocks
-// (pair k1 rows) x (pair k2 columns), k1 <= k2, are independent of each other and are rotated in
-// place.  The accumulated rotations V live in LDS when they fit, else in the layer's scratch matrix.
+// by cyclic two-sided Jacobi in fp64: jacobi_block_kernel up to width 160, jacobi_kernel above, with H and a slice of the accumulated
+// rotations V in LDS.
 // On exit tmat[:, k] is the eigenvector of the k-th largest eigenvalue, so that P~ = Z tmat[:, :r] are
 // the leading left singular vectors (Definition 3) and Q = Y tmat[:, :r] = M^T P~.  status gets
 // sigma_1 and sigma_r = sqrt(eigenvalue), and the iteration count the next refresh needs.
@@ -747,27 +745,20 @@ __device__ inline int jacobi_pos0(int j, int n) {
     return j < half ? 2 * j : 2 * (n - 1 - j) + 1;
 }
 
-// position before the tournament's step of the player that ends up at position x (inverse of jacobi_next_pos)
-__device__ inline int jacobi_prev_pos(int x, int n) {
-    const int half = n / 2, k = x >> 1;
-    if (x == 0 || n <= 2) return x;
-    if (x & 1) return k == 0 ? 2 : x - 2;                   // bottom[k] <- bottom[k - 1], bottom[0] <- top[1]
-    return k == half - 1 ? x + 1 : x + 2;                   // top[k] <- top[k + 1], the last one <- bottom[half - 1]
-}
-
-// Rotation that annihilates apq of a 2 x 2 diagonal block
+// Rotation that annihilates apq of a 2 x 2 diagonal block: the half of the angle whose cosine and sine are |d| / h and b / h, d =
+// aqq - app, b = 2 apq, h^2 = d^2 + b^2, so (c, s) is (1 + |d| / h, +-b / h) normalised.  The quotients by h may be off by a little (one
+// Newton step on the hardware estimate: the entry comes out at 1e-12 of what it was), the norm may not.
 __device__ inline void jacobi_angle(double app, double apq, double aqq, double& c, double& sn) {
-    c = 1.0;
-    sn = 0.0;
-    if (fabs(apq) > 1e-300 && apq * apq > 1e-36 * fabs(app * aqq)) {
-        // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)), tau = (aqq - app) / (2 apq), written with one division
-        // (square root and quotient from the hardware estimates with Newton steps; b^2 is a normal number by the test above)
-        const double d = aqq - app, b = 2.0 * apq;
-        const double h2 = __builtin_fma(d, d, b * b);
-        const double tt = (d >= 0.0 ? b : -b) * rcp_nr(fabs(d) + h2 * rsqrt_nr(h2));
-        c = rsqrt_nr(__builtin_fma(tt, tt, 1.0));
-        sn = tt * c;
-    }
+    const bool turns = fabs(apq) > 1e-150 && apq * apq > 1e-36 * fabs(app * aqq);
+    const double d = aqq - app, b = 2.0 * apq;
+    const double h2 = turns ? __builtin_fma(d, d, b * b) : 1.0;               // (a normal number by the test above)
+    double ih = __builtin_amdgcn_rsq(h2);
+    ih = __builtin_fma(0.5 * ih, __builtin_fma(-(h2 * ih), ih, 1.0), ih);
+    const double x = turns ? __builtin_fma(fabs(d), ih, 1.0) : 1.0;
+    const double y = turns ? (d >= 0.0 ? b : -b) * ih : 0.0;
+    const double in = rsqrt_nr(__builtin_fma(x, x, y * y));
+    c = x * in;
+    sn = y * in;
 }
 // J^T A J for the off-diagonal block (slot k1) x (slot k2) ...
 __device__ inline void jacobi_rotate(double c1, double s1, double c2, double s2, double app, double apq, double aqp, double aqq, double (&o)[4]) {
@@ -797,42 +788,115 @@ __device__ inline void jacobi_rotation(const double* a, int n, int rd, int k, do
     jacobi_angle(a[sym_idx(2 * k, 2 * k, n)], a[sym_idx(2 * k, 2 * k + 1, n)], a[sym_idx(2 * k + 1, 2 * k + 1, n)], c, sn);
     jacobi_note(c, sn, n, rd, k, cs, pq);
 }
-// Slot k's rotation of round rd from the H and the rotations (cs0) of the round before, n >= 4: pt, pb are the positions its two
-// players have in that round, in two different slots
-__device__ inline void jacobi_rotation_ahead(const double* a, int n, int rd, int k, int pt, int pb, const double* cs0, double* cs, int* pq) {
-    const int half = n / 2, kt = pt >> 1, kb = pb >> 1;
-    const double ct = cs0[kt], st = cs0[half + kt], cb = cs0[kb], sb = cs0[half + kb];
-    double p0, p1, p2, q0, q1, q2, o[4], c, sn;
-    jacobi_rotate_diag(ct, st, a[sym_idx(2 * kt, 2 * kt, n)], a[sym_idx(2 * kt, 2 * kt + 1, n)], a[sym_idx(2 * kt + 1, 2 * kt + 1, n)], p0, p1, p2);
-    jacobi_rotate_diag(cb, sb, a[sym_idx(2 * kb, 2 * kb, n)], a[sym_idx(2 * kb, 2 * kb + 1, n)], a[sym_idx(2 * kb + 1, 2 * kb + 1, n)], q0, q1, q2);
-    jacobi_rotate(ct, st, cb, sb, a[sym_idx(2 * kt, 2 * kb, n)], a[sym_idx(2 * kt, 2 * kb + 1, n)],
-                  a[sym_idx(2 * kt + 1, 2 * kb, n)], a[sym_idx(2 * kt + 1, 2 * kb + 1, n)], o);
-    const double top_row = pb & 1 ? o[1] : o[0], bottom_row = pb & 1 ? o[3] : o[2];
-    jacobi_angle(pt & 1 ? p2 : p0, pt & 1 ? bottom_row : top_row, pb & 1 ? q2 : q0, c, sn);
-    jacobi_note(c, sn, n, rd, k, cs, pq);
+// rank of eigenvalue j = number of eigenvalues that come before it (ties by index); eval (or null): the eigenvalues in that order
+__device__ inline void ritz_ranks(const double* lam, int* rank_of, int w, double* eval) {
+    for (int j = threadIdx.x; j < w; j += blockDim.x) {
+        const double lj = lam[j];
+        int rank = 0;
+        for (int k = 0; k < w; ++k) {
+            const double lk = lam[k];
+            rank += (lk > lj || (lk == lj && k < j)) ? 1 : 0;
+        }
+        rank_of[j] = rank;
+        if (eval) eval[rank] = lj;
+    }
+}
+// What a refresh leaves in the layer's status words, from the Ritz values in L.eval; by the threads of one workgroup.
+constexpr int kJacobiMaxWidth = 200;       // of jacobi_kernel: five 2 x 2 blocks per thread
+__device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budget, float* sigma_out) {
+    const int t = threadIdx.x, r = L.r;
+    // Iterations for a cut without a gap (see refresh_iterations).  Where the count that the subspace needs is out of
+    // reach, what is asked of the step is its error (Lemma 2 / Eq. (6): ||M - P~ P~^T M||^2 = sum_{i > r} sigma_i^2
+    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= rho^3 (rho / (2 - rho))^(k - 3), rho = theta_b / theta_i,
+    // after k iterations from any start (theta: Ritz values = squared singular value estimates; three of them are not shifted), costs at most
+    // sin^2(theta_i) (theta_i - theta_b) on top of the optimum: the directions well above the cut cost nothing after
+    // two iterations, the ones in the cluster at the cut have little to lose.  The count is the smallest k for which
+    // the sum of these is below 1e-5 of ||M||^2 >= sum of the Ritz values: a tenth of the 1e-4 the step is held to,
+    // because the Ritz values are those of the layer's previous refresh and error feedback has flattened the spectrum
+    // further since (with 5e-5 the counts came out at 3 to 10 and left 1e-4 to 3e-4).
+    // Measured on 7B-shaped bf16 layers (sigma_{b+1} / sigma_r = 0.98): after 3 steps of error feedback 2 iterations
+    // leave 3e-6 ||M||^2; after 60 steps, with ||E|| = 0.3 ||M||, 4 leave 1.8e-4, 8 leave 5.8e-5, 16 leave 1.5e-5.
+    // (one wave, in a fixed order; the powers by a product per count, as pow() takes a microsecond of the chain for each)
+    int ke = 255;
+    if (t < 64) {
+        constexpr int kEach = (kJacobiMaxWidth + 63) / 64;
+        const double lb = w > r ? L.eval[w - 1] : 0.0;
+        double tr = 0.0, term[kEach], plain[kEach], shifted[kEach];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            const int i = t + 64 * u;
+            const double li = i < w ? L.eval[i] : 0.0;
+            tr += fmax(li, 0.0);
+            const bool counts = i < r && lb > 0.0 && li > lb;
+            const double rho = counts ? lb / li : 0.0;
+            plain[u] = rho * rho;
+            shifted[u] = plain[u] / ((2.0 - rho) * (2.0 - rho));
+            term[u] = counts ? plain[u] * plain[u] * (li - lb) : 0.0;
+        }
+        for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
+        for (int k = 2; k <= 64; ++k) {
+            double part = 0.0;
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) part += term[u];
+            for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
+            if (part <= 1e-5 * tr) {
+                ke = k;
+                break;
+            }
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) term[u] *= k < kPlainIterations ? plain[u] : shifted[u];
+        }
+    }
+    for (int k = t; k < r; k += blockDim.x) {
+        const float sg = (float)sqrt(fmax(L.eval[k], 0.0));
+        if (sigma_out) sigma_out[k] = sg;
+        if (k == 0) L.status[2] = __float_as_int(sg);
+        if (k == r - 1) L.status[3] = __float_as_int(sg);
+    }
+    if (t == 0) {
+        // The iteration contracts the error of the leading r-dimensional subspace by about rho = theta_b / theta_r per plain
+        // step and rho / (2 - rho) per shifted one (theta = Ritz values, the smallest one of the block standing
+        // in for sigma_{b+1}^2); the next refresh of this layer needs as many steps as 1e-5 takes (a tenth of
+        // the 1e-4 bar on the subspace), plus one.  (Error feedback drives M towards rho = 1: what is not
+        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)  A cut counts as one
+        // without a gap where plain steps would be more than the option asks for: of 7B-shaped layers in such a run most need
+        // 17 to 25 plain steps or 12 to 14 shifted ones, and their error needs 4 or 5 (a block of them 6.0 ms per refresh, 6.5
+        // with as many as converge).
+        int k_next = 255;
+        const double lr = L.eval[r - 1], lb = L.eval[w - 1];
+        if (w > r && lr > 0.0 && lb >= 0.0) {
+            const double rho = lb / lr;
+            if (rho < 0.999) {
+                const double plain = log(fmax(rho, 1e-12)), left = log(1e-5) - kPlainIterations * plain;
+                const int unshifted = rho <= 1e-12 ? 2 : (int)ceil(log(1e-5) / plain) + 1;
+                k_next = left >= 0.0 || unshifted > budget ? unshifted
+                                                           : kPlainIterations + (int)ceil(left / (plain - log(2.0 - rho))) + 1;
+            }
+        }
+        L.status[4] = max(2, min(255, k_next));
+        L.status[9] = ke;
+        L.status[11] = 0;
+        L.status[5] = sweeps;
+        L.status[8] = min(L.status[8] + 1, 1 << 20);
+    }
 }
 
+// Widths above kJacobiBlockWidth, round-robin ordering with w/2 disjoint rotations per round.
 // grid = (slices, layers): every workgroup of a layer repeats the (deterministic) iteration on H and
 // accumulates the rotations into its own slice of v_rows rows of V, which is independent of the other rows.
 //
 // H is stored by POSITION in the tournament, not by matrix index: the 2 x 2 block (slot k1) x (slot k2) sits at
 // the same LDS addresses in every round, is rotated by the two slots' rotations, and its four entries are written
 // to where the tournament moves their row and column players.  Source and destination addresses of a thread's
-// blocks are therefore computed once.  A round in two orders:
-//   AHEAD   read and rotate (registers), and beside it the next round's rotations, which the last threads work out from the same
-//           entries for themselves | barrier | write, and V <- V J on the columns the slots hold | barrier
-//   else    read and rotate | barrier | write | barrier | the next round's rotations from the new diagonal blocks, while the other
-//           waves run V <- V J | barrier
-// The second hides the rotations behind the update of V where that is long, and leaves all threads to H (see launch_jacobi).
+// blocks are therefore computed once.  A round:
+//   read and rotate | barrier | write | barrier | the next round's rotations from the new diagonal blocks, while the other
+//   waves run V <- V J | barrier
 // V stays indexed by matrix index.
-// NBLK: 2 x 2 blocks of H per thread, at least (w/2)(w/2 + 1)/2 over the h_threads first threads of the workgroup, which update H.
-// With AHEAD the others have nothing to do but the rotations: beside blocks of their own they would be the last at the barrier.
-template <int NBLK, bool AHEAD>
+// NBLK: 2 x 2 blocks of H per thread, at least (w/2)(w/2 + 1)/2 over the workgroup.
+template <int NBLK>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
-                                                      int slot_rows, int h_threads, int budget, float* __restrict__ sigma_out) {
-    __shared__ int s_ke;
-    __shared__ double s_sum;
+                                                      int slot_rows, int budget, float* __restrict__ sigma_out) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     const int w = L.thin[role].width;
     const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
@@ -882,11 +946,11 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
         const int total = (half * (half + 1)) / 2;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) {
-            const int e = t + b * (AHEAD ? h_threads : nt);
+            const int e = t + b * nt;
             bk[b] = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) adr[b][q] = 0;
-            if ((!AHEAD || t < h_threads) && e < total) {
+            if (e < total) {
                 const int dk = e / half, k1 = e - dk * half;
                 int k2 = k1 + dk;
                 k2 -= k2 >= half ? half : 0;
@@ -903,9 +967,6 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             }
         }
     }
-    // (AHEAD) the slot whose rotations this thread works out (-1: none)
-    const int slot = AHEAD && nt - 1 - t < half ? nt - 1 - t : -1;
-    const int prev_top = slot < 0 ? 0 : jacobi_prev_pos(2 * slot, n), prev_bottom = slot < 0 ? 0 : jacobi_prev_pos(2 * slot + 1, n);
     __syncthreads();
     int cur = 0, sweeps = 0;
     for (int sweep = 0; sweep < kJacobiMaxSweeps; ++sweep) {
@@ -932,8 +993,6 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
             const double* cs = csb + cur * n;
             const int* pq = pqb + cur * n;
             // H <- J^T H J on this thread's blocks: rows by slot k1's rotation, columns by slot k2's
-            if (AHEAD && slot >= 0 && rd + 1 < n - 1)
-                jacobi_rotation_ahead(a, n, rd + 1, slot, prev_top, prev_bottom, cs, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             double o[NBLK][4];
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
@@ -960,10 +1019,8 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
                 if (!diag) a[adr[b][2] >> 16] = o[b][2];
                 a[adr[b][3] >> 16] = o[b][3];
             }
-            if constexpr (!AHEAD) {
-                __syncthreads();
-                if (rd + 1 < n - 1 && t < half) jacobi_rotation(a, n, rd + 1, t, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
-            }
+            __syncthreads();
+            if (rd + 1 < n - 1 && t < half) jacobi_rotation(a, n, rd + 1, t, csb + (cur ^ 1) * n, pqb + (cur ^ 1) * n);
             for (int i = ty; i < nv; i += tyw)
                 for (int k = tx; k < half; k += txw) {
                     const int p = pq[k], q = pq[half + k];
@@ -982,95 +1039,289 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
     double* lam = csb;                                 // [n], the rotation buffers are free now
     for (int j = t; j < n; j += nt) { const int x = jacobi_pos0(j, n); lam[j] = a[sym_idx(x, x, n)]; }
     __syncthreads();
-    // sort: rank of eigenvalue j = number of eigenvalues that come before it (ties by index)
-    int* rank_of = pqb;
+    int* rank_of = pqb;                                // (2 n entries available)
     double* __restrict__ tm = L.tmat;
-    for (int j = t; j < w; j += nt) {
-        const double lj = lam[j];
-        int rank = 0;
-        for (int k = 0; k < w; ++k) {
-            const double lk = lam[k];
-            rank += (lk > lj || (lk == lj && k < j)) ? 1 : 0;
-        }
-        rank_of[j] = rank;     // 2n entries available
-        if (blockIdx.x == 0) L.eval[rank] = lj;
-    }
+    ritz_ranks(lam, rank_of, w, blockIdx.x == 0 ? L.eval : nullptr);
     __syncthreads();
     for (int i = ty; i < nv; i += tyw)
         if (row0 + i < w)
             for (int j = tx; j < w; j += txw) tm[(int64_t)(row0 + i) * w + rank_of[j]] = v[i * n + j];
-    if (blockIdx.x != 0) return;
-    const int r = L.r;
-    // Iterations for a cut without a gap (see refresh_iterations).  Where the count that the subspace needs is out of
-    // reach, what is asked of the step is its error (Lemma 2 / Eq. (6): ||M - P~ P~^T M||^2 = sum_{i > r} sigma_i^2
-    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= rho^3 (rho / (2 - rho))^(k - 3), rho = theta_b / theta_i,
-    // after k iterations from any start (theta: Ritz values = squared singular value estimates; three of them are not shifted), costs at most
-    // sin^2(theta_i) (theta_i - theta_b) on top of the optimum: the directions well above the cut cost nothing after
-    // two iterations, the ones in the cluster at the cut have little to lose.  The count is the smallest k for which
-    // the sum of these is below 1e-5 of ||M||^2 >= sum of the Ritz values: a tenth of the 1e-4 the step is held to,
-    // because the Ritz values are those of the layer's previous refresh and error feedback has flattened the spectrum
-    // further since (with 5e-5 the counts came out at 3 to 10 and left 1e-4 to 3e-4).
-    // Measured on 7B-shaped bf16 layers (sigma_{b+1} / sigma_r = 0.98): after 3 steps of error feedback 2 iterations
-    // leave 3e-6 ||M||^2; after 60 steps, with ||E|| = 0.3 ||M||, 4 leave 1.8e-4, 8 leave 5.8e-5, 16 leave 1.5e-5.
-    if (t == 0) s_ke = 255;
-    {
-        double tr = 0.0;
-        for (int j = 0; j < w; ++j) tr += fmax(lam[j], 0.0);
-        const double lb = w > r ? L.eval[w - 1] : 0.0, target = 1e-5 * tr;
-        for (int k = 2; k <= 64; ++k) {
-            if (t == 0) s_sum = 0.0;
+    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, budget, sigma_out);
+}
+
+// v of lane (lane ^ 2^B), B < 3, and of lane (lane ^ 8 * 2^B): moves on the data path, no LDS
+template <int CTRL> __device__ __forceinline__ double dpp_move(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+template <int B> __device__ __forceinline__ double from_column(double v) {
+    if constexpr (B == 0) return dpp_move<0xb1>(v);                   // quad_perm 1 0 3 2
+    else if constexpr (B == 1) return dpp_move<0x4e>(v);              // quad_perm 2 3 0 1
+    else return dpp_move<0x1b>(dpp_move<0x141>(v));                   // half rows mirrored (^ 7), quad_perm 3 2 1 0 (^ 3)
+}
+template <int B> __device__ __forceinline__ int swapped_rows(int v) {
+    // (the first result has each upper row replaced by the lower one, the second each lower row by the upper one)
+    if constexpr (B == 1) {
+        const auto x = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return threadIdx.x & 16 ? x[0] : x[1];
+    } else {
+        const auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return threadIdx.x & 32 ? x[0] : x[1];
+    }
+}
+template <int B> __device__ __forceinline__ double from_row(double v) {
+    if constexpr (B == 0) return dpp_move<0x128>(v);                  // row_ror 8
+    else return __hiloint2double(swapped_rows<B>(__double2hiint(v)), swapped_rows<B>(__double2loint(v)));
+}
+__device__ __forceinline__ double from_lane(int byte_address, double v) {
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(byte_address, __double2hiint(v)),
+                            __builtin_amdgcn_ds_bpermute(byte_address, __double2loint(v)));
+}
+
+// ---- Jacobi on 8 x 8 blocks, widths up to kJacobiBlockWidth.
+// One wave works on the 16 indices of a pair of blocks (a 16 x 16 part of H) in registers: lane (k1, k2) holds the 2 x 2 block
+// (slot k1) x (slot k2), and rows k1 and k1 + 8 of slot k2's columns of the part's accumulated rotations.  A phase pairs the indices that
+// differ in bit `split` and below: slot k holds the index with that bit 0 and the k-th other bits, and the one with that bit 1 and
+// the k ^ g-th; the 2^split rounds run g through a Gray code, so that between rounds one bit of k changes.  Split 3: the pairs
+// across the two blocks, 2, 1 and 0: those inside both.
+constexpr int kJacobiBlockWidth = 160;
+__device__ inline int block_at(int I, int K) { return ((K * (K + 1)) / 2 + I) * 64; }     // I <= K
+// entry of a block; the columns of a row are permuted so that neither rows nor columns meet on a bank
+__device__ inline int in_block(int i, int k) { return 8 * i + (k ^ i); }
+// entry (e, f) of the pair's 16 x 16 part, p < q
+__device__ inline int in_pair(int e, int f, int pp, int pq, int qq) {
+    const int i = e & 7, k = f & 7;
+    return (e ^ f) & 8 ? pq + (e & 8 ? in_block(k, i) : in_block(i, k)) : (e & 8 ? qq : pp) + in_block(i, k);
+}
+// h: blocks of H, jac: 16 x 16 rotations of this pair, row by row
+template <int SPLIT>
+__device__ __forceinline__ void jacobi_phase(double* h, double* jac, int pp, int pq, int qq, bool first) {
+    constexpr int low = (1 << SPLIT) - 1;
+    const int lane = threadIdx.x & 63, k1 = lane >> 3, k2 = lane & 7;
+    const int e0 = (k1 & low) | ((k1 & ~low) << 1), e1 = e0 | (1 << SPLIT);
+    const int f0 = (k2 & low) | ((k2 & ~low) << 1), f1 = f0 | (1 << SPLIT);
+    const int from1 = 4 * 9 * k1, from2 = 4 * 9 * k2;
+    double x[4] = {h[in_pair(e0, f0, pp, pq, qq)], h[in_pair(e0, f1, pp, pq, qq)], h[in_pair(e1, f0, pp, pq, qq)], h[in_pair(e1, f1, pp, pq, qq)]};
+    double u0, u1, v0, v1;
+    if (first) {
+        u0 = k1 == f0 ? 1.0 : 0.0; u1 = k1 == f1 ? 1.0 : 0.0;
+        v0 = k1 + 8 == f0 ? 1.0 : 0.0; v1 = k1 + 8 == f1 ? 1.0 : 0.0;
+    } else {
+        u0 = jac[16 * k1 + f0]; u1 = jac[16 * k1 + f1];
+        v0 = jac[16 * k1 + 128 + f0]; v1 = jac[16 * k1 + 128 + f1];
+    }
+    static_for<0, low + 1>([&](auto round) {
+        constexpr int rd = decltype(round)::value;
+        double c, s, o[4];
+        jacobi_angle(x[0], x[1], x[3], c, s);                         // (of use on lanes k1 = k2)
+        const double c1 = from_lane(from1, c), s1 = from_lane(from1, s), c2 = from_lane(from2, c), s2 = from_lane(from2, s);
+        jacobi_rotate(c1, s1, c2, s2, x[0], x[1], x[2], x[3], o);
+        const double t0 = c2 * u0 - s2 * u1, t1 = c2 * v0 - s2 * v1;
+        u1 = s2 * u0 + c2 * u1;
+        v1 = s2 * v0 + c2 * v1;
+        u0 = t0;
+        v0 = t1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = o[q];
+        if constexpr (SPLIT > 0) {
+            constexpr int bit = rd < low ? __builtin_ctz(rd + 1) : SPLIT - 1;      // (the last one back to g = 0)
+            x[1] = from_column<bit>(x[1]);
+            x[2] = from_row<bit>(x[2]);
+            x[3] = from_row<bit>(from_column<bit>(x[3]));
+            u1 = from_column<bit>(u1);
+            v1 = from_column<bit>(v1);
+        }
+    });
+    auto put = [&](int e, int f, double val) {
+        if (e > f) return;
+        h[in_pair(e, f, pp, pq, qq)] = val;
+        if (!((e ^ f) & 8)) h[in_pair(f, e, pp, pq, qq)] = val;
+    };
+    put(e0, f0, x[0]);
+    put(e0, f1, x[1]);
+    put(e1, f0, x[2]);
+    put(e1, f1, x[3]);
+    jac[16 * k1 + f0] = u0;
+    jac[16 * k1 + f1] = u1;
+    jac[16 * k1 + 128 + f0] = v0;
+    jac[16 * k1 + 128 + f1] = v1;
+}
+
+// The same outcome as jacobi_kernel.  A sweep is a tournament of the nb blocks of 8 indices: in each round nb / 2 waves rotate
+// their pair's 16 x 16 part and accumulate the rotations J (the pairs across the two blocks; in a sweep's first round those inside
+// them too), then all waves apply them, H_ab <- J_a^T H_ab J_b and V <- V J_b in 16 x 16 parts on the fp64 matrix cores.
+// H: upper triangle of blocks in LDS (width 160: 149 of 160 KB with 16 rows of V; 168 does not fit); V^T: nb * 8 columns of v_rows (a
+// multiple of 16) each.
+// What bounds it: the instructions of the rotating waves, 8 rounds of about 600 cycles (of 1000 where three of ten such waves share
+// a SIMD), then the matrix cores and addresses of the update, 4000 cycles at width 80 and 11000 at 160.  A rotation at a time over the
+// whole of H moves all of H through LDS for each of 8 nb - 1 rounds per sweep (0.7 us per round at width 16, 1.1 at 80, 2.2 at 160).
+// us per decomposition that way and this: one layer of width 12 54 -> 26, 16 53 -> 24, 40 187 -> 97, 120 815 -> 493, 144 1552 ->
+// 863, 160 1772 -> 750; 7 layers of width 80 488 to 578 -> 240 to 253, 64 601 -> 302; 128 of width 104 1088 -> 571, 256 of 24 131 -> 79.
+template <int NT>
+__global__ __launch_bounds__(NT) void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids, int role,
+                                                          int v_rows, int slot_rows, int budget, float* __restrict__ sigma_out) {
+    const LayerDev& L = layers[ids[blockIdx.y]];
+    const int w = L.thin[role].width;
+    const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
+    const int np = (w + 15) / 16, nb = 2 * np, n = 8 * nb, n_blk = (nb * (nb + 1)) / 2;
+    const int row0 = blockIdx.x * v_rows;
+    if (row0 >= w) return;                                 // (a narrower layer than the launch's widest)
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* h = reinterpret_cast<double*>(smem);
+    double* jac = h + n_blk * 64;                          // [np][16][16]
+    double* vt = jac + np * 256;                           // [n][v_rows]
+    double* red = vt + n * v_rows;                         // [2][16] per-wave partial sums of the convergence test
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), li = lane & 15, lk = lane >> 4;
+    constexpr int nw = NT / 64;
+    // wave wv's blocks (I, K), I <= K: wv, wv + nw, ... column by column
+    auto each_block = [&](auto&& f) {
+        int K = 0, I = wv;
+        for (int b = wv; b < n_blk; b += nw, I += nw) {
+            while (I > K) I -= ++K;
+            f(b, I, K);
+        }
+    };
+    const int bi = lane >> 3, bk = lane & 7;
+    const int ntri = (w * (w + 1)) / 2;
+    each_block([&](int b, int I, int K) {
+        const int i = 8 * I + bi, j = 8 * K + bk;
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+        if (i < w && j < w) {
+            const PSGD_GLOBAL double* g = as_global(L.gram) + tri_idx(min(i, j), max(i, j), w);
+            int sp = 0;
+            for (; sp + 4 <= n_slots; sp += 4) {
+                s0 += g[(int64_t)sp * ntri]; s1 += g[(int64_t)(sp + 1) * ntri];
+                s2 += g[(int64_t)(sp + 2) * ntri]; s3 += g[(int64_t)(sp + 3) * ntri];
+            }
+            for (; sp < n_slots; ++sp) s0 += g[(int64_t)sp * ntri];
+        }
+        h[b * 64 + in_block(bi, bk)] = (s0 + s1) + (s2 + s3);
+    });
+    for (int j = wv; j < n; j += nw)
+        for (int i = lane; i < v_rows; i += 64) vt[j * v_rows + i] = row0 + i == j ? 1.0 : 0.0;
+    __syncthreads();
+    const int n_tiles = (np * (np - 1)) / 2, n_items = n_tiles + np * (v_rows / 16);
+    auto blocks_of = [&](int pair, int rd, int& p, int& q) {
+        const int x = jacobi_top(pair, rd, nb), y = jacobi_bottom(pair, rd, nb);
+        p = min(x, y);
+        q = max(x, y);
+    };
+    // entries (li & 7, 4 c + lk) of a block and the other way round
+    const int at_row[2] = {in_block(li & 7, lk), in_block(li & 7, 4 + lk)}, at_col[2] = {in_block(lk, li & 7), in_block(4 + lk, li & 7)};
+    int sweeps = 0;
+    for (int sweep = 0; sweep < kJacobiMaxSweeps; ++sweep) {
+        // convergence: off-diagonal mass relative to the diagonal, added up in a fixed order: the same bits in every workgroup of
+        // the layer, whose slices of V only fit together if all of them run the same number of sweeps
+        double off = 0.0, dia = 0.0;
+        each_block([&](int b, int I, int K) {
+            const double x = h[b * 64 + in_block(bi, bk)];
+            if (I != K) off += 2.0 * x * x;
+            else if (bi == bk) dia += x * x;
+            else off += x * x;
+        });
+        for (int o = 32; o > 0; o >>= 1) { off += __shfl_down(off, o); dia += __shfl_down(dia, o); }
+        if (lane == 0) { red[wv] = off; red[16 + wv] = dia; }
+        __syncthreads();
+        double off_all = 0.0, dia_all = 0.0;
+        for (int q = 0; q < nw; ++q) { off_all += red[q]; dia_all += red[16 + q]; }
+        if (off_all <= 1e-20 * dia_all) break;
+        sweeps = sweep + 1;
+#pragma unroll 1
+        for (int rd = 0; rd < nb - 1; ++rd) {
+#pragma unroll 1
+            for (int b = wv; b < np; b += nw) {
+                int p, q;
+                blocks_of(b, rd, p, q);
+                const int pp = block_at(p, p), pq = block_at(p, q), qq = block_at(q, q);
+                if (rd == 0) {
+                    jacobi_phase<2>(h, jac + 256 * b, pp, pq, qq, true);
+                    wave_sync();
+                    jacobi_phase<1>(h, jac + 256 * b, pp, pq, qq, false);
+                    wave_sync();
+                    jacobi_phase<0>(h, jac + 256 * b, pp, pq, qq, false);
+                    wave_sync();
+                }
+                jacobi_phase<3>(h, jac + 256 * b, pp, pq, qq, rd != 0);
+            }
             __syncthreads();
-            double part = 0.0;
-            for (int i = t; i < r; i += nt) {
-                const double li = L.eval[i];
-                if (lb > 0.0 && li > lb) {
-                    const double rho = lb / li;
-                    part += pow(rho, 2.0 * k) * pow(2.0 - rho, -2.0 * max(k - kPlainIterations, 0)) * (li - lb);
+            int a = 0, k = wv;                             // tile (a, a + 1 + k) of the upper triangle of pairs
+#pragma unroll 1
+            for (int item = wv; item < n_items; item += nw, k += nw) {
+                if (item < n_tiles) {
+                    while (k >= np - 1 - a) { k -= np - 1 - a; ++a; }
+                    const int b = a + 1 + k;
+                    int pa, qa, pb, qb;
+                    blocks_of(a, rd, pa, qa);
+                    blocks_of(b, rd, pb, qb);
+                    // T = H_ab: as the A operand lane (li, lk) reads row li; the product's row 4 v + lk, column li.  [half of a][half of b]
+                    const int rows[2] = {pa, qa}, cols[2] = {pb, qb};
+                    int base[2][2];
+                    bool turned[2][2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            turned[i][j] = rows[i] > cols[j];
+                            base[i][j] = block_at(min(rows[i], cols[j]), max(rows[i], cols[j]));
+                        }
+                    double tv[4], ja[4], jb[4];
+                    int out[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int z = c >> 1;
+                        const int by_row0 = base[0][z] + (turned[0][z] ? at_col[c & 1] : at_row[c & 1]);
+                        const int by_row1 = base[1][z] + (turned[1][z] ? at_col[c & 1] : at_row[c & 1]);
+                        tv[c] = h[li & 8 ? by_row1 : by_row0];
+                        const int by_col0 = base[z][0] + (turned[z][0] ? at_row[c & 1] : at_col[c & 1]);
+                        const int by_col1 = base[z][1] + (turned[z][1] ? at_row[c & 1] : at_col[c & 1]);
+                        out[c] = li & 8 ? by_col1 : by_col0;
+                        jb[c] = jac[256 * b + 64 * c + lane];
+                        ja[c] = jac[256 * a + 64 * c + lane];
+                    }
+                    // (without the fence the loads are made one by one between the MFMAs)
+                    __builtin_amdgcn_sched_barrier(0);
+                    doublex4 x = {0.0, 0.0, 0.0, 0.0}, y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x = __builtin_amdgcn_mfma_f64_16x16x4f64(tv[c], jb[c], x, 0, 0, 0);
+                    // (row 4 v + lk of T J_b is what the B operand of step v takes)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y = __builtin_amdgcn_mfma_f64_16x16x4f64(ja[c], x[c], y, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) h[out[v]] = y[v];
+                } else {
+                    const int e = item - n_tiles, b = e % np, r0 = 16 * (e / np);
+                    int p, q;
+                    blocks_of(b, rd, p, q);
+                    double* v0 = vt + 8 * p * v_rows + r0 + li;
+                    double* v1 = vt + 8 * q * v_rows + r0 + li;
+                    double jb[4], xv[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        jb[c] = jac[256 * b + 64 * c + lane];
+                        xv[c] = (c & 2 ? v1 : v0)[(4 * (c & 1) + lk) * v_rows];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    doublex4 y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y = __builtin_amdgcn_mfma_f64_16x16x4f64(jb[c], xv[c], y, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) (v & 2 ? v1 : v0)[(4 * (v & 1) + lk) * v_rows] = y[v];
                 }
             }
-            if (part > 0.0) atomicAdd(&s_sum, part);
             __syncthreads();
-            const bool ok = s_sum <= target;          // (the same value in every thread)
-            __syncthreads();
-            if (ok) {
-                if (t == 0) s_ke = k;
-                break;
-            }
         }
     }
     __syncthreads();
-    for (int k = t; k < r; k += nt) {
-        const float sg = (float)sqrt(fmax(L.eval[k], 0.0));
-        if (sigma_out) sigma_out[k] = sg;
-        if (k == 0) L.status[2] = __float_as_int(sg);
-        if (k == r - 1) L.status[3] = __float_as_int(sg);
-    }
-    if (t == 0) {
-        // The iteration contracts the error of the leading r-dimensional subspace by about rho = theta_b / theta_r per plain
-        // step and rho / (2 - rho) per shifted one (theta = Ritz values, the smallest one of the block standing
-        // in for sigma_{b+1}^2); the next refresh of this layer needs as many steps as 1e-5 takes (a tenth of
-        // the 1e-4 bar on the subspace), plus one.  (Error feedback drives M towards rho = 1: what is not
-        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)  A cut counts as one
-        // without a gap where plain steps would be more than the option asks for: of 7B-shaped layers in such a run most need
-        // 17 to 25 plain steps or 12 to 14 shifted ones, and their error needs 4 or 5 (a block of them 6.0 ms per refresh, 6.5
-        // with as many as converge).
-        int k_next = 255;
-        const double lr = L.eval[r - 1], lb = L.eval[w - 1];
-        if (w > r && lr > 0.0 && lb >= 0.0) {
-            const double rho = lb / lr;
-            if (rho < 0.999) {
-                const double plain = log(fmax(rho, 1e-12)), left = log(1e-5) - kPlainIterations * plain;
-                const int unshifted = rho <= 1e-12 ? 2 : (int)ceil(log(1e-5) / plain) + 1;
-                k_next = left >= 0.0 || unshifted > budget ? unshifted
-                                                           : kPlainIterations + (int)ceil(left / (plain - log(2.0 - rho))) + 1;
-            }
-        }
-        L.status[4] = max(2, min(255, k_next));
-        L.status[9] = s_ke;
-        L.status[11] = 0;
-        L.status[5] = sweeps;
-        L.status[8] = min(L.status[8] + 1, 1 << 20);
-    }
+    double* lam = jac;                                     // [n], and the ranks: the rotations are done
+    int* rank_of = reinterpret_cast<int*>(lam + n);
+    for (int j = t; j < n; j += NT) lam[j] = h[block_at(j >> 3, j >> 3) + in_block(j & 7, j & 7)];
+    __syncthreads();
+    ritz_ranks(lam, rank_of, w, blockIdx.x == 0 ? L.eval : nullptr);
+    __syncthreads();
+    double* __restrict__ tm = L.tmat;
+    for (int i = wv; i < min(v_rows, w - row0); i += nw)
+        for (int j = lane; j < w; j += 64) tm[(int64_t)(row0 + i) * w + rank_of[j]] = vt[j * v_rows + i];
+    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, budget, sigma_out);
 }
 
 size_t jacobi_lds_bytes(int w, int v_rows) {
@@ -1078,51 +1329,50 @@ size_t jacobi_lds_bytes(int w, int v_rows) {
     return (size_t)(2 * n + 32 + n * sym_stride(n) + v_rows * n) * sizeof(double) + (size_t)2 * n * sizeof(int);
 }
 
+size_t jacobi_block_lds_bytes(int w, int v_rows) {
+    const int np = (w + 15) / 16, nb = 2 * np;
+    return (size_t)(nb * (nb + 1) / 2 * 64 + np * 256 + 8 * nb * v_rows + 32) * sizeof(double);
+}
+
 // slot_rows: rows per partial Gram matrix of thin[role] (kOneSlot: gram_sum_kernel has added them up)
 // budget: iterations that the option refresh_iters asks for
 hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int budget, float* sigma_out,
                          hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
-    const int n = (w + 1) & ~1;
-    // rows of V per workgroup: as few as 8 while the chip has idle compute units, and no more than fit in LDS
-    int slices = 256 / n_ids;
-    slices = slices < 1 ? 1 : slices;
-    int v_rows = (n + slices - 1) / slices;
-    v_rows = v_rows < 8 ? 8 : v_rows;
     constexpr size_t kLdsCap = 159 * 1024;     // of the 160 KB a workgroup can have
-    while (v_rows > 1 && jacobi_lds_bytes(w, v_rows) > kLdsCap) --v_rows;
-    if (jacobi_lds_bytes(w, v_rows) > kLdsCap) return hipErrorInvalidValue;
-    v_rows = v_rows > n ? n : v_rows;
-    const size_t lds = jacobi_lds_bytes(w, v_rows);
-    const int n_blocks = ((n / 2) * (n / 2 + 1)) / 2;
-    // 256 threads for narrow blocks (the rounds are latency-bound there; one wavefront at width 12: 56 -> 67 us), else 1024.  (With
-    // three to five blocks per thread the kernel spills a few registers; 512 threads with twice the registers measured slower.)
-    const int threads = w <= 48 ? 256 : 1024;
-    dim3 grid((n + v_rows - 1) / v_rows, n_ids), block(threads);
-    // Rotations ahead or not.  One layer, us per sweep at the same number of sweeps, otherwise and ahead: width 48 48.0 and 42.5, 64 61
-    // and 57, 80 96.5 and 88.5, 112 163 and 142, 128 205 and 192, 144 301 and 260, 152 352 and 341; from 160 on the threads that are
-    // left for H hold a block more each, 160 357 and 367, 176 536 and 675.  With more than 16 rows of V per workgroup their
-    // update hides the rotations: width 80, 80 rows (256 layers) 183 and 198; 96, 24 rows 146 and 158; 128, 16 rows 262 and 257, 32
-    // rows 273 and 306 (the other way round: 80, 40 rows 146 and 142).  Up to width 48 it is ahead with any number of rows (48, 48 rows 84 and 79).
-    const bool ahead = w <= 48 || (w <= 152 && v_rows <= 16);
-    const int h_threads = ahead ? threads - 64 * ((n / 2 + 63) / 64) : threads;
-    const int per_thread = (n_blocks + h_threads - 1) / h_threads;
-    void (*kfn)(const LayerDev*, const int*, int, int, int, int, int, float*) = nullptr;
-    switch (per_thread) {
-        case 1: kfn = ahead ? jacobi_kernel<1, true> : jacobi_kernel<1, false>; break;
-        case 2: kfn = ahead ? jacobi_kernel<2, true> : jacobi_kernel<2, false>; break;
-        case 3: kfn = ahead ? jacobi_kernel<3, true> : jacobi_kernel<3, false>; break;
-        case 4: kfn = ahead ? jacobi_kernel<4, true> : jacobi_kernel<4, false>; break;
-        case 5: kfn = ahead ? nullptr : jacobi_kernel<5, false>; break;
-        default: break;
+    // rows of V per workgroup: as few as its kernel takes while the chip has idle compute units, and no more than fit in LDS
+    const int slices = 256 / n_ids < 1 ? 1 : 256 / n_ids;
+    size_t lds;
+    int v_rows;
+    if (w <= kJacobiBlockWidth) {
+        v_rows = ((w + slices - 1) / slices + 15) / 16 * 16;
+        while (v_rows > 16 && jacobi_block_lds_bytes(w, v_rows) > kLdsCap) v_rows -= 16;
+        lds = jacobi_block_lds_bytes(w, v_rows);
+        const int threads = w <= 48 ? 256 : w <= 96 ? 512 : 1024;
+        auto kfn = threads == 256 ? jacobi_block_kernel<256> : threads == 512 ? jacobi_block_kernel<512> : jacobi_block_kernel<1024>;
+        if (lds > kLdsCap) return hipErrorInvalidValue;
+        if (lds > 48 * 1024) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kfn, dim3((w + v_rows - 1) / v_rows, n_ids), dim3(threads), lds, st, layers, ids, role, v_rows, slot_rows, budget, sigma_out);
+        return hipGetLastError();
     }
-    if (!kfn) return hipErrorInvalidValue;
+    const int n = (w + 1) & ~1;
+    v_rows = (n + slices - 1) / slices;
+    v_rows = v_rows < 8 ? 8 : v_rows;
+    while (v_rows > 1 && jacobi_lds_bytes(w, v_rows) > kLdsCap) --v_rows;
+    v_rows = v_rows > n ? n : v_rows;
+    lds = jacobi_lds_bytes(w, v_rows);
+    if (lds > kLdsCap || w > kJacobiMaxWidth) return hipErrorInvalidValue;
+    // (with four or five blocks per thread the kernel spills a few registers; 512 threads with twice the registers measured slower)
+    constexpr int kThreadsWide = 1024;
+    auto kfn = ((n / 2) * (n / 2 + 1)) / 2 <= 4 * kThreadsWide ? jacobi_kernel<4> : jacobi_kernel<5>;
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, v_rows, slot_rows, h_threads, budget, sigma_out);
+    hipLaunchKernelGGL(kfn, dim3((n + v_rows - 1) / v_rows, n_ids), dim3(kThreadsWide), lds, st, layers, ids, role, v_rows, slot_rows, budget, sigma_out);
     return hipGetLastError();
 }
 
