@@ -169,50 +169,64 @@ template <int I> __device__ __forceinline__ double bcast_by_row(double v) {
     return __hiloint2double(hi, lo);
 }
 
-// Right-looking Cholesky A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
+// Right-looking factorisation A = R^T R of a scaled W x W matrix (W <= 16) by a wavefront in registers, without LDS traffic or
 // barriers.  x and y are 16 x 16 matrices in the accumulator layout of v_mfma_f64_16x16x4_f64 (x[v]: row 4 v + (lane >> 4),
-// column lane & 15), x the matrix (upper part) and y an identity, which the row operations turn into R^{-T}: y[v] ends up as
-// T[column][row], T = R^{-1}, and no separate inversion is needed.  Step k scales row k, which one row of lanes holds, and
-// takes its multiples off the rows below with one MFMA each for x and y, the other rows of lanes supplying zeros: what bounds
-// the chain is the square root and one MFMA, not the up to 15 row updates of 2 moves and 2 FMAs each.
-// (As row updates: refresh of 256 x 128 fp32 r = 4 306 us, 274 to 286 now; of 4096 x 4096 r = 8 1145, and 1123 to 1170.  The blocked
-// factorisation takes as long with either: 37 to 39 us at width 80, 78 to 84 at 160, slot sum included.)
+// column lane & 15), x the matrix (upper part, finite) and y an identity, which the row operations turn into R^{-T}: y[v] ends up as
+// T[column][row], T = R^{-1}, and no separate inversion is needed.  Step k takes the multiples of row k, which one row of lanes
+// holds, off the rows below with one MFMA each for x and y, the other rows of lanes supplying zeros.  The rows stay as they are
+// (A = L D L^T): a step needs 1 / pivot, and the square roots, of all rows at once, come at the end.  What bounds the chain is that
+// reciprocal and one MFMA (76 cycles): about 320 cycles a step (f64 operations wait while
+// the other MFMA runs), and 425 with row k scaled by its square root and selected row by row in the step.
 // A dependent column (flagged in badmask, or pivot not above tol2) makes row k of R the k-th row of the identity and skips
 // the update.  rjj: R_jj of column j = lane & 15 (of the columns that are not dependent).  badmask, min_piv and rjj are the same in all
 // rows of lanes.  Selects, not branches: at every merge point the compiler would copy the register array.
 template <int W>
 __device__ __forceinline__ void factor_in_registers(doublex4& x, doublex4& y, double tol2, int& badmask, double& min_piv, double& rjj) {
     const int j = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
-    int bad = badmask;
-    double low = min_piv, diag = 1.0;
+    const int bad = __builtin_amdgcn_readfirstlane(badmask);
+    // (y's step is issued when the next pivot has been read: between the two MFMAs of a step the wave could issue nothing, and the
+    // compiler's wait for x would count from the second)
+    double m = 0.0;
     static_for<0, W>([&](auto kc) {
         constexpr int k = decltype(kc)::value, v = k >> 2, r = k & 3;
-        const bool own = q == r;
-        const double piv = bcast_row<k>(x[v]);                                    // (means the pivot in row r of lanes only)
-        const bool dep = ((bad >> k) & 1) || !(piv > tol2);
-        const bool go = own && !dep;
-        bad |= own && dep ? (1 << k) : 0;
-        low = (go && piv < low) ? piv : low;
-        const double rinv = rsqrt_nr(go ? piv : 1.0);
-        const double xk = go ? x[v] * rinv : 0.0, yk = go ? y[v] * rinv : 0.0;
-        diag = go && j == k ? xk : diag;
-        x[v] = own ? (dep ? (j == k ? 1.0 : 0.0) : xk) : x[v];
-        y[v] = go ? yk : y[v];
+        double inv = 0.0;
+        bool goes = false;
         if constexpr (k + 1 < W) {
-            const double m = j > k ? -xk : 0.0;
-            x = __builtin_amdgcn_mfma_f64_16x16x4f64(m, xk, x, 0, 0, 0);
-            y = __builtin_amdgcn_mfma_f64_16x16x4f64(m, yk, y, 0, 0, 0);
+            const double piv = bcast_row<k>(x[v]);                                // (means the pivot in row r of lanes only)
+            goes = q == r && j > k && !((bad >> k) & 1) && piv > tol2;
+            inv = __builtin_amdgcn_rcp(piv);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (k > 0) {
+                y = __builtin_amdgcn_mfma_f64_16x16x4f64(m, y[(k - 1) >> 2], y, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int it = 0; it < 2; ++it) inv = __builtin_fma(__builtin_fma(-piv, inv, 1.0), inv, inv);
+            m = x[v] * (goes ? -inv : 0.0);
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(m, x[v], x, 0, 0, 0);
+        } else if constexpr (k > 0) {
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(m, y[(k - 1) >> 2], y, 0, 0, 0);
         }
     });
-    // every row of lanes knows its own steps: together
-    badmask = 0;
-    min_piv = 1.0;
-    static_for<0, 4>([&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-        badmask |= __builtin_amdgcn_readlane(bad, 16 * r);
-        const double p = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(low), 16 * r), __builtin_amdgcn_readlane(__double2loint(low), 16 * r));
-        min_piv = p < min_piv ? p : min_piv;
+    // row k has not changed since step k: the pivots are x's diagonal
+    double low = min_piv, diag = 1.0;
+    badmask = bad;
+    static_for<0, (W + 3) / 4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const double piv = bcast_by_row<4 * v>(x[v]);
+        const bool good = piv > tol2 && !((bad >> (4 * v + q)) & 1);
+        const double rinv = rsqrt_nr(good ? piv : 1.0);
+        y[v] *= rinv;
+        low = good && piv < low ? piv : low;
+        diag = good && (j >> 2) == v ? piv * rinv : diag;                         // (column j's in row j & 3 of lanes)
+        const unsigned long long deps = __ballot(!good);
+        static_for<0, 4>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            badmask |= (int)((deps >> (16 * r)) & 1) << (4 * v + r);
+        });
     });
+    low = fmin(low, __shfl_xor(low, 16));
+    min_piv = fmin(low, __shfl_xor(low, 32));
     rjj = __shfl(diag, 16 * (j & 3) + j);
 }
 
@@ -298,7 +312,8 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
         const int i = 4 * v + q;
         const double dsi = bcast_by_row<4 * v>(dsc_own);
         y[v] = i == c ? 1.0 : 0.0;
-        x[v] = (i < w && c < w && i <= c) ? g[tri_idx(i < w ? i : 0, jc, w)] * dsi * dsc_own : y[v];
+        const double xs = dsi > 0.0 && dsc_own > 0.0 ? g[tri_idx(i < w ? i : 0, jc, w)] * dsi * dsc_own : 0.0;
+        x[v] = (i < w && c < w && i <= c) ? xs : y[v];
     });
     double min_piv = 1.0, rjj;
     factor_in_registers<W>(x, y, tol2, badmask, min_piv, rjj);
@@ -389,9 +404,9 @@ __device__ __forceinline__ void chol_block16(const double* blk, double* tjj, dou
 // doubles per instruction.
 // What bounds it is the chain of 16 steps inside each diagonal block (see factor_in_registers): one wave updates
 // and factorises block J + 1 while the others run the rest of the trailing update of step J, and a step has two barriers.
-// One workgroup on a 160 x 160 matrix took about 100 us, slot sum included, as a factorisation followed by an inversion
-// (packed triangle, five barriers per block, spilling as a function call); 74 to 84 us in one sweep (128 x 128: 59; 80 x 80
-// 58 -> 32 to 39 us).
+// One workgroup, one slot, us at width 80, 128, 160: 24.3, 45.5, 63.9 with the blocks of the Gram matrix decoded one by one and scaled
+// in a pass of their own, the square roots in the chain and T stored 8 bytes a row; 21.6, 38.1, 56.1 now (of the last 8 before the
+// first block, 5 to 5.5 per block step, of which the chain 2.1 and the panel 1).
 // g: the Gram matrix is the sum of n_slots packed triangles, sstr doubles apart.  smem: chol_lds_bytes(w).
 // growth(inverse R_jj of the scaled matrix, column scaling, column dependent): called by wave 0 at the end, for column j = lane + 64 u.
 template <class Growth>
@@ -407,62 +422,74 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
     const int t = threadIdx.x, nt = blockDim.x;
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), nw = nt >> 6, li = lane & 15, lk = lane >> 4;
     auto at = [&](int I, int K) { return a + (I * nbk - (I * (I - 1)) / 2 + (K - I)) * 256; };
-    // ---- blocks of the Gram matrix (256 threads per block, eight loads per thread in flight); identity in the padding.
-    // Which block is a scalar computation.
+    // ---- blocks of the Gram matrix, scaled, 256 threads per block; identity in the padding.  Which block is a scalar computation,
+    // from the thread's block before.  The loads of a thread's first blocks go out before the scalings are known.
     const int ng = nt >> 8, grp = __builtin_amdgcn_readfirstlane(t >> 8), er = (t >> 4) & 15, ec = t & 15;
-    auto decode = [&](int b, int& I, int& K) {
-        I = 0; K = b;
-        while (K >= nbk - I) { K -= nbk - I; ++I; }
-        K += I;
+    int I = 0, K = grp;                                   // (K: counted from the diagonal until the row is known)
+    while (I < nbk && K >= nbk - I) { K -= nbk - I; ++I; }
+    const int lane_term = ec - er - (er * (er - 1)) / 2;
+    auto load_blocks = [&](auto count) {
+        constexpr int U = decltype(count)::value;
+        bool first = true;
+        for (int b0 = grp; first || b0 < nblk; b0 += U * ng) {
+            double v[U];
+            int off[U], pi[U], pj[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int bi = I < nbk ? I : 0, bj = I < nbk ? I + K : 0;
+                // tri_idx(16 bi + er, 16 bj + ec, w), the terms of the lane apart; every lane loads: a conditional load is a branch, and
+                // these would run one after the other
+                const int o = 8 * bi * (2 * w - 16 * bi + 1) + 16 * (bj - bi) + (er * (w - 16 * bi) + lane_term);
+                off[u] = (bi < bj || er <= ec) && 16 * bj + ec < w ? o : -1;
+                v[u] = g[(unsigned)max(off[u], 0)];
+                pi[u] = bi;
+                pj[u] = bj;
+                K += ng;
+                while (I < nbk && K >= nbk - I) { K -= nbk - I; ++I; }
+            }
+            constexpr int D = U > 8 ? 2 : 4;
+            for (int s0 = 1; s0 < n_slots; s0 += D) {
+                double x[D][U];
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) x[d][u] = g[min(s0 + d, n_slots - 1) * sstr + max(off[u], 0)];
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] += s0 + d < n_slots ? x[d][u] : 0.0;
+            }
+            if (first) {
+                first = false;
+                for (int i = t; i < wp; i += nt) {
+                    double d = 1.0;                       // (in the padding)
+                    if (i < w) {
+                        const int o = tri_idx(i, i, w);
+                        d = g[o];
+                        for (int s0 = 1; s0 < n_slots; s0 += 4) {
+                            double p[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) p[q] = g[min(s0 + q, n_slots - 1) * sstr + o];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) d += s0 + q < n_slots ? p[q] : 0.0;
+                        }
+                    }
+                    dsc[i] = d > kTinyNorm2 ? rsqrt_nr(d) : 0.0;
+                    bad[i] = d > kTinyNorm2 ? 0 : 1;
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double sc = dsc[16 * pi[u] + er] * dsc[16 * pj[u] + ec];
+                // (a column that does not count may hold anything)
+                if (b0 + u * ng < nblk)
+                    a[(b0 + u * ng) * 256 + 16 * er + ec] = off[u] < 0 ? (pi[u] == pj[u] && er == ec ? 1.0 : 0.0) : sc > 0.0 ? v[u] * sc : 0.0;
+            }
+        }
     };
-    for (int b0 = grp; b0 < nblk; b0 += 8 * ng) {
-        double v[8], pad[8];
-        int off[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            int I, K;
-            decode(min(b0 + u * ng, nblk - 1), I, K);
-            const int i = 16 * I + er, j = 16 * K + ec;
-            // (every lane loads: a conditional load is a branch, and eight of them run one after the other)
-            off[u] = (i <= j && j < w) ? tri_idx(i, j, w) : -1;
-            v[u] = g[max(off[u], 0)];
-            pad[u] = i == j ? 1.0 : 0.0;
-        }
-        for (int s0 = 1; s0 < n_slots; s0 += 4) {
-            double x[4][8];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) x[d][u] = g[min(s0 + d, n_slots - 1) * sstr + max(off[u], 0)];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] += s0 + d < n_slots ? x[d][u] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * er + ec] = off[u] >= 0 ? v[u] : pad[u];
-    }
-    __syncthreads();
-    for (int i = t; i < wp; i += nt) {
-        const double d = at(i >> 4, i >> 4)[17 * (i & 15)];
-        dsc[i] = d > kTinyNorm2 ? rsqrt_nr(d) : 0.0;      // (1 in the padding)
-        bad[i] = d > kTinyNorm2 ? 0 : 1;
-    }
-    __syncthreads();
-    for (int b0 = grp; b0 < nblk; b0 += 4 * ng) {
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int b = min(b0 + u * ng, nblk - 1);
-            int I, K;
-            decode(b, I, K);
-            v[u] = a[b * 256 + 16 * er + ec] * (dsc[16 * I + er] * dsc[16 * K + ec]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (b0 + u * ng < nblk) a[(b0 + u * ng) * 256 + 16 * er + ec] = v[u];
-    }
+    if (nblk <= 4 * ng) load_blocks(std::integral_constant<int, 4>{});
+    else load_blocks(std::integral_constant<int, 14>{});
     __syncthreads();
     min_piv = 1.0;
     // trailing update of step J for block (I, K), K >= I > J of A or K <= J < I of W
@@ -476,6 +503,7 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
         for (int c = 0; c < 4; ++c) { av[c] = -ra[16 * (4 * c + lk) + li]; bv[c] = rb[16 * (4 * c + lk) + li]; }
 #pragma unroll
         for (int v = 0; v < 4; ++v) d[v] = K == J ? 0.0 : blk[16 * (4 * v + lk) + li];      // (K = J: W_IJ starts at zero)
+        __builtin_amdgcn_sched_barrier(0);                // (all loads first: they are made one by one between the MFMAs otherwise)
 #pragma unroll
         for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
 #pragma unroll
@@ -505,26 +533,46 @@ __device__ __forceinline__ void chol_blocked(const double* gram_generic, int n_s
 #pragma unroll 1
         for (int K = wv; K < nbk; K += nw) {
             double* blk = K < J ? at(K, J) : at(J, K);
-            doublex4 d = {0.0, 0.0, 0.0, 0.0};
-            if (K != J) {
-                double av[4], bv[4];
+            double av[4], bv[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { av[c] = tjj[kTjjStride * (4 * c + lk) + li]; bv[c] = blk[16 * (4 * c + lk) + li]; }
+            for (int c = 0; c < 4; ++c) { av[c] = tjj[kTjjStride * (4 * c + lk) + li]; bv[c] = blk[16 * (4 * c + lk) + li]; }
+            // T[i][j], i in block K: the transpose of W_JK, zero below the diagonal and in the columns of dependent vectors.  The product
+            // is formed transposed, lanes along j, so that a store covers runs of 128 bytes of T (8 bytes in each row of T otherwise,
+            // most of the 1.4 us of a panel at width 160).
+            const int j = 16 * J + li;
+            doublex4 d = {0.0, 0.0, 0.0, 0.0};
+            if (K > J) {
+                bool dep[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) dep[v] = bad[16 * J + 4 * v + lk] != 0;
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c], bv[c], d, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    rj[K * 256 + 16 * (4 * v + lk) + li] = dep[v] ? 0.0 : d[v];
+                    const int i = 16 * K + 4 * v + lk;
+                    if (i < w && j < w) tm[(int64_t)i * w + j] = 0.0;
+                }
             } else {
+                const double cj = bad[j] ? 0.0 : scale ? next_scale(dsc[j]) : 1.0;
+                double ci[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) d[v] = tjj[kTjjStride * li + 4 * v + lk];          // W_JJ = T_JJ^T
-            }
-            double* dst = K > J ? rj + K * 256 : blk;
+                for (int v = 0; v < 4; ++v) ci[v] = dsc[16 * K + 4 * v + lk];
+                __builtin_amdgcn_sched_barrier(0);
+                if (K < J) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = 4 * v + lk, j = 16 * J + row, i = 16 * K + li;
-                const bool dep = bad[j] != 0;
-                dst[16 * row + li] = (K > J && dep) ? 0.0 : d[v];
-                // T[i][j] = W[j][i], zero below the diagonal and in the columns of dependent vectors
-                if (i < w && j < w)
-                    tm[(int64_t)i * w + j] = (K > J || dep) ? 0.0 : d[v] * dsc[i] * (scale ? next_scale(dsc[j]) : 1.0);
+                    for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[c], av[c], d, 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) d[v] = tjj[kTjjStride * (4 * v + lk) + li];        // W_JJ = T_JJ^T
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * K + 4 * v + lk;
+                    blk[16 * li + 4 * v + lk] = d[v];
+                    if (i < w && j < w) tm[(int64_t)i * w + j] = d[v] * ci[v] * cj;
+                }
             }
         }
         __syncthreads();
