@@ -861,8 +861,6 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide || tiny ? kOneSlot : kGramRows1, asked_iterations(ctx), sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
                         final_cp, -1, -2, 0.0, false, 3, 0, L.st));
-    L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZQ, ROLE_Q, APPLY_RITZ,
-                        final_cp, -1, -2, 0.0, false, 3, 0, L.st));
     L.prof_mute = false;
 }
 

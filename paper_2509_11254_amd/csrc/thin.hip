@@ -334,6 +334,10 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
                                                                 int mode, int cp, int gate, int w_out_max, int which) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
+    if (blockIdx.z != 0) {
+        src_role = ROLE_ZQ;
+        dst_role = ROLE_Q;
+    }
     const int need2 = L.status[1];
     if (mode == APPLY_PASS2 && !need2) return;
     const bool do_gram = (mode == APPLY_PASS1) && need2;
@@ -531,6 +535,10 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
                                                                        int w_out_max, int which) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
+    if (blockIdx.z != 0) {
+        src_role = ROLE_ZQ;
+        dst_role = ROLE_Q;
+    }
     const int need2 = L.status[1];
     if (mode == APPLY_PASS2 && !need2) return;
     const bool do_gram = (mode == APPLY_PASS1) && need2;
@@ -599,6 +607,8 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
 
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
+// mode APPLY_RITZ: ROLE_ZP -> ROLE_P, and in the same launch (z = 1) ROLE_ZQ -> ROLE_Q, which shares nothing with it but tmat (as
+// two launches a refresh of 256 x 128 r = 4 took 199 us, 190 now, of 4096 x 4096 r = 8 940, 928 now)
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
 // (the others: 128)
 // which: operand copies to leave when cp > 0 (1 = outer-product, 2 = transposed, 3 = both; + 4: the outer-product ones are
@@ -608,6 +618,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                         bool small, int which, int slot_rows, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     if (w_out > w_in || (small && (w_in > kCholRegWidth || w_out != w_in || src_role != dst_role || mode == APPLY_RITZ))) return hipErrorInvalidValue;
+    const int n_sides = mode == APPLY_RITZ ? 2 : 1;
     dim3 grid(max_lenP / kGramRows2, n_ids), block(kThreads);
     if (!small && w_in <= kApplyStreamMaxWidth) {
         // a few rounds of workgroups over the whole launch, each walking several tiles of its layer
@@ -624,7 +635,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kfn, dim3(per_layer, n_ids), block, lds, st, layers, ids, src_role, dst_role,
+        hipLaunchKernelGGL(kfn, dim3(per_layer, n_ids, n_sides), block, lds, st, layers, ids, src_role, dst_role,
                            mode, cp, gate, w_out, which);
         return hipGetLastError();
     }
@@ -634,7 +645,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(apply_wide_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(apply_wide_kernel, grid, dim3(kApplyWideThreads), lds, st, layers, ids, src_role, dst_role, mode, cp,
+        hipLaunchKernelGGL(apply_wide_kernel, dim3(grid.x, n_ids, n_sides), dim3(kApplyWideThreads), lds, st, layers, ids, src_role, dst_role, mode, cp,
                            gate, w_in, w_out, which);
         return hipGetLastError();
     }
