@@ -375,7 +375,7 @@ def run_workload(name, args, primary):
 
     def k_of(st):
         k = st.refresh_iters_next
-        return k if 0 < k <= 16 else (14 if k <= 0 else min(14, st.refresh_iters_no_gap))
+        return k if 0 < k <= 16 else (16 if k <= 0 else min(16, st.refresh_iters_no_gap))
     # The same step early in a run: E reset to zero, then refreshes with three SSP-Comp steps between them; the third
     # one (the first whose iteration count is the layer's own) is timed.  The refresh timed above meets the state
     # after this benchmark's long stretch of error feedback (||E|| of the order of ||M||, the spectrum flat at the
@@ -391,8 +391,8 @@ def run_workload(name, args, primary):
     refresh_early_ms = timed(lambda i: comp_plain.compress_refresh(sets[2 % args.sets], E, Q, P), 1)
     # refresh arithmetic: block width b, k iterations of two products of 2 m n b flops each (+ the forming product)
     b_w = min(wl.r + max(8, wl.r // 4) + 7 & ~7, min(s.n for s in wl.layers))
-    # iterations per layer as the device decides them: the count for the subspace where 16 would do without shift, else the
-    # count for the error, at most 14
+    # iterations per layer as the device decides them: the count for the subspace if within the budget of 16, else
+    # the count for the error
     k_layers = [k_of(s_) for s_ in st_next]
     k_run = sum(k_layers) / len(k_layers)
     refresh_flops = sum(4.0 * s.rows * s.cols * b_w * k for s, k in zip(wl.layers, k_layers))

@@ -84,19 +84,17 @@ typedef struct {
 } psgd_layer_desc;
 
 typedef struct {
-    int32_t refresh_iters;      /* maximum number of subspace iterations of the SVD refresh (at most 255), in iterations
-                                   without shift; 0 = default (16).  From the third on the iterations are shifted by half the
-                                   last squared singular value of the block, which brings them further, and a seventh of those
-                                   are left out (16: 14 at most).  A layer's first two refreshes on a workspace run as
-                                   many as that (the second is the first to meet the state error feedback builds up),
-                                   unless by the singular values found so far the subspace has converged to what the
-                                   precision of the products leaves of it, where any refresh ends.  Later ones run the
+    int32_t refresh_iters;      /* maximum number of subspace iterations of the SVD refresh (at most 255); 0 = default
+                                   (16).  A layer's first two refreshes on a workspace run all of them (the second
+                                   is the first to meet the state error feedback builds up), unless by the singular
+                                   values found so far the subspace has converged to what the precision of the
+                                   products leaves of it, where any refresh ends.  Later ones run the
                                    number that the convergence factor rho = (theta_b/theta_r)^2 seen at its
-                                   last refresh needs for 1e-5, plus one, if as many without shift would be within the
-                                   maximum (rho <= 0.46 for 16); if not -- no gap after sigma_r to converge
+                                   last refresh needs for 1e-5, plus one, if that is within the maximum
+                                   (rho <= 0.46 for 16); if it is not -- no gap after sigma_r to converge
                                    across in the budget -- they run what keeps the error of the step
                                    within 1e-5 ||M||^2 of the optimum of Eq. (6) by the same Ritz values, at
-                                   least 2                                                              */
+                                   least 2, at most the maximum                                         */
     int32_t refresh_oversample; /* extra block columns beyond r; negative = default max(8, r/4); the
                                    block width r + oversample (r: the largest of the context) is rounded
                                    up to a multiple of 8 and capped at the smallest n of the context, or,
@@ -148,8 +146,8 @@ typedef struct {
 typedef struct {
     int32_t rank_deficient; /* number of columns of P~ zeroed by the rank test                  */
     int32_t refresh_iters_next; /* iterations the layer's next refresh needs to converge, from the Ritz
-                                   values of the last one (0: not known yet; above the maximum: those without
-                                   shift, and it will run refresh_iters_no_gap of them, see refresh_iters)  */
+                                   values of the last one (0: not known yet; above the maximum: it will
+                                   run refresh_iters_no_gap of them, see refresh_iters)                 */
     float sigma_max;        /* refresh only: largest and r-th Ritz value (singular value estimates) */
     float sigma_r;
     int32_t refresh_iters_no_gap; /* iterations the next refresh runs when the count above is beyond the

@@ -55,7 +55,7 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
                         bool small, int which, int slot_rows, hipStream_t st);
 hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, int max_len, int w, int dst_role,
                              int src_role, int warm, uint32_t seed, hipStream_t st);
-hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int budget, float* sigma_out,
+hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st);
 bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays, bool refresh);
 size_t tiny_lds_bytes(int64_t rows, int64_t cols);
@@ -819,13 +819,8 @@ double tol2_of(const psgd_ctx* c) {
     return t * t;
 }
 
-// Most iterations a layer's refresh runs: what the option asks for, less a seventh of those that may be shifted, which leave no
-// larger error than all of them without shift (see iteration_shift).
-int asked_iterations(const psgd_ctx* c) { return c->opt.refresh_iters > 0 ? c->opt.refresh_iters : 16; }
-int iteration_budget(const psgd_ctx* c) {
-    const int k = asked_iterations(c);
-    return k - std::max(k - 2, 0) / 7;
-}
+// Most iterations a layer's refresh runs
+int iteration_budget(const psgd_ctx* c) { return c->opt.refresh_iters > 0 ? c->opt.refresh_iters : 16; }
 
 // Block subspace iteration + Rayleigh-Ritz for the layers of `L`: leaves P~ (Ritz vectors of the r
 // largest singular values) in thin[ROLE_P] and Q = M^T P~ in thin[ROLE_Q].
@@ -858,7 +853,7 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     const bool wide = wz > kWideWidth;
     if (wide) L.note(launch_gram_sum(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, L.gram_rows_n, L.gram_rows_t, -1, 0, L.st));
     if (!tiny) L.second_pass_deferred(wz, cpz, tol2);
-    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide || tiny ? kOneSlot : kGramRows1, asked_iterations(ctx), sigma_out, L.st));
+    L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide || tiny ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
                         final_cp, -1, -2, 0.0, false, 3, 0, L.st));
     L.prof_mute = false;

@@ -304,7 +304,6 @@ __device__ inline int resolve_epilogue(const LayerDev& L, int epi_flags, int gat
 // Whether the Z that a factorisation inside the subspace iteration orthonormalises is followed by a Y that may be left as
 // it is: from the second iteration on, except in the layer's last one.
 constexpr int kOrthYIterations = 1;
-constexpr int kPlainIterations = kOrthYIterations + 2;      // of a refresh whose Y is orthonormalised no further: the first two and the last
 __device__ inline bool scales_next(const LayerDev& L, int role, int gate) {
     return gate >= 0 && role == ROLE_ZP && (gate & 0xff) >= kOrthYIterations && gate_open(L, gate_with_kind(gate, 1));
 }

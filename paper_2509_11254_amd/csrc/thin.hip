@@ -814,12 +814,12 @@ __device__ inline void ritz_ranks(const double* lam, int* rank_of, int w, double
 }
 // What a refresh leaves in the layer's status words, from the Ritz values in L.eval; by the threads of one workgroup.
 constexpr int kJacobiMaxWidth = 200;       // of jacobi_kernel: five 2 x 2 blocks per thread
-__device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budget, float* sigma_out) {
+__device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, float* sigma_out) {
     const int t = threadIdx.x, r = L.r;
     // Iterations for a cut without a gap (see refresh_iterations).  Where the count that the subspace needs is out of
     // reach, what is asked of the step is its error (Lemma 2 / Eq. (6): ||M - P~ P~^T M||^2 = sum_{i > r} sigma_i^2
-    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= rho^3 (rho / (2 - rho))^(k - 3), rho = theta_b / theta_i,
-    // after k iterations from any start (theta: Ritz values = squared singular value estimates; three of them are not shifted), costs at most
+    // at the optimum).  Direction i <= r of the block, still off by sin(theta_i) <= (theta_b / theta_i)^k after k
+    // iterations from any start (theta: Ritz values = squared singular value estimates), costs at most
     // sin^2(theta_i) (theta_i - theta_b) on top of the optimum: the directions well above the cut cost nothing after
     // two iterations, the ones in the cluster at the cut have little to lose.  The count is the smallest k for which
     // the sum of these is below 1e-5 of ||M||^2 >= sum of the Ritz values: a tenth of the 1e-4 the step is held to,
@@ -832,7 +832,7 @@ __device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budg
     if (t < 64) {
         constexpr int kEach = (kJacobiMaxWidth + 63) / 64;
         const double lb = w > r ? L.eval[w - 1] : 0.0;
-        double tr = 0.0, term[kEach], plain[kEach], shifted[kEach];
+        double tr = 0.0, term[kEach], rho2[kEach];
 #pragma unroll
         for (int u = 0; u < kEach; ++u) {
             const int i = t + 64 * u;
@@ -840,9 +840,8 @@ __device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budg
             tr += fmax(li, 0.0);
             const bool counts = i < r && lb > 0.0 && li > lb;
             const double rho = counts ? lb / li : 0.0;
-            plain[u] = rho * rho;
-            shifted[u] = plain[u] / ((2.0 - rho) * (2.0 - rho));
-            term[u] = counts ? plain[u] * plain[u] * (li - lb) : 0.0;
+            rho2[u] = rho * rho;
+            term[u] = counts ? rho2[u] * rho2[u] * (li - lb) : 0.0;
         }
         for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
         for (int k = 2; k <= 64; ++k) {
@@ -855,7 +854,7 @@ __device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budg
                 break;
             }
 #pragma unroll
-            for (int u = 0; u < kEach; ++u) term[u] *= k < kPlainIterations ? plain[u] : shifted[u];
+            for (int u = 0; u < kEach; ++u) term[u] *= rho2[u];
         }
     }
     for (int k = t; k < r; k += blockDim.x) {
@@ -865,24 +864,16 @@ __device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budg
         if (k == r - 1) L.status[3] = __float_as_int(sg);
     }
     if (t == 0) {
-        // The iteration contracts the error of the leading r-dimensional subspace by about rho = theta_b / theta_r per plain
-        // step and rho / (2 - rho) per shifted one (theta = Ritz values, the smallest one of the block standing
+        // The iteration contracts the error of the leading r-dimensional subspace by about
+        // rho = theta_b / theta_r per step (theta = Ritz values, the smallest one of the block standing
         // in for sigma_{b+1}^2); the next refresh of this layer needs as many steps as 1e-5 takes (a tenth of
         // the 1e-4 bar on the subspace), plus one.  (Error feedback drives M towards rho = 1: what is not
-        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)  A cut counts as one
-        // without a gap where plain steps would be more than the option asks for: of 7B-shaped layers in such a run most need
-        // 17 to 25 plain steps or 12 to 14 shifted ones, and their error needs 4 or 5 (a block of them 6.0 ms per refresh, 6.5
-        // with as many as converge).
+        // sent accumulates in E until it is as large as what is.  The launches cap the count, see gate_open.)
         int k_next = 255;
         const double lr = L.eval[r - 1], lb = L.eval[w - 1];
         if (w > r && lr > 0.0 && lb >= 0.0) {
             const double rho = lb / lr;
-            if (rho < 0.999) {
-                const double plain = log(fmax(rho, 1e-12)), left = log(1e-5) - kPlainIterations * plain;
-                const int unshifted = rho <= 1e-12 ? 2 : (int)ceil(log(1e-5) / plain) + 1;
-                k_next = left >= 0.0 || unshifted > budget ? unshifted
-                                                           : kPlainIterations + (int)ceil(left / (plain - log(2.0 - rho))) + 1;
-            }
+            if (rho < 0.999) k_next = (rho <= 1e-12) ? 2 : (int)ceil(log(1e-5) / log(rho)) + 1;
         }
         L.status[4] = max(2, min(255, k_next));
         L.status[9] = ke;
@@ -907,7 +898,7 @@ __device__ inline void ritz_notes(const LayerDev& L, int w, int sweeps, int budg
 template <int NBLK>
 __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict__ layers,
                                                       const int* __restrict__ ids, int role, int v_rows,
-                                                      int slot_rows, int budget, float* __restrict__ sigma_out) {
+                                                      int slot_rows, float* __restrict__ sigma_out) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     const int w = L.thin[role].width;
     const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
@@ -1057,7 +1048,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const LayerDev* __restrict
     for (int i = ty; i < nv; i += tyw)
         if (row0 + i < w)
             for (int j = tx; j < w; j += txw) tm[(int64_t)(row0 + i) * w + rank_of[j]] = v[i * n + j];
-    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, budget, sigma_out);
+    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, sigma_out);
 }
 
 // v of lane (lane ^ 2^B), B < 3, and of lane (lane ^ 8 * 2^B): moves on the data path, no LDS
@@ -1170,7 +1161,7 @@ __device__ __forceinline__ void jacobi_phase(double* h, double* jac, int pp, int
 // 863, 160 1772 -> 750; 7 layers of width 80 488 to 578 -> 240 to 253, 64 601 -> 302; 128 of width 104 1088 -> 571, 256 of 24 131 -> 79.
 template <int NT>
 __global__ __launch_bounds__(NT) void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids, int role,
-                                                          int v_rows, int slot_rows, int budget, float* __restrict__ sigma_out) {
+                                                          int v_rows, int slot_rows, float* __restrict__ sigma_out) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     const int w = L.thin[role].width;
     const int n_slots = (side_len(L, side_of_role(L.transposed, role)) + slot_rows - 1) / slot_rows;
@@ -1332,7 +1323,7 @@ __global__ __launch_bounds__(NT) void jacobi_block_kernel(const LayerDev* __rest
     double* __restrict__ tm = L.tmat;
     for (int i = wv; i < min(v_rows, w - row0); i += nw)
         for (int j = lane; j < w; j += 64) tm[(int64_t)(row0 + i) * w + rank_of[j]] = vt[j * v_rows + i];
-    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, budget, sigma_out);
+    if (blockIdx.x == 0) ritz_notes(L, w, sweeps, sigma_out);
 }
 
 size_t jacobi_lds_bytes(int w, int v_rows) {
@@ -1346,8 +1337,7 @@ size_t jacobi_block_lds_bytes(int w, int v_rows) {
 }
 
 // slot_rows: rows per partial Gram matrix of thin[role] (kOneSlot: gram_sum_kernel has added them up)
-// budget: iterations that the option refresh_iters asks for
-hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, int budget, float* sigma_out,
+hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
                          hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     constexpr size_t kLdsCap = 159 * 1024;     // of the 160 KB a workgroup can have
@@ -1366,7 +1356,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kfn, dim3((w + v_rows - 1) / v_rows, n_ids), dim3(threads), lds, st, layers, ids, role, v_rows, slot_rows, budget, sigma_out);
+        hipLaunchKernelGGL(kfn, dim3((w + v_rows - 1) / v_rows, n_ids), dim3(threads), lds, st, layers, ids, role, v_rows, slot_rows, sigma_out);
         return hipGetLastError();
     }
     const int n = (w + 1) & ~1;
@@ -1383,7 +1373,7 @@ hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int 
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kfn, dim3((n + v_rows - 1) / v_rows, n_ids), dim3(kThreadsWide), lds, st, layers, ids, role, v_rows, slot_rows, budget, sigma_out);
+    hipLaunchKernelGGL(kfn, dim3((n + v_rows - 1) / v_rows, n_ids), dim3(kThreadsWide), lds, st, layers, ids, role, v_rows, slot_rows, sigma_out);
     return hipGetLastError();
 }
 

@@ -99,3 +99,67 @@ def test_ends_when_converged(rows, cols, r, n_layers, kind):
             assert np.linalg.norm(e - (m - p @ q.T)) <= 2e-6 * np.linalg.norm(m)
         for x in case.E:
             x.zero_()
+
+
+def _iterate(m, start, iters):
+    """Z and Y = M^T Z after `iters` iterations Z = orth(M Y), Y = M^T Z."""
+    y = start
+    for _ in range(iters):
+        z, _ = np.linalg.qr(m @ y)
+        y = m.T @ z
+    return z, y
+
+
+def _ritz_vectors(z, y, r):
+    return z @ np.linalg.eigh(y.T @ y)[1][:, ::-1][:, :r]
+
+
+def _start(warm, layer, b):
+    n, r = warm.shape
+    return np.concatenate([warm.astype(np.float64), orc.counter_uniform(SEED, layer, n, b)[:, r:]], axis=1)
+
+
+def _tall(x, rows, cols):
+    return x.astype(np.float64) if rows >= cols else x.T.astype(np.float64)
+
+
+# One direction so far above the rest that the factor of Z asks for an orthonormal Y in every iteration (300 at two planes, 5000
+# at three), no gap at the cut: no more is left above the optimum than 16 iterations in fp64 leave.  And the iterations that the layer
+# asks for are those that its spectrum needs, with and without a gap.
+@pytest.mark.parametrize("rows,cols,r,b", [(200, 150, 8, 16), (520, 333, 8, 16), (408, 500, 32, 40), (700, 512, 76, 96)])
+@pytest.mark.parametrize("planes", [2, 3])
+@pytest.mark.parametrize("outlier", [True])
+@pytest.mark.parametrize("gap", [False, True])
+def test_every_iteration_asked_for(rows, cols, r, b, planes, outlier, gap):
+    rng = np.random.default_rng(rows + 7 * r)
+    n = min(rows, cols)
+    s = 0.95 ** (np.arange(n) / (b - r))
+    if gap:
+        s[r:] *= 0.75
+    if outlier:
+        s[0] = 300.0 if planes == 2 else 5000.0
+    mat = _spectrum_matrix(rng, rows, cols, s)
+    warm = rng.standard_normal((n, r)).astype(np.float32)
+    case = Case([(rows, cols)], r, 1, synth.F32, lds=[(cols + 7) // 8 * 8], precision=planes, seed=SEED)
+    case.upload([[mat]], [np.zeros((rows, cols), np.float32)], [warm])
+    case.compress(refresh=True)
+    m = _tall(mat, rows, cols)
+    sv = np.linalg.svd(m, compute_uv=False)
+    z16, y16 = _iterate(m, _start(warm, 0, b), 16)
+    plain, fewer = (np.sum(sv[:r] ** 2) - np.sum(np.linalg.svd(_iterate(m, _start(warm, 0, b), k)[1], compute_uv=False)[:r] ** 2) for k in (16, 14))
+    # (P~ orthonormal to 64 bits: its rounding times sigma_1 is more than what is looked for)
+    p, _ = np.linalg.qr(case.outputs(0)[0])
+    excess = np.sum(sv[:r] ** 2) - np.sum((m.T @ p) ** 2)
+    # an error of 2^-24 (two planes 2^-17) of sigma_1 in each column of a product
+    slack = 4 * r * (2.0 ** (-24 if planes == 3 else -17) * sv[0]) ** 2 + 1e-13 * np.sum(sv ** 2)
+    st = case.comp.status(0)
+    theta = np.sort(np.linalg.eigvalsh(y16.T @ y16))[::-1]
+    rho = theta[b - 1] / theta[r - 1]
+    count = int(np.ceil(np.log(1e-5) / np.log(rho))) + 1
+    lost = [np.sum((theta[b - 1] / theta[:r]) ** (2 * k) * (theta[:r] - theta[b - 1])) for k in range(2, 65)]
+    no_gap = 2 + int(np.argmax(np.array(lost) <= 1e-5 * theta.sum()))
+    print(rows, cols, r, "excess", excess, "16 iterations", plain, "14", fewer, "asks for", st.refresh_iters_next, count, st.refresh_iters_no_gap, no_gap)
+    assert excess <= 1.05 * plain + slack
+    # (by the library's Ritz values: those of the last columns have not settled, or carry the rounding of the products)
+    assert abs(st.refresh_iters_next - count) <= max(1, 0.05 * count)
+    assert abs(st.refresh_iters_no_gap - no_gap) <= 1
