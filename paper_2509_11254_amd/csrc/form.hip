@@ -45,10 +45,10 @@ template <int NB, int PL, int LAZY> constexpr size_t form_lds_bytes() {
 // The end of a row-mode product on 32-row blocks: the four waves' partial results (each over its quarter of every
 // step's reduction range) are added through LDS, and the block's 32 x cp result goes out -- as one of n_split partial
 // sums for finish_kernel, or as rows of the result, then with the block's partial Gram matrix if the launch asks for
-// it (one slot per 32 rows).  shift: see tile_epilogue.
+// it (one slot per 32 rows).
 template <int NB>
 __device__ inline void row_epilogue(unsigned char* smem, const floatx16 (&acc)[NB], const LayerDev& L, int out_role,
-                                    int epi_flags, int sp, int ob, int n_split, double shift = 0.0) {
+                                    int epi_flags, int sp, int ob, int n_split) {
     constexpr int cp = 32 * NB;
     const int t = threadIdx.x;
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -83,8 +83,7 @@ __device__ inline void row_epilogue(unsigned char* smem, const floatx16 (&acc)[N
         const bool gram = (epi_flags & EPI_KIND_MASK) == EPI_GRAM;
         for (int i = t; i < FR * cp; i += kThreads) {
             const int row = i / cp, col = i - row * cp;
-            float v = total(row, col);
-            if (shift != 0.0 && col < T.width && row0 + row < L.rows) v = (float)((double)v - shift * (double)as_global(T.ptr)[(int64_t)(row0 + row) * T.ld + col]);
+            const float v = total(row, col);
             if (gram) red[row * RW + col] = v;
             if (col < T.width && row0 + row < L.rows) as_global(T.ptr)[(int64_t)(row0 + row) * T.ld + col] = v;
         }
@@ -688,7 +687,7 @@ __global__ __launch_bounds__(kThreads, 2) void row_prod_kernel(const LayerDev* _
     } else {
         for (int it = 0; it < n_loc; ++it) step(it, xa);
     }
-    row_epilogue<NB>(smem, acc, L, out_role, epi_flags, sp, ob, n_split, iteration_shift(L, out_role, gate));
+    row_epilogue<NB>(smem, acc, L, out_role, epi_flags, sp, ob, n_split);
 }
 
 // ---------------------------------------------------------------------------------------------------------------

@@ -212,45 +212,13 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
 
 // Epilogue on a complete ROWS x cp output tile held in LDS as fp32 [ROWS][tw]: store the rows of the
 // thin result, then either the partial Gram matrix of these rows (fp64, upper triangle, slot = block
-// index) or the split-bf16 operand copies of the rows.  shift: subtract that multiple of the rows being replaced first.
-// Called by all NT threads of the workgroup.
+// index) or the split-bf16 operand copies of the rows.  Called by all NT threads of the workgroup.
 template <int ROWS, int NT = kThreads>
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
-                                     int out_lenP, int cp, int epi, float* otile, int tw, bool kept = false,
-                                     int copies = 3, double* red = nullptr, double shift = 0.0) {
+                                     int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
+                                     int copies = 3, double* red = nullptr) {
     const int t = threadIdx.x;
     const int w = T.width;
-    if (shift != 0.0) {
-        // the rows hold what they are replaced by, the Z of the iteration before (see iteration_shift)
-        const PSGD_GLOBAL float* old = as_global(T.ptr) + (int64_t)ob * ROWS * T.ld;
-        const int n_rows = min(ROWS, out_len - ob * ROWS);
-        const float inv_w = 1.0f / (float)w;
-        if (T.ld == w && (w & 3) == 0) {
-            for (int e0 = 4 * t; e0 < n_rows * w; e0 += 16 * NT) {
-                floatx4 z[4];
-#pragma unroll
-                for (int d = 0; d < 4; ++d) z[d] = *reinterpret_cast<const PSGD_GLOBAL floatx4*>(old + (e0 + 4 * d * NT < n_rows * w ? e0 + 4 * d * NT : e0));
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const int e = e0 + 4 * d * NT;
-                    if (e >= n_rows * w) continue;
-                    int row = (int)(((float)e + 0.5f) * inv_w);
-                    int c = e - row * w;
-                    if (c < 0) { --row; c += w; } else if (c >= w) { ++row; c -= w; }
-                    float* o = otile + row * tw + c;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = (float)((double)o[q] - shift * (double)z[d][q]);
-                }
-            }
-        } else {
-            for (int e = t; e < n_rows * w; e += NT) {
-                const int row = e / w, col = e % w;
-                float& o = otile[row * tw + col];
-                o = (float)((double)o - shift * (double)old[(int64_t)row * T.ld + col]);
-            }
-        }
-        __syncthreads();
-    }
     if (copies != 2) {
         PSGD_GLOBAL float* dst = as_global(T.ptr) + (int64_t)ob * ROWS * T.ld;
         const int n_rows = min(ROWS, out_len - ob * ROWS);
@@ -683,7 +651,7 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
             otile[row * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, nullptr, FORM ? 0.0 : iteration_shift(L, out_role, gate));
+    tile_epilogue<BT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
 // The products that only read M from kWideProd blocks of 32 columns on.  A workgroup of prod_kernel has a compute unit (nearly) to
@@ -914,7 +882,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
             for (int v = 0; v < 16; ++v) otile[(32 * rg + 8 * (v >> 2) + 4 * lg + (v & 3)) * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, nullptr, iteration_shift(L, out_role, gate));
+    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
@@ -928,7 +896,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
 // chol_gate >= -1: the last workgroup to finish a layer goes on to factorise the sum of the partial Gram
 // matrices (first CholeskyQR pass) if that gate is open, unless the layer is one where the apply kernel
 // does that for itself; -2: no factorisation follows, or one in a launch of its own.
-// ITER: inside the subspace iteration (gate >= 0), with its shift and notes.
+// ITER: inside the subspace iteration (gate >= 0), with its gates and notes.
 static_assert(BT == kGramRows1, "one partial Gram matrix per output block of a product");
 template <int FB, int NT, bool ITER>
 __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__ layers,
@@ -1008,7 +976,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__
     }
     __syncthreads();
     double* red = FB == BT && T.width <= 16 ? reinterpret_cast<double*>(smem + (((size_t)FB * tw * sizeof(float) + 7) & ~(size_t)7)) : nullptr;
-    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red, ITER ? iteration_shift(L, out_role, gate) : 0.0);
+    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red);
     // (FB = 64 is for widths whose factorisation is a launch of its own)
     if constexpr (FB == BT) {
         if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && (!ITER || gate_open(L, chol_gate))) {

@@ -135,15 +135,14 @@ struct LayerDev {
     double* gram;           // [slots][w(w+1)/2] partial Gram matrices (packed upper triangles), one slot per
                             // row block of the producer
     double* tmat;           // [wmax*wmax] small factor applied from the right
-    double* eval;           // [wz + 2]: Ritz values; during the subspace iteration the scales of Z's columns and, at wz, the
-                            // reference of its shift (see iteration_shift)
+    double* eval;           // [wz + 2]: Ritz values; during the subspace iteration the scales of Z's columns
     int* status;            // [kStatusWords] : 0 rank_deficient, 1 second-pass-needed flag, 2 sigma_max bits, 3 sigma_r bits,
                             //       4 iterations the next refresh needs (0 = not known yet), 5 Jacobi sweeps of the last
                             //       refresh, 6 and 7 arrival counters of finish_kernel and apply_kernel, 8 refreshes this
                             //       layer has run in this workspace, 9 iterations its next refresh runs if its cut has no
                             //       gap (see refresh_iterations), 10 whether this iteration's Y is orthonormalised (see Spread),
                             //       11 iterations after which the running refresh has converged (0: not known, see
-                            //       converged_after), 12 shifted iterations of the running refresh
+                            //       converged_after)
 };
 
 __host__ __device__ inline int side_of_role(int transposed, int role) {
@@ -247,8 +246,8 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 
 // Launches inside the subspace iteration carry a gate (-1 outside it), see make_gate: the iteration the launch
 // belongs to, its kind, the iteration budget and the number of iterations the host launches this time.
-// A layer runs k iterations at most (it ends sooner where it converges, see converged_after): the whole budget in its first two refreshes (the first knows nothing; the second is the
-// first to meet the error-feedback state, whose spectrum is flatter at the cut than that of the first step's plain
+// A layer runs k iterations at most (it ends sooner where it converges, see converged_after): the whole budget in its first
+// two refreshes (the first knows nothing; the second is the first to meet the error-feedback state, whose spectrum is flatter at the cut than that of the first step's plain
 // gradient: on a 4096 x 4096 run sigma_{b+1}/sigma_r went from 0.13 at t = 0 to 0.43 at t = 10, and the count taken
 // from t = 0 left sin(theta) = 2e-4); after that status[4] (what
 // its spectrum needs to converge, from the Ritz values of its last refresh) when that is within the budget; and
@@ -308,48 +307,25 @@ __device__ inline bool scales_next(const LayerDev& L, int role, int gate) {
     return gate >= 0 && role == ROLE_ZP && (gate & 0xff) >= kOrthYIterations && gate_open(L, gate_with_kind(gate, 1));
 }
 
-
-// The shift of the subspace iteration.  Z' = (M M^T - x) Z with x = c / 2 turns the directions outside the block, whose squared
-// singular values lie in [0, c], by at most c / 2 and the r-th by theta_r - c / 2: the error shrinks by rho / (2 - rho), rho = c / theta_r, where
-// M M^T alone gives rho -- twice the exponent where the cut has no gap, and as x Z is what the product writes over, for one read of
-// the thin block.  c is taken from the factor R of the iteration before: R_jj over the norm s_j of the stored column of Z is what a
-// column that has lined up grew by, theta_j - x, and a mixture of directions outside [of values in 0 .. c] grows by at most c / 2, so that x +
-// min R_jj / s_j comes out at theta_b (singular value b, the block's last) from below, and never above c for columns that have not lined up.
-// Not shifted: the iterations up to the one after Y was orthonormalised (Z would have to be multiplied by the same factor), layers
-// with dependent columns (theta_b = 0), and the last (a plain step leaves of Z's rounding what it always left).
-// A model of the iteration (fp32 storage, both plane counts; nine matrices of 256 x 128 to 1500 x 1000, blocks of 16 to 120, after 0 to 200
-// refreshes of error feedback, three starts each) needs 4 to 14 iterations for the error that 16 without shift leave, both of
-// the subspace and of the compression; shifts in the order of Chebyshev points save one more and ask for an orthonormal Y two to five times as often.
-// Measured, refreshes of 16 iterations and these, us, in a run and the first on a new matrix: 256 x 128 fp32 r = 4 275 -> 238 and
-// 404 -> 285, 4096 x 4096 r = 8 1132 -> 976 and 1490 -> 999, 8192 x 8192 r = 128 8747 -> 7028 and 8122 -> 7840, a 7B-shaped bf16 block r = 64
-// 5980 -> 5059 and 9034 -> 7697.
-__device__ inline double iteration_shift(const LayerDev& L, int role, int gate) {
-    if (gate < 0 || role != ROLE_ZP) return 0.0;
-    const int it = gate & 0xff;
-    if (it <= kOrthYIterations || it >= run_iterations(L, gate) - 1 || L.status[10] != 0) return 0.0;
-    return 0.5 * L.eval[L.wz];
-}
 // What a factorisation inside the iteration notes besides its result: the powers of two of next_scale and whether Y is to be
-// orthonormalised; with NOTE_SHIFTS also c, from an iteration that may shift (above), with NOTE_FIRST_Y c from the first Y (Y^T Y = Z^T M M^T Z).
-enum IterationNote { NOTE_SCALE = 1, NOTE_SHIFTS = 2, NOTE_FIRST_Y = 4 };
+// orthonormalised; with NOTE_GROWTH also what the columns grew by (R_jj over the norm of the stored column of Z of the iteration
+// before; not known where Y was orthonormalised), and from it whether the iteration has converged.
+enum IterationNote { NOTE_SCALE = 1, NOTE_GROWTH = 2 };
 __device__ inline int iteration_notes(const LayerDev& L, int role, int gate) {
-    if (gate < 0) return 0;
-    const int it = gate & 0xff;
-    if (role == ROLE_ZQ) return it == 0 ? NOTE_FIRST_Y : 0;
-    return !scales_next(L, role, gate) ? 0 : it > kOrthYIterations && L.status[10] == 0 ? NOTE_SCALE | NOTE_SHIFTS : NOTE_SCALE;
+    if (gate < 0 || !scales_next(L, role, gate)) return 0;
+    return (gate & 0xff) > kOrthYIterations && L.status[10] == 0 ? NOTE_SCALE | NOTE_GROWTH : NOTE_SCALE;
 }
-// Iterations after which the refresh ends, from its iteration `it`, 0 if it is not clear yet: one more, without shift, when those
-// made so far and that one shrink the error by 2^-37.8 (two planes 2^-29.9), 10^-4 of what the products' rounding leaves of the subspace -- the start
-// may be that far off.  rho: c / theta_r, theta_r from the smallest R_jj / s_j of the first r columns, is low by what the block has
-// not yet found outside itself: after it + 1 iterations directions that a random column holds 1 / sqrt(n) of show up to
-// a factor n^(1 / (2 it + 2)).
-__device__ inline int converged_after(int planes, int n, int it, double c, double theta_r, int shifted) {
-    const float rho = (float)(c / theta_r) * exp2f(__log2f((float)n) * 0.5f / (float)(it + 1));
+// Iterations after which the refresh ends, from its iteration `it`, 0 if it is not clear yet: one more when those made so far and
+// that one shrink the error by 2^-37.8 (two planes 2^-29.9), 10^-4 of what the products' rounding leaves of the subspace -- the start
+// may be that far off.  An iteration shrinks it by rho = theta_{b+1} / theta_r at most; theta_b, the smallest growth, stands in for theta_{b+1},
+// and the smallest of the first r columns for theta_r.  Both are low by what the block has not yet found outside itself: after it + 1
+// iterations directions that a random column holds 1 / sqrt(n) of show up to a factor n^(1 / (2 it + 2)).
+// (A block without columns beyond the r-th has rho >= 1 by this and runs all its iterations.)
+__device__ inline int converged_after(int planes, int n, int it, double theta_b, double theta_r) {
+    const float rho = (float)(theta_b / theta_r) * exp2f(__log2f((float)n) * 0.5f / (float)(it + 1));
     if (!(rho < 1.0f)) return 0;
-    const float plain = __log2f(fmaxf(rho, 1e-30f));
-    return (float)(it + 2) * plain - (float)shifted * __log2f(2.0f - rho) <= (planes == 3 ? -37.8f : -29.9f) ? it + 2 : 0;
+    return (float)(it + 2) * __log2f(fmaxf(rho, 1e-30f)) <= (planes == 3 ? -37.8f : -29.9f) ? it + 2 : 0;
 }
-
 
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double doublex4;
 

@@ -236,12 +236,11 @@ __device__ __forceinline__ void note_block(Spread& spread, double rjj, double ds
     spread.add_block(__builtin_amdgcn_frexp_exp(norm * norm), __builtin_amdgcn_frexp_exp((rjj * norm) * (rjj * norm)), counts);
 }
 
-// The state behind the shift of the subspace iteration (see iteration_shift): in the layer's eval and status words, or in the
-// registers of the wave that factorises (scale: of column lane & 15).
+// What a factorisation inside the iteration notes (see IterationNote), where the wave that factorises keeps it in registers instead of
+// the layer's eval and status words (scale: of column lane & 15).
 struct IterationState {
-    double c = 0.0, scale = 1.0;
-    int shifted = 0, asks = 0, ends = 0;
-    bool shifts = false;                // this iteration's product is shifted by c / 2
+    double scale = 1.0;
+    int asks = 0, ends = 0;
 };
 constexpr double kLargest = 1e300;
 // minimum over the 16 lanes of a row of lanes; over the wave
@@ -256,22 +255,13 @@ __device__ inline double min_wave(double v) {
     return fmin(v, __shfl_xor(v, 32));
 }
 // What a factorisation tells the next iterations, by one wave.  low, low_r: smallest growth of all columns and of the first r
-// (NOTE_FIRST_Y: smallest R_jj^2).  Called before status[10] is rewritten.
 __device__ inline void note_iteration(const LayerDev& L, int note, int it, double low, double low_r, bool dependent, bool asks, IterationState* own) {
-    const bool first_y = (note & NOTE_FIRST_Y) != 0, shifts = (note & NOTE_SHIFTS) != 0;
-    const double c0 = own ? own->c : L.eval[L.wz], x = shifts ? 0.5 * c0 : 0.0;
-    const int shifted = first_y ? 0 : (own ? own->shifted : L.status[12]) + (x > 0.0 ? 1 : 0);
-    const double c = dependent ? 0.0 : first_y ? low : shifts ? x + low : c0;
-    const int ends = shifts && !dependent && !asks ? converged_after(L.planes, min(L.rows, L.cols), it, c, x + low_r, shifted) : 0;
+    const int ends = (note & NOTE_GROWTH) && !dependent && !asks ? converged_after(L.planes, min(L.rows, L.cols), it, low, low_r) : 0;
     if (own) {
-        own->c = c;
-        own->shifted = shifted;
         own->asks = asks ? 1 : 0;
         own->ends = ends;
-    } else if ((threadIdx.x & 63) == 0) {
-        L.eval[L.wz] = c;
-        L.status[12] = shifted;
-        if (ends > 0) L.status[11] = ends;
+    } else if (ends > 0 && (threadIdx.x & 63) == 0) {
+        L.status[11] = ends;
     }
 }
 
@@ -327,14 +317,12 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     if (note && (write_status || own)) {
         // (own: the caller keeps the state in registers, lane c column c's)
         const double norm = rjj * __builtin_amdgcn_rcp(good ? dsc_own : 1.0);
-        const double prev = own ? own->scale : (note & NOTE_SHIFTS) ? L.eval[jc] : 1.0;
-        const double grew = good ? (note & NOTE_FIRST_Y ? norm * norm : norm / prev) : kLargest;
+        const double prev = own ? own->scale : (note & NOTE_GROWTH) ? L.eval[jc] : 1.0;
+        const double grew = good ? norm / prev : kLargest;
         note_iteration(L, note, it, min_lane16(grew), min_lane16(c < L.r ? grew : kLargest), (badmask & ((1 << w) - 1)) != 0,
-                       (note & NOTE_SCALE) && spread.asks(L.planes, min_piv), own);
-        if (note & NOTE_SCALE) {
-            if (own) own->scale = csc;
-            else if ((threadIdx.x & 63) < w) L.eval[jc] = csc;
-        }
+                       spread.asks(L.planes, min_piv), own);
+        if (own) own->scale = csc;
+        else if ((threadIdx.x & 63) < w) L.eval[jc] = csc;
     }
     // lane (q, c): entries 4 v + q of row c of tmat = D T with the dependent columns zeroed
     if (c < w) {
@@ -628,7 +616,7 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
     double prev[kMaxWaveColumns];
     if constexpr (!NARROW) {
 #pragma unroll
-        for (int u = 0; u < kMaxWaveColumns; ++u) prev[u] = t < 64 && (note & NOTE_SHIFTS) ? as_global(L.eval)[min(t + 64 * u, w - 1)] : 1.0;
+        for (int u = 0; u < kMaxWaveColumns; ++u) prev[u] = t < 64 && (note & NOTE_GROWTH) ? as_global(L.eval)[min(t + 64 * u, w - 1)] : 1.0;
     }
     double low = kLargest, low_r = kLargest;
     auto growth = [&](auto&& inverse_of, const double* dsc, const int* bad) {
@@ -638,17 +626,17 @@ __device__ __forceinline__ void chol_body(const LayerDev& L, int role, double to
             const int j = t + 64 * u;
             if (j >= w) continue;
             if (!bad[j]) {
-                const double norm = 1.0 / (inverse_of(j) * dsc[j]), grew = note & NOTE_FIRST_Y ? norm * norm : norm / prev[u];
+                const double grew = 1.0 / (inverse_of(j) * dsc[j]) / prev[u];
                 low = fmin(low, grew);
                 if (j < L.r) low_r = fmin(low_r, grew);
             }
-            if (scale) as_global(L.eval)[j] = next_scale(dsc[j]);
+            as_global(L.eval)[j] = next_scale(dsc[j]);
         }
         low = min_wave(low);
         low_r = min_wave(low_r);
     };
     auto outcome = [&](int nbad, double min_piv, const Spread& spread) {
-        if (note && write_status) note_iteration(L, note, it, low, low_r, nbad > 0, scale && spread.asks(L.planes, min_piv), nullptr);
+        if (note && write_status) note_iteration(L, note, it, low, low_r, nbad > 0, spread.asks(L.planes, min_piv), nullptr);
         const int need2 = (allow2 && min_piv < kSecondPassPivot) ? 1 : 0;
         if (need2_out) *need2_out = need2;
         if (write_status) {

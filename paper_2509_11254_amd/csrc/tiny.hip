@@ -124,9 +124,7 @@ __device__ __forceinline__ void tiny_form(const LayerDev& L, float* M, int ldm) 
 // fine: fp64 sums of single accumulators of 8 steps, for the last two products of a refresh.  One that ends when it has converged leaves its columns
 // less settled, which the Rayleigh-Ritz step makes up for with another rounding of both factors (error of E against 64 bits 6.3e-7
 // after 16 iterations, 6.8e-7 after 7, and 6.4e-7 with these sums; in all products they take 3 % longer).
-// shift: X <- A Y - shift X
-__device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X, double shift = 0.0,
-                                         bool fine = false) {
+__device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X, bool fine = false) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
     int oa[4];
 #pragma unroll
@@ -176,10 +174,7 @@ __device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * tile + 4 * lk + v;
-            if (row >= m) continue;
-            float& x = X[row * kTinyStride + li];
-            if (shift != 0.0) sum[v] -= shift * (double)x;
-            x = (float)sum[v];                             // (columns from w on: zero)
+            if (row < m) X[row * kTinyStride + li] = (float)sum[v];       // (columns from w on: zero)
         }
     }
     __syncthreads();
@@ -284,7 +279,7 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X
 
 struct TinyLds {
     float *m, *x, *y;
-    double *tm, *gram, *shift;
+    double *tm, *gram;
     int *need2, *asks_ends;                                // asks_ends: IterationState::asks + 2 ends
     int ldm;
     __device__ TinyLds(const LayerDev& L, unsigned char* smem) {
@@ -296,7 +291,6 @@ struct TinyLds {
         gram = reinterpret_cast<double*>(smem + t.gram);
         need2 = reinterpret_cast<int*>(smem + t.flags);
         asks_ends = need2 + 1;
-        shift = reinterpret_cast<double*>(smem + t.flags + 8);
         ldm = tiny_ldm(L.cols);
     }
 };
@@ -426,19 +420,18 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
     __syncthreads();
     const int sl = tr ? 1 : S.ldm, ss = tr ? S.ldm : 1;
     IterationState state;                                  // (wave 0's)
-    double shift = 0.0;
     bool asked = false;
 #pragma unroll 1
     for (int it = 0; it < k_iters; ++it) {
-        const bool last = it == k_iters - 1, may_shift = it > kOrthYIterations && !last && !asked;
-        tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x, may_shift ? shift : 0.0, last);
+        const bool last = it == k_iters - 1, grows = it > kOrthYIterations && !asked;
+        tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x, last);
 #pragma unroll 1
         for (int pass = 1; pass <= 2; ++pass) {
             tiny_gram(S.x, m, w, reinterpret_cast<double*>(S.y), S.gram);
             if (t < 64) {
-                const int note = pass == 2 || last || it < kOrthYIterations ? 0 : may_shift ? NOTE_SCALE | NOTE_SHIFTS : NOTE_SCALE;
+                const int note = pass == 2 || last || it < kOrthYIterations ? 0 : grows ? NOTE_SCALE | NOTE_GROWTH : NOTE_SCALE;
                 chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, note, it, &state);
-                if (note && t == 0) { *S.asks_ends = state.asks + 2 * state.ends; *S.shift = 0.5 * state.c; }
+                if (note && t == 0) *S.asks_ends = state.asks + 2 * state.ends;
             }
             __syncthreads();
             const bool again = *S.need2 != 0;
@@ -449,18 +442,12 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
             asked = (*S.asks_ends & 1) != 0;
             const int ends = *S.asks_ends >> 1;
             if (ends > 0 && ends < k_iters) k_iters = ends;
-            shift = *S.shift;
         }
-        tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y, 0.0, last);
+        tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y, last);
         if (!last && (it < kOrthYIterations || asked)) {
-            // (the Gram scratch overwrites Z: the next product is not shifted)
             tiny_gram(S.y, n, w, reinterpret_cast<double*>(S.x), S.gram);
-            if (t < 64) {
-                chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, it == 0 ? NOTE_FIRST_Y : 0, it, &state);
-                if (it == 0 && t == 0) *S.shift = 0.5 * state.c;
-            }
+            if (t < 64) chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, 0);
             __syncthreads();
-            if (it == 0) shift = *S.shift;
             tiny_apply(S.y, n, w, S.tm);
         }
     }
