@@ -135,14 +135,15 @@ struct LayerDev {
     double* gram;           // [slots][w(w+1)/2] partial Gram matrices (packed upper triangles), one slot per
                             // row block of the producer
     double* tmat;           // [wmax*wmax] small factor applied from the right
-    double* eval;           // [wz + 2]: Ritz values; during the subspace iteration the scales of Z's columns
+    double* eval;           // [wz + 2]: Ritz values; during the subspace iteration the scales of Z's columns and, at wz, by how much
+                            // its error has shrunk (see note_iteration)
     int* status;            // [kStatusWords] : 0 rank_deficient, 1 second-pass-needed flag, 2 sigma_max bits, 3 sigma_r bits,
                             //       4 iterations the next refresh needs (0 = not known yet), 5 Jacobi sweeps of the last
                             //       refresh, 6 and 7 arrival counters of finish_kernel and apply_kernel, 8 refreshes this
                             //       layer has run in this workspace, 9 iterations its next refresh runs if its cut has no
                             //       gap (see refresh_iterations), 10 whether this iteration's Y is orthonormalised (see Spread),
                             //       11 iterations after which the running refresh has converged (0: not known, see
-                            //       converged_after)
+                            //       note_iteration)
 };
 
 __host__ __device__ inline int side_of_role(int transposed, int role) {
@@ -246,7 +247,7 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 
 // Launches inside the subspace iteration carry a gate (-1 outside it), see make_gate: the iteration the launch
 // belongs to, its kind, the iteration budget and the number of iterations the host launches this time.
-// A layer runs k iterations at most (it ends sooner where it converges, see converged_after): the whole budget in its first
+// A layer runs k iterations at most (it ends sooner where it converges, see note_iteration): the whole budget in its first
 // two refreshes (the first knows nothing; the second is the first to meet the error-feedback state, whose spectrum is flatter at the cut than that of the first step's plain
 // gradient: on a 4096 x 4096 run sigma_{b+1}/sigma_r went from 0.13 at t = 0 to 0.43 at t = 10, and the count taken
 // from t = 0 left sin(theta) = 2e-4); after that status[4] (what
@@ -315,16 +316,18 @@ __device__ inline int iteration_notes(const LayerDev& L, int role, int gate) {
     if (gate < 0 || !scales_next(L, role, gate)) return 0;
     return (gate & 0xff) > kOrthYIterations && L.status[10] == 0 ? NOTE_SCALE | NOTE_GROWTH : NOTE_SCALE;
 }
-// Iterations after which the refresh ends, from its iteration `it`, 0 if it is not clear yet: one more when those made so far and
-// that one shrink the error by 2^-37.8 (two planes 2^-29.9), 10^-4 of what the products' rounding leaves of the subspace -- the start
-// may be that far off.  An iteration shrinks it by rho = theta_{b+1} / theta_r at most; theta_b, the smallest growth, stands in for theta_{b+1},
-// and the smallest of the first r columns for theta_r.  Both are low by what the block has not yet found outside itself: after it + 1
-// iterations directions that a random column holds 1 / sqrt(n) of show up to a factor n^(1 / (2 it + 2)).
-// (A block without columns beyond the r-th has rho >= 1 by this and runs all its iterations.)
-__device__ inline int converged_after(int planes, int n, int it, double theta_b, double theta_r) {
+// The end of a refresh that has converged: one more iteration when those made so far and that one shrink the error by 2^-37.8 (two
+// planes 2^-29.9), 10^-4 of what the products' rounding leaves of the subspace -- the start may be that far off.  Iteration `it`
+// shrinks it by rho = theta_{b+1} / theta_r at most; its smallest growth of a column, theta_b, stands in for theta_{b+1}, and the smallest of
+// the first r columns for theta_r.  Both are low by what the block has not yet found outside itself: after it + 1 iterations
+// directions that a random column holds 1 / sqrt(n) of show up to a factor n^(1 / (2 it + 2)).  (A block without columns beyond the
+// r-th has rho >= 1 by this and runs all its iterations.)
+// Each iteration counts with the rho that it showed itself, the two before the first that shows it with that one's: a start block
+// orthogonal to the leading directions but for rounding (the first r columns; the others only hold some of them) grows at
+// the rate of what it holds, rho >= 1, until they come up, and it is then that its error begins to shrink.
+__device__ inline float log2_rho(int n, int it, double theta_b, double theta_r) {
     const float rho = (float)(theta_b / theta_r) * exp2f(__log2f((float)n) * 0.5f / (float)(it + 1));
-    if (!(rho < 1.0f)) return 0;
-    return (float)(it + 2) * __log2f(fmaxf(rho, 1e-30f)) <= (planes == 3 ? -37.8f : -29.9f) ? it + 2 : 0;
+    return rho < 1.0f ? __log2f(fmaxf(rho, 1e-30f)) : 0.0f;
 }
 
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double doublex4;

@@ -239,7 +239,7 @@ __device__ __forceinline__ void note_block(Spread& spread, double rjj, double ds
 // What a factorisation inside the iteration notes (see IterationNote), where the wave that factorises keeps it in registers instead of
 // the layer's eval and status words (scale: of column lane & 15).
 struct IterationState {
-    double scale = 1.0;
+    double scale = 1.0, shrunk = 0.0;
     int asks = 0, ends = 0;
 };
 constexpr double kLargest = 1e300;
@@ -255,13 +255,23 @@ __device__ inline double min_wave(double v) {
     return fmin(v, __shfl_xor(v, 32));
 }
 // What a factorisation tells the next iterations, by one wave.  low, low_r: smallest growth of all columns and of the first r
+// (see log2_rho).  shrunk: log2 of what the error has come down by.
 __device__ inline void note_iteration(const LayerDev& L, int note, int it, double low, double low_r, bool dependent, bool asks, IterationState* own) {
-    const int ends = (note & NOTE_GROWTH) && !dependent && !asks ? converged_after(L.planes, min(L.rows, L.cols), it, low, low_r) : 0;
+    constexpr int kFirst = kOrthYIterations + 1;          // the first iteration whose growth can be known
+    double shrunk = it <= kFirst ? 0.0 : own ? own->shrunk : L.eval[L.wz];
+    int ends = 0;
+    if ((note & NOTE_GROWTH) && !dependent) {
+        const float by = log2_rho(min(L.rows, L.cols), it, low, low_r);
+        shrunk += it == kFirst ? (kFirst + 1) * by : by;
+        if (!asks && shrunk + by <= (L.planes == 3 ? -37.8 : -29.9)) ends = it + 2;
+    }
     if (own) {
+        own->shrunk = shrunk;
         own->asks = asks ? 1 : 0;
         own->ends = ends;
-    } else if (ends > 0 && (threadIdx.x & 63) == 0) {
-        L.status[11] = ends;
+    } else if ((threadIdx.x & 63) == 0) {
+        L.eval[L.wz] = shrunk;
+        if (ends > 0) L.status[11] = ends;
     }
 }
 

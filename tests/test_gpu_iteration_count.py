@@ -219,3 +219,25 @@ def test_gap_after_the_block(rows, cols, r, b):
     got = outside(case.outputs(0)[0])
     print(rows, cols, r, "outside the block", got, "16 iterations", plain, "rounding", rounding)
     assert got <= 2 * plain + 16 * rounding
+
+
+# A warm start orthogonal to the leading directions: the columns beyond it hold some of them, the others come up from its rounding
+# to fp32, and until they have the block grows like one that has converged.  Columns beyond the rank that are fewer than those directions,
+# down to one, and the default number.  Factorised in one launch, by the apply kernel, by finish_kernel and by a launch of its own.
+@pytest.mark.parametrize("rows,cols,r,over", [(200, 150, 6, 2), (150, 200, 14, 2), (520, 333, 7, 1), (333, 520, 22, 2), (640, 333, 38, 2),
+                                              (500, 408, 62, 2), (408, 500, 32, -1), (700, 512, 120, -1)])
+def test_start_orthogonal_to_the_leading_directions(rows, cols, r, over):
+    rng = np.random.default_rng(rows + 7 * r)
+    n, n_layers = min(rows, cols), 3
+    s = np.r_[np.linspace(2.0, 1.0, r), 0.3 * np.linspace(1.0, 0.5, n - r)]
+    mats = [_spectrum_matrix(rng, rows, cols, s) for _ in range(n_layers)]
+    svds = [np.linalg.svd(_tall(x, rows, cols), full_matrices=False) for x in mats]
+    case = Case([(rows, cols)] * n_layers, r, 1, synth.F32, lds=[(cols + 7) // 8 * 8] * n_layers, seed=SEED, refresh_oversample=over)
+    case.upload([[x] for x in mats], [np.zeros((rows, cols), np.float32)] * n_layers, [v[r:2 * r].T.astype(np.float32) for _, _, v in svds])
+    case.compress(refresh=True)
+    for l, (u, sv, _) in enumerate(svds):
+        got = orc.sin_theta_max(u[:, :r], case.outputs(l)[0])
+        # what 16 iterations leave of a direction that rounding holds 2^-25 / sqrt(n) of is below the rounding of a product
+        rounding = 2.0 ** -24 * sv[0] / (sv[r - 1] - sv[r])
+        print(rows, cols, r, "layer", l, "sin", got, "rounding", rounding)
+        assert got <= 16 * rounding, l
