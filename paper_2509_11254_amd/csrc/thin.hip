@@ -757,14 +757,11 @@ __device__ inline int jacobi_pos0(int j, int n) {
 }
 
 // Rotation that annihilates apq of a 2 x 2 diagonal block: the half of the angle whose cosine and sine are |d| / h and b / h, d =
-// aqq - app, b = 2 apq, h^2 = d^2 + b^2, so (c, s) is (1 + |d| / h, +-b / h) normalised.  The quotients by h may be off by a little (one
-// Newton step on the hardware estimate: the entry comes out at 1e-12 of what it was), the norm may not.
+// aqq - app, b = 2 apq, h^2 = d^2 + b^2, so (c, s) is (1 + |d| / h, +-b / h) normalised.
 __device__ inline void jacobi_angle(double app, double apq, double aqq, double& c, double& sn) {
     const bool turns = fabs(apq) > 1e-150 && apq * apq > 1e-36 * fabs(app * aqq);
     const double d = aqq - app, b = 2.0 * apq;
-    const double h2 = turns ? __builtin_fma(d, d, b * b) : 1.0;               // (a normal number by the test above)
-    double ih = __builtin_amdgcn_rsq(h2);
-    ih = __builtin_fma(0.5 * ih, __builtin_fma(-(h2 * ih), ih, 1.0), ih);
+    const double ih = rsqrt_nr(turns ? __builtin_fma(d, d, b * b) : 1.0);     // (of a normal number, by the test above)
     const double x = turns ? __builtin_fma(fabs(d), ih, 1.0) : 1.0;
     const double y = turns ? (d >= 0.0 ? b : -b) * ih : 0.0;
     const double in = rsqrt_nr(__builtin_fma(x, x, y * y));

@@ -65,14 +65,6 @@ __device__ inline double rsqrt_nr(double x) {
     return y;
 }
 
-// 1 / x for finite normal x: hardware estimate refined by two Newton steps (full fp64 accuracy)
-__device__ inline double rcp_nr(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return y;
-}
-
 // Power of two next to a column's scaling 1 / ||x||, kept within what fp32 can hold.  Z = X T columns multiplied by it
 // give Y = M^T Z columns of norm about 1 where X = M Y' did with a Y' of such columns, so that a Y that is not
 // orthonormalised (see Spread) does not drift out of range however small the gradients are.
