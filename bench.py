@@ -392,7 +392,8 @@ def run_workload(name, args, primary):
     # refresh arithmetic: block width b, k iterations of two products of 2 m n b flops each (+ the forming product)
     b_w = min(wl.r + max(8, wl.r // 4) + 7 & ~7, min(s.n for s in wl.layers))
     # iterations per layer as the device decides them: the count for the subspace if within the budget of 16, else
-    # the count for the error
+    # the count for the error.  A refresh that finds that it has converged before makes fewer, which nothing reports: these counts,
+    # and the rates made of them, are upper bounds.
     k_layers = [k_of(s_) for s_ in st_next]
     k_run = sum(k_layers) / len(k_layers)
     refresh_flops = sum(4.0 * s.rows * s.cols * b_w * k for s, k in zip(wl.layers, k_layers))

@@ -121,9 +121,9 @@ __device__ __forceinline__ void tiny_form(const LayerDev& L, float* M, int ldm) 
 // X (m x w) = A Y, A(i, k) = M[i si + k sk] (m x n), Y (n x w): a wave per 16 rows, the operands of the next 16 steps of the reduction
 // requested before the products of these.  fp32 sums run over 16 steps, their sums in pairs are fp64: with fp32 sums over a quarter of
 // the reduction the result was 8 % further from 64 bits than that of the split operands' longer accumulators.
-// fine: fp64 sums of single accumulators of 8 steps, for the last two products of a refresh.  One that ends when it has converged leaves its columns
-// less settled, which the Rayleigh-Ritz step makes up for with another rounding of both factors (error of E against 64 bits 6.3e-7
-// after 16 iterations, 6.8e-7 after 7, and 6.4e-7 with these sums; in all products they take 3 % longer).
+// fine: fp64 sums of single accumulators of 8 steps, for the last two products of a refresh.  One that ends when it has converged leaves
+// its columns less settled, which the Rayleigh-Ritz step makes up for with another rounding of both factors (256 x 128 r = 4, error of E
+// against 64 bits, mean of eight matrices: 6.38e-7 after 16 iterations without these sums, 6.36e-7 after 8 with them; in all products they take 3 % longer).
 __device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X, bool fine = false) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
     int oa[4];

@@ -241,3 +241,26 @@ def test_start_orthogonal_to_the_leading_directions(rows, cols, r, over):
         rounding = 2.0 ** -24 * sv[0] / (sv[r - 1] - sv[r])
         print(rows, cols, r, "layer", l, "sin", got, "rounding", rounding)
         assert got <= 16 * rounding, l
+
+
+# Whether a refresh has ended before its maximum: it leaves the same bits as one with a smaller maximum that it does not reach, and
+# others where it has not converged by then
+@pytest.mark.parametrize("rows,cols,r", [(200, 150, 8), (640, 333, 8), (333, 640, 24), (500, 408, 32), (700, 512, 76), (640, 520, 144)])
+@pytest.mark.parametrize("planes,fewer", [(2, 8), (3, 10)])
+@pytest.mark.parametrize("gap", [False, True])
+def test_ends_before_its_maximum(rows, cols, r, planes, fewer, gap):
+    rng = np.random.default_rng(rows + 7 * r)
+    n = min(rows, cols)
+    s = np.linspace(2.0, 1.0, n)
+    if gap:
+        s[r:] *= 0.05               # (8.6 powers of two or more per iteration: 30 and 38 are asked of them)
+    mat = _spectrum_matrix(rng, rows, cols, s)
+    warm = rng.standard_normal((n, r)).astype(np.float32)
+    out = []
+    for iters in (fewer, 16, 40):
+        case = Case([(rows, cols)], r, 1, synth.F32, lds=[(cols + 7) // 8 * 8], precision=planes, seed=SEED, refresh_iters=iters)
+        case.upload([[mat]], [np.zeros((rows, cols), np.float32)], [warm])
+        case.compress(refresh=True)
+        out.append(case.outputs(0))
+    same = [all(np.array_equal(a, b) for a, b in zip(out[0], x)) for x in out[1:]]
+    assert same == [gap, gap]

@@ -133,8 +133,8 @@ def test_refreshes_where_the_cut_has_no_gap(which):
             p, q, e_after = case.outputs(0)
             # (no subspace bar here: sigma_{r+1} / sigma_r is 0.9 and more in these runs, beyond any iteration budget)
             res = _check_refreshed_step(mat, p, q, e_after, wl.r, "%s t=%d" % (which, t), subspace=False)
-            runs = 16 if t < 6 else (st.refresh_iters_next if st.refresh_iters_next <= 16 else min(16, st.refresh_iters_no_gap))
-            print(which, "t", t, "asked", st.refresh_iters_next, "no-gap count", st.refresh_iters_no_gap, "runs", runs, res, flush=True)
+            most = 16 if t < 6 else (st.refresh_iters_next if st.refresh_iters_next <= 16 else min(16, st.refresh_iters_no_gap))
+            print(which, "t", t, "asked", st.refresh_iters_next, "no-gap count", st.refresh_iters_no_gap, "runs at most", most, res, flush=True)
             assert 2 <= st.refresh_iters_no_gap <= 255 or t == 0
             if t >= 6 and st.refresh_iters_next > 16:
                 reduced += 1
