@@ -322,9 +322,9 @@ __device__ inline int iteration_notes(const LayerDev& L, int role, int gate) {
 // the first r columns for theta_r.  Both are low by what the block has not yet found outside itself: after it + 1 iterations
 // directions that a random column holds 1 / sqrt(n) of show up to a factor n^(1 / (2 it + 2)).  (A block without columns beyond the
 // r-th has rho >= 1 by this and runs all its iterations.)
-// Each iteration counts with the rho that it showed itself, the two before the first that shows it with that one's: a start block
-// orthogonal to the leading directions but for rounding (the first r columns; the others only hold some of them) grows at
-// the rate of what it holds, rho >= 1, until they come up, and it is then that its error begins to shrink.
+// Each iteration counts with the rho that it showed itself, the first two with that of the third (none of the three where that one
+// does not show it): a start block orthogonal to the leading directions but for rounding (the first r columns; the others only hold
+// some of them) grows at the rate of what it holds, rho >= 1, until they come up, and it is then that its error begins to shrink.
 __device__ inline float log2_rho(int n, int it, double theta_b, double theta_r) {
     const float rho = (float)(theta_b / theta_r) * exp2f(__log2f((float)n) * 0.5f / (float)(it + 1));
     return rho < 1.0f ? __log2f(fmaxf(rho, 1e-30f)) : 0.0f;

@@ -607,8 +607,8 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
 
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
-// mode APPLY_RITZ: ROLE_ZP -> ROLE_P, and in the same launch (z = 1) ROLE_ZQ -> ROLE_Q, which shares nothing with it but tmat (as
-// two launches a refresh of 256 x 128 r = 4 took 199 us, 190 now, of 4096 x 4096 r = 8 940, 928 now)
+// mode APPLY_RITZ: ROLE_ZP -> ROLE_P, and in the same launch (z = 1) ROLE_ZQ -> ROLE_Q, which shares nothing with it but tmat
+// (as two launches: 9 us more per refresh of 256 x 128 r = 4, 12 of 4096 x 4096 r = 8)
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
 // (the others: 128)
 // which: operand copies to leave when cp > 0 (1 = outer-product, 2 = transposed, 3 = both; + 4: the outer-product ones are
