@@ -286,14 +286,38 @@ __device__ inline bool allow2_of(const LayerDev& L, int a2gate) {
     return gate_open(L, a2gate);
 }
 
+// What the notes of a narrow factorisation are made from (column lane & 15).
+struct NarrowFactor { double dsc, rjj, min_piv; int badmask; };
+// The notes (see IterationNote), by the wave that has factorised; the next iteration needs them, not the application of the factor.
+__device__ __forceinline__ void narrow_notes(const LayerDev& L, int w, int note, int it, const NarrowFactor& f, bool write_status, IterationState* own) {
+    const int c = threadIdx.x & 15, jc = c < w ? c : 0;
+    const bool good = c < w && !((f.badmask >> c) & 1);
+    Spread spread;
+    note_block(spread, f.rjj, f.dsc, good);
+    const bool asks = spread.asks(L.planes, f.min_piv);
+    if (write_status || own) {
+        // (own: the caller keeps the state in registers, lane c column c's)
+        const double csc = next_scale(f.dsc);
+        const double norm = f.rjj * __builtin_amdgcn_rcp(good ? f.dsc : 1.0);
+        const double prev = own ? own->scale : (note & NOTE_GROWTH) ? L.eval[jc] : 1.0;
+        const double grew = good ? norm / prev : kLargest;
+        note_iteration(L, note, it, min_lane16(grew), min_lane16(c < L.r ? grew : kLargest), (f.badmask & ((1 << w) - 1)) != 0, asks, own);
+        if (own) own->scale = csc;
+        else if ((threadIdx.x & 63) < w) L.eval[jc] = csc;
+    }
+    if (write_status && (threadIdx.x & 63) == 0) L.status[10] = asks ? 1 : 0;
+}
+
 // The factorisation for w <= 16 by one wavefront (see factor_in_registers).  g: the summed Gram matrix (packed upper triangle,
 // LDS).  Same arithmetic and outputs as the general path of chol_body.  W: compiled width (w <= W); rows and columns
-// w .. W-1 are those of an identity matrix.
+// w .. W-1 are those of an identity matrix.  later: the notes are left to the caller (narrow_notes).
 template <int W>
 __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                            bool allow2, double* tm, bool write_status, int* need2_out, int note,
-                                           int it, IterationState* own) {
-    const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+                                           int it, NarrowFactor* later) {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));                           // (what depends on the lane is not kept in registers over the caller's loop)
+    const int c = t & 15, q = (t >> 4) & 3;
     const int jc = c < w ? c : 0;
     const double djj = g[tri_idx(jc, jc, w)];
     const double dsc_own = djj > kTinyNorm2 ? rsqrt_nr(djj) : 0.0;
@@ -309,23 +333,13 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     });
     double min_piv = 1.0, rjj;
     factor_in_registers<W>(x, y, tol2, badmask, min_piv, rjj);
-    Spread spread;
-    const bool good = c < w && !((badmask >> c) & 1);
-    const double csc = next_scale(dsc_own);
+    const NarrowFactor f{dsc_own, rjj, min_piv, badmask};
     if (note & NOTE_SCALE) {                              // (uniform: every lane takes part in the broadcasts)
+        const double csc = next_scale(dsc_own);
         static_for<0, 4>([&](auto vc) { constexpr int v = decltype(vc)::value; y[v] *= bcast_by_row<4 * v>(csc); });
-        note_block(spread, rjj, dsc_own, good);
     }
-    if (note && (write_status || own)) {
-        // (own: the caller keeps the state in registers, lane c column c's)
-        const double norm = rjj * __builtin_amdgcn_rcp(good ? dsc_own : 1.0);
-        const double prev = own ? own->scale : (note & NOTE_GROWTH) ? L.eval[jc] : 1.0;
-        const double grew = good ? norm / prev : kLargest;
-        note_iteration(L, note, it, min_lane16(grew), min_lane16(c < L.r ? grew : kLargest), (badmask & ((1 << w) - 1)) != 0,
-                       spread.asks(L.planes, min_piv), own);
-        if (own) own->scale = csc;
-        else if ((threadIdx.x & 63) < w) L.eval[jc] = csc;
-    }
+    if (later) *later = f;
+    else if (note) narrow_notes(L, w, note, it, f, write_status, nullptr);
     // lane (q, c): entries 4 v + q of row c of tmat = D T with the dependent columns zeroed
     if (c < w) {
 #pragma unroll
@@ -342,7 +356,6 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
             if (pass == 1) {
                 L.status[0] = nbad;
                 L.status[1] = need2;
-                if (note & NOTE_SCALE) L.status[10] = spread.asks(L.planes, min_piv) ? 1 : 0;
             } else {
                 L.status[0] = max(L.status[0], nbad);
             }
@@ -350,14 +363,14 @@ __device__ __forceinline__ void chol_in_registers_w(const LayerDev& L, const dou
     }
 }
 
-// note: see IterationNote (it: the iteration); own: the iteration's state where the caller keeps it
+// note: see IterationNote (it: the iteration)
 __device__ __forceinline__ void chol_in_registers(const LayerDev& L, const double* g, int w, double tol2, int pass,
                                          bool allow2, double* tm, bool write_status, int* need2_out, int note, int it = 0,
-                                         IterationState* own = nullptr) {
-    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
-    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
-    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
-    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, own);
+                                         NarrowFactor* later = nullptr) {
+    if (w <= 4) chol_in_registers_w<4>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, later);
+    else if (w <= 8) chol_in_registers_w<8>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, later);
+    else if (w <= 12) chol_in_registers_w<12>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, later);
+    else chol_in_registers_w<16>(L, g, w, tol2, pass, allow2, tm, write_status, need2_out, note, it, later);
 }
 
 // Diagonal 16 x 16 block of the blocked factorisation, by one wavefront in registers: factorises the block `blk` (row-major,

@@ -9,39 +9,51 @@
 // stays in LDS.  M and the thin matrices are fp32 as in memory, the products run on v_mfma_f32_16x16x4_f32 (fp32 operands and
 // sums: no operand planes), Gram matrices, factorisation and its application in fp64 as in the general path.  The product that E
 // loses is the one that the updates apply (tiny_residual_planes; with three planes one that differs from it by roundings of fp32).
-// A step of a 256 x 128 fp32 layer with four workers (with psgd_decompress) 39.1 -> 32 us, of a 64 x 64 one 38.2 -> 16, sixteen
-// of 104 x 104 43.5 -> 23; a refresh 559 -> 288, 425 -> 156, 601 -> 240.  Of the 28 us of the first, 8 go to the gradients (one
-// compute unit reads at 64 bytes per clock: 4.3 us for 640 KB), the rest to LDS round trips of the products.
+// A step of a 256 x 128 fp32 layer with four workers (with psgd_decompress) takes 39.1 us in the general path, 31.9 with the thin
+// matrices row by row in LDS, read 4 bytes at a time, and E stored 4 bytes at a time, 25.0 now.  Of the 21.6 of its kernel 7.2 go to
+// the gradients (one compute unit reads at 64 bytes per clock: 4.3 us for 640 KB), 2.3 to each product, 4 to E, 3.5 to Gram matrix,
+// factorisation and its application.  A refresh at two to sixteen iterations 249 -> 222, an iteration 15 -> 13: products 2.9 and
+// 3.4 (their MFMAs 1.7), Gram matrix 1.2, factorisation 3.6, application 1.1.
 #include "thin_dev.h"
 
 namespace psgd {
 
 constexpr int kTinyThreads = 768;        // (the factorisation needs more registers than 1024 leave, and with 512 the products wait for LDS)
 constexpr int kTinyWaves = kTinyThreads / 64;
-constexpr int kTinyStride = 16;                        // floats per row of a thin matrix in LDS
+constexpr int kTinyCols = 16;                          // columns of a thin matrix in LDS (zero from its width on)
 constexpr int kTinyGramWaves = 4;                      // waves that share the rows of a Gram matrix
 constexpr size_t kTinyScratch = kTinyGramWaves * 256 * sizeof(double);
 constexpr size_t kTinyLds = 160 * 1024;
 constexpr int64_t kTinyStepElements = 400000, kTinyRefreshElements = 2400000, kTinyRefreshAlways = 8192;
 
-// Row stride of M in LDS: whole 16-byte pieces, an odd number of them, so that 16 rows times 4 columns (the A operand of M Y) lie
-// in 64 different banks
+// Row stride of M in LDS, and of the thin matrices, which lie there column by column: whole 16-byte pieces, an odd number of them,
+// so that the 16-byte pieces that 16 lanes read from 16 rows lie in different banks
 __host__ __device__ inline int tiny_ldm(int cols) { return 4 * (((cols + 3) / 4) | 1); }
-struct TinyLayout { size_t x, y, tm, gram, flags, end; };
-__host__ __device__ inline TinyLayout tiny_layout(int rows, int cols) {
+struct TinyLayout {
+    size_t x, y, tm, gram, flags, end;
+    int ldx, ldy;                                          // of the thin matrices on the long and on the short side
+};
+__host__ __device__ inline TinyLayout tiny_layout_as(int rows, int cols, bool odd) {
     const int m = rows > cols ? rows : cols, n = rows > cols ? cols : rows;
-    auto thin = [](int len) {
-        const size_t b = ((size_t)len * kTinyStride * sizeof(float) + 15) & ~(size_t)15;
+    TinyLayout t;
+    t.ldx = odd ? tiny_ldm(m) : (m + 3) & ~3;
+    t.ldy = odd ? tiny_ldm(n) : (n + 3) & ~3;
+    auto thin = [](int ld) {
+        const size_t b = (size_t)kTinyCols * ld * sizeof(float);
         return b > kTinyScratch ? b : kTinyScratch;     // (each of the two also serves as the other's Gram scratch)
     };
-    TinyLayout t;
     t.x = (size_t)rows * tiny_ldm(cols) * sizeof(float);
-    t.y = t.x + thin(m);
-    t.tm = t.y + thin(n);
+    t.y = t.x + thin(t.ldx);
+    t.tm = t.y + thin(t.ldy);
     t.gram = t.tm + 256 * sizeof(double);
     t.flags = t.gram + 136 * sizeof(double);
     t.end = t.flags + 16;
     return t;
+}
+// (the thin matrices without the odd number of pieces where that is what makes the layer fit)
+__host__ __device__ inline TinyLayout tiny_layout(int rows, int cols) {
+    const TinyLayout t = tiny_layout_as(rows, cols, true);
+    return t.end <= kTinyLds ? t : tiny_layout_as(rows, cols, false);
 }
 // Whether a layer's step, or refresh, fits (r: widest thin matrix of it).  n_arrays: gradients and E, which one compute unit reads at
 // 0.08 to 0.1 ns per element: not longer than the general path's launches take.  256 x 128 fp32, us: step, 8 workers 33 against 41, 11
@@ -118,87 +130,191 @@ __device__ __forceinline__ void tiny_form(const LayerDev& L, float* M, int ldm) 
     }
 }
 
-// X (m x w) = A Y, A(i, k) = M[i si + k sk] (m x n), Y (n x w): a wave per 16 rows, the operands of the next 16 steps of the reduction
-// requested before the products of these.  fp32 sums run over 16 steps, their sums in pairs are fp64: with fp32 sums over a quarter of
+// One block of 16 reduction steps: a[q], b hold steps k0 + 4 lk + u (u = 0 .. 3) of Q tiles and of the thin operand, in two
+// chains of sums each.  FIRST: the chains start here.  G = 0: 16 x 16 tiles, lane (li, lk) of b holds column li.  G = 1: the
+// first 4 G columns only, in blocks of 4 x 4: four lanes of reduction steps keep sums of their own (8 clocks for 4 columns
+// against 32 for 16); lane l of b[g] holds column 4 g + (l & 3) of the steps of lk = l >> 4.
+template <int Q, int G, bool FIRST>
+__device__ __forceinline__ void tiny_steps(const floatx4 (&a)[Q], const floatx4 (&b)[G ? G : 1], floatx4 (&c)[2][Q][G ? G : 1]) {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int g = 0; g < (G ? G : 1); ++g) {
+                floatx4& d = c[u & 1][q][g];
+                const floatx4 from = FIRST && u < 2 ? zero : d;
+                if constexpr (G == 0) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][u], b[g][u], from, 0, 0, 0);
+                else d = __builtin_amdgcn_mfma_f32_4x4x1f32(a[q][u], b[g][u], from, 0, 0, 0);
+            }
+}
+
+// X (m x w) = A Y.  ALONG: the reduction runs along the rows of M, A(i, k) = M[i][k] (m rows); else down its columns, A(i, k) =
+// M[k][i].  Both operands of a wave's next 16 steps are requested before the products of these: one 16-byte read of the thin
+// matrix for Q tiles of 16 rows, and 16 bytes of a row of M for each of them, or 4 Q bytes of four rows (tile q: columns Q i + q).  (4-byte reads,
+// 8 for 4 MFMAs: 256 x 128 3.8 and 4.4 us, now 2.9 and 3.4, at r = 4 in blocks of 4 x 4 2.3 and 2.4.)
+// fp32 sums run over 16 steps, their sums in pairs are fp64: with fp32 sums over a quarter of
 // the reduction the result was 8 % further from 64 bits than that of the split operands' longer accumulators.
 // fine: fp64 sums of single accumulators of 8 steps, for the last two products of a refresh.  One that ends when it has converged leaves
 // its columns less settled, which the Rayleigh-Ritz step makes up for with another rounding of both factors (256 x 128 r = 4, error of E
 // against 64 bits, mean of eight matrices: 6.38e-7 after 16 iterations without these sums, 6.36e-7 after 8 with them; in all products they take 3 % longer).
-__device__ __forceinline__ void tiny_mul(const float* M, int si, int sk, int m, int n, const float* Y, int w, float* X, bool fine = false) {
+template <bool ALONG, int Q, int G>
+__device__ __forceinline__ void tiny_mul_tiles(const float* M, int ldm, int m, int n, const float* Y, int ldy, float* X, int ldx, bool fine) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
-    int oa[4];
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    constexpr int NG = G ? G : 1;
+    const int n32 = n & ~31;
+    const float* bl = Y + (G ? li & 3 : li) * ldy + 4 * lk;
+    for (int task = wv; 16 * Q * task < m; task += kTinyWaves) {
+        const int i0 = 16 * Q * task;
+        const float* ar[ALONG ? Q : 1];
+        if constexpr (ALONG) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) oa[u] = (4 * u + lk) * sk;
-    const float* bl = Y + lk * kTinyStride + li;
-    const int n16 = n & ~15;
-    for (int tile = wv; 16 * tile < m; tile += kTinyWaves) {
-        const float* ar = M + min(16 * tile + li, m - 1) * si;
-        double sum[4] = {0.0, 0.0, 0.0, 0.0};
-        float a[4], b[4];
-        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-        auto fetch = [&](int k0) {
+            for (int q = 0; q < Q; ++q) ar[q] = M + min(i0 + 16 * q + li, m - 1) * ldm + 4 * lk;
+        } else {
+            ar[0] = M + 4 * lk * ldm + min(i0 + Q * li, ldm - Q);       // (columns past the last: their results are dropped)
+        }
+        struct Operands { floatx4 a[Q], b[NG]; };
+        auto fetch = [&](Operands& o, int k0) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { a[u] = ar[k0 * sk + oa[u]]; b[u] = bl[(k0 + 4 * u) * kTinyStride]; }
+            for (int g = 0; g < NG; ++g) o.b[g] = *reinterpret_cast<const floatx4*>(bl + 4 * g * ldy + k0);
+            if constexpr (ALONG) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) o.a[q] = *reinterpret_cast<const floatx4*>(ar[q] + k0);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float* p = ar[0] + (k0 + u) * ldm;
+                    if constexpr (Q == 2) {
+                        const floatx2 v = *reinterpret_cast<const floatx2*>(p);
+                        o.a[0][u] = v.x;
+                        o.a[1][u] = v.y;
+                    } else {
+                        o.a[0][u] = *p;
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);                 // (requested here, not where the registers of the last steps are free again)
         };
-        if (n16 > 0) fetch(0);
-        floatx4 c0 = zero, c1 = zero;
-        for (int k0 = 0; k0 < n16; k0 += 16) {
-            float ac[4], bc[4];
+        double sum[Q][NG][4];
+        floatx4 c[2][Q][NG];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { ac[u] = a[u]; bc[u] = li < w ? b[u] : 0.f; }
-            fetch(min(k0 + 16, n16 - 16));
-            c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[0], bc[0], c0, 0, 0, 0);
-            c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[2], bc[2], c1, 0, 0, 0);
-            c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[1], bc[1], c0, 0, 0, 0);
-            c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[3], bc[3], c1, 0, 0, 0);
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[q][g][v] = 0.0;
+        auto add_up = [&](bool each) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        sum[q][g][v] += each ? (double)c[0][q][g][v] + (double)c[1][q][g][v] : (double)(c[0][q][g][v] + c[1][q][g][v]);
+        };
+        Operands now, next;
+        if (n32 > 0) fetch(now, 0);
+        for (int k0 = 0; k0 < n32; k0 += 32) {
+            fetch(next, k0 + 16);
+            tiny_steps<Q, G, true>(now.a, now.b, c);
+            fetch(now, min(k0 + 32, n32 - 16));
             if (fine) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sum[v] += (double)c0[v] + (double)c1[v];
-                c0 = zero;
-                c1 = zero;
-            } else if ((k0 & 16) || k0 + 16 >= n16) {
-                const floatx4 c = c0 + c1;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sum[v] += (double)c[v];
-                c0 = zero;
-                c1 = zero;
+                add_up(true);
+                tiny_steps<Q, G, true>(next.a, next.b, c);
+                add_up(true);
+            } else {
+                tiny_steps<Q, G, false>(next.a, next.b, c);
+                add_up(false);
             }
         }
-        for (int k0 = n16; k0 < n; k0 += 4) {
-            const int k = k0 + lk, kc = min(k, n - 1);
-            const float av = ar[kc * sk], bv = Y[kc * kTinyStride + li];
-            const floatx4 c = __builtin_amdgcn_mfma_f32_16x16x4f32(k < n ? av : 0.f, k < n && li < w ? bv : 0.f, zero, 0, 0, 0);
+        for (int k0 = n32; k0 < n; k0 += 16) {                 // the last steps, those from n on as zeros
+            const int kl = k0 + 4 * lk, at = kl < n ? k0 : -4 * lk;       // (reads stay within rows of whole 16-byte pieces)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sum[v] += (double)c[v];
+            for (int g = 0; g < NG; ++g) now.b[g] = *reinterpret_cast<const floatx4*>(bl + 4 * g * ldy + at);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = kl + u < n;
+#pragma unroll
+                for (int g = 0; g < NG; ++g) now.b[g][u] = in ? now.b[g][u] : 0.f;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const float x = ALONG ? ar[ALONG ? q : 0][at + u] : ar[0][(in ? k0 + u : -4 * lk) * ldm + q];
+                    now.a[q][u] = in ? x : 0.f;
+                }
+            }
+            tiny_steps<Q, G, true>(now.a, now.b, c);
+            add_up(fine);
         }
+        // row 4 lk + v of tile q, column li; G: row 4 (li >> 2) + v, column 4 g + (li & 3), after the sums over lk
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = 16 * tile + 4 * lk + v;
-            if (row < m) X[row * kTinyStride + li] = (float)sum[v];       // (columns from w on: zero)
+        for (int g = 0; g < NG; ++g) {
+            int row = 4 * lk, col = li;
+            bool mine = true;
+            if constexpr (G > 0) {
+                row = 4 * (li >> 2);
+                col = 4 * g + (li & 3);
+                mine = lk == g;
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double s = sum[q][g][v];
+                        s += __shfl_xor(s, 16);
+                        sum[q][g][v] = s + __shfl_xor(s, 32);
+                    }
+            }
+            if constexpr (ALONG || Q == 1) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int i = i0 + 16 * q + row;
+                    if (mine && i < m)
+                        *reinterpret_cast<floatx4*>(X + col * ldx + i) = floatx4{(float)sum[q][g][0], (float)sum[q][g][1], (float)sum[q][g][2], (float)sum[q][g][3]};
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int i = i0 + 2 * row + 4 * h;
+                    if (mine && i < m)
+                        *reinterpret_cast<floatx4*>(X + col * ldx + i) =
+                            floatx4{(float)sum[0][g][2 * h], (float)sum[1][g][2 * h], (float)sum[0][g][2 * h + 1], (float)sum[1][g][2 * h + 1]};
+                }
+            }
         }
     }
-    __syncthreads();
+}
+// Two tiles per wave where that leaves two waves for each of the compute unit's four SIMDs (with one, its sums' additions and
+// the end of the reduction are not hidden).  No barrier at the end.  (Columns of X that are not formed keep what they hold.)
+template <int G>
+__device__ __forceinline__ void tiny_mul_as(const float* M, int ldm, bool along, int m, int n, const float* Y, int ldy, float* X, int ldx, bool fine) {
+    if (along) {
+        if (m > 192) tiny_mul_tiles<true, 2, G>(M, ldm, m, n, Y, ldy, X, ldx, fine);
+        else tiny_mul_tiles<true, 1, G>(M, ldm, m, n, Y, ldy, X, ldx, fine);
+    } else {
+        if (m > 192) tiny_mul_tiles<false, 2, G>(M, ldm, m, n, Y, ldy, X, ldx, fine);
+        else tiny_mul_tiles<false, 1, G>(M, ldm, m, n, Y, ldy, X, ldx, fine);
+    }
+}
+__device__ __forceinline__ void tiny_mul(const float* M, int ldm, bool along, int m, int n, int w, const float* Y, int ldy, float* X, int ldx) {
+    if (w <= 4) tiny_mul_as<1>(M, ldm, along, m, n, Y, ldy, X, ldx, false);
+    else tiny_mul_as<0>(M, ldm, along, m, n, Y, ldy, X, ldx, false);
 }
 
 // g = X^T X (packed upper triangle, fp64), X (len x w); red: kTinyScratch bytes
-__device__ __forceinline__ void tiny_gram(const float* X, int len, int w, double* red, double* g) {
+__device__ __forceinline__ void tiny_gram(const float* X, int ldx, int len, int w, double* red, double* g) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
     if (wv < kTinyGramWaves) {
         doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-        const float* xl = X + lk * kTinyStride + li;
-        constexpr int step = 4 * kTinyGramWaves;
-        int k0 = 4 * wv;
-        for (; k0 + 3 * step + 4 <= len; k0 += 4 * step) {       // (four whole steps)
-            float x[4];
+        const float* xl = X + li * ldx + 4 * lk;
+        for (int k0 = 16 * wv; k0 < len; k0 += 16 * kTinyGramWaves) {       // rows k0 + 4 lk + u
+            const bool some = k0 + 4 * lk < len;
+            const floatx4 x = *reinterpret_cast<const floatx4*>(some ? xl + k0 : X);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = xl[(k0 + u * step) * kTinyStride];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u], (double)x[u], acc, 0, 0, 0);
-        }
-        for (; k0 < len; k0 += step) {
-            const float x0 = X[min(k0 + lk, len - 1) * kTinyStride + li];
-            const double x = k0 + lk < len ? (double)x0 : 0.0;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc, 0, 0, 0);
+            for (int u = 0; u < 4; ++u) {
+                const double d = k0 + 4 * lk + u < len ? (double)x[u] : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, acc, 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[wv * 256 + 64 * v + lane] = acc[v];
@@ -215,42 +331,41 @@ __device__ __forceinline__ void tiny_gram(const float* X, int len, int w, double
 }
 
 // X <- X T in place (len x w; T: w x w in LDS), fp64; a wave reads its 16 rows before it writes them
-__device__ __forceinline__ void tiny_apply(float* X, int len, int w, const double* tm) {
+__device__ __forceinline__ void tiny_apply(float* X, int ldx, int len, int w, const double* tm) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, lk = lane >> 4;
-    double b[4];
+    double t[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) b[u] = (4 * u + lk < w && li < w) ? tm[(4 * u + lk) * w + li] : 0.0;
+    for (int u = 0; u < 4; ++u) t[u] = (4 * u + lk < w && li < w) ? tm[(4 * u + lk) * w + li] : 0.0;
     for (int tile = wv; 16 * tile < len; tile += kTinyWaves) {
-        const float* xa = X + min(16 * tile + li, len - 1) * kTinyStride + lk;
+        const int row = 16 * tile + li;
+        float* xa = X + lk * ldx + min(row, len - 1);
         doublex4 acc = {0.0, 0.0, 0.0, 0.0};
         float a[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = xa[4 * u];
+        for (int u = 0; u < 4; ++u) a[u] = 4 * u + lk < w ? xa[4 * u * ldx] : 0.f;       // (the columns beyond may hold anything)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[u], b[u], acc, 0, 0, 0);
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[u], (double)a[u], acc, 0, 0, 0);
+        // (column 4 v + lk of row li)
+        if (row < len) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = 16 * tile + 4 * v + lk;
-            if (row < len) X[row * kTinyStride + li] = (float)acc[v];
+            for (int v = 0; v < 4; ++v) xa[4 * v * ldx] = (float)acc[v];
         }
     }
     __syncthreads();
 }
 
 // thin result in LDS -> memory
-__device__ __forceinline__ void tiny_store(const ThinRef& T, const float* X, int len, int w) {
+__device__ __forceinline__ void tiny_store(const ThinRef& T, const float* X, int ldx, int len, int w) {
     PSGD_GLOBAL float* dst = as_global(T.ptr);
     const int ld = T.ld;
     for (int e = threadIdx.x; e < len * w; e += kTinyThreads) {
         const int row = e / w, c = e - row * w;
-        dst[(int64_t)row * ld + c] = X[row * kTinyStride + c];
+        dst[(int64_t)row * ld + c] = X[c * ldx + row];
     }
 }
 
-// outer-product operand copies (32 columns) of a thin matrix in LDS, zero beyond it.  KEEP: the first two planes also replace the
-// matrix in LDS, eight columns of a row (32 bytes) by those of plane 0 and those of plane 1.
-template <bool KEEP>
-__device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X, int len, int lenP, int w) {
+// outer-product operand copies (32 columns) of a thin matrix in LDS, zero beyond it
+__device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, const float* X, int ldx, int len, int lenP, int w) {
     PSGD_GLOBAL bf16_t* dn[kMaxPlanes];
 #pragma unroll
     for (int k = 0; k < kMaxPlanes; ++k) dn[k] = as_global(K.n[k < planes ? k : 0]);
@@ -260,7 +375,7 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const bool in = row < len && c0 + u < w;
-            const float x = X[in ? row * kTinyStride + c0 + u : 0];
+            const float x = X[in ? (c0 + u) * ldx + row : 0];
             bf16_t q[kMaxPlanes];
             split_planes<kMaxPlanes>(in ? x : 0.f, q);
 #pragma unroll
@@ -269,11 +384,6 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, float* X
 #pragma unroll
         for (int k = 0; k < kMaxPlanes; ++k)
             if (k < planes) *reinterpret_cast<PSGD_GLOBAL bf16x8*>(dn[k] + 8 * v) = o[k];
-        if (KEEP && row < len && c0 < 16) {                    // (what this thread alone has read)
-            bf16x8* own = reinterpret_cast<bf16x8*>(X + row * kTinyStride + c0);
-            own[0] = o[0];
-            own[1] = o[1];
-        }
     }
 }
 
@@ -281,7 +391,7 @@ struct TinyLds {
     float *m, *x, *y;
     double *tm, *gram;
     int *need2, *asks_ends;                                // asks_ends: IterationState::asks + 2 ends
-    int ldm;
+    int ldm, ldx, ldy;
     __device__ TinyLds(const LayerDev& L, unsigned char* smem) {
         const TinyLayout t = tiny_layout(L.rows, L.cols);
         m = reinterpret_cast<float*>(smem);
@@ -292,34 +402,49 @@ struct TinyLds {
         need2 = reinterpret_cast<int*>(smem + t.flags);
         asks_ends = need2 + 1;
         ldm = tiny_ldm(L.cols);
+        ldx = t.ldx;
+        ldy = t.ldy;
     }
 };
 
-// E = M - X_L X_W^T from the two planes that tiny_pack has left in place of the factors.  What the updates subtract is the
-// product of these planes, 2^-17 from that of the factors themselves, and E has to hold what they leave: the same plane products
-// in the same order as in the outer-product kernels, so that E plus the update is M to the rounding of E.  (bf16 gradients, four
-// workers, compress alone: 256 x 128 28.8 us with the fp32 product of the factors, 26.0 with this; 64 x 64 11.4 and 11.6.  Splitting the
-// factors here again, 31.0 and 12.1.)
-__device__ __forceinline__ void tiny_residual_planes(const LayerDev& L, const float* M, int ldm, const float* xl, const float* xw) {
+// Four consecutive elements of E, of row `row` from column c on
+__device__ __forceinline__ void tiny_put(PSGD_GLOBAL float* out, int64_t ld, int rows, int cols, int row, int c, const floatx4& e) {
+    if (row >= rows || c >= cols) return;
+    PSGD_GLOBAL float* p = out + (int64_t)row * ld + c;
+    if (c + 4 <= cols) *reinterpret_cast<PSGD_GLOBAL floatx4*>(p) = e;
+    else for (int q = 0; q < cols - c; ++q) p[q] = e[q];
+}
+
+// E = M - X_L X_W^T from the two planes that tiny_pack has left in the operand copies (the same workgroup's stores, behind a
+// barrier).  What the updates subtract is the product of these planes, 2^-17 from that of the factors themselves, and E has to hold
+// what they leave: the same plane products in the same order as in the outer-product kernels, so that E plus the update is M to the
+// rounding of E.
+__device__ __forceinline__ void tiny_residual_planes(const LayerDev& L, const float* M, int ldm) {
     const int rows = L.rows, cols = L.cols;
     const int64_t ld = L.ld;
     PSGD_GLOBAL float* out = as_global(L.S);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 31, lg = lane >> 5;
+    const PSGD_GLOBAL bf16x8* l0 = reinterpret_cast<const PSGD_GLOBAL bf16x8*>(as_global(L.pack[SIDE_L].n[0]));
+    const PSGD_GLOBAL bf16x8* l1 = reinterpret_cast<const PSGD_GLOBAL bf16x8*>(as_global(L.pack[SIDE_L].n[1]));
+    const PSGD_GLOBAL bf16x8* w0 = reinterpret_cast<const PSGD_GLOBAL bf16x8*>(as_global(L.pack[SIDE_W].n[0]));
+    const PSGD_GLOBAL bf16x8* w1 = reinterpret_cast<const PSGD_GLOBAL bf16x8*>(as_global(L.pack[SIDE_W].n[1]));
     const int nc = (cols + 31) / 32, n_tiles = ((rows + 31) / 32) * nc;
     for (int tile = wv; tile < n_tiles; tile += kTinyWaves) {
-        const int I = tile / nc, J = tile - I * nc, row0 = 32 * I + 4 * lg, col = 32 * J + li;
-        const bf16x8* a = reinterpret_cast<const bf16x8*>(xl + min(32 * I + li, rows - 1) * kTinyStride + 8 * lg);
-        const bf16x8* b = reinterpret_cast<const bf16x8*>(xw + min(col, cols - 1) * kTinyStride + 8 * lg);
+        const int I = tile / nc, J = tile - I * nc, row = 32 * I + li;
+        // (fragment of a 32-row block: 128 pieces, of which the first 64 hold columns 0 .. 15)
+        const bf16x8 a0 = w0[128 * J + lane], a1 = w1[128 * J + lane], b0 = l0[128 * I + lane], b1 = l1[128 * I + lane];
         floatx16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc, 0, 0, 0);
+        const float* mr = M + min(row, rows - 1) * ldm;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = row0 + 8 * (v >> 2) + (v & 3);
-            if (row < rows && col < cols) out[(int64_t)row * ld + col] = M[row * ldm + col] - acc[v];
+        for (int v = 0; v < 4; ++v) {
+            const int c = 32 * J + 8 * v + 4 * lg;
+            const floatx4 x = *reinterpret_cast<const floatx4*>(mr + min(c, ldm - 4));
+            tiny_put(out, ld, rows, cols, row, c, floatx4{x[0] - acc[4 * v], x[1] - acc[4 * v + 1], x[2] - acc[4 * v + 2], x[3] - acc[4 * v + 3]});
         }
     }
 }
@@ -331,68 +456,70 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     const int tr = L.transposed, rows = L.rows, cols = L.cols, m = tr ? cols : rows, n = tr ? rows : cols, w = L.r, t = threadIdx.x;
     {
         const PSGD_GLOBAL float* q = as_global(L.thin[ROLE_Q].ptr);
-        for (int e = t; e < n * w; e += kTinyThreads) { const int i = e / w; S.y[i * kTinyStride + e - i * w] = q[e]; }
+        for (int e = t; e < n * w; e += kTinyThreads) { const int i = e / w; S.y[(e - i * w) * S.ldy + i] = q[e]; }
+        for (int e = w * S.ldy + t; e < kTinyCols * S.ldy; e += kTinyThreads) S.y[e] = 0.f;
+        for (int e = w * S.ldx + t; e < kTinyCols * S.ldx; e += kTinyThreads) S.x[e] = 0.f;
     }
     if (L.gdt == 0) tiny_form<false, false>(L, S.m, S.ldm); else tiny_form<true, false>(L, S.m, S.ldm);
     __syncthreads();
-    // M_log(i, k): row i, column k of the matrix with the long side first
-    const int sl = tr ? 1 : S.ldm, ss = tr ? S.ldm : 1;
-    tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x);
+    tiny_mul(S.m, S.ldm, !tr, m, n, w, S.y, S.ldy, S.x, S.ldx);
+    __syncthreads();
     for (int pass = 1; pass <= 2; ++pass) {
-        tiny_gram(S.x, m, w, reinterpret_cast<double*>(S.y), S.gram);
+        tiny_gram(S.x, S.ldx, m, w, reinterpret_cast<double*>(S.y), S.gram);
         if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1, S.tm, true, S.need2, 0);
         __syncthreads();
         const bool again = *S.need2 != 0;
-        tiny_apply(S.x, m, w, S.tm);
+        tiny_apply(S.x, S.ldx, m, w, S.tm);
         if (!again) break;                                 // (the second pass asks for no third)
     }
-    tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y);
-    tiny_store(L.thin[ROLE_P], S.x, m, w);
-    tiny_store(L.thin[ROLE_Q], S.y, n, w);
-    float* xl = tr ? S.y : S.x;
-    float* xw = tr ? S.x : S.y;
+    const int side_x = tr ? SIDE_W : SIDE_L, side_y = tr ? SIDE_L : SIDE_W;
+    tiny_mul(S.m, S.ldm, tr, n, m, w, S.x, S.ldx, S.y, S.ldy);
+    // (P~ goes out while other waves are still at the product)
+    tiny_store(L.thin[ROLE_P], S.x, S.ldx, m, w);
+    tiny_pack(L.pack[side_x], L.planes, S.x, S.ldx, m, tr ? L.colsP : L.rowsP, w);
+    __syncthreads();
+    tiny_store(L.thin[ROLE_Q], S.y, S.ldy, n, w);
+    tiny_pack(L.pack[side_y], L.planes, S.y, S.ldy, n, tr ? L.rowsP : L.colsP, w);
     if (L.planes == 2) {
-        __syncthreads();                                   // (what tiny_store reads is replaced)
-        tiny_pack<true>(L.pack[SIDE_L], 2, xl, rows, L.rowsP, w);
-        tiny_pack<true>(L.pack[SIDE_W], 2, xw, cols, L.colsP, w);
         __syncthreads();
-        tiny_residual_planes(L, S.m, S.ldm, xl, xw);
+        tiny_residual_planes(L, S.m, S.ldm);
         return;
     }
-    tiny_pack<false>(L.pack[SIDE_L], L.planes, xl, rows, L.rowsP, w);
-    tiny_pack<false>(L.pack[SIDE_W], L.planes, xw, cols, L.colsP, w);
-    // E = M - P~ Q^T, 16 x 16 blocks, four of them at a time (three planes hold the factors to fp32: the product of the planes and
-    // this one differ by roundings of fp32 sums)
+    const float* xl = tr ? S.y : S.x;
+    const float* xw = tr ? S.x : S.y;
+    // E = M - P~ Q^T, 16 x 16 blocks, formed transposed (a lane then holds four consecutive elements of a row;
+    // three planes hold the factors to fp32: the product of the planes and this one differ by roundings of fp32 sums)
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), li = lane & 15, lk = lane >> 4;
-    const int nc = (cols + 15) / 16, n_tiles = ((rows + 15) / 16) * nc;
+    const int ldl = tr ? S.ldy : S.ldx, ldw = tr ? S.ldx : S.ldy, ldm = S.ldm;
     const int64_t ld = L.ld;
     PSGD_GLOBAL float* out = as_global(L.S);
-    constexpr int B = 4;
-    for (int tile0 = wv; tile0 < n_tiles; tile0 += B * kTinyWaves) {
-        floatx4 acc[B], acc2[B];
-        int row0[B], col[B];
+    // a wave's share: a quarter of the blocks of a block row, kept in step with its operand of that row (4 nr shares)
+    const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, nq = (nc + 3) / 4;
+    for (int share = wv; share < 4 * nr; share += kTinyWaves) {
+        const int row = 16 * (share >> 2) + li, rowc = min(row, rows - 1), j0 = (share & 3) * nq, j1 = min(nc, j0 + nq);
+        float a[4];
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int tile = min(tile0 + b * kTinyWaves, n_tiles - 1), I = tile / nc, J = tile - I * nc;      // (scalar; the last again)
-            row0[b] = 16 * I;
-            col[b] = 16 * J + li;
-            const float* la = xl + min(16 * I + li, rows - 1) * kTinyStride + lk;
-            const float* wb = xw + min(col[b], cols - 1) * kTinyStride + lk;
-            acc[b] = acc2[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < 4; ++u) a[u] = 4 * u < w ? xl[(4 * u + lk) * ldl + rowc] : 0.f;
+        const float* mr = S.m + rowc * ldm + 4 * lk;
+        const float* wb = xw + lk * ldw + li;
+        for (int j = j0; j < j1; ++j) {
+            const bool inside = 16 * j + 16 <= cols;           // (uniform)
+            const floatx4 x = *reinterpret_cast<const floatx4*>(inside ? mr + 16 * j : S.m + rowc * ldm + min(16 * j + 4 * lk, ldm - 4));
+            const float* b = inside ? wb + 16 * j : xw + lk * ldw + min(16 * j + li, cols - 1);
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = acc, e;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                floatx4& c = u < 2 ? acc[b] : acc2[b];
-                if (4 * u < w) c = __builtin_amdgcn_mfma_f32_16x16x4f32(la[4 * u], wb[4 * u], c, 0, 0, 0);
+                floatx4& c = u < 2 ? acc : acc2;
+                if (4 * u < w) c = __builtin_amdgcn_mfma_f32_16x16x4f32(b[4 * u * ldw], a[u], c, 0, 0, 0);
             }
-        }
+            if (w <= 8) {                                      // (one sum: the difference is rounded once either way)
+                e = x - acc;
+            } else {
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            if (tile0 + b * kTinyWaves >= n_tiles) continue;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = row0[b] + 4 * lk + v;
-                if (row < rows && col[b] < cols) out[(int64_t)row * ld + col[b]] = (float)((double)S.m[row * S.ldm + col[b]] - ((double)acc[b][v] + (double)acc2[b][v]));
+                for (int v = 0; v < 4; ++v) e[v] = (float)((double)x[v] - ((double)acc[v] + (double)acc2[v]));
             }
+            if (inside && row < rows) *reinterpret_cast<PSGD_GLOBAL floatx4*>(out + (int64_t)row * ld + 16 * j + 4 * lk) = e;
+            else tiny_put(out, ld, rows, cols, row, 16 * j + 4 * lk, e);
         }
     }
 }
@@ -413,48 +540,65 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
         const int n_copy = warm ? min(Q.width, w) : 0;
         for (int e = t; e < n * w; e += kTinyThreads) {
             const int i = e / w, c = e - i * w;
-            S.y[i * kTinyStride + c] = c < n_copy ? q[(int64_t)i * Q.ld + c] : start_value(seed, lid, i, c);
+            S.y[c * S.ldy + i] = c < n_copy ? q[(int64_t)i * Q.ld + c] : start_value(seed, lid, i, c);
         }
+        for (int e = w * S.ldy + t; e < kTinyCols * S.ldy; e += kTinyThreads) S.y[e] = 0.f;
     }
     if (L.gdt == 0) tiny_form<false, true>(L, S.m, S.ldm); else tiny_form<true, true>(L, S.m, S.ldm);
     __syncthreads();
-    const int sl = tr ? 1 : S.ldm, ss = tr ? S.ldm : 1;
-    IterationState state;                                  // (wave 0's)
+    // (the last wave's, which makes the notes of a factorisation beside the product that follows: of the products of most sizes it has
+    // no tile)
+    IterationState state;
     bool asked = false;
 #pragma unroll 1
     for (int it = 0; it < k_iters; ++it) {
         const bool last = it == k_iters - 1, grows = it > kOrthYIterations && !asked;
-        tiny_mul(S.m, sl, ss, m, n, S.y, w, S.x, last);
+        int noted = 0;
+        tiny_mul_as<0>(S.m, S.ldm, !tr, m, n, S.y, S.ldy, S.x, S.ldx, last);
+        __syncthreads();
 #pragma unroll 1
         for (int pass = 1; pass <= 2; ++pass) {
-            tiny_gram(S.x, m, w, reinterpret_cast<double*>(S.y), S.gram);
+            tiny_gram(S.x, S.ldx, m, w, reinterpret_cast<double*>(S.y), S.gram);
+            const int note = pass == 2 || last || it < kOrthYIterations ? 0 : grows ? NOTE_SCALE | NOTE_GROWTH : NOTE_SCALE;
+            noted = note != 0 ? note : noted;
             if (t < 64) {
-                const int note = pass == 2 || last || it < kOrthYIterations ? 0 : grows ? NOTE_SCALE | NOTE_GROWTH : NOTE_SCALE;
-                chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, note, it, &state);
-                if (note && t == 0) *S.asks_ends = state.asks + 2 * state.ends;
+                NarrowFactor f;
+                chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, note, it, &f);
+                if (note && t < 16) {
+                    // (the Gram matrix has been read)
+                    S.gram[t] = f.dsc;
+                    S.gram[16 + t] = f.rjj;
+                    if (t == 0) { S.gram[32] = f.min_piv; S.need2[2] = f.badmask; }
+                }
             }
             __syncthreads();
             const bool again = *S.need2 != 0;
-            tiny_apply(S.x, m, w, S.tm);
+            tiny_apply(S.x, S.ldx, m, w, S.tm);
             if (!again) break;
         }
+        if (noted && t >= kTinyThreads - 64) {
+            const NarrowFactor f{S.gram[t & 15], S.gram[16 + (t & 15)], S.gram[32], S.need2[2]};
+            narrow_notes(L, w, noted, it, f, true, &state);
+            if ((t & 63) == 0) *S.asks_ends = state.asks + 2 * state.ends;
+        }
+        tiny_mul_as<0>(S.m, S.ldm, tr, n, m, S.x, S.ldx, S.y, S.ldy, last);
+        __syncthreads();
         if (it >= kOrthYIterations && !last) {
             asked = (*S.asks_ends & 1) != 0;
             const int ends = *S.asks_ends >> 1;
             if (ends > 0 && ends < k_iters) k_iters = ends;
         }
-        tiny_mul(S.m, ss, sl, n, m, S.x, w, S.y, last);
         if (!last && (it < kOrthYIterations || asked)) {
-            tiny_gram(S.y, n, w, reinterpret_cast<double*>(S.x), S.gram);
+            tiny_gram(S.y, S.ldy, n, w, reinterpret_cast<double*>(S.x), S.gram);
             if (t < 64) chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, 0);
             __syncthreads();
-            tiny_apply(S.y, n, w, S.tm);
+            tiny_apply(S.y, S.ldy, n, w, S.tm);
         }
     }
-    tiny_store(L.thin[ROLE_ZP], S.x, m, w);
-    tiny_store(L.thin[ROLE_ZQ], S.y, n, w);
+    tiny_store(L.thin[ROLE_ZP], S.x, S.ldx, m, w);
+    tiny_store(L.thin[ROLE_ZQ], S.y, S.ldy, n, w);
     __syncthreads();
-    tiny_gram(S.y, n, w, reinterpret_cast<double*>(S.x), S.gram);
+    tiny_gram(S.y, S.ldy, n, w, reinterpret_cast<double*>(S.x), S.gram);
     for (int e = t; e < (w * (w + 1)) / 2; e += kTinyThreads) as_global(L.gram)[e] = S.gram[e];
     if (t == 0) L.status[1] = 0;                           // (nothing is left to do for a second pass)
 }

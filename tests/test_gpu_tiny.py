@@ -164,3 +164,15 @@ def test_hard_starts(rows, cols, kind):
             assert not live.any()
         if refresh and opts["refresh_iters"] == 4 and kind != "close":
             assert abs(np.sum(e ** 2) - np.sum(sv[r:] ** 2)) <= 1e-6 * nm ** 2
+
+
+# one and two tiles of 16 rows per wave (192 and 193 rows or columns), reductions that end 1, 15, 16, 17 and 31 steps after a
+# multiple of 32, thin matrices without the odd stride in LDS (168 x 200 and 272 x 120 fit only so)
+EDGES = [(192, 65), (193, 79), (65, 193), (80, 192), (81, 95), (168, 200), (272, 120), (4, 31)]
+
+
+@pytest.mark.parametrize("r", [3, 4, 5, 16])
+@pytest.mark.parametrize("n_workers,dtype", [(2, synth.F32), (1, synth.BF16)])
+def test_step_at_the_edges_of_tiles(monkeypatch, r, n_workers, dtype):
+    monkeypatch.setitem(globals(), "SHAPES", EDGES)
+    test_step(r, n_workers, dtype)
