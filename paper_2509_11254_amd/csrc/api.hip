@@ -50,7 +50,8 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
 hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows_n, int slot_rows_t,
                            int gate, int flagged, hipStream_t st);
 hipError_t launch_max_m(const LayerDev* layers, const int* ids, int n_ids, int max_rows, hipStream_t st);
-int finish_rows(int w);
+int finish_rows(int w, int max_blocks, int n_ids);
+int apply_rows(int max_lenP, int n_ids, int w_in);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, int slot_rows, hipStream_t st);
@@ -667,19 +668,21 @@ struct Launcher {
         const int ww = w > 0 ? w : 32 * nb;
         const bool wide = sums_first(ww, p_like ? std::max(norm.longest, tr.longest) : std::max(norm.shortest_max, tr.shortest_max));
         const int fin_gate = wide ? -2 : chol_gate;
+        int fin_rows = kGramRows1;
         if (split_n || split_t) {
             // (one launch for both orientations where both are split)
             const int* ids = split_n && split_t ? ids_all : split_n ? ids_norm : ids_tr;
             const int n_ids = split_n && split_t ? n_all : split_n ? n_norm : n_tr;
             const int most = std::max(split_n ? norm.blocks[mode_n] : 0, split_t ? tr.blocks[mode_t] : 0);
+            fin_rows = finish_rows(ww, most, n_ids);
             note(launch_finish(p_like, kind_n, kind, layers, ids, n_ids, most, 32 * nb, out_role, epi | (ef & (EPI_KEPT | EPI_HALF)), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         }
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
         // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
         // per 128 rows)
         if (rv2 && !split_n && epi == EPI_GRAM && !gram32) note(launch_thin_gram(layers, ids_norm, n_norm, norm.blocks[0], out_role, 32 * nb, gate, 0, st));
-        gram_rows_n = gram32 ? 32 : split_n ? finish_rows(ww) : kGramRows1;
-        gram_rows_t = split_t ? finish_rows(ww) : kGramRows1;
+        gram_rows_n = gram32 ? 32 : split_n ? fin_rows : kGramRows1;
+        gram_rows_t = split_t ? fin_rows : kGramRows1;
         if (chol_gate >= -1) {
             // (the many 32-row slots are added up before at any width; the launches for an orthonormal Y that only a few
             // layers ask for are kept few: there the factorisation adds the slots up itself)
@@ -717,7 +720,7 @@ struct Launcher {
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, g, -2, 0, 0, st));
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), g, -2, 0, 0, st));
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
         }
     }
@@ -745,7 +748,7 @@ struct Launcher {
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, kGramRows1, -1, 0, st));
         if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
-        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, -1, -2, 0, 0, st));
+        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), -1, -2, 0, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
     // 32-row blocks per workgroup of the outer-product kernels and the grid that goes with them.  Four blocks, one per wave, and the

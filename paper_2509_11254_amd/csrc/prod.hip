@@ -1106,18 +1106,23 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
     return hipGetLastError();
 }
 
-// Rows per workgroup and Gram slot.  w: widest block of the launch
-int finish_rows(int w) { return w > kWideWidth ? BT / 2 : BT; }
+// Rows per workgroup and Gram slot.  w: widest block of the launch; max_blocks: 128-row blocks of its longest layer.  Above width 32 64
+// rows, and 32 where 64 leave compute units idle (8192 x 160 with the Gram matrix 26 -> 20 us, the sum over twice the slots 5.3 -> 7.3), but for results of up to 2048 rows, whose partial
+// Gram matrices the factorisation may add up by itself.
+int finish_rows(int w, int max_blocks, int n_ids) {
+    return w <= kWideWidth ? BT : max_blocks > 2048 / BT && 2 * max_blocks * n_ids <= 128 ? BT / 4 : BT / 2;
+}
 
 // max_blocks: 128-row blocks of the longest result of the launch's layers
 hipError_t launch_finish(bool p_like, int kind_n, int kind_t, const LayerDev* layers, const int* ids, int n_ids, int max_blocks,
                          int cp, int out_role, int epi, int gate, int chol_gate, int a2gate, double tol2, int w,
                          int local_ok, hipStream_t st) {
     if (n_ids <= 0 || max_blocks <= 0) return hipSuccess;
-    const int fb = finish_rows(w > 0 ? w : cp);
+    const int fb = finish_rows(w > 0 ? w : cp, max_blocks, n_ids);
     dim3 grid(max_blocks * (BT / fb), n_ids), block(fb == BT ? kThreads : 2 * kThreads);
     auto kfn = fb == BT ? (gate >= 0 ? finish_kernel<BT, kThreads, true> : finish_kernel<BT, kThreads, false>)
-                        : (gate >= 0 ? finish_kernel<BT / 2, 2 * kThreads, true> : finish_kernel<BT / 2, 2 * kThreads, false>);
+             : fb == BT / 2 ? (gate >= 0 ? finish_kernel<BT / 2, 2 * kThreads, true> : finish_kernel<BT / 2, 2 * kThreads, false>)
+                        : (gate >= 0 ? finish_kernel<BT / 4, 2 * kThreads, true> : finish_kernel<BT / 4, 2 * kThreads, false>);
     size_t lds = (size_t)fb * (cp + 1) * sizeof(float);
     if (fb == BT) lds += 8 + (kThreads / 64) * 256 * sizeof(double);            // (layers of widths up to 16: see gram_tile_f64)
     if (chol_gate >= -1 && chol_lds_bytes_upto(w) > lds) lds = chol_lds_bytes_upto(w);

@@ -49,16 +49,16 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const LayerDev* __restri
 }
 
 // Operand copies of rows of an orthonormalised matrix (apply kernels; `which` as for launch_apply).
-template <int NT>
+template <int NT, int ROWS>
 __device__ __forceinline__ void write_copies(const LayerDev& L, int role, int side, const float* so, int ow, int cp, int i0, int lenP, int which, int gate) {
     if (which & 8) {
         const bool scaled = scales_next(L, role, gate);
         const int w = L.thin[role].width;
         const PSGD_GLOBAL double* scale = as_global(L.eval);
-        write_half<NT>(L, side, so, ow, cp, i0, kGramRows2, [=](int c) { return HalfOperands::of_orthonormal(scaled && c < w ? scale[c] : 1.0); });
+        write_half<NT>(L, side, so, ow, cp, i0, ROWS, [=](int c) { return HalfOperands::of_orthonormal(scaled && c < w ? scale[c] : 1.0); });
         which &= ~2;
     }
-    if (which & 3) write_packs<0, NT>(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
+    if (which & 3) write_packs<0, NT>(L.pack[side], L.planes, so, ow, cp, i0, ROWS, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
 }
 
 // role_b < 0: one role
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
             }
         }
         if (do_gram) gram_tile_f64(so, ow, kGramRows2, w_out, L.gram + (int64_t)tile * ((w_out * (w_out + 1)) / 2));
-        else if (do_pack) write_copies<kThreads>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
+        else if (do_pack) write_copies<kThreads, kGramRows2>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
         __syncthreads();
     }
 }
@@ -553,6 +553,7 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
 // straight from L2, four steps ahead.
 // --------------------------------------------------------------------------------------------
 constexpr int kApplyWideThreads = 1024;
+template <int ROWS>
 __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const LayerDev* __restrict__ layers,
                                                                        const int* __restrict__ ids, int src_role,
                                                                        int dst_role, int mode, int cp, int gate, int w_in_max,
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
     const bool do_pack = !do_gram && cp > 0;
     const int side = side_of_role(L.transposed, src_role);
     const int len = side_len(L, side), lenP = side_lenP(L, side);
-    const int i0 = blockIdx.x * kGramRows2;
+    const int i0 = blockIdx.x * ROWS;
     if (i0 >= (do_pack ? lenP : len)) return;
     const ThinRef X = L.thin[src_role];
     const ThinRef Y = L.thin[dst_role];
@@ -579,20 +580,21 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
     const int xs = ((w_in_max + 15) & ~15) + 1;
     const int wo16 = (w_out_max + 15) & ~15, ow = (cp > wo16 ? cp : wo16) + 1;
     extern __shared__ __align__(16) unsigned char smem[];
-    float* sx = reinterpret_cast<float*>(smem);            // [64][xs]  x tile, zero beyond the matrix
-    float* so = sx + (size_t)kGramRows2 * xs;              // [64][ow]  result tile, zero beyond w_out
+    float* sx = reinterpret_cast<float*>(smem);            // [ROWS][xs]  x tile, zero beyond the matrix
+    float* so = sx + (size_t)ROWS * xs;              // [ROWS][ow]  result tile, zero beyond w_out
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
-    for (int i = wv; i < kGramRows2; i += kApplyWideThreads / 64) {
+    for (int i = wv; i < ROWS; i += kApplyWideThreads / 64) {
         const bool in = i0 + i < len;
         const PSGD_GLOBAL float* xr = as_global(X.ptr) + (int64_t)(in ? i0 + i : 0) * X.ld;
         for (int c = lane; c < kpad; c += 64) sx[i * xs + c] = (in && c < w_in) ? xr[c] : 0.f;
         for (int c = lane; c < ow; c += 64) so[i * ow + c] = 0.f;
     }
     __syncthreads();
-    const int rg = wv & 3, cg = wv >> 2;
+    constexpr int RG = ROWS / 16, CG = kApplyWideThreads / 64 / RG;
+    const int rg = wv % RG, cg = wv / RG;
     const float* __restrict__ xa = sx + (16 * rg + li) * xs + lk;
     const PSGD_GLOBAL double* __restrict__ tm = as_global(L.tmat);
-    for (int ct = cg; ct < n_ct; ct += 4) {
+    for (int ct = cg; ct < n_ct; ct += CG) {
         const int col = 16 * ct + li;
         const int kend = upper ? min(kpad, 16 * (ct + 1)) : kpad;
         const bool col_ok = col < w_in;
@@ -620,13 +622,19 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
         }
     }
     __syncthreads();
-    const int rows_valid = min(len, i0 + kGramRows2) - i0;
+    const int rows_valid = min(len, i0 + ROWS) - i0;
     for (int i = wv; i < rows_valid; i += kApplyWideThreads / 64) {
         PSGD_GLOBAL float* yr = as_global(Y.ptr) + (int64_t)(i0 + i) * Y.ld;
         for (int c = lane; c < w_out; c += 64) yr[c] = so[i * ow + c];
     }
-    if (do_gram) gram_tile_f64(so, ow, kGramRows2, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
-    else if (do_pack) write_copies<kApplyWideThreads>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
+    if (do_gram) gram_tile_f64(so, ow, ROWS, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
+    else if (do_pack) write_copies<kApplyWideThreads, ROWS>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
+}
+
+// Rows per workgroup, and per partial Gram matrix of its result, of a launch at widths up to w_in.  apply_wide_kernel: 32 where 64
+// leave compute units idle (8192 x 160 24 -> 16 us, 8192 x 128 20 -> 14; with more tiles than compute units its reads of tmat are what grows).
+int apply_rows(int max_lenP, int n_ids, int w_in) {
+    return w_in > kApplyStreamMaxWidth && (max_lenP / kGramRows2) * n_ids <= 256 ? 32 : kGramRows2;
 }
 
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
@@ -665,11 +673,13 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
     }
     if (!small) {
         const int wi16 = (w_in + 15) & ~15, wo16 = (w_out + 15) & ~15;
-        const size_t lds = (size_t)kGramRows2 * (wi16 + 1 + (cp > wo16 ? cp : wo16) + 1) * sizeof(float);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(apply_wide_kernel),
+        const int rows = apply_rows(max_lenP, n_ids, w_in);
+        const size_t lds = (size_t)rows * (wi16 + 1 + (cp > wo16 ? cp : wo16) + 1) * sizeof(float);
+        auto kfn = rows == 32 ? apply_wide_kernel<32> : apply_wide_kernel<kGramRows2>;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(apply_wide_kernel, dim3(grid.x, n_ids, n_sides), dim3(kApplyWideThreads), lds, st, layers, ids, src_role, dst_role, mode, cp,
+        hipLaunchKernelGGL(kfn, dim3(max_lenP / rows, n_ids, n_sides), dim3(kApplyWideThreads), lds, st, layers, ids, src_role, dst_role, mode, cp,
                            gate, w_in, w_out, which);
         return hipGetLastError();
     }

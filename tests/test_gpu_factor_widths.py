@@ -5,8 +5,8 @@ import numpy as np
 import pytest
 
 from oracle import psgd_oracle as orc
-from paper_2509_11254_amd import synth
-from gpu_harness import Case
+from paper_2509_11254_amd import psgd, synth
+from gpu_harness import Case, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -186,3 +186,34 @@ def test_many_partial_gram_matrices(shapes, op, r):
             assert orc.rel_fro(p, orc.ssp_comp(qs[l].astype(np.float64), [ml]).p_tilde) <= 1e-4, l
         else:
             assert abs(np.sum(e ** 2) - np.sum(np.linalg.svd(ml, compute_uv=False)[r:] ** 2)) <= 1e-4 * nm ** 2, l
+
+
+# results of 17 to 64 blocks of 128 rows, alone: 32 rows per workgroup and partial Gram matrix; one block fewer, and a batch: 64
+@pytest.mark.parametrize("shapes", [[(2049, 300)], [(300, 2176)], [(2048, 300)], [(8192, 200)], [(8193, 200)], [(5000, 260), (260, 5000)]])
+@pytest.mark.parametrize("r", [97, 128])
+def test_second_pass_of_wide_blocks(shapes, r):
+    """Columns of P that are dependent to 10^-4: the first CholeskyQR pass leaves 10^-8, and asks for the second."""
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r)
+    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_F32, (cols + 7) // 8 * 8) for rows, cols in shapes], 1)
+    G, E, Q, P, M = [], [], [], [], []
+    for rows, cols in shapes:
+        m, n = max(rows, cols), min(rows, cols)
+        ld = (cols + 7) // 8 * 8
+        u = torch.linalg.qr(torch.randn((rows, n), generator=gen, device="cuda", dtype=torch.float64))[0]
+        v = torch.linalg.qr(torch.randn((cols, n), generator=gen, device="cuda", dtype=torch.float64))[0]
+        g = torch.zeros((rows, ld), device="cuda")
+        g[:, :cols] = (u @ v.T).float()
+        q = torch.randn((n, r), generator=gen, device="cuda")
+        q[:, r // 2:] = q[:, :r - r // 2] + 1e-4 * torch.randn((n, r - r // 2), generator=gen, device="cuda")
+        G.append([g])
+        E.append(torch.zeros_like(g))
+        Q.append(q.contiguous())
+        P.append(torch.zeros((m, r), device="cuda"))
+        M.append(g[:, :cols].double() if rows >= cols else g[:, :cols].double().T)
+    comp.compress(G, E, Q, P)
+    for l in range(len(shapes)):
+        p = P[l].double()
+        assert float((p.T @ p - torch.eye(r, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6, l
+        assert float((Q[l].double() - M[l].T @ p).norm()) <= 2e-6 * float(M[l].norm()), l
