@@ -653,13 +653,16 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
     const int n_sides = mode == APPLY_RITZ ? 2 : 1;
     dim3 grid(max_lenP / kGramRows2, n_ids), block(kThreads);
     if (!small && w_in <= kApplyStreamMaxWidth) {
-        // a few rounds of workgroups over the whole launch, each walking several tiles of its layer
-        // (config 4, width 64: 0.54 ms with one round of 512 workgroups, 0.43 with four, 0.42 with eight, 0.45 with 16)
-        int per_layer = (8 * 512 + n_ids - 1) / n_ids;
-        if (per_layer > (int)grid.x) per_layer = grid.x;
-        if (per_layer < 1) per_layer = 1;
         // (triangular tmat up to width 80: its fragments fit the registers)
         const int kp16 = (mode != APPLY_RITZ && w_in <= 80) ? (w_in + 15) / 16 : 0;
+        // a few rounds of workgroups over the whole launch, each walking several tiles of its layer
+        // (config 4, width 64: 0.54 ms with one round of 512 workgroups, 0.43 with four, 0.42 with eight, 0.45 with 16)
+        // Above width 64, up to 4096 tiles: one round, of two per compute unit (us per refresh with a workgroup per tile, and with two,
+        // three, four per compute unit: 7B-shaped block, width 80, 3071 and 3020, 3064, 3063; three 1B-shaped ones in fp32 3652 and 3564,
+        // 3583, 3584; at width 40 in bf16 5018 and 5053, 5029, 5000).
+        int per_layer = ((w_in > 64 && (int)grid.x * n_ids <= 8 * 512 ? 2 * 256 : 8 * 512) + n_ids - 1) / n_ids;
+        if (per_layer > (int)grid.x) per_layer = grid.x;
+        if (per_layer < 1) per_layer = 1;
         const size_t lds = apply_stream_lds(w_in, w_out, cp, mode != APPLY_RITZ, kp16);
         // (widths up to 16 are the `small` chain's: kp16 >= 2 here)
         auto kfn = kp16 == 2 ? apply_stream_kernel<2> : kp16 == 3 ? apply_stream_kernel<3>
