@@ -265,8 +265,8 @@ LayerRegion layer_region(const psgd_ctx* c, const Plan& p) {
     for (int s = 0; s < 2; ++s) R.z[s] = take((size_t)len[s] * p.wz * sizeof(float));
     const size_t w2 = (size_t)(p.wz + 2) * (p.wz + 2);
     const int max_lenP = lenP[0] > lenP[1] ? lenP[0] : lenP[1];
-    // one partial Gram matrix per 64 rows of the widest block, or per 32 and per 64 rows of a narrow P (the first pass of its
-    // factorisation and, while that is being read, the second)
+    // one partial Gram matrix per 64 rows of the widest block as a full square (as packed triangles: one per 32 rows), or triangles per
+    // 32 and per 64 rows of a narrow P (the first pass of its factorisation and, while that is being read, the second)
     const size_t tri = (size_t)p.d.r * (p.d.r + 1) / 2, pass12 = p.d.r <= 16 ? (size_t)(kGramRows2 / 32 + 1) * tri : 0;
     R.gram = take((size_t)(max_lenP / kGramRows2) * std::max(w2, pass12) * sizeof(double));
     R.tmat = take(w2 * sizeof(double));

@@ -11,7 +11,8 @@
 // Arithmetic: M and X are split into two or three bf16 planes each (x = p0 + p1 (+ p2), each plane the
 // rounded remainder of the ones before: 16 or 24 mantissa bits) and the product is accumulated in
 // fp32 from the plane products with plane-index sum <= 1 (three products) or <= 2 (six), smallest
-// first, with v_mfma_f32_32x32x16_bf16.
+// first, with v_mfma_f32_32x32x16_bf16.  Wide products that only read M may take two fp16 planes of scaled operands in place of
+// three bf16 ones (HalfOperands): three plane products, 24 bits.
 // The S tile goes global -> registers (coalesced 16-byte loads, summed over workers) -> LDS in the
 // k-contiguous layout the MFMA A operand wants; the thin operand arrives pre-split and transposed.
 #include <algorithm>
