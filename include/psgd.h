@@ -107,8 +107,7 @@ typedef struct {
                                    0 = default (1e-5)                                                */
     int32_t precision;          /* bf16 planes per fp32 operand of the matrix-core products: 2 = three
                                    products per term (16 mantissa bits), 3 = six products (24 bits,
-                                   fp32-faithful; large contexts at widths from 96 on: two fp16 planes of scaled
-                                   operands, three products, 24 bits); 0 = default: 3 if any layer has fp32 gradients,
+                                   fp32-faithful); 0 = default: 3 if any layer has fp32 gradients,
                                    else 2.  The products of small layers (see psgd_compress) do without
                                    planes, the updates' P~ Q^T has them in every case                 */
     int32_t m_policy;           /* where M = mean G + E lives between the passes of an SSP step: 1 = stored

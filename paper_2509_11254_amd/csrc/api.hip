@@ -16,7 +16,7 @@
 #include "psgd_dev.h"
 
 namespace psgd {
-hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, bool half, const LayerDev* layers,
+hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers,
                        const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st);
 hipError_t launch_form_row(int nb, int planes, bool gbf, bool onew, int lazy, const LayerDev* layers, const int* ids,
                            int n_ids, int max_tiles, int out_role, int epi, int nt_m, const int* xtab, int xstride,
@@ -46,10 +46,9 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
 hipError_t launch_pack(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int role_a, int role_b,
                        int cp, int which, hipStream_t st);
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, int find_max, hipStream_t st);
+                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, hipStream_t st);
 hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows_n, int slot_rows_t,
                            int gate, int flagged, hipStream_t st);
-hipError_t launch_max_m(const LayerDev* layers, const int* ids, int n_ids, int max_rows, hipStream_t st);
 int finish_rows(int w, int max_blocks, int n_ids);
 int apply_rows(int max_lenP, int n_ids, int w_in);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
@@ -117,7 +116,6 @@ struct psgd_ctx {
     bool lazy = false;       // deferred residual: E_{t+1} = M - P~ Q^T is applied by the next forming pass
     bool lazy_tr = false;    // ... also for the layers stored with rows < cols (column-mode forming pass: width 32 only)
     bool pending = false;    // the E buffers of the row-major layers hold M_t, their residual is still owed
-    int64_t elements = 0;    // of all layers
     double kernel_bytes[3] = {0.0, 0.0, 0.0};   // algorithmic bytes of the three streaming kernels of one SSP step
     int grad_kind = 0;                          // 1: every layer has fp32 gradients, 2: every layer bf16, 0: mixed
     bool nt_m = false;                          // the row-major layers' M is too large to be found in a cache again
@@ -593,7 +591,6 @@ struct Launcher {
     bool lazy_form = false;   // the forming pass of the row-major layers also applies their pending residual
     bool lazy_share = false;  // ... and the transposed operand copies of Q_{t-1} are what the step before left: they hold
                               // the kept Q, which the pass then need not read
-    bool half = false;        // products that only read M take fp16 operands, and the transposed copies are made so (see half_products)
     bool kept_packs = false;  // compress step with a deferred residual: the outer-product operand copies of its P~ and Q
                               // are the kept ones in the layers that have them
     bool use_xtab = true;     // PSGD_XTAB=0 (environment, measurement knob): plain layer-by-layer launch order
@@ -619,7 +616,7 @@ struct Launcher {
 
     // operand copies of caller-supplied thin matrices: the transposed ones for a product, the others for an
     // outer-product kernel
-    enum { PACK_OUTER = 1, PACK_TRANSPOSED = 2, PACK_HALF = 8 };
+    enum { PACK_OUTER = 1, PACK_TRANSPOSED = 2 };
     void pack(int role, int cp, int which, int role_b = -1) {
         note(launch_pack(layers, ids_all, n_all, max_lenP(), role, role_b, cp, which, st));
     }
@@ -629,8 +626,7 @@ struct Launcher {
               double tol2 = 0.0, int w = 0, bool small = false) {
         // normal storage: P-like result is L-side -> row mode; transposed storage: column mode
         const int k = prof_begin(p_like ? PSGD_PROF_SWEEP1 : PSGD_PROF_SWEEP2);
-        const int ef = epi | (keep_e ? EPI_KEEP_E : 0) | (kept_packs && epi == EPI_PACK ? EPI_KEPT : 0) |
-                       (half ? (form ? EPI_MAX : epi == EPI_ITERATE ? EPI_HALF : 0) : 0);
+        const int ef = epi | (keep_e ? EPI_KEEP_E : 0) | (kept_packs && epi == EPI_PACK ? EPI_KEPT : 0);
         const bool onew = ctx->n_workers == 1;
         const SplitKind kind = (SplitKind)split_kind(form, gate);      // (where prod_kernel runs)
         const int mode_n = p_like ? 0 : 1, mode_t = 1 - mode_n;
@@ -652,11 +648,11 @@ struct Launcher {
         if (c2) note(launch_col_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][1], out_role, ef, gate, ctx->nt_m ? 1 : 0, xtab_c, ctx->xstride, ctx->xtiles_c, st));
         else if (r2) note(launch_row_prod(nb, ctx->planes, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), gate, ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
         else if (v2) note(launch_form_row(nb, ctx->planes, ctx->grad_kind == 2, onew, lazy_form ? (lazy_share ? 2 : 1) : 0, layers, ids_norm, n_norm, norm.tiles[SPLIT_V2][0], out_role, gram32 ? ef : (ef & ~EPI_KIND_MASK), ctx->nt_m ? 1 : 0, xtab, ctx->xstride, ctx->xtiles, st));
-        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, half && !form, layers, ids_norm, n_norm, norm.tiles[kind][mode_n], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
+        else note(launch_prod(nb, ctx->planes, !p_like, form, form && p_like && lazy_form, onew, layers, ids_norm, n_norm, norm.tiles[kind][mode_n], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
         // (the row product of the layers stored with rows < cols stays on 128 x 64 tiles: 990 x 3741 fp32 r = 6 72.8 us per step
         // against 76.2 on 32 x 256 tiles, eight 2048 x 5632 r = 16 530 against 556, 22 of them in bf16 r = 32 1327 against 1358,
         // four 4096 x 11008 r = 64 1015 against 1089; single long ones are up to 5 % faster there, 1024 x 100000 712 and 695)
-        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, half && !form, layers, ids_tr, n_tr, tr.tiles[kind][mode_t], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
+        note(launch_prod(nb, ctx->planes, p_like, form, form && p_like && lazy_form && ctx->lazy_tr, onew, layers, ids_tr, n_tr, tr.tiles[kind][mode_t], out_role, ef, gate, ctx->nt_read ? 1 : 0, st));
         prof_end(k);
         // split reductions are completed (and the epilogue run) by a second, small launch, whose last
         // workgroup per layer also factorises the Gram matrix; unsplit products need a launch for that
@@ -675,7 +671,7 @@ struct Launcher {
             const int n_ids = split_n && split_t ? n_all : split_n ? n_norm : n_tr;
             const int most = std::max(split_n ? norm.blocks[mode_n] : 0, split_t ? tr.blocks[mode_t] : 0);
             fin_rows = finish_rows(ww, most, n_ids);
-            note(launch_finish(p_like, kind_n, kind, layers, ids, n_ids, most, 32 * nb, out_role, epi | (ef & (EPI_KEPT | EPI_HALF)), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
+            note(launch_finish(p_like, kind_n, kind, layers, ids, n_ids, most, 32 * nb, out_role, epi | (ef & EPI_KEPT), gate, fin_gate, a2gate, tol2, ww, small ? 1 : 0, st));
         }
         // (an unsplit launch of that kernel writes one partial Gram matrix per 32-row block itself; only where the apply kernel
         // factorises for itself and would have more than 64 of them to add up, a small pass over the result leaves one
@@ -691,13 +687,13 @@ struct Launcher {
             if (wide && !few) note(launch_gram_sum(layers, ids_all, n_all, ww, out_role, gram_rows_n, gram_rows_t, chol_gate, 0, st));
             else if (gram32 && !small) note(launch_gram_sum(layers, ids_norm, n_norm, ww, out_role, gram_rows_n, gram_rows_t, chol_gate, 0, st));
             if (wide) {
-                note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, few ? gram_rows_n : kOneSlot, few ? gram_rows_t : kOneSlot, chol_gate, a2gate, 0, half && form ? 1 : 0, st));
+                note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, few ? gram_rows_n : kOneSlot, few ? gram_rows_t : kOneSlot, chol_gate, a2gate, 0, st));
             } else {
                 // (not where the apply kernel factorises every layer for itself)
                 const bool local_n = small && (p_like ? norm.longest : norm.shortest_max) <= kLocalCholMaxRows;
                 const bool local_t = small && (p_like ? tr.longest : tr.shortest_max) <= kLocalCholMaxRows;
-                if (!split_n && !local_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, 0, chol_gate, a2gate, small ? 1 : 0, 0, st));
-                if (!split_t && !local_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, 0, kGramRows1, chol_gate, a2gate, small ? 1 : 0, 0, st));
+                if (!split_n && !local_n) note(launch_chol(layers, ids_norm, n_norm, w, out_role, tol2, 1, gram32 ? kOneSlot : kGramRows1, 0, chol_gate, a2gate, small ? 1 : 0, st));
+                if (!split_t && !local_t) note(launch_chol(layers, ids_tr, n_tr, w, out_role, tol2, 1, 0, kGramRows1, chol_gate, a2gate, small ? 1 : 0, st));
             }
         }
     }
@@ -716,11 +712,11 @@ struct Launcher {
         // factorisation itself; otherwise the second factorisation is a launch of its own
         const bool small = w <= 16;
         // (inside the iteration only products read the result: no outer-product copies)
-        const int wh = (gate >= 0 ? PACK_TRANSPOSED : (PACK_OUTER | PACK_TRANSPOSED | (kept_packs ? 4 : 0))) | (half ? PACK_HALF : 0);
+        const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_OUTER | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), g, -2, 0, 0, st));
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), g, -2, 0, st));
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
         }
     }
@@ -733,7 +729,7 @@ struct Launcher {
         const int blocks = (max_lenP() + 127) / 128;
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZP, cp, -1, 1, st));
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, kGramRows1, -1, 1, st));
-        note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -2, 0, 0, st));
+        note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -2, 0, st));
         for (int role : {ROLE_ZP, ROLE_ZQ})
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, st));
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZQ, cp, -1, 1, st));
@@ -746,9 +742,9 @@ struct Launcher {
         note(launch_thin_gram(layers, ids_all, n_all, blocks, out_role, cp, -1, 0, st));
         const bool wide = sums_first(w, max_len());
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, kGramRows1, -1, 0, st));
-        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, 0, st));
+        if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
-        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), -1, -2, 0, 0, st));
+        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
     // 32-row blocks per workgroup of the outer-product kernels and the grid that goes with them.  Four blocks, one per wave, and the
@@ -826,15 +822,6 @@ double tol2_of(const psgd_ctx* c) {
     return t * t;
 }
 
-// Whether the products on an M that is formed run on fp16 operands (see HalfOperands): where three bf16 planes would take six plane
-// products, at the widths whose products the matrix cores bound, and where these are most of a call.  us, three planes and fp16:
-// refreshes of two 1B-shaped fp32 blocks (97 million elements) r = 64 3339 and 2899, four of hidden size 1024 (51 million) r = 56 2330 and 2169, 4096 x 4096
-// (17 million) r = 72 1151 and 1130, 1000 x 3001 734 and 745; steps of 8192 x 8192 r = 128 600 and 571, of 1111 x 777 143 and 146.  The
-// largest |M| has to be known: found by the forming pass of the same call, or by a pass over the M of psgd_refresh;
-// not in psgd_compress_finish, whose caller may have replaced M since.
-constexpr int64_t kHalfElements = (int64_t)8 << 20;
-bool half_products(const psgd_ctx* c, int cp) { return c->planes == 3 && cp >= 96 && c->elements >= kHalfElements; }
-
 // Most iterations a layer's refresh runs
 int iteration_budget(const psgd_ctx* c) { return c->opt.refresh_iters > 0 ? c->opt.refresh_iters : 16; }
 
@@ -851,9 +838,7 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     if (tiny) L.note(launch_tiny_iterate(L.layers, L.ids_all, L.n_all, ctx->tiny_lds, tol2, iters, warm ? 1 : 0, ctx->opt.seed, L.st));
     if (!tiny) L.note(launch_init_block(L.layers, L.ids_all, L.n_all, L.max_len(), wz, ROLE_ZQ, ROLE_Q, warm ? 1 : 0,
                              ctx->opt.seed, L.st));
-    L.half = half_products(ctx, cpz);
-    if (L.half && !form_first) L.note(launch_max_m(L.layers, L.ids_all, L.n_all, L.max_rows, L.st));
-    if (!tiny) L.pack(ROLE_ZQ, cpz, Launcher::PACK_TRANSPOSED | (L.half && !form_first ? Launcher::PACK_HALF : 0));
+    if (!tiny) L.pack(ROLE_ZQ, cpz, Launcher::PACK_TRANSPOSED);
     for (int it = 0; it < n_launch && !tiny; ++it) {
         // every layer runs its own number of iterations (decided on the device from the Ritz values of
         // its previous refresh); launches past that number find their gate closed and exit at once
@@ -867,7 +852,6 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
         L.prod_orth(false, false, nbz, ROLE_ZQ, wz, tol2, cpz, 1, Launcher::PASS2_NEVER, it >= kOrthYIterations);
     }
     L.gate = -1;
-    L.half = false;
     // Rayleigh-Ritz on H = Y^T Y (its partial Gram matrices are the last product's)
     const bool wide = wz > kWideWidth;
     if (wide) L.note(launch_gram_sum(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, L.gram_rows_n, L.gram_rows_t, -1, 0, L.st));
@@ -916,7 +900,6 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
         p.m = (int)(d.rows >= d.cols ? d.rows : d.cols);
         p.n = (int)(d.rows >= d.cols ? d.cols : d.rows);
         (p.transposed ? c->lists.tr : c->lists.norm).push_back(l);
-        c->elements += d.rows * d.cols;
         if (d.r > rmax) rmax = d.r;
     }
     // launch order: the largest layers first (a launch ends with its shortest-lived workgroups)
@@ -1139,7 +1122,6 @@ int psgd_compress(psgd_ctx* ctx, void* workspace, void* stream, const void* cons
     const bool re = ctx->reform_m;
     const int K = ctx->opt.power_iters > 0 ? ctx->opt.power_iters : 1;
     L.kept_packs = ctx->lazy;
-    L.half = K == 1 && !re && half_products(ctx, cp);
     for (int k = 0; k < K; ++k) {
         L.keep_e = re;
         L.lazy_form = ctx->pending;            // E of the row-major layers is M_{t-1} - (kept P~)(kept Q)^T

@@ -11,8 +11,7 @@
 // Arithmetic: M and X are split into two or three bf16 planes each (x = p0 + p1 (+ p2), each plane the
 // rounded remainder of the ones before: 16 or 24 mantissa bits) and the product is accumulated in
 // fp32 from the plane products with plane-index sum <= 1 (three products) or <= 2 (six), smallest
-// first, with v_mfma_f32_32x32x16_bf16.  Wide products that only read M may take two fp16 planes of scaled operands in place of
-// three bf16 ones (HalfOperands): three plane products, 24 bits.
+// first, with v_mfma_f32_32x32x16_bf16.
 // The S tile goes global -> registers (coalesced 16-byte loads, summed over workers) -> LDS in the
 // k-contiguous layout the MFMA A operand wants; the thin operand arrives pre-split and transposed.
 #include <algorithm>
@@ -217,7 +216,7 @@ __device__ inline void store_m8(const LayerDev& L, const TileAddr& a, const floa
 template <int ROWS, int NT = kThreads>
 __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int out_side, int ob, int out_len,
                                      int out_lenP, int cp, int epi, const float* otile, int tw, bool kept = false,
-                                     int copies = 3, double* red = nullptr, bool half = false) {
+                                     int copies = 3, double* red = nullptr) {
     const int t = threadIdx.x;
     const int w = T.width;
     if (copies != 2) {
@@ -242,12 +241,6 @@ __device__ inline void tile_epilogue(const LayerDev& L, const ThinRef& T, int ou
     }
     if (epi == EPI_GRAM) {
         gram_tile_f64<NT>(otile, tw, ROWS, w, L.gram + (int64_t)ob * ((w * (w + 1)) / 2), red);
-    } else if (epi == EPI_PACK && half) {
-        // (Y = M^T Z of the subspace iteration, copies = 2; Z carries the scales in eval)
-        const float top = *HalfOperands::max_m(L);
-        const PSGD_GLOBAL double* scale = as_global(L.eval);
-        write_half<NT>(L, out_side, otile, tw, cp, ob * ROWS, ROWS,
-                       [=](int c) { return HalfOperands::of_product(top, max(L.rows, L.cols), c < w ? scale[c] : 1.0); });
     } else if (epi == EPI_PACK) {
         write_packs<0, NT>(L.pack[out_side], L.planes, otile, tw, cp, ob * ROWS, ROWS, out_lenP, copies, kept ? L.lzf[out_side] : nullptr);
     }
@@ -405,8 +398,6 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
                 bq[i][k] = *reinterpret_cast<const PSGD_GLOBAL uintx4*>(as_global(XK.t[k]) + goff);
         }
     };
-    constexpr bool TOP = FORM && PL == 3 && NB >= 3;             // (contexts whose products on M run on fp16 operands)
-    float top = 0.f;
     floatx4 d[LAZY ? 2 : 1][4];
     auto corr_to_lds = [&]() {
 #pragma unroll
@@ -517,10 +508,6 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
             float4 m[8];
             tile_finish<FORM, (NB <= 2 && !LAZY), ONEW>(L, a, inv_n, p0, p1, m);
             if (store_m) store_m8(L, a, m);
-            if constexpr (TOP) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) top = fmaxf(top, fmaxf(fmaxf(fabsf(m[u].x), fabsf(m[u].y)), fmaxf(fabsf(m[u].z), fabsf(m[u].w))));
-            }
             if (!COLMODE) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
@@ -632,13 +619,6 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
         if (LAZY && it + 1 < n_loc) corr_mfma();
         __syncthreads();
     }
-    if constexpr (TOP) {
-        if (epi_flags & EPI_MAX) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-            if (lane == 0) HalfOperands::wave_max(L)[4 * tile + wv] = top;
-        }
-    }
     const int out_lenP = side_lenP(L, out_side);
     const ThinRef T = L.thin[out_role];
     if (n_split > 1) {
@@ -681,9 +661,6 @@ __global__ __launch_bounds__(kThreads, (prod_lds_elems<NB, PL>(LAZY) * 4 <= 160 
 // are in fragment order, so a fragment is 1 KB of consecutive memory on both sides).  Eight waves: the halves h take 32 of a
 // chunk's 64 reduction steps each, one barrier per chunk, and add their sums at the end (half as long: error of E against 64
 // bits 3.1e-5 -> 2.2e-5 in a refresh of 8192 x 8192 fp32 r = 128); the two waves of a SIMD multiply and split in turn.
-// HALF: the operands are two fp16 planes (HalfOperands; PL = 2), three products in place of six and two thirds of the thin operand's
-// bytes: 8192 x 8192 width 160 118 -> 77 us (50 of it M alone, 12 the thin operand), and fewer roundings: the error above 2.2e-5 -> 1.9e-5.  (Waves of 64 rows and
-// a quarter of the steps, half the LDS reads of the thin operand: 83 us.)
 // Per launch, prod_kernel and this: 8192 x 8192 width 160, three planes, 163 -> 121 us either way (1.06 PFLOP/s of plane products; a
 // library product of 8192^3 in bf16 reaches 1.2), 7B-shaped block width 96, two planes, rows 241 -> 203 us and
 // columns (col_prod_kernel) 223 -> 181, of which 20 to 40 is the non-temporal hint.  With M straight to registers 127 to 130 and 288: a load of 32 rows takes 16 bytes of each, and the lines are fetched again.  Not below
@@ -693,12 +670,12 @@ constexpr int kWideProd = 3;
 template <int NB, int PL> constexpr int wide_operand_elems() { return PL * (BK / 16) * NB * 512; }      // one chunk of the thin operand
 // chunks of M in LDS: two where they fit a compute unit's 160 KB, and where one workgroup per compute unit is all there is
 constexpr int kWideTile = BT * BK * 4;
-template <int NB, int PL, bool HALF> constexpr int wide_stages() {
+template <int NB, int PL> constexpr int wide_stages() {
     const int operand = 2 * 2 * wide_operand_elems<NB, PL>();
-    return operand + kWideTile <= 80 * 1024 && !HALF ? 1 : operand + 2 * kWideTile <= 160 * 1024 ? 2 : 1;
+    return operand + kWideTile <= 80 * 1024 ? 1 : operand + 2 * kWideTile <= 160 * 1024 ? 2 : 1;
 }
-template <int NB, int PL, bool HALF> constexpr size_t wide_lds_bytes() {
-    return std::max((size_t)(2 * 2 * wide_operand_elems<NB, PL>() + wide_stages<NB, PL, HALF>() * kWideTile), (size_t)BT * (32 * NB + 1) * sizeof(float));
+template <int NB, int PL> constexpr size_t wide_lds_bytes() {
+    return std::max((size_t)(2 * 2 * wide_operand_elems<NB, PL>() + wide_stages<NB, PL>() * kWideTile), (size_t)BT * (32 * NB + 1) * sizeof(float));
 }
 
 #define PSGD_LDS __attribute__((address_space(3)))
@@ -733,7 +710,7 @@ __device__ __forceinline__ void wide_load_a(const PSGD_GLOBAL float* S, int64_t 
     }
 }
 
-template <int NB, int PL, bool COLMODE, bool HALF>
+template <int NB, int PL, bool COLMODE>
 __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids,
                                                                     int cp, int out_role, int epi_flags, int gate, int nt_s) {
     const LayerDev& L = layers[ids[blockIdx.y]];
@@ -757,13 +734,12 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
     auto chunk_at = [&](int it) { const int c = it + rot; return ch0 + (c >= n_loc ? c - n_loc : c); };
 
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int BUF = wide_operand_elems<NB, PL>(), BPL = BUF / PL, STAGES = wide_stages<NB, PL, HALF>();
+    constexpr int BUF = wide_operand_elems<NB, PL>(), BPL = BUF / PL, STAGES = wide_stages<NB, PL>();
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rg = wv & 3, h = wv >> 2;
     const int li = lane & 31, lg = lane >> 5;
 
     const PackRef& X = L.pack[COLMODE ? SIDE_L : SIDE_W];
-    const float top = HALF ? *HalfOperands::max_m(L) : 0.f, scale_m = HALF ? ldexpf(1.0f, HalfOperands::of_m(top)) : 1.0f;
     PSGD_LDS bf16_t* const b_lds = (PSGD_LDS bf16_t*)smem;   // two buffers of PL planes of [BK / 16][NB] fragments
     const PSGD_GLOBAL bf16_t* const xt[3] = {as_global(X.t[0]), as_global(X.t[1]), as_global(X.t[PL - 1])};
     const PSGD_GLOBAL float* const S = as_global(L.S);
@@ -827,42 +803,32 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
             asm volatile("" ::: "memory");
             if (it + STAGES < n_loc) load_a(it + STAGES);
         }
-        using Frag = std::conditional_t<HALF, halfx8, bf16x8>;
-        Frag av[2][PL];
+        bf16x8 av[2][PL];
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if constexpr (HALF) {
-                    _Float16 q[2];
-                    split_half(x[s][u] * scale_m, q[0], q[1]);
-                    av[s][0][u] = q[0];
-                    av[s][1][u] = q[1];
-                } else {
-                    bf16_t q[PL];
-                    split_planes<PL>(x[s][u], q);
+                bf16_t q[PL];
+                split_planes<PL>(x[s][u], q);
 #pragma unroll
-                    for (int k = 0; k < PL; ++k) av[s][k][u] = q[k];
-                }
+                for (int k = 0; k < PL; ++k) av[s][k][u] = q[k];
             }
         const PSGD_LDS bf16_t* bb = b_lds + (it & 1) * BUF + 2 * h * NB * 512 + lane * 8;
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                Frag bv[PL];
+                bf16x8 bv[PL];
 #pragma unroll
-                for (int k = 0; k < PL; ++k) bv[k] = *reinterpret_cast<const PSGD_LDS Frag*>(bb + k * BPL + (s * NB + nb) * 512);
+                for (int k = 0; k < PL; ++k) bv[k] = *reinterpret_cast<const PSGD_LDS bf16x8*>(bb + k * BPL + (s * NB + nb) * 512);
                 // smallest products first
 #pragma unroll
                 for (int sum = 2 * (PL - 1); sum >= 0; --sum)
 #pragma unroll
                     for (int ka = 0; ka < PL; ++ka) {
                         const int kb = sum - ka;
-                        if (kb >= 0 && kb < PL && keep_term<PL>(ka, kb)) {
-                            if constexpr (HALF) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s][ka], bv[kb], acc[nb], 0, 0, 0);
-                            else acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[s][ka], bv[kb], acc[nb], 0, 0, 0);
-                        }
+                        if (kb >= 0 && kb < PL && keep_term<PL>(ka, kb))
+                            acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[s][ka], bv[kb], acc[nb], 0, 0, 0);
                     }
             }
     }
@@ -886,11 +852,6 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
                 const floatx4 o = ex[((nb * 4 + rg) * 4 + vq) * 64 + lane];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) acc[nb][4 * vq + u] += o[u];
-            }
-            if constexpr (HALF) {
-                const int ex = -(HalfOperands::of_m(top) + HalfOperands::exponents(L, COLMODE ? SIDE_L : SIDE_W)[32 * nb + li]);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[nb][v] = ldexpf(acc[nb][v], ex);
             }
         }
     const int out_lenP = side_lenP(L, out_side);
@@ -921,8 +882,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
             for (int v = 0; v < 16; ++v) otile[(32 * rg + 8 * (v >> 2) + 4 * lg + (v & 3)) * tw + 32 * nb + li] = acc[nb][v];
         }
     __syncthreads();
-    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, nullptr,
-                                    HALF && (epi_flags & EPI_HALF));
+    tile_epilogue<BT, kWideThreads>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies);
 }
 
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
@@ -1016,8 +976,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__
     }
     __syncthreads();
     double* red = FB == BT && T.width <= 16 ? reinterpret_cast<double*>(smem + (((size_t)FB * tw * sizeof(float) + 7) & ~(size_t)7)) : nullptr;
-    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red,
-                          FB != BT && (epi_flags & EPI_HALF));
+    tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red);
     // (FB = 64 is for widths whose factorisation is a launch of its own)
     if constexpr (FB == BT) {
         if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && (!ITER || gate_open(L, chol_gate))) {
@@ -1026,42 +985,6 @@ __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__
                 chol_body(L, out_role, tol2, 1, FB, allow2_of(L, a2gate), smem, L.tmat, true, nullptr, ITER ? iteration_notes(L, out_role, chol_gate) : 0, nullptr, chol_gate & 0xff);
         }
     }
-}
-
-// The largest |M| of a layer whose M the library has not formed, for products on fp16 operands: one number per workgroup, and of these
-// the largest.
-__global__ __launch_bounds__(kThreads) void max_m_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids) {
-    const LayerDev& L = layers[ids[blockIdx.y]];
-    __shared__ float red[4];
-    const int t = threadIdx.x, rows = L.rows, cols = L.cols, quads = (cols + 3) / 4;
-    const PSGD_GLOBAL float* S = as_global(L.S);
-    float top = 0.f;
-    for (int r = blockIdx.x; r < rows; r += gridDim.x)
-        for (int q = t; q < quads; q += kThreads) {
-            const float4 x = ld_f32x4(S + (int64_t)r * L.ld + 4 * q);
-            const int left = cols - 4 * q;
-            top = fmaxf(top, fmaxf(fmaxf(fabsf(x.x), left > 1 ? fabsf(x.y) : 0.f), fmaxf(left > 2 ? fabsf(x.z) : 0.f, left > 3 ? fabsf(x.w) : 0.f)));
-        }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-    if ((t & 63) == 0) red[t >> 6] = top;
-    __syncthreads();
-    if (t == 0) HalfOperands::wave_max(L)[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-__global__ __launch_bounds__(64) void max_of_kernel(const LayerDev* __restrict__ layers, const int* __restrict__ ids, int n) {
-    const LayerDev& L = layers[ids[blockIdx.y]];
-    float top = 0.f;
-    for (int i = threadIdx.x; i < n; i += 64) top = fmaxf(top, HalfOperands::wave_max(L)[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-    if (threadIdx.x == 0) *HalfOperands::max_m(L) = top;
-}
-hipError_t launch_max_m(const LayerDev* layers, const int* ids, int n_ids, int max_rows, hipStream_t st) {
-    if (n_ids <= 0) return hipSuccess;
-    const int n = max_rows < 512 ? max_rows : 512;         // (there is room for 4 per row of the longer side)
-    hipLaunchKernelGGL(max_m_kernel, dim3(n, n_ids), dim3(kThreads), 0, st, layers, ids);
-    hipLaunchKernelGGL(max_of_kernel, dim3(1, n_ids), dim3(64), 0, st, layers, ids, n);
-    return hipGetLastError();
 }
 
 // Partial Gram matrices of a thin matrix that did not come out of one of these products (the averaged P of a
@@ -1144,7 +1067,7 @@ size_t prod_lds_bytes(int nb, int planes, bool lazy = false) {
 }
 
 template <int NB, int PL>
-static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, bool half, const LayerDev* layers, const int* ids,
+static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers, const int* ids,
                             int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st) {
     if (n_ids <= 0 || max_tiles <= 0) return hipSuccess;
     dim3 grid(max_tiles, n_ids), block(kThreads);
@@ -1174,19 +1097,9 @@ static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, bool 
         }
     } else if (form && onew) { if (colmode) PSGD_LAUNCH(true, true, false, true); else PSGD_LAUNCH(false, true, false, true); }
     else if (form) { if (colmode) PSGD_LAUNCH(true, true); else PSGD_LAUNCH(false, true); }
-    else if (NB >= kWideProd && PL == 3 && half) {
-        if constexpr (NB >= kWideProd && PL == 3) {
-            constexpr size_t bytes = wide_lds_bytes<NB, 2, true>();
-            auto kfn = colmode ? wide_prod_kernel<NB, 2, true, true> : wide_prod_kernel<NB, 2, false, true>;
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(kfn, grid, dim3(kWideThreads), bytes, st, layers, ids, cp, out_role, epi, gate, nt_s);
-        }
-    } else if (half) {
-        return hipErrorInvalidValue;
-    } else if constexpr (NB >= kWideProd && wide_lds_bytes<NB, PL, false>() <= 160 * 1024) {
-        constexpr size_t bytes = wide_lds_bytes<NB, PL, false>();
-        auto kfn = colmode ? wide_prod_kernel<NB, PL, true, false> : wide_prod_kernel<NB, PL, false, false>;
+    else if constexpr (NB >= kWideProd && wide_lds_bytes<NB, PL>() <= 160 * 1024) {
+        constexpr size_t bytes = wide_lds_bytes<NB, PL>();
+        auto kfn = colmode ? wide_prod_kernel<NB, PL, true> : wide_prod_kernel<NB, PL, false>;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kfn, grid, dim3(kWideThreads), bytes, st, layers, ids, cp, out_role, epi, gate, nt_s);
@@ -1200,13 +1113,12 @@ static hipError_t launch_nb(bool colmode, bool form, bool lazy, bool onew, bool 
 // lazy: the forming pass also applies the pending rank-r correction (row mode, form, nb <= 4).
 // onew: every layer of the launch has one worker (forming passes only; ignored otherwise).
 // nt_s: read M with the non-temporal hint (products from width 96 on that only read it)
-// half: a product that only reads M takes fp16 operands (see HalfOperands; three planes, width 96 and more)
-hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, bool half, const LayerDev* layers,
+hipError_t launch_prod(int nb, int planes, bool colmode, bool form, bool lazy, bool onew, const LayerDev* layers,
                        const int* ids, int n_ids, int max_tiles, int out_role, int epi, int gate, int nt_s, hipStream_t st) {
 #define PSGD_CASE(N)                                                                                          \
     case N:                                                                                                   \
-        return planes == 2 ? launch_nb<N, 2>(colmode, form, lazy, onew, half, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st) \
-                           : launch_nb<N, 3>(colmode, form, lazy, onew, half, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st);
+        return planes == 2 ? launch_nb<N, 2>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st) \
+                           : launch_nb<N, 3>(colmode, form, lazy, onew, layers, ids, n_ids, max_tiles, out_role, epi, gate, nt_s, st);
     switch (nb) {
         PSGD_CASE(1) PSGD_CASE(2) PSGD_CASE(3) PSGD_CASE(4) PSGD_CASE(5) PSGD_CASE(6)
         default: return hipErrorInvalidValue;

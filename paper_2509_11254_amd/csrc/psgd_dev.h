@@ -15,7 +15,6 @@ namespace psgd {
 typedef __bf16 bf16_t;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
@@ -76,9 +75,7 @@ enum Epilogue { EPI_NONE = 0, EPI_GRAM = 1, EPI_PACK = 2, EPI_KIND_MASK = 3,
                 EPI_ITERATE = 3,     // Y = M^T Z of the subspace iteration: EPI_GRAM in a layer's last iteration and where Y
                                      // is orthonormalised, else only the transposed operand copies (see resolve_epilogue)
                 EPI_KEEP_E = 16,     // flag: a FORM pass uses M but leaves E in place (M is formed again later)
-                EPI_KEPT = 32,       // flag: EPI_PACK writes the kept copies in place of the working ones (PackRef::n)
-                EPI_HALF = 64,       // flag: transposed copies (PackRef::t) in fp16, see HalfOperands
-                EPI_MAX = 128 };     // flag: a FORM pass notes the largest |M| of each of its waves
+                EPI_KEPT = 32 };     // flag: EPI_PACK writes the kept copies in place of the working ones (PackRef::n)
 enum Role { ROLE_P = 0, ROLE_Q = 1, ROLE_ZP = 2, ROLE_ZQ = 3, ROLE_COUNT = 4 };
 
 struct ThinRef {
@@ -245,67 +242,6 @@ __device__ inline void write_packs(const PackRef& K, int planes, const float* ti
 #pragma unroll
         for (int k = 0; k < NPL; ++k)
             if (k < planes) *reinterpret_cast<PSGD_GLOBAL bf16x8*>(dt[k] + off) = o[k];
-    }
-}
-
-// Operands of a product in fp16.  Two fp16 planes of a number scaled by a power of two, each the rounded remainder of the one before,
-// hold 24 bits of it, as three bf16 planes do, and a product then takes three plane products, not six; what fp16 lacks is
-// range.  M is scaled so that its largest element is just below 2^15, a column of a thin matrix by the largest power of two for which that
-// is certain of every element, and the result by the inverse of both: exact but for elements below 2^-29 of these bounds, which
-// lose relative, not absolute accuracy: 2^-40 of the bound, where fp32 sums over them lose 2^-24.  (Scales that are exact powers of two,
-// from the largest |M|: nothing is read twice for them.)  The bounds of a column are 1 where the columns are orthonormal, and |M| sqrt(m) times the column's
-// scale in Y = M^T Z (Cauchy-Schwarz).  The exponents of a side's copies, and on P's side the largest |M| and what it is found from,
-// lie where the third bf16 plane of the transposed copies would be.
-struct HalfOperands {
-    static constexpr int kTop = 15, kMaxAt = 192;          // ints before the largest |M| (as many as a block has columns at most)
-    __device__ static PSGD_GLOBAL int* exponents(const LayerDev& L, int side) { return reinterpret_cast<PSGD_GLOBAL int*>(as_global(L.pack[side].t[2])); }
-    __device__ static PSGD_GLOBAL float* max_m(const LayerDev& L) {
-        return reinterpret_cast<PSGD_GLOBAL float*>(exponents(L, side_of_role(L.transposed, ROLE_P)) + kMaxAt);
-    }
-    __device__ static PSGD_GLOBAL float* wave_max(const LayerDev& L) { return max_m(L) + 4; }
-    // waves that note a maximum in a forming pass of prod_kernel
-    __device__ static int waves(const LayerDev& L) {
-        const int out_len = L.transposed ? L.cols : L.rows;
-        return 4 * ((out_len + 127) / 128) * L.split[SPLIT_FORM][L.transposed];
-    }
-    // exponent of the power of two that M is multiplied by
-    __device__ static int of_m(float max_m) { return max(-126, min(126, kTop - __builtin_amdgcn_frexp_expf(max_m))); }
-    // ... a column of a matrix with orthonormal columns that carries the power of two `scale`
-    __device__ static int of_orthonormal(double scale) { return kTop - __builtin_amdgcn_frexp_exp(scale); }
-    // ... the same column of M^T of that matrix; m: length of the columns of M
-    __device__ static int of_product(float max_m, int m, double scale) {
-        const int log_m = 32 - __clz(m - 1);               // (rounded up; m >= 1)
-        return kTop - (__builtin_amdgcn_frexp_expf(max_m) + (log_m + 1) / 2 + __builtin_amdgcn_frexp_exp(scale) - 1);
-    }
-};
-__device__ inline void split_half(float x, _Float16& h, _Float16& l) {
-    h = (_Float16)x;
-    l = (_Float16)(x - (float)h);
-}
-// Transposed operand copies of `nrows` finished rows in fp16 (as write_packs, the other copies apart); exponent(c): of column c.
-template <int NT, class Exponent>
-__device__ inline void write_half(const LayerDev& L, int side, const float* tile, int tw, int cp, int row0, int nrows, Exponent&& exponent) {
-    PSGD_GLOBAL bf16_t* const d0 = as_global(L.pack[side].t[0]);
-    PSGD_GLOBAL bf16_t* const d1 = as_global(L.pack[side].t[1]);
-    const int t = threadIdx.x;
-    if (row0 == 0)
-        for (int c = t; c < cp; c += NT) HalfOperands::exponents(L, side)[c] = exponent(c);
-    for (int v = t; v < cp * (nrows / 8); v += NT) {
-        const int ln = v & 63, frag = v >> 6;
-        int k16, nb;
-        divmod_small(frag, cp >> 5, k16, nb);
-        const int c = 32 * nb + (ln & 31), ib = 16 * k16 + 8 * (ln >> 5), ex = exponent(c);
-        halfx8 h, l;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            _Float16 a, b;
-            split_half(ldexpf(tile[(ib + u) * tw + c], ex), a, b);
-            h[u] = a;
-            l[u] = b;
-        }
-        const int64_t off = pack_t_offset(row0 + ib, c, cp);
-        *reinterpret_cast<PSGD_GLOBAL halfx8*>(d0 + off) = h;
-        *reinterpret_cast<PSGD_GLOBAL halfx8*>(d1 + off) = l;
     }
 }
 

@@ -13,7 +13,6 @@ namespace psgd {
 // --------------------------------------------------------------------------------------------
 // grid.z walks the roles to pack (role_a, then role_b when two are asked for); which: 1 = outer-product copies (what
 // the outer-product kernels read), 2 = transposed copies (what the products read), 3 = both
-// (+ 8: the transposed ones in fp16, of numbers in [-1, 1])
 __global__ __launch_bounds__(kThreads) void pack_kernel(const LayerDev* __restrict__ layers,
                                                         const int* __restrict__ ids, int role_a, int role_b,
                                                         int cp, int which) {
@@ -44,21 +43,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const LayerDev* __restri
         }
     }
     __syncthreads();
-    if (which & 8) write_half<kThreads>(L, side, tile, tw, cp, i0, 64, [](int) { return HalfOperands::of_orthonormal(1.0); });
-    else write_packs(L.pack[side], L.planes, tile, tw, cp, i0, 64, lenP, which);
-}
-
-// Operand copies of rows of an orthonormalised matrix (apply kernels; `which` as for launch_apply).
-template <int NT, int ROWS>
-__device__ __forceinline__ void write_copies(const LayerDev& L, int role, int side, const float* so, int ow, int cp, int i0, int lenP, int which, int gate) {
-    if (which & 8) {
-        const bool scaled = scales_next(L, role, gate);
-        const int w = L.thin[role].width;
-        const PSGD_GLOBAL double* scale = as_global(L.eval);
-        write_half<NT>(L, side, so, ow, cp, i0, ROWS, [=](int c) { return HalfOperands::of_orthonormal(scaled && c < w ? scale[c] : 1.0); });
-        which &= ~2;
-    }
-    if (which & 3) write_packs<0, NT>(L.pack[side], L.planes, so, ow, cp, i0, ROWS, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
+    write_packs(L.pack[side], L.planes, tile, tw, cp, i0, 64, lenP, which);
 }
 
 // role_b < 0: one role
@@ -103,21 +88,12 @@ template <int NT>
 __global__ __launch_bounds__(NT) void chol_kernel(const LayerDev* __restrict__ layers,
                                                   const int* __restrict__ ids, int role, double tol2,
                                                   int pass, int slot_rows_n, int slot_rows_t, int gate, int a2gate,
-                                                  int local_ok, int find_max) {
+                                                  int local_ok) {
     const LayerDev& L = layers[ids[blockIdx.y]];
     if (!gate_open(L, gate)) return;
     if (pass == 2 && L.status[1] == 0) return;
     if (pass == 1 && local_chol(L, role, local_ok)) return;       // the apply kernel factorises for itself
     extern __shared__ __align__(16) unsigned char smem[];
-    if (find_max && threadIdx.x >= NT - 64) {
-        // (the largest |M| of the forming pass before, by the last wave, whose first loads these are)
-        float top = 0.f;
-        const int n = HalfOperands::waves(L);
-        for (int i = threadIdx.x & 63; i < n; i += 64) top = fmaxf(top, HalfOperands::wave_max(L)[i]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-        if ((threadIdx.x & 63) == 0) *HalfOperands::max_m(L) = top;
-    }
     chol_body(L, role, tol2, pass, L.transposed ? slot_rows_t : slot_rows_n, allow2_of(L, a2gate), smem, L.tmat, true, nullptr,
               pass == 1 ? iteration_notes(L, role, gate) : 0, nullptr, gate & 0xff);
 }
@@ -171,7 +147,7 @@ hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, in
 // Widths above 32 get 512 threads: the panels and trailing updates of the blocked factorisation are dealt to the waves
 // (1024 threads halve the registers a thread may hold, and measured slower).
 hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w, int role, double tol2, int pass,
-                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, int find_max, hipStream_t st) {
+                       int slot_rows_n, int slot_rows_t, int gate, int a2gate, int local_ok, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     const bool wide = w > 32;
     dim3 grid(1, n_ids), block(wide ? 512 : kThreads);
@@ -183,7 +159,7 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kfn, grid, block, lds, st, layers, ids, role, tol2, pass, slot_rows_n, slot_rows_t, gate, a2gate,
-                       local_ok, find_max);
+                       local_ok);
     return hipGetLastError();
 }
 
@@ -540,7 +516,7 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
             }
         }
         if (do_gram) gram_tile_f64(so, ow, kGramRows2, w_out, L.gram + (int64_t)tile * ((w_out * (w_out + 1)) / 2));
-        else if (do_pack) write_copies<kThreads, kGramRows2>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
+        else if (do_pack) write_packs(L.pack[side], L.planes, so, ow, cp, i0, kGramRows2, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
         __syncthreads();
     }
 }
@@ -628,7 +604,7 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
         for (int c = lane; c < w_out; c += 64) yr[c] = so[i * ow + c];
     }
     if (do_gram) gram_tile_f64(so, ow, ROWS, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
-    else if (do_pack) write_copies<kApplyWideThreads, ROWS>(L, src_role, side, so, ow, cp, i0, lenP, which, gate);
+    else if (do_pack) write_packs<0, kApplyWideThreads>(L.pack[side], L.planes, so, ow, cp, i0, ROWS, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
 }
 
 // Rows per workgroup, and per partial Gram matrix of its result, of a launch at widths up to w_in.  apply_wide_kernel: 32 where 64
@@ -644,7 +620,7 @@ int apply_rows(int max_lenP, int n_ids, int w_in) {
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
 // (the others: 128)
 // which: operand copies to leave when cp > 0 (1 = outer-product, 2 = transposed, 3 = both; + 4: the outer-product ones are
-// the layer's kept copies where it has them -- the P~ of a compress step with a deferred residual; + 8: the transposed ones in fp16)
+// the layer's kept copies where it has them -- the P~ of a compress step with a deferred residual)
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, int slot_rows, hipStream_t st) {

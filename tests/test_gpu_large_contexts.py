@@ -1,6 +1,7 @@
-"""Products on fp16 operands (fp32 gradients, widths from 96 on, contexts of many elements): steps, refreshes and psgd_refresh of ragged
-layers of both orientations beside a large one, at magnitudes from 1e-28 to 1e34 and with outliers, against fp64.  (Below, the third bf16 plane of the factors that the residual multiplies, 2^-18 of
-elements of 1e-4 of this, leaves the normal numbers.)"""
+"""Wide products (fp32 gradients, widths from 96 on) in contexts of many elements: steps, refreshes and psgd_refresh of ragged
+layers of both orientations beside a large one, at magnitudes from 1e-28 to 1e34, with outliers and with columns of very different
+size, against fp64.  (Below 1e-28, the third bf16 plane of the factors that the residual multiplies, 2^-18 of elements of 1e-4 of
+this, leaves the normal numbers.)"""
 import pytest
 
 from paper_2509_11254_amd import psgd
@@ -54,7 +55,7 @@ def _check(M, E, Q, P, scale):
         norm = float((m / scale).norm())
         tag = (l, rows, cols)
         assert float((p.T @ p - torch.eye(p.shape[1], device="cuda", dtype=torch.float64)).abs().max()) < 2e-6, tag
-        # fp32 sums of products exact to 2^-24
+        # fp32 sums (row by row and tighter: test_each_row_to_its_own_size)
         assert float(((q - m.T @ p) / scale).norm()) <= 1e-6 * norm, tag
         assert float(((e - (m - p @ q.T)) / scale).norm()) <= 1e-6 * norm, tag
         assert ld == cols or bool(torch.isnan(E[l][:, cols:]).all()), tag
@@ -105,3 +106,61 @@ def test_refresh(r, scale, outliers):
             sv = torch.linalg.svdvals(m / scale)
             left = (m - P[l].double() @ Q[l].double().T) / scale
             assert float((left.norm() ** 2 - (sv[r:] ** 2).sum()).abs()) <= 1e-5 * float((sv ** 2).sum()), l
+
+
+def _uneven(r, n_workers, dtype):
+    """Gradients and E whose columns (of the matrix with the long side first) span 36 binary orders: three quarters of them of one
+    size, the others 2^-8 to 2^-36 of it."""
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r)
+    G, E, Q, P = [], [], [], []
+    for rows, cols, ld in LAYERS:
+        k = min(rows, cols)
+        d = torch.ones(k, device="cuda")
+        d[3::4] = 2.0 ** -(8.0 + 4.0 * (torch.arange(len(d[3::4]), device="cuda") % 8))
+        d = d if rows >= cols else d[:, None]
+        G.append([torch.zeros((rows, ld), device="cuda", dtype=dtype) for _ in range(n_workers)])
+        for g in G[-1]:
+            g[:, :cols] = (torch.randn((rows, cols), generator=gen, device="cuda") * d).to(dtype)
+        e = torch.zeros((rows, ld), device="cuda")
+        e[:, :cols] = 0.01 * torch.randn((rows, cols), generator=gen, device="cuda") * d
+        E.append(e)
+        Q.append(torch.randn((k, r), generator=gen, device="cuda"))
+        P.append(torch.zeros((max(rows, cols), r), device="cuda"))
+    return G, E, Q, P
+
+
+@pytest.mark.parametrize("op", ["compress", "compress_refresh"])
+@pytest.mark.parametrize("n_workers,bf16,opts", [(1, False, {}), (2, False, {}), (1, True, {"precision": 3}),
+                                                 (1, False, {"lazy_residual": True}),
+                                                 (1, False, {"lazy_residual": True, "q_resident": True})])
+@pytest.mark.parametrize("r", [70, 128])
+def test_each_row_to_its_own_size(r, n_workers, bf16, opts, op):
+    """Three planes hold every element of M to 2^-24 of itself, however small it is beside the largest.  So each row of
+    Q = M^T P~ is good to fp32 sums over its own column of M, and so is each column of E: K = 6 len / 16 additions of 2^-24 of
+    at most ||m_j||, as independent roundings, and some for the operands; in a refresh for each of the block's columns."""
+    torch = torch_mod()
+    dtype = torch.bfloat16 if bf16 else torch.float32
+    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_BF16 if bf16 else psgd.PSGD_F32, ld) for rows, cols, ld in LAYERS], n_workers, **opts)
+    G, E, Q, P = _uneven(r, n_workers, dtype)
+    M = []
+    for g, e, (rows, cols, ld) in zip(G, E, LAYERS):
+        m = sum(x[:, :cols].double() for x in g) / n_workers + e[:, :cols].double()
+        M.append(m if rows >= cols else m.T)
+    getattr(comp, op)(G, E, Q, P)
+    if opts.get("lazy_residual"):
+        comp.flush_residual(E)
+    for l, (rows, cols, ld) in enumerate(LAYERS):
+        m, p, q = M[l], P[l].double(), Q[l].double()
+        size = m.norm(dim=0)
+        tag = (l, rows, cols)
+        columns = 1 if op == "compress" else r + max(8, r // 4)
+        bound = 2.0 ** -24 * ((6 * m.shape[0] / 16) ** 0.5 + 4) * columns ** 0.5
+        worst = float(((q - m.T @ p).abs().amax(dim=1) / size).max())
+        assert worst <= bound, (tag, worst, bound)
+        e = E[l][:, :cols].double()
+        e = e if rows >= cols else e.T
+        bound = 2.0 ** -24 * ((6 * r / 16) ** 0.5 + 4)
+        worst = float(((e - (m - p @ q.T)).norm(dim=0) / (size + q.norm(dim=1) * r ** 0.5)).max())
+        assert worst <= bound, (tag, worst, bound)
