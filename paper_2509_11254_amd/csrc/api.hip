@@ -50,7 +50,6 @@ hipError_t launch_chol(const LayerDev* layers, const int* ids, int n_ids, int w,
 hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows_n, int slot_rows_t,
                            int gate, int flagged, hipStream_t st);
 int finish_rows(int w, int max_blocks, int n_ids);
-int apply_rows(int max_lenP, int n_ids, int w_in);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
                         bool small, int which, int slot_rows, hipStream_t st);
@@ -716,7 +715,7 @@ struct Launcher {
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
         if (pass2 == PASS2_ALWAYS) {
-            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), g, -2, 0, st));
+            if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, g, -2, 0, st));
             note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
         }
     }
@@ -744,7 +743,7 @@ struct Launcher {
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, kGramRows1, -1, 0, st));
         if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
-        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, apply_rows(max_lenP(), n_all, w), apply_rows(max_lenP(), n_all, w), -1, -2, 0, st));
+        if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, -1, -2, 0, st));
         note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
     }
     // 32-row blocks per workgroup of the outer-product kernels and the grid that goes with them.  Four blocks, one per wave, and the

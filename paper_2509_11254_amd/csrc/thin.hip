@@ -528,8 +528,10 @@ __global__ __launch_bounds__(kThreads) void apply_stream_kernel(const LayerDev* 
 // group) walks every fourth 16-column tile of the result along the reduction index with the fragments of tmat loaded
 // straight from L2, four steps ahead.
 // --------------------------------------------------------------------------------------------
+// PARTS: a workgroup that leaves a partial Gram matrix takes PARTS tiles of ROWS rows for it, kGramRows2 in all.  The second
+// factorisation is one workgroup, which adds these matrices up: 256 of 32 rows took it 522 us at 8192 x 128, 128 of 64 rows 285.
 constexpr int kApplyWideThreads = 1024;
-template <int ROWS>
+template <int ROWS, int PARTS>
 __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const LayerDev* __restrict__ layers,
                                                                        const int* __restrict__ ids, int src_role,
                                                                        int dst_role, int mode, int cp, int gate, int w_in_max,
@@ -548,6 +550,8 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
     const int len = side_len(L, side), lenP = side_lenP(L, side);
     const int i0 = blockIdx.x * ROWS;
     if (i0 >= (do_pack ? lenP : len)) return;
+    if (PARTS > 1 && do_gram && blockIdx.x % PARTS != 0) return;       // (the workgroup of the first of these rows takes them all)
+    const int parts = PARTS > 1 && do_gram ? PARTS : 1;
     const ThinRef X = L.thin[src_role];
     const ThinRef Y = L.thin[dst_role];
     const int w_in = X.width, w_out = Y.width;
@@ -557,60 +561,69 @@ __global__ __launch_bounds__(kApplyWideThreads) void apply_wide_kernel(const Lay
     const int wo16 = (w_out_max + 15) & ~15, ow = (cp > wo16 ? cp : wo16) + 1;
     extern __shared__ __align__(16) unsigned char smem[];
     float* sx = reinterpret_cast<float*>(smem);            // [ROWS][xs]  x tile, zero beyond the matrix
-    float* so = sx + (size_t)ROWS * xs;              // [ROWS][ow]  result tile, zero beyond w_out
+    float* so = sx + (size_t)ROWS * xs;                    // [PARTS ROWS][ow]  result tile, zero beyond w_out
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
-    for (int i = wv; i < ROWS; i += kApplyWideThreads / 64) {
-        const bool in = i0 + i < len;
-        const PSGD_GLOBAL float* xr = as_global(X.ptr) + (int64_t)(in ? i0 + i : 0) * X.ld;
-        for (int c = lane; c < kpad; c += 64) sx[i * xs + c] = (in && c < w_in) ? xr[c] : 0.f;
-        for (int c = lane; c < ow; c += 64) so[i * ow + c] = 0.f;
-    }
-    __syncthreads();
     constexpr int RG = ROWS / 16, CG = kApplyWideThreads / 64 / RG;
     const int rg = wv % RG, cg = wv / RG;
     const float* __restrict__ xa = sx + (16 * rg + li) * xs + lk;
     const PSGD_GLOBAL double* __restrict__ tm = as_global(L.tmat);
-    for (int ct = cg; ct < n_ct; ct += CG) {
-        const int col = 16 * ct + li;
-        const int kend = upper ? min(kpad, 16 * (ct + 1)) : kpad;
-        const bool col_ok = col < w_in;
-        auto frag = [&](int k) {                           // (k + lk may pass the end: that row counts as zero)
-            const bool ok = col_ok && k + lk < w_in;
-            const double v = tm[ok ? (int64_t)(k + lk) * w_in + col : 0];
-            return ok ? v : 0.0;
-        };
-        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-        double b[4], bn[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = frag(4 * u);
-        for (int k = 0; k < kend; k += 16) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) bn[u] = frag(k + 16 + 4 * u);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xa[k + 4 * u], b[u], acc, 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) b[u] = bn[u];
+    for (int part = 0; part < parts; ++part) {
+        const int p0 = i0 + part * ROWS;
+        float* po = so + (size_t)(part * ROWS) * ow;
+        if (part > 0) __syncthreads();                     // (the x tile has been read)
+        for (int i = wv; i < ROWS; i += kApplyWideThreads / 64) {
+            const bool in = p0 + i < len;
+            const PSGD_GLOBAL float* xr = as_global(X.ptr) + (int64_t)(in ? p0 + i : 0) * X.ld;
+            for (int c = lane; c < kpad; c += 64) sx[i * xs + c] = (in && c < w_in) ? xr[c] : 0.f;
+            for (int c = lane; c < ow; c += 64) po[i * ow + c] = 0.f;
         }
-        if (col < w_out) {
+        __syncthreads();
+        for (int ct = cg; ct < n_ct; ct += CG) {
+            const int col = 16 * ct + li;
+            const int kend = upper ? min(kpad, 16 * (ct + 1)) : kpad;
+            const bool col_ok = col < w_in;
+            auto frag = [&](int k) {                           // (k + lk may pass the end: that row counts as zero)
+                const bool ok = col_ok && k + lk < w_in;
+                const double v = tm[ok ? (int64_t)(k + lk) * w_in + col : 0];
+                return ok ? v : 0.0;
+            };
+            doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+            double b[4], bn[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) so[(16 * rg + 4 * v + lk) * ow + col] = (float)acc[v];
+            for (int u = 0; u < 4; ++u) b[u] = frag(4 * u);
+            for (int k = 0; k < kend; k += 16) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) bn[u] = frag(k + 16 + 4 * u);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xa[k + 4 * u], b[u], acc, 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) b[u] = bn[u];
+            }
+            if (col < w_out) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) po[(16 * rg + 4 * v + lk) * ow + col] = (float)acc[v];
+            }
         }
     }
     __syncthreads();
-    const int rows_valid = min(len, i0 + ROWS) - i0;
+    const int rows_valid = min(len, i0 + parts * ROWS) - i0;
     for (int i = wv; i < rows_valid; i += kApplyWideThreads / 64) {
         PSGD_GLOBAL float* yr = as_global(Y.ptr) + (int64_t)(i0 + i) * Y.ld;
         for (int c = lane; c < w_out; c += 64) yr[c] = so[i * ow + c];
     }
-    if (do_gram) gram_tile_f64(so, ow, ROWS, w_out, L.gram + (int64_t)blockIdx.x * ((w_out * (w_out + 1)) / 2));
+    if (do_gram) gram_tile_f64(so, ow, PARTS * ROWS, w_out, L.gram + (int64_t)(blockIdx.x / PARTS) * ((w_out * (w_out + 1)) / 2));
     else if (do_pack) write_packs<0, kApplyWideThreads>(L.pack[side], L.planes, so, ow, cp, i0, ROWS, lenP, which & 3, (which & 4) ? L.lzf[side] : nullptr);
 }
 
-// Rows per workgroup, and per partial Gram matrix of its result, of a launch at widths up to w_in.  apply_wide_kernel: 32 where 64
-// leave compute units idle (8192 x 160 24 -> 16 us, 8192 x 128 20 -> 14; with more tiles than compute units its reads of tmat are what grows).
-int apply_rows(int max_lenP, int n_ids, int w_in) {
-    return w_in > kApplyStreamMaxWidth && (max_lenP / kGramRows2) * n_ids <= 256 ? 32 : kGramRows2;
+// Rows per workgroup of apply_wide_kernel: 32 where 64 leave compute units idle, up to one workgroup of 64 per unit (kernel, 8192 x 160
+// 24 -> 16 us, 8192 x 128 20 -> 14; step of 4096 x 4096 bf16 r = 128 218 -> 212 us).  With more tiles its reads of tmat are what grows,
+// and what is left is within 1 % either way: 20000 x 2048 r = 100 534 and, on 32 rows, 531 us, refreshes of three 8192 x 4096
+// r = 128 2739 and 2707, of fourteen 2048 x 2048 r = 110 2458 and 2469.  Where the launch may leave Gram matrices, up to half of
+// that: beyond, the workgroups that leave them are more than half the units and twice as long (16384 x 2048 r = 100, 256 tiles: step
+// 346 either way, 663 and 688 where its second pass is asked for).
+static int apply_rows(int max_lenP, int n_ids, int mode) {
+    return (max_lenP / kGramRows2) * n_ids <= (mode == APPLY_PASS1 ? 128 : 256) ? 32 : kGramRows2;
 }
 
 // w_in / w_out: upper bounds of the operand widths over the addressed layers (LDS sizing only)
@@ -652,9 +665,10 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
     }
     if (!small) {
         const int wi16 = (w_in + 15) & ~15, wo16 = (w_out + 15) & ~15;
-        const int rows = apply_rows(max_lenP, n_ids, w_in);
-        const size_t lds = (size_t)rows * (wi16 + 1 + (cp > wo16 ? cp : wo16) + 1) * sizeof(float);
-        auto kfn = rows == 32 ? apply_wide_kernel<32> : apply_wide_kernel<kGramRows2>;
+        const int rows = apply_rows(max_lenP, n_ids, mode), rows_out = mode == APPLY_PASS1 ? kGramRows2 : rows;
+        const size_t lds = ((size_t)rows * (wi16 + 1) + (size_t)rows_out * ((cp > wo16 ? cp : wo16) + 1)) * sizeof(float);
+        auto kfn = rows == kGramRows2 ? apply_wide_kernel<kGramRows2, 1>
+                 : mode == APPLY_PASS1 ? apply_wide_kernel<32, kGramRows2 / 32> : apply_wide_kernel<32, 1>;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -188,7 +188,9 @@ def test_many_partial_gram_matrices(shapes, op, r):
             assert abs(np.sum(e ** 2) - np.sum(np.linalg.svd(ml, compute_uv=False)[r:] ** 2)) <= 1e-4 * nm ** 2, l
 
 
-# results of 17 to 64 blocks of 128 rows, alone: 32 rows per workgroup and partial Gram matrix; one block fewer, and a batch: 64
+# finish_kernel on 32 rows per workgroup and partial Gram matrix: results of 17 to 64 blocks of 128 rows, alone; on 64: one block
+# fewer or more, and a batch of more than 64.  apply_wide_kernel on 32 rows (a partial Gram matrix stands for 64 all the same): up to
+# 128 tiles of 64 rows, 8192 alone the last; on 64: one more, and a batch of more than 128
 @pytest.mark.parametrize("shapes", [[(2049, 300)], [(300, 2176)], [(2048, 300)], [(8192, 200)], [(8193, 200)], [(5000, 260), (260, 5000)]])
 @pytest.mark.parametrize("r", [97, 128])
 def test_second_pass_of_wide_blocks(shapes, r):
