@@ -52,7 +52,7 @@ hipError_t launch_gram_sum(const LayerDev* layers, const int* ids, int n_ids, in
 int finish_rows(int w, int max_blocks, int n_ids);
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
-                        bool small, int which, int slot_rows, hipStream_t st);
+                        bool small, int which, int slot_rows, int stream_wgs, hipStream_t st);
 hipError_t launch_init_block(const LayerDev* layers, const int* ids, int n_ids, int max_len, int w, int dst_role,
                              int src_role, int warm, uint32_t seed, hipStream_t st);
 hipError_t launch_jacobi(const LayerDev* layers, const int* ids, int n_ids, int w, int role, int slot_rows, float* sigma_out,
@@ -139,6 +139,7 @@ struct psgd_ctx {
     void* outs_ws = nullptr;     // workspace that holds the current table of decompress outputs
     void* msgd_ws = nullptr;     // ... and of the momentum and weight buffers of psgd_decompress_msgd / _adam
     void* m2_ws = nullptr;       // ... and of the second-moment buffers of psgd_decompress_adam
+    int stream_wgs[2] = {0, 0};                 // see one_round
     // every layer's step (plain, one power iteration) or refresh runs in one workgroup that holds M in LDS (tiny.hip)
     bool tiny_step = false, tiny_refresh = false;
     size_t tiny_lds = 0;
@@ -592,6 +593,7 @@ struct Launcher {
                               // the kept Q, which the pass then need not read
     bool kept_packs = false;  // compress step with a deferred residual: the outer-product operand copies of its P~ and Q
                               // are the kept ones in the layers that have them
+    int stream_wgs[2] = {0, 0};   // launch_apply on a P-like, a Q-like result
     bool use_xtab = true;     // PSGD_XTAB=0 (environment, measurement knob): plain layer-by-layer launch order
     bool use_xtab_c = true;   // PSGD_XTAB_C=0 (likewise): the same for the column-mode product alone
 
@@ -713,10 +715,10 @@ struct Launcher {
         // (inside the iteration only products read the result: no outer-product copies)
         const int wh = gate >= 0 ? PACK_TRANSPOSED : (PACK_OUTER | PACK_TRANSPOSED | (kept_packs ? 4 : 0));
         prod(p_like, form, nb, out_role, if_asked ? EPI_ITERATE : EPI_GRAM, g, a2, tol2, w, small);
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, pass2 == PASS2_ALWAYS ? APPLY_PASS1 : APPLY_PASS1_ONLY, cp, g, a2, tol2, small, wh, gram_rows_n, stream_wgs[p_like ? 0 : 1], st));
         if (pass2 == PASS2_ALWAYS) {
             if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, g, -2, 0, st));
-            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, st));
+            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, g, a2, tol2, small, wh, 0, stream_wgs[p_like ? 0 : 1], st));
         }
     }
     // The second CholeskyQR pass on Z after the subspace iteration, for the layers whose last factorisation of Z asked for
@@ -730,7 +732,7 @@ struct Launcher {
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZP, kGramRows1, kGramRows1, -1, 1, st));
         note(launch_chol(layers, ids_all, n_all, w, ROLE_ZP, tol2, 2, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -2, 0, st));
         for (int role : {ROLE_ZP, ROLE_ZQ})
-            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, st));
+            note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, role, role, APPLY_PASS2, 0, -1, -2, tol2, w <= 16, 0, 0, stream_wgs[role == ROLE_ZP ? 0 : 1], st));
         note(launch_thin_gram(layers, ids_all, n_all, blocks, ROLE_ZQ, cp, -1, 1, st));
         if (w > kWideWidth) note(launch_gram_sum(layers, ids_all, n_all, w, ROLE_ZQ, kGramRows1, kGramRows1, -1, 1, st));     // (as Jacobi expects them)
     }
@@ -742,9 +744,9 @@ struct Launcher {
         const bool wide = sums_first(w, max_len());
         if (wide) note(launch_gram_sum(layers, ids_all, n_all, w, out_role, kGramRows1, kGramRows1, -1, 0, st));
         if (!small || max_len() > kLocalCholMaxRows) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 1, wide ? kOneSlot : kGramRows1, wide ? kOneSlot : kGramRows1, -1, -1, small ? 1 : 0, st));
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS1, cp, -1, -1, tol2, small, 3, kGramRows1, stream_wgs[0], st));
         if (!small) note(launch_chol(layers, ids_all, n_all, w, out_role, tol2, 2, kGramRows2, kGramRows2, -1, -2, 0, st));
-        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, st));
+        note(launch_apply(layers, ids_all, n_all, max_lenP(), w, w, out_role, out_role, APPLY_PASS2, cp, -1, -1, tol2, small, 3, 0, stream_wgs[0], st));
     }
     // 32-row blocks per workgroup of the outer-product kernels and the grid that goes with them.  Four blocks, one per wave, and the
     // column operand staged for one tile, up to nb * planes = 6.  Wider operands leave a compute unit room for two such
@@ -801,6 +803,31 @@ void geometry(const Plan& p, Launcher& L) {
     }
 }
 
+// Workgroups per layer of a launch of apply_stream_kernel above width 64 on all of `plan` (side: 0 P-like results, 1 Q-like) that make
+// one round of two per compute unit: a workgroup loads 30 KB of the factor's fragments once for several tiles, and no second
+// round runs half empty.  The most that leave the layers together, each of which uses no more than it has tiles, at 512, and the launch at
+// 4096, the others of which find nothing to do.  0, as many as launch_apply takes at any width: up to one and a half rounds of tiles,
+// and above eight.  us per refresh, several rounds and one: 772 tiles (7B-shaped block r = 64) 7860 and 7800, 782 (50000 x 1024 r = 72) 1291 and
+// 1261, 896 (fourteen 4096 x 4096 r = 64) 10510 and 10340, 1600 (a hundred 1024 x 1024 r = 72) 2479 and 2333, 3840 (120 of 512 x 2048
+// r = 68) 3565 and 2724; 768 (twenty-four 2048 x 2048 r = 64) 3044 and 3075, 640 (forty 1024 x 1024 r = 72) 1400 and 1421.  As many
+// for each layer whatever its size: 8192 x 2048 beside thirty 256 x 256 r = 64 3850 and 4250, one such launch then walking 128 tiles with 17.
+int one_round(const std::vector<Plan>& plan, int side) {
+    auto tiles = [side](const Plan& p) { return (int)((side == 0 ? std::max(p.rowsP, p.colsP) : std::min(p.rowsP, p.colsP)) / kGramRows2); };
+    int64_t all = 0;
+    int hi = 1;
+    for (const Plan& p : plan) { all += tiles(p); hi = std::max(hi, tiles(p)); }
+    if (all <= 512 + 256 || all > 8 * 512) return 0;
+    hi = std::min<int>(hi, (8 * 512 + (int)plan.size() - 1) / (int)plan.size());
+    int lo = 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        int64_t wgs = 0;
+        for (const Plan& p : plan) wgs += std::min(tiles(p), mid);
+        if (wgs <= 512) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
 Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
     Launcher L{};
     L.ctx = ctx; L.ws = reinterpret_cast<char*>(workspace); L.st = st;
@@ -811,6 +838,7 @@ Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
     L.ids_all = ids; L.ids_norm = ids + nl; L.ids_tr = ids + 2 * (size_t)nl;
     L.n_all = nl; L.n_norm = (int)ctx->lists.norm.size(); L.n_tr = (int)ctx->lists.tr.size();
     for (const Plan& p : ctx->plan) geometry(p, L);
+    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = ctx->stream_wgs[s];
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab = v == 1; }
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB_C"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab_c = v == 1; }
     return L;
@@ -857,7 +885,7 @@ void refresh_sequence(psgd_ctx* ctx, Launcher& L, bool form_first, bool warm, fl
     if (!tiny) L.second_pass_deferred(wz, cpz, tol2);
     L.note(launch_jacobi(L.layers, L.ids_all, L.n_all, wz, ROLE_ZQ, wide || tiny ? kOneSlot : kGramRows1, sigma_out, L.st));
     L.note(launch_apply(L.layers, L.ids_all, L.n_all, L.max_lenP(), wz, ctx->rmax, ROLE_ZP, ROLE_P, APPLY_RITZ,
-                        final_cp, -1, -2, 0.0, false, 3, 0, L.st));
+                        final_cp, -1, -2, 0.0, false, 3, 0, L.stream_wgs[0], L.st));
     L.prof_mute = false;
 }
 
@@ -956,6 +984,7 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
             c->tiny_lds = std::max(c->tiny_lds, tiny_lds_bytes(p.d.rows, p.d.cols));
         }
         c->lazy_tr = c->lazy && c->cpc == 32;
+        for (int s = 0; s < 2; ++s) c->stream_wgs[s] = one_round(c->plan, s);
     }
     if (rc != PSGD_OK) { delete c; return rc; }
     {
@@ -1358,6 +1387,7 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     L.ids_norm = ids; L.n_norm = p.transposed ? 0 : 1;
     L.ids_tr = ids; L.n_tr = p.transposed ? 1 : 0;
     geometry(one, L);
+    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = one_round({one}, s);
     refresh_sequence(ctx, L, false, false, sigma, 0);
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;

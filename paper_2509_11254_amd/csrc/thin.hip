@@ -630,13 +630,14 @@ static int apply_rows(int max_lenP, int n_ids, int mode) {
 // small: every layer of the launch is narrow (w_in <= 16) and the chain runs the per-workgroup factorisation
 // mode APPLY_RITZ: ROLE_ZP -> ROLE_P, and in the same launch (z = 1) ROLE_ZQ -> ROLE_Q, which shares nothing with it but tmat
 // (as two launches: 9 us more per refresh of 256 x 128 r = 4, 12 of 4096 x 4096 r = 8)
+// stream_wgs: workgroups per layer of apply_stream_kernel above width 64 (see one_round; 0: as below)
 // slot_rows: rows per partial Gram matrix that the first pass's per-workgroup factorisation adds up in the row-major layers
 // (the others: 128)
 // which: operand copies to leave when cp > 0 (1 = outer-product, 2 = transposed, 3 = both; + 4: the outer-product ones are
 // the layer's kept copies where it has them -- the P~ of a compress step with a deferred residual)
 hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int max_lenP, int w_in, int w_out,
                         int src_role, int dst_role, int mode, int cp, int gate, int a2gate, double tol2,
-                        bool small, int which, int slot_rows, hipStream_t st) {
+                        bool small, int which, int slot_rows, int stream_wgs, hipStream_t st) {
     if (n_ids <= 0) return hipSuccess;
     if (w_out > w_in || (small && (w_in > kCholRegWidth || w_out != w_in || src_role != dst_role || mode == APPLY_RITZ))) return hipErrorInvalidValue;
     const int n_sides = mode == APPLY_RITZ ? 2 : 1;
@@ -646,10 +647,8 @@ hipError_t launch_apply(const LayerDev* layers, const int* ids, int n_ids, int m
         const int kp16 = (mode != APPLY_RITZ && w_in <= 80) ? (w_in + 15) / 16 : 0;
         // a few rounds of workgroups over the whole launch, each walking several tiles of its layer
         // (config 4, width 64: 0.54 ms with one round of 512 workgroups, 0.43 with four, 0.42 with eight, 0.45 with 16)
-        // Above width 64, up to 4096 tiles: one round, of two per compute unit (us per refresh with a workgroup per tile, and with two,
-        // three, four per compute unit: 7B-shaped block, width 80, 3071 and 3020, 3064, 3063; three 1B-shaped ones in fp32 3652 and 3564,
-        // 3583, 3584; at width 40 in bf16 5018 and 5053, 5029, 5000).
-        int per_layer = ((w_in > 64 && (int)grid.x * n_ids <= 8 * 512 ? 2 * 256 : 8 * 512) + n_ids - 1) / n_ids;
+        // Above width 64 one round where the caller has counted it out (see one_round; at width 40 in bf16 5018 us and 5053)
+        int per_layer = w_in > 64 && stream_wgs > 0 ? stream_wgs : (8 * 512 + n_ids - 1) / n_ids;
         if (per_layer > (int)grid.x) per_layer = grid.x;
         if (per_layer < 1) per_layer = 1;
         const size_t lds = apply_stream_lds(w_in, w_out, cp, mode != APPLY_RITZ, kp16);

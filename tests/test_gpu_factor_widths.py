@@ -219,3 +219,33 @@ def test_second_pass_of_wide_blocks(shapes, r):
         p = P[l].double()
         assert float((p.T @ p - torch.eye(r, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6, l
         assert float((Q[l].double() - M[l].T @ p).norm()) <= 2e-6 * float(M[l].norm()), l
+
+
+# widths of 65 to 96, 769 to 4096 tiles of 64 rows in all: few workgroups per layer walk several tiles each (a long layer beside
+# short ones, both orientations, lengths that end within a tile); and one tile fewer, a workgroup per tile
+@pytest.mark.parametrize("shapes", [[(20000, 100)] + [(100 + 37 * i, 100 + i) for i in range(1, 30)] + [(104, 300 + 41 * i) for i in range(20)],
+                                    [(1021, 103)] * 49, [(104, 1024)] * 48, [(49153, 100)]])
+@pytest.mark.parametrize("op", ["compress", "compress_refresh"])
+def test_walks_of_several_tiles(shapes, op):
+    torch = torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(len(shapes))
+    r = 70
+    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_F32, (cols + 7) // 8 * 8) for rows, cols in shapes], 1)
+    G, E, Q, P, M = [], [], [], [], []
+    for rows, cols in shapes:
+        n, ld = min(rows, cols), (cols + 7) // 8 * 8
+        g = torch.zeros((rows, ld), device="cuda")
+        g[:, :cols] = torch.randn((rows, cols), generator=gen, device="cuda")
+        G.append([g])
+        E.append(torch.zeros_like(g))
+        Q.append(torch.randn((n, r), generator=gen, device="cuda"))
+        P.append(torch.zeros((max(rows, cols), r), device="cuda"))
+        M.append(g[:, :cols].double() if rows >= cols else g[:, :cols].double().T)
+    getattr(comp, op)(G, E, Q, P)
+    for l, (rows, cols) in enumerate(shapes):
+        m, p, q = M[l], P[l].double(), Q[l].double()
+        e = E[l][:, :cols].double() if rows >= cols else E[l][:, :cols].double().T
+        assert float((p.T @ p - torch.eye(r, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6, l
+        assert float((q - m.T @ p).norm()) <= 2e-6 * float(m.norm()), l
+        assert float((e - (m - p @ q.T)).norm()) <= 2e-6 * float(m.norm()), l
