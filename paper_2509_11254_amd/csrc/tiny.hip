@@ -30,7 +30,7 @@ constexpr int64_t kTinyStepElements = 400000, kTinyRefreshElements = 2400000, kT
 // so that the 16-byte pieces that 16 lanes read from 16 rows lie in different banks
 __host__ __device__ inline int tiny_ldm(int cols) { return 4 * (((cols + 3) / 4) | 1); }
 struct TinyLayout {
-    size_t x, y, tm, gram, flags, end;
+    size_t x, y, gram, flags, end;
     int ldx, ldy;                                          // of the thin matrices on the long and on the short side
 };
 __host__ __device__ inline TinyLayout tiny_layout_as(int rows, int cols, bool odd) {
@@ -40,12 +40,11 @@ __host__ __device__ inline TinyLayout tiny_layout_as(int rows, int cols, bool od
     t.ldy = odd ? tiny_ldm(n) : (n + 3) & ~3;
     auto thin = [](int ld) {
         const size_t b = (size_t)kTinyCols * ld * sizeof(float);
-        return b > kTinyScratch ? b : kTinyScratch;     // (each of the two also serves as the other's Gram scratch)
+        return b > kTinyScratch ? b : kTinyScratch;     // (each of the two also serves as the other's Gram scratch, and then for its factor)
     };
     t.x = (size_t)rows * tiny_ldm(cols) * sizeof(float);
     t.y = t.x + thin(t.ldx);
-    t.tm = t.y + thin(t.ldy);
-    t.gram = t.tm + 256 * sizeof(double);
+    t.gram = t.y + thin(t.ldy);
     t.flags = t.gram + 136 * sizeof(double);
     t.end = t.flags + 16;
     return t;
@@ -389,7 +388,7 @@ __device__ __forceinline__ void tiny_pack(const PackRef& K, int planes, const fl
 
 struct TinyLds {
     float *m, *x, *y;
-    double *tm, *gram;
+    double *tmx, *tmy, *gram;                              // tmx, tmy: the factor of x, of y (where the other one was)
     int *need2, *asks_ends;                                // asks_ends: IterationState::asks + 2 ends
     int ldm, ldx, ldy;
     __device__ TinyLds(const LayerDev& L, unsigned char* smem) {
@@ -397,7 +396,8 @@ struct TinyLds {
         m = reinterpret_cast<float*>(smem);
         x = reinterpret_cast<float*>(smem + t.x);
         y = reinterpret_cast<float*>(smem + t.y);
-        tm = reinterpret_cast<double*>(smem + t.tm);
+        tmx = reinterpret_cast<double*>(y);
+        tmy = reinterpret_cast<double*>(x);
         gram = reinterpret_cast<double*>(smem + t.gram);
         need2 = reinterpret_cast<int*>(smem + t.flags);
         asks_ends = need2 + 1;
@@ -466,10 +466,10 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     __syncthreads();
     for (int pass = 1; pass <= 2; ++pass) {
         tiny_gram(S.x, S.ldx, m, w, reinterpret_cast<double*>(S.y), S.gram);
-        if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1, S.tm, true, S.need2, 0);
+        if (t < 64) chol_in_registers(L, S.gram, w, tol2, pass, pass == 1, S.tmx, true, S.need2, 0);
         __syncthreads();
         const bool again = *S.need2 != 0;
-        tiny_apply(S.x, S.ldx, m, w, S.tm);
+        tiny_apply(S.x, S.ldx, m, w, S.tmx);
         if (!again) break;                                 // (the second pass asks for no third)
     }
     const int side_x = tr ? SIDE_W : SIDE_L, side_y = tr ? SIDE_L : SIDE_W;
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
             noted = note != 0 ? note : noted;
             if (t < 64) {
                 NarrowFactor f;
-                chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tm, true, S.need2, note, it, &f);
+                chol_in_registers(L, S.gram, w, tol2, pass, pass == 1 && last, S.tmx, true, S.need2, note, it, &f);
                 if (note && t < 16) {
                     // (the Gram matrix has been read)
                     S.gram[t] = f.dsc;
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
             }
             __syncthreads();
             const bool again = *S.need2 != 0;
-            tiny_apply(S.x, S.ldx, m, w, S.tm);
+            tiny_apply(S.x, S.ldx, m, w, S.tmx);
             if (!again) break;
         }
         if (noted && t >= kTinyThreads - 64) {
@@ -590,9 +590,9 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_iterate_kernel(const LayerD
         }
         if (!last && (it < kOrthYIterations || asked)) {
             tiny_gram(S.y, S.ldy, n, w, reinterpret_cast<double*>(S.x), S.gram);
-            if (t < 64) chol_in_registers(L, S.gram, w, tol2, 1, false, S.tm, true, S.need2, 0);
+            if (t < 64) chol_in_registers(L, S.gram, w, tol2, 1, false, S.tmy, true, S.need2, 0);
             __syncthreads();
-            tiny_apply(S.y, S.ldy, n, w, S.tm);
+            tiny_apply(S.y, S.ldy, n, w, S.tmy);
         }
     }
     tiny_store(L.thin[ROLE_ZP], S.x, S.ldx, m, w);

@@ -173,3 +173,13 @@ def test_kernel_bytes_of_a_one_launch_step():
     assert comp.kernel_bytes("sweep1") == 6 * matrix + thin * (128 + 256 + 128) + copies
     lazy = psgd.Compressor([(256, 128, 4, psgd.PSGD_F32)], 4, lazy_residual=True, allocate=False)
     assert lazy.kernel_bytes("sweep1") > 6 * matrix and lazy.kernel_bytes("residual") == 0
+
+
+# M and the thin matrices in 160 KB of LDS to the last bytes: 16 columns of whole 16-byte pieces take up to 384 bytes more than their rows
+@pytest.mark.parametrize("rows,cols", [(175, 192), (199, 170), (199, 172), (209, 157), (219, 154), (4, 1905), (1, 2242), (12, 1358)])
+def test_the_largest_layers_of_one_launch(rows, cols):
+    r = min(4, rows)
+    comp = psgd.Compressor([(rows, cols, r, psgd.PSGD_F32, (cols + 7) // 8 * 8)], 1, allocate=False)
+    m, n = max(rows, cols), min(rows, cols)
+    copies = 3 * 2 * 32 * sum((x + 127) // 128 * 128 for x in (rows, cols))
+    assert comp.kernel_bytes("sweep1") == 3 * 4 * rows * cols + 4 * r * (m + 2 * n) + copies

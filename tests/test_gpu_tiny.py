@@ -167,7 +167,7 @@ def test_hard_starts(rows, cols, kind):
 
 
 # one and two tiles of 16 rows per wave (192 and 193 rows or columns), reductions that end 1, 15, 16, 17 and 31 steps after a
-# multiple of 32, thin matrices without the odd stride in LDS (168 x 200 and 272 x 120 fit only so)
+# multiple of 32, large ones
 EDGES = [(192, 65), (193, 79), (65, 193), (80, 192), (81, 95), (168, 200), (272, 120), (4, 31)]
 
 
@@ -176,3 +176,18 @@ EDGES = [(192, 65), (193, 79), (65, 193), (80, 192), (81, 95), (168, 200), (272,
 def test_step_at_the_edges_of_tiles(monkeypatch, r, n_workers, dtype):
     monkeypatch.setitem(globals(), "SHAPES", EDGES)
     test_step(r, n_workers, dtype)
+
+
+# the last sizes that fit: with an odd number of 16-byte pieces per column of a thin matrix in LDS, without it, and the first that do not fit
+# (the general path)
+LAST = [(175, 192), (199, 172), (209, 157), (4, 1905), (177, 189), (246, 137), (128, 265), (29, 853), (176, 200), (172, 199), (206, 171)]
+
+
+@pytest.mark.parametrize("r", [4, 16])
+@pytest.mark.parametrize("n_workers,dtype", [(2, synth.F32), (1, synth.BF16)])
+def test_the_last_sizes_that_fit(monkeypatch, r, n_workers, dtype):
+    for shape in LAST:
+        monkeypatch.setitem(globals(), "SHAPES", [shape])
+        test_step(r, n_workers, dtype)
+        if r < 16 and min(shape) > 8:
+            test_refresh(r, n_workers, dtype)
