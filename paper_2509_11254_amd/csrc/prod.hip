@@ -888,7 +888,8 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_prod_kernel(const LayerD
 // Sum of the partial products of a split launch + the same epilogue.  One workgroup per FB-row output block (and partial
 // Gram matrix); the partials are added in split order, so the result is deterministic.
 // FB = 128 for narrow blocks.  Above width 32 the kernel is a pass over [split][width][rows] floats and the fp64 MFMAs of the
-// Gram matrix, with no more workgroups than row blocks: 64 rows each give it twice as many, of 512 threads.
+// Gram matrix, with no more workgroups than row blocks: 64 rows each give it twice as many, of 512 threads, and 32 four times (see
+// finish_rows).
 // It waits for memory, not for bandwidth: a thread requests 16 pieces of 16 bytes at a time, four items of up to four
 // partial sums or two of eight, where it has one item 8 or 32 (sums past the last are requested as the last one again, and not added).
 // One launch serves both orientations (p_like: the result is on the long side; kind_n, kind_t: SplitKind of the launches whose
@@ -977,7 +978,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(const LayerDev* __restrict__
     __syncthreads();
     double* red = FB == BT && T.width <= 16 ? reinterpret_cast<double*>(smem + (((size_t)FB * tw * sizeof(float) + 7) & ~(size_t)7)) : nullptr;
     tile_epilogue<FB, NT>(L, T, out_side, ob, out_len, out_lenP, cp, epi, otile, tw, (epi_flags & EPI_KEPT) != 0, copies, red);
-    // (FB = 64 is for widths whose factorisation is a launch of its own)
+    // (fewer rows are for widths whose factorisation is a launch of its own)
     if constexpr (FB == BT) {
         if (epi == EPI_GRAM && chol_gate >= -1 && !local_chol(L, out_role, local_ok) && (!ITER || gate_open(L, chol_gate))) {
             const int n_wg = (out_len + FB - 1) / FB;      // = number of Gram slots
@@ -1030,9 +1031,12 @@ hipError_t launch_thin_gram(const LayerDev* layers, const int* ids, int n_ids, i
     return hipGetLastError();
 }
 
-// Rows per workgroup and Gram slot.  w: widest block of the launch; max_blocks: 128-row blocks of its longest layer.  Above width 32 64
-// rows, and 32 where 64 leave compute units idle (8192 x 160 with the Gram matrix 26 -> 20 us, the sum over twice the slots 5.3 -> 7.3), but for results of up to 2048 rows, whose partial
-// Gram matrices the factorisation may add up by itself.
+// Rows per workgroup and Gram slot.  w: widest block of the launch; max_blocks: 128-row blocks of its longest layer.  128 up to width
+// 32.  Above, 64, and 32 where 64 make no more workgroups than half the compute units: from there on the chip is filled well enough by
+// 64, and the sum over twice the Gram matrices costs more than is gained (8192 x 160, 128 workgroups, 26 -> 20 us and the sum 5.3 -> 7.3; us
+// per refresh on 64 rows and 32: 2304 x 2304 fp32 r = 40 706 and 669, 4096 x 4096 r = 40 867 and 842, 8192 x 8192 bf16 r = 128 2094 and
+// 2067; with 157 workgroups, 10000 x 2048 fp32 r = 64, 2551 and 2604, with 256, 16384 x 2048 r = 100, 1360 and 1373, two 8192 x 8192 bf16
+// r = 128 2673 and 2698).  Not for results of up to 2048 rows, whose partial Gram matrices the factorisation may add up by itself.
 int finish_rows(int w, int max_blocks, int n_ids) {
     return w <= kWideWidth ? BT : max_blocks > 2048 / BT && 2 * max_blocks * n_ids <= 128 ? BT / 4 : BT / 2;
 }

@@ -55,12 +55,15 @@ __host__ __device__ inline TinyLayout tiny_layout(int rows, int cols) {
     return t.end <= kTinyLds ? t : tiny_layout_as(rows, cols, false);
 }
 // Whether a layer's step, or refresh, fits (r: widest thin matrix of it).  n_arrays: gradients and E, which one compute unit reads at
-// 0.08 to 0.1 ns per element: not longer than the general path's launches take.  256 x 128 fp32, us: step, 8 workers 33 against 41, 11
-// workers 42.4 and 42.8.  A refresh has more launches to save, and a general launch over a matrix of kTinyRefreshAlways elements is
-// one or two workgroups, which take as long per worker: 256 x 128 at two iterations, 64 workers 309 against 350, 96 398 and 398, 128
-// 481 and 440 (bf16 96 379 and 390, 128 456 and 386); 200 x 160 96 403 and 429, 128 491 and 472; 128 x 128 256 workers 566 and 616;
-// 64 x 64 301 and 578.  Not the number of layers, one workgroup each: 256 x 128, one worker, step of 1, 256, 4096 layers 26,
-// 37, 599 against 37, 102, 1250, refreshes at two iterations 170, 259, 2600 against 365, 812, 8250; 64 x 64 10, 13, 178 against 36, 65, 522.
+// 0.06 to 0.1 ns per element: not longer than the general path's launches take.  us, one launch and the general path, psgd_compress
+// alone: 256 x 128 fp32 r = 4, 8 workers 26 and 38, 11 (the last) 29 and 39; at 426000 elements, 12 workers, 41 and 41, at r = 16 46 and 44, 128 x
+// 256 r = 16 48 and 43, 24 x 900 18 workers 56 and 42, though 128 x 128 25 workers 39 and 50 and bf16 31 to 42 and 36 to 54.
+// A refresh has more launches to save, and a general launch over a matrix of kTinyRefreshAlways elements is one or two workgroups, which
+// take as long per worker: 256 x 128 r = 4 where it runs four iterations, 64 workers 278 and 331, 96 (the last) 366 and 384, 128 455 and 408 (bf16 96
+// 347 and 369, 128 428 and 414); 200 x 160 96 374 and 402; 128 x 128 256 workers 539 and 599; 64 x 64 279 and 600.  (With refresh_iters = 2 the
+// general path is the faster one from 32 workers on, 165 and 162, 96 345 and 241: the rule does not look at the budget.)
+// Not the number of layers, one workgroup each: 256 x 128, one worker, in a graph, step of 1, 256, 4096 layers 24, 36, 515 against
+// 38, 100, 1199, refreshes at two iterations 92, 139, 1456 against 138, 280, 3002; 64 x 64 16, 19, 168 and 72, 93, 773 against 36, 64, 495 and 134, 204, 1451.
 bool tiny_fits(int64_t rows, int64_t cols, int r, int n_arrays, bool refresh) {
     if (r > kCholRegWidth || rows * cols > (int64_t)(kTinyLds / sizeof(float))) return false;
     if (refresh ? n_arrays * (rows * cols - kTinyRefreshAlways) > kTinyRefreshElements : n_arrays * rows * cols > kTinyStepElements) return false;
