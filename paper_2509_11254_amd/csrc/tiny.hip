@@ -496,10 +496,11 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     const int ldl = tr ? S.ldy : S.ldx, ldw = tr ? S.ldx : S.ldy, ldm = S.ldm;
     const int64_t ld = L.ld;
     PSGD_GLOBAL float* out = as_global(L.S);
-    // a wave's share: a quarter of the blocks of a block row, kept in step with its operand of that row (4 nr shares)
-    const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, nq = (nc + 3) / 4;
-    for (int share = wv; share < 4 * nr; share += kTinyWaves) {
-        const int row = 16 * (share >> 2) + li, rowc = min(row, rows - 1), j0 = (share & 3) * nq, j1 = min(nc, j0 + nq);
+    // a wave's share: a quarter of the blocks of a block row, kept in step with its operand of that row; all of one block, half of
+    // two (as quarters, three of the twelve waves had all the blocks of up to 16 columns: step of 1036 x 9 fp32 41.0 -> 33.0 us, of 600 x 32 28.8 -> 26.4)
+    const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, parts = min(nc - 1, 2), nq = (nc + (1 << parts) - 1) >> parts;
+    for (int share = wv; share < nr << parts; share += kTinyWaves) {
+        const int row = 16 * (share >> parts) + li, rowc = min(row, rows - 1), j0 = (share & ((1 << parts) - 1)) * nq, j1 = min(nc, j0 + nq);
         float a[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) a[u] = 4 * u < w ? xl[(4 * u + lk) * ldl + rowc] : 0.f;

@@ -168,7 +168,7 @@ def test_hard_starts(rows, cols, kind):
 
 # one and two tiles of 16 rows per wave (192 and 193 rows or columns), reductions that end 1, 15, 16, 17 and 31 steps after a
 # multiple of 32, large ones
-EDGES = [(192, 65), (193, 79), (65, 193), (80, 192), (81, 95), (168, 200), (272, 120), (4, 31)]
+EDGES = [(192, 65), (193, 79), (65, 193), (80, 192), (81, 95), (168, 200), (272, 120), (4, 31), (300, 15), (310, 16), (200, 17), (150, 33)]
 
 
 @pytest.mark.parametrize("r", [3, 4, 5, 16])
