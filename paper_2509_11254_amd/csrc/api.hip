@@ -139,7 +139,7 @@ struct psgd_ctx {
     void* outs_ws = nullptr;     // workspace that holds the current table of decompress outputs
     void* msgd_ws = nullptr;     // ... and of the momentum and weight buffers of psgd_decompress_msgd / _adam
     void* m2_ws = nullptr;       // ... and of the second-moment buffers of psgd_decompress_adam
-    int stream_wgs[2] = {0, 0};                 // see one_round
+    int stream_wgs[2][2] = {};                  // of steps, of refreshes (see one_round)
     // every layer's step (plain, one power iteration) or refresh runs in one workgroup that holds M in LDS (tiny.hip)
     bool tiny_step = false, tiny_refresh = false;
     size_t tiny_lds = 0;
@@ -807,25 +807,28 @@ void geometry(const Plan& p, Launcher& L) {
 // one round of two per compute unit: a workgroup loads 30 KB of the factor's fragments once for several tiles, and no second
 // round runs half empty.  The most that leave the layers together, each of which uses no more than it has tiles, at 512, and the launch at
 // 4096, the others of which find nothing to do.  0, as many as launch_apply takes at any width: up to one and a half rounds of tiles,
-// and above eight.  us per refresh, several rounds and one: 772 tiles (7B-shaped block r = 64) 7860 and 7800, 782 (50000 x 1024 r = 72) 1291 and
+// and above eight, and where a long layer beside short ones would walk more tiles per workgroup than there are rounds (refresh: a thirty-second
+// part more is still the faster side).  us per refresh, several rounds and one: 772 tiles (7B-shaped block r = 64) 7860 and 7800, 782 (50000 x 1024 r = 72) 1291 and
 // 1261, 896 (fourteen 4096 x 4096 r = 64) 10510 and 10340, 1600 (a hundred 1024 x 1024 r = 72) 2479 and 2333, 3840 (120 of 512 x 2048
-// r = 68) 3565 and 2724; 768 (twenty-four 2048 x 2048 r = 64) 3044 and 3075, 640 (forty 1024 x 1024 r = 72) 1400 and 1421.  As many
-// for each layer whatever its size: 8192 x 2048 beside thirty 256 x 256 r = 64 3850 and 4250, one such launch then walking 128 tiles with 17.
-int one_round(const std::vector<Plan>& plan, int side) {
+// r = 68) 3565 and 2724; 768 (twenty-four 2048 x 2048 r = 64) 3044 and 3075, 640 (forty 1024 x 1024 r = 72) 1400 and 1421.  Long walks, refresh
+// r = 76: 16384 x 1024 beside seventy 512 x 512, 37 tiles each, 6508 and 10778, 20000 x 300 (two) beside twenty 1000 x 1000, 4 tiles, 4153 and
+// 4243; steps r = 95: those 796 and 1531, 512 and 523, 30000 x 256 beside six 5000 x 512, 7 tiles, 397 and 436, five 11109 x 303 beside five 923 x 378,
+// 174 tiles on 86 workgroups, 390 and 403 (refresh 3125 and 3123).
+int one_round(const std::vector<Plan>& plan, int side, bool refresh) {
     auto tiles = [side](const Plan& p) { return (int)((side == 0 ? std::max(p.rowsP, p.colsP) : std::min(p.rowsP, p.colsP)) / kGramRows2); };
     int64_t all = 0;
-    int hi = 1;
-    for (const Plan& p : plan) { all += tiles(p); hi = std::max(hi, tiles(p)); }
+    int longest = 1;
+    for (const Plan& p : plan) { all += tiles(p); longest = std::max(longest, tiles(p)); }
     if (all <= 512 + 256 || all > 8 * 512) return 0;
-    hi = std::min<int>(hi, (8 * 512 + (int)plan.size() - 1) / (int)plan.size());
-    int lo = 1;
+    int lo = 1, hi = std::min<int>(longest, (8 * 512 + (int)plan.size() - 1) / (int)plan.size());
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
         int64_t wgs = 0;
         for (const Plan& p : plan) wgs += std::min(tiles(p), mid);
         if (wgs <= 512) lo = mid; else hi = mid - 1;
     }
-    return lo;
+    const int rounds = (int)((all + 511) / 512);
+    return longest <= rounds * lo + (refresh ? longest / 32 : 0) ? lo : 0;
 }
 
 Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
@@ -838,7 +841,7 @@ Launcher batch_launcher(psgd_ctx* ctx, void* workspace, hipStream_t st) {
     L.ids_all = ids; L.ids_norm = ids + nl; L.ids_tr = ids + 2 * (size_t)nl;
     L.n_all = nl; L.n_norm = (int)ctx->lists.norm.size(); L.n_tr = (int)ctx->lists.tr.size();
     for (const Plan& p : ctx->plan) geometry(p, L);
-    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = ctx->stream_wgs[s];
+    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = ctx->stream_wgs[0][s];
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab = v == 1; }
     { static int v = -1; if (v < 0) { const char* e = std::getenv("PSGD_XTAB_C"); v = (e && e[0] == '0') ? 0 : 1; } L.use_xtab_c = v == 1; }
     return L;
@@ -984,7 +987,7 @@ int psgd_init(psgd_ctx** out, int n_layers, const psgd_layer_desc* layers, int n
             c->tiny_lds = std::max(c->tiny_lds, tiny_lds_bytes(p.d.rows, p.d.cols));
         }
         c->lazy_tr = c->lazy && c->cpc == 32;
-        for (int s = 0; s < 2; ++s) c->stream_wgs[s] = one_round(c->plan, s);
+        for (int s = 0; s < 2; ++s) { c->stream_wgs[0][s] = one_round(c->plan, s, false); c->stream_wgs[1][s] = one_round(c->plan, s, true); }
     }
     if (rc != PSGD_OK) { delete c; return rc; }
     {
@@ -1275,6 +1278,7 @@ int psgd_compress_refresh(psgd_ctx* ctx, void* workspace, void* stream, const vo
     if (rc != PSGD_OK) return rc;
     ctx->factors_ws = nullptr;
     Launcher L = batch_launcher(ctx, workspace, st);
+    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = ctx->stream_wgs[1][s];
     if (ctx->pending) {
         // the subspace iteration forms M from a materialised E: settle what the deferred residual owes first
         L.prof_mute = true;
@@ -1387,7 +1391,7 @@ int psgd_refresh(psgd_ctx* ctx, void* workspace, void* stream, int layer, const 
     L.ids_norm = ids; L.n_norm = p.transposed ? 0 : 1;
     L.ids_tr = ids; L.n_tr = p.transposed ? 1 : 0;
     geometry(one, L);
-    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = one_round({one}, s);
+    for (int s = 0; s < 2; ++s) L.stream_wgs[s] = one_round({one}, s, true);
     refresh_sequence(ctx, L, false, false, sigma, 0);
     if (L.err != hipSuccess) return fail_hip(ctx, L.err);
     return PSGD_OK;

@@ -221,10 +221,12 @@ def test_second_pass_of_wide_blocks(shapes, r):
         assert float((Q[l].double() - M[l].T @ p).norm()) <= 2e-6 * float(M[l].norm()), l
 
 
-# widths of 65 to 96, 769 to 4096 tiles of 64 rows in all: few workgroups per layer walk several tiles each (a long layer beside
-# short ones, both orientations, lengths that end within a tile); and one tile fewer, a workgroup per tile
+# widths of 65 to 96, 769 to 4096 tiles of 64 rows in all: few workgroups per layer walk several tiles each (layers of different
+# lengths, both orientations, lengths that end within a tile); one tile fewer, and a long layer beside short ones: a workgroup per
+# tile; 174 tiles beside short ones on 86 workgroups: few in the refresh alone
 @pytest.mark.parametrize("shapes", [[(20000, 100)] + [(100 + 37 * i, 100 + i) for i in range(1, 30)] + [(104, 300 + 41 * i) for i in range(20)],
-                                    [(1021, 103)] * 49, [(104, 1024)] * 48, [(49153, 100)]])
+                                    [(1021, 103)] * 49, [(104, 1024)] * 48, [(49153, 100)],
+                                    [(9000, 104)] * 2 + [(100, 8000)] * 10, [(11109, 103)] * 5 + [(923, 128)] * 5])
 @pytest.mark.parametrize("op", ["compress", "compress_refresh"])
 def test_walks_of_several_tiles(shapes, op):
     torch = torch_mod()
