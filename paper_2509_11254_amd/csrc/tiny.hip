@@ -497,10 +497,12 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(const LayerDev*
     const int64_t ld = L.ld;
     PSGD_GLOBAL float* out = as_global(L.S);
     // a wave's share: a quarter of the blocks of a block row, kept in step with its operand of that row; all of one block, half of
-    // two (as quarters, three of the twelve waves had all the blocks of up to 16 columns: step of 1036 x 9 fp32 41.0 -> 33.0 us, of 600 x 32 28.8 -> 26.4)
-    const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, parts = min(nc - 1, 2), nq = (nc + (1 << parts) - 1) >> parts;
+    // two (as quarters, three of the twelve waves had all the blocks of up to 16 columns: step of 1036 x 9 fp32 41.0 -> 33.0 us, of 600 x 32 28.8 -> 26.4).
+    // The larger quarters go round (rounded up, with the last waves idle: 400 x 70 r = 8, four workers 36.4 -> 34.8, 246 x 137 r = 2 27.7 -> 26.4)
+    const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, parts = min(nc - 1, 2);
     for (int share = wv; share < nr << parts; share += kTinyWaves) {
-        const int row = 16 * (share >> parts) + li, rowc = min(row, rows - 1), j0 = (share & ((1 << parts) - 1)) * nq, j1 = min(nc, j0 + nq);
+        const int I = share >> parts, part = (share + I) & ((1 << parts) - 1);
+        const int row = 16 * I + li, rowc = min(row, rows - 1), j0 = (nc * part) >> parts, j1 = (nc * (part + 1)) >> parts;
         float a[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) a[u] = 4 * u < w ? xl[(4 * u + lk) * ldl + rowc] : 0.f;
